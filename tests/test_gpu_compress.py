@@ -35,3 +35,16 @@ def test_quantize_next_to_half_integers_bit_exact(bits, group):
     q_ref, s_ref = oracle.quantize_pack(w, bits, group)
     assert np.array_equal(s.view(torch.int16).cpu().numpy().view(np.uint16), s_ref)
     assert np.array_equal(q.cpu().numpy(), q_ref)
+
+
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("rows,cols,group", [(1, 64, 64), (3, 192, 2), (5, 192, 6), (2, 320, 10), (7, 1056, 96), (129, 2048, 2048)])
+def test_dequantize_odd_groups_and_tails(bits, rows, cols, group):
+    rng = np.random.default_rng(rows * cols + group)
+    q = rng.integers(0, 256, (rows, cols * bits // 8)).astype(np.uint8)
+    s = rng.integers(0, 0x7c00, (rows, cols // group)).astype(np.uint16)        # any finite binary16, subnormals too
+    w = moeq.moe_dequantize(torch.from_numpy(q).to(DEV), torch.from_numpy(s.view(np.int16)).to(DEV), cols, bits, group)
+    torch.cuda.synchronize()
+    u = np.stack([(q >> (bits * i)) & (2 ** bits - 1) for i in range(8 // bits)], -1).reshape(rows, cols).astype(np.int32)
+    ref = np.repeat(s.view(np.float16).astype(np.float32), group, axis=1) * (u - 2 ** (bits - 1)).astype(np.float32)
+    assert np.array_equal(w.cpu().numpy(), ref)
