@@ -160,7 +160,8 @@ size_t moe_workspace_bytes(const moeq_layer *layer, int32_t max_tokens);
 #define MOEQ_PATH_ONE_KERNEL 1     /* columns layout: one streaming kernel per 32 tokens, vector instr.   */
 #define MOEQ_PATH_ONE_KERNEL_MX 2  /* columns layout: the same with matrix-core instructions              */
 #define MOEQ_PATH_GROUPED_GEMM 3   /* 32 tokens or more, either layout: pairs grouped by expert, GEMMs   */
-#define MOEQ_PATH_STREAM 4         /* stream + columns layouts: one streaming kernel on integer dot products */
+#define MOEQ_PATH_STREAM 4         /* stream + columns layouts: streaming kernels on integer dot products (one token: one
+                                      kernel; more: the pairs grouped by expert, every expert streamed once for 16 pairs) */
 int32_t moe_layer_path(const moeq_layer *layer, int32_t n_tokens);
 
 /* Codes bytes of a packed [rows][cols] matrix; *scale_bytes_opt receives the bytes of its scales.
@@ -260,7 +261,8 @@ moeq_status moe_unprepare_in(const void *stream_buf, int64_t rows, int64_t cols,
 /* Measurement aid, per layer. While `which` names a kernel, every moe_layer_forward call on THIS
  * layer records start_event just before and stop_event just after that kernel on the call's stream
  * (hipEvent_t handles created by the caller with timing enabled, which must outlive the setting),
- * so a benchmark can time the dominant kernel alone. For MOEQ_KERNEL_FUSED the two events are
+ * so a benchmark can time the dominant kernel alone. For MOEQ_KERNEL_FUSED the two events bracket the kernels of
+ * a call of several tokens on a stream layer; elsewhere they are
  * attached to the kernel launch itself and receive the begin and end of the kernel's execution
  * (what a kernel trace reports), without the dispatch before it. which = 0 turns it off (the
  * default). The setting is part of the layer handle: change it only while no other thread is

@@ -39,7 +39,8 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Workspace carving. Both paths keep idx, gate and logits; the two-kernel path adds the chosen experts'
 // records and h (fp32), the one-kernel path the partial output vectors.
 struct WsLayout {
-  size_t idx_off, gate_off, logits_off, sel_off, h_off, part_off, prefill_off, total;
+  size_t idx_off, gate_off, logits_off, sel_off, h_off, part_off, prefill_off, batch_off, total;
+  bool batch;      // the call runs the grouped streaming kernels (decode_batch.hip)
 };
 
 // Calls with at least this many tokens run as grouped GEMMs on the matrix cores (when the shape allows);
@@ -49,8 +50,15 @@ constexpr int64_t kPrefillMinTokens = 32;
 // partial output vectors (tokens x slices x d_model floats) does not grow with the call.
 constexpr int32_t kDecodeChunk = 32;
 bool use_prefill(const moeq_layer* layer, int64_t T);
+// Calls of at least this many tokens on a layer in the stream layout group their pairs by expert (a single token has
+// nothing to share, and its one kernel is faster than the four of the grouped form); they are taken in launches of at
+// most kBatchMaxPairs pairs.
+constexpr int64_t kBatchMinTokens = 2;
+inline int64_t batch_tokens(int32_t k) { return kBatchMaxPairs / k; }
 
-WsLayout ws_layout(const moeq_layer* layer, int64_t T) {
+// batch: whether calls on a stream layer may take the grouped form (its pieces share the place of the partial vectors).
+// A call whose workspace holds the ungrouped form only runs that one.
+WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool batch = true) {
   const LayerDims& L = layer->dims;
   WsLayout w{};
   const size_t slots = (size_t)T * L.top_k;
@@ -64,7 +72,17 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T) {
     w.part_off = tail;
     w.prefill_off = tail;           // a call uses one of the two
     const size_t grouped = use_prefill(layer, T) ? prefill_ws(L, T).total : 0;
-    w.total = tail + (part > grouped ? part : grouped);
+    size_t most = part > grouped ? part : grouped;
+    w.batch = batch && layer->in_layout == MOEQ_IN_STREAM && T >= kBatchMinTokens;
+    if (w.batch) {
+      // (the layer calls and, with one choice per token, the single-expert call)
+      const int64_t nk = T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), n1 = T < batch_tokens(1) ? T : batch_tokens(1);
+      const size_t bk = batch_ws(L, nk, L.top_k, layer->bits_mask).total, b1 = batch_ws(L, n1, 1, layer->bits_mask).total;
+      w.batch_off = tail;
+      if (bk > most) most = bk;
+      if (b1 > most) most = b1;
+    }
+    w.total = tail + most;
   } else {
     w.sel_off = tail;
     w.h_off = w.sel_off + align_up(slots * sizeof(DevExpert), 256);
@@ -92,6 +110,12 @@ int inline_router_max() {
     return want < cap ? want : cap;
   }();
   return v;
+}
+
+// The layout for a call with ws_bytes of workspace: without the grouped form where only that fits.
+WsLayout ws_layout_for(const moeq_layer* layer, int64_t T, size_t ws_bytes) {
+  const WsLayout w = ws_layout(layer, T);
+  return w.batch && ws_bytes < w.total ? ws_layout(layer, T, false) : w;
 }
 
 inline moeq_status dev(hipError_t e) { return e == hipSuccess ? MOEQ_OK : MOEQ_EDEVICE; }
@@ -220,7 +244,7 @@ moeq_status moe_layer_create(const moeq_layer_desc* desc, void* table_dev, size_
   L->plan = plan;
   if (hipMemcpy(table_dev, tab.data(), tab.size() * sizeof(DevExpert), hipMemcpyHostToDevice) != hipSuccess ||
       init_attrs_decode_fused() != hipSuccess || init_attrs_ffn_decode() != hipSuccess ||
-      init_attrs_prefill() != hipSuccess) {
+      init_attrs_prefill() != hipSuccess || init_attrs_decode_batch() != hipSuccess) {
     (void)hipGetLastError();
     delete L;
     return MOEQ_EDEVICE;
@@ -243,7 +267,7 @@ moeq_status moe_router_topk(const moeq_layer* layer, const void* x, int32_t n_to
   if (n_tokens == 0) return MOEQ_OK;
   if (!x || !topk_idx || !topk_gate || ((uintptr_t)x & 15u)) return MOEQ_EINVAL;
   if (n_tokens > 65535) return MOEQ_EUNSUPPORTED;
-  const WsLayout w = ws_layout(layer, n_tokens);
+  const WsLayout w = ws_layout_for(layer, n_tokens, ws_bytes);
   if (!ws || ws_bytes < w.total) return MOEQ_EWORKSPACE;
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   float* logits = (float*)((char*)ws + w.logits_off);
@@ -261,10 +285,21 @@ moeq_status moe_expert_ffn_q(const moeq_layer* layer, int32_t expert, const void
   if (n_tokens == 0) return MOEQ_OK;
   if (!x || !y || ((uintptr_t)x & 15u) || ((uintptr_t)y & 3u)) return MOEQ_EINVAL;
   if (n_tokens > 65535) return MOEQ_EUNSUPPORTED;
-  const WsLayout w = ws_layout(layer, n_tokens);
+  const WsLayout w = ws_layout_for(layer, n_tokens, ws_bytes);
   if (!ws || ws_bytes < w.total) return MOEQ_EWORKSPACE;
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
+  if (w.batch) {
+    const size_t x_row = (size_t)layer->dims.d_model * (layer->dims.x_bf16 ? 2 : 4);
+    for (int64_t t0 = 0; t0 < n_tokens; t0 += batch_tokens(1)) {
+      const int32_t n = (int32_t)(n_tokens - t0 < batch_tokens(1) ? n_tokens - t0 : batch_tokens(1));
+      if (launch_moe_batch(layer->dims, layer->table, nullptr, nullptr, false, expert, layer->bits[(size_t)expert],
+                           (const char*)x + (size_t)t0 * x_row, n, nullptr, nullptr, gate_opt ? gate_opt + t0 : nullptr,
+                           accumulate ? 1 : 0, (char*)ws + w.batch_off, y + (size_t)t0 * layer->dims.d_model, st) != hipSuccess)
+        return MOEQ_EDEVICE;
+    }
+    return MOEQ_OK;
+  }
   if (layer->out_layout == MOEQ_OUT_COLUMNS) {
     float* part = (float*)((char*)ws + w.part_off);
     const size_t x_row = (size_t)layer->dims.d_model * (layer->dims.x_bf16 ? 2 : 4);
@@ -301,7 +336,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
   if (!x || !y || ((uintptr_t)x & 15u) || ((uintptr_t)y & 3u)) return MOEQ_EINVAL;
   if ((int64_t)n_tokens * layer->dims.top_k > 65535) return MOEQ_EUNSUPPORTED;
   const LayerDims& L = layer->dims;
-  const WsLayout w = ws_layout(layer, n_tokens);
+  const WsLayout w = ws_layout_for(layer, n_tokens, ws_bytes);
   if (!ws || ws_bytes < w.total) return MOEQ_EWORKSPACE;
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   const bool given = given_idx != nullptr;
@@ -321,6 +356,27 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     const PrefillWs pw = prefill_ws(L, n_tokens);
     return dev(launch_prefill(L, layer->table, x, n_tokens, idx, gate, (char*)ws + w.prefill_off, pw, y,
                               layer->out_layout == MOEQ_OUT_COLUMNS, layer->in_layout == MOEQ_IN_STREAM, st));
+  }
+  if (w.batch) {
+    // the pairs grouped by expert; routed inside for few experts, else by the router kernels
+    const bool route_inline = !given && L.n_experts <= (inline_router_max() < batch_inline_router_max() ? inline_router_max()
+                                                                                                        : batch_inline_router_max());
+    if (!given && !route_inline) {
+      if (launch_router_logits(L, layer->router_w, layer->router_bias, x, n_tokens, logits, st) != hipSuccess ||
+          launch_topk(L, logits, n_tokens, idx, gate, nullptr, st) != hipSuccess)
+        return MOEQ_EDEVICE;
+    }
+    const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
+    ScopedEvents ev(layer, MOEQ_KERNEL_FUSED, st);
+    for (int64_t t0 = 0; t0 < n_tokens; t0 += batch_tokens(L.top_k)) {
+      const int32_t n = (int32_t)(n_tokens - t0 < batch_tokens(L.top_k) ? n_tokens - t0 : batch_tokens(L.top_k));
+      const size_t s0 = (size_t)t0 * (size_t)L.top_k;
+      if (launch_moe_batch(L, layer->table, layer->router_w, layer->router_bias, route_inline, -1, layer->bits_mask,
+                           (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, gate + s0, 0, (char*)ws + w.batch_off,
+                           y + (size_t)t0 * L.d_model, st) != hipSuccess)
+        return MOEQ_EDEVICE;
+    }
+    return MOEQ_OK;
   }
   if (layer->out_layout == MOEQ_OUT_COLUMNS) {
     // one streaming kernel for the whole layer, then the ordered sum of its partial output vectors
@@ -393,7 +449,7 @@ moeq_status moe_layer_forward_static(const moeq_layer* layer, const void* x, int
                                      int32_t* topk_idx_opt, float* topk_gate_opt, void* stream) {
   if (!layer || n_tokens < 0) return MOEQ_EINVAL;
   if (n_tokens == 0) return MOEQ_OK;
-  if (ws_layout(layer, n_tokens).total > kStaticScratchBytes) return MOEQ_EWORKSPACE;   // beyond the fixed scratch
+  if (ws_layout_for(layer, n_tokens, kStaticScratchBytes).total > kStaticScratchBytes) return MOEQ_EWORKSPACE;   // beyond the fixed scratch
   void* ws = static_scratch();
   if (!ws) return MOEQ_EDEVICE;
   return layer_forward_impl(layer, x, n_tokens, y, topk_idx_opt, topk_gate_opt, nullptr, nullptr, ws,

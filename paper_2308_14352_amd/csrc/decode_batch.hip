@@ -1,0 +1,801 @@
+// Decode calls of a few tokens on a layer in the stream + columns layouts (a batch of sequences decoded together):
+// the (token, choice) pairs are grouped by expert, and every expert's packed weights are streamed ONCE for up to 16 of
+// its pairs, against all of them on the matrix cores (Section 2.1: only the chosen experts work on a token; Section
+// 3.2: the codes are decompressed by the mirror of the linear quantization - here they stay integers all the way into
+// the multiplier).
+//
+// Arithmetic: that of decode_stream.hip. The activations of a scale group (128 columns) are block-floating-point
+// integers of up to 15 bits and a sign, split into two signed bytes x_int = lo + 256 hi; codes enter as bytes (2- and
+// 4-bit codes with their offset, which is taken off with the group's sum of x_int; 8-bit codes made signed by one XOR).
+// v_mfma_i32_16x16x64_i8 gives the exact integer sums of 16 tokens x 16 rows; per group sum * 2^e * scale in fp32.
+//
+// Kernels (launch_moe_batch):
+//   k_batch_prep     per token: router + top-k, x as byte digits in the operand order of every bitwidth of the layer
+//   k_batch_in       W_in / W_gate, activation, h as byte digits (a unit of 128 rows is one scale group of W_out)
+//   k_batch_out      W_out over 1024 columns of d_ff, partial outputs per pair
+//   k_batch_combine  y[t] = sum_j gate_j * (sum of the pair's partial outputs), in a fixed order
+//
+// What bounds it: the bytes of the distinct experts. With one workgroup per (slice, token), as for a single token, a
+// call of T tokens pays T times the unpack arithmetic. Mixtral layer (8 experts, 2 / 4 bits, d_ff 14336): 8 tokens
+// 230 -> 130-150 us, 23 tokens 640 -> 157 us (550 MB: 3.5 TB/s over the whole call; k_batch_in 100, k_batch_out 47, the two
+// small kernels 6.5 and 6).
+#include <hip/hip_ext.h>
+
+#include "decode_core.h"
+
+namespace moeq {
+namespace {
+
+constexpr int kBD = 4096;                 // d_model
+constexpr int kBGroup = 128;              // scale group of all matrices
+constexpr int kBGroups = kBD / kBGroup;   // scale groups of a row of W_in
+constexpr int kBTok = 16;                 // pairs of a work item (columns of the matrix instruction)
+constexpr int kBWaves = 8;                // wavefronts of a k_batch_in workgroup
+constexpr int kBOutGroups = 8;            // scale groups of d_ff a k_batch_out workgroup takes
+constexpr int kBOutRows = 256;            // output rows a k_batch_out workgroup takes (64 per wavefront)
+constexpr int kBInlineMaxE = 64;          // the router runs inside k_batch_prep for at most this many experts
+
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ i32x4_t mfma_i8(const i32x4_t& a, const i32x4_t& b, const i32x4_t& c) {
+  return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+}
+
+// The 128 columns of a scale group are two operands (op) of 64; lane (m or n = l % 16, kb = l / 16) holds 16 of an
+// operand's columns, byte j of them being column operand_col(..., j) of the group. W_in / W_gate in the stream layout:
+// the words that one swap of half wavefronts brings together (k_batch_in); W_out in columns: word columns 4 apart.
+template <int BITS, bool OUT>
+__device__ __forceinline__ int operand_col(int op, int kb, int j) {
+  if constexpr (!OUT) {
+    if constexpr (BITS == 4) return 64 * (kb & 1) + 32 * (kb >> 1) + 16 * op + 8 * (j >> 3) + 2 * (j & 3) + ((j >> 2) & 1);
+    else if constexpr (BITS == 2) return 64 * (kb & 1) + 16 * (kb >> 1) + 32 * op + 4 * (j & 3) + (j >> 2);
+    else return 64 * (kb & 1) + 16 * (kb >> 1) + 32 * op + j;
+  } else {
+    if constexpr (BITS == 4) return 64 * op + 32 * (j >> 3) + 8 * kb + 2 * (j & 3) + ((j >> 2) & 1);
+    else if constexpr (BITS == 2) return 64 * op + 16 * kb + 4 * (j & 3) + (j >> 2);
+    else return 64 * op + 16 * (j >> 2) + 4 * kb + (j & 3);
+  }
+}
+
+// 16 codes as operand bytes: from two words (4 bits), one word (2 bits), four words (8 bits)
+__device__ __forceinline__ i32x4_t codes16_4(uint32_t w0, uint32_t w1) {
+  return (i32x4_t){(int)(w0 & 0x0f0f0f0fu), (int)((w0 >> 4) & 0x0f0f0f0fu), (int)(w1 & 0x0f0f0f0fu), (int)((w1 >> 4) & 0x0f0f0f0fu)};
+}
+__device__ __forceinline__ i32x4_t codes16_2(uint32_t w) {
+  return (i32x4_t){(int)(w & 0x03030303u), (int)((w >> 2) & 0x03030303u), (int)((w >> 4) & 0x03030303u), (int)((w >> 6) & 0x03030303u)};
+}
+__device__ __forceinline__ i32x4_t codes16_8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  return (i32x4_t){(int)(a ^ 0x80808080u), (int)(b ^ 0x80808080u), (int)(c ^ 0x80808080u), (int)(d ^ 0x80808080u)};
+}
+// what a code's offset adds to a dot product, in units of the sum of x_int
+template <int BITS> constexpr int code_offset() { return BITS == 8 ? 0 : 1 << (BITS - 1); }
+
+__device__ __forceinline__ uint32_t lo_byte(int v) { return (uint32_t)v & 255u; }
+__device__ __forceinline__ uint32_t hi_byte(int v) { return (uint32_t)((v + 128) >> 8) & 255u; }
+
+// Lanes 32..63 of a against lanes 0..31 of b: a = (a.lower, b.lower), b = (a.upper, b.upper).
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(a, b, false, false));
+  a = r.x;
+  b = r.y;
+}
+
+// A work item: up to kBTok pairs of one expert.
+struct BatchItem { int32_t e, n; uint8_t pair[kBTok]; int32_t bits, pad; };
+static_assert(sizeof(BatchItem) == 32, "two 16-byte pieces");
+
+struct BatchArgs {
+  LayerDims L;
+  const DevExpert* table;
+  const float* Wr;
+  const float* bias;
+  const void* x;
+  int32_t T, k, fixed_expert, bits_mask, route_inline;
+  int32_t* idx;          // [T][k] written by k_batch_prep (route_inline) or read (unused with a fixed expert)
+  float* gate;           // [T][k] likewise
+  uint8_t* XQ;           // [bitwidths][T][kBGroups][op][digit][kb][16]: x as operand bytes
+  float* XS;             // [T][kBGroups] 2^e of every group (NaN: the group holds a non-finite value)
+  int32_t* XSUM;         // [T][kBGroups] sum of x_int
+  uint8_t* HQ;           // [pairs][d_ff / 128][op][digit][kb][16]: h likewise, in the order of its expert's bitwidth
+  float* HS;             // [pairs][d_ff / 128]
+  int32_t* HSUM;
+  BatchItem* items;      // written by workgroup 0 of k_batch_in
+  int32_t* n_items;
+  float* part;           // [d_ff / 1024 rounded up][pairs][d_model]
+};
+
+__device__ __forceinline__ int bits_slot(int mask, int bits) {
+  return __popc((unsigned)mask & ((unsigned)bits - 1u) & 14u);      // bitwidths 2, 4, 8 are the bits of the mask
+}
+
+// x_int of eight values of a scale group that the 16 lanes of a DPP row share; returns 2^e (NaN if a value of the
+// group is not finite, x_int = 0 then) and the group's sum of x_int.
+__device__ __forceinline__ float group_ints(const float (&v)[8], int (&xi)[8], int& sum) {
+  float m = 0.f;
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    m = fmaxf(m, fabsf(v[i]));
+    bad = bad || !(fabsf(v[i]) < INFINITY);
+  }
+  m = bad ? INFINITY : m;
+  m = fmaxf(m, dpp<kDppXor1>(m));
+  m = fmaxf(m, dpp<kDppXor2>(m));
+  m = fmaxf(m, dpp<kDppRor4>(m));
+  m = fmaxf(m, dpp<kDppRor8>(m));
+  // the largest magnitude m * 2^-e lies in [2^14, 32639], what a signed byte pair holds: one bit more than the digits of
+  // k_moe_stream, because h has one exponent per 128 values here and one per 64 there
+  int e = 0;
+  if (m > 0.f && m < INFINITY) {
+    e = __builtin_amdgcn_frexp_expf(m) - 15;
+    e += m * pow2f(min(max(-e, -120), 120)) > 32639.f ? 1 : 0;
+  }
+  e = min(max(e, -120), 120);
+  const float dn = pow2f(-e);
+  sum = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    xi[i] = m < INFINITY ? __float2int_rn(v[i] * dn) : 0;
+    sum += xi[i];
+  }
+  sum += dppi<kDppXor1>(sum);
+  sum += dppi<kDppXor2>(sum);
+  sum += dppi<kDppRor4>(sum);
+  sum += dppi<kDppRor8>(sum);
+  return m < INFINITY ? pow2f(e) : __builtin_nanf("");
+}
+
+// ---------------------------------------------------------------------------------------------
+// Workgroup = one token, thread t holds columns 8 t .. 8 t + 7. The router's sums are those of k_moe_stream, term by
+// term, so a token's routing does not depend on how many tokens share its call.
+__global__ __launch_bounds__(512) void k_batch_prep(BatchArgs G) {
+  __shared__ __align__(16) int16_t XI[kBD];
+  __shared__ float rpart[kBWaves * kBInlineMaxE];
+  __shared__ float lg[kBInlineMaxE];
+  const LayerDims& L = G.L;
+  const int token = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, E = L.n_experts;
+  const XItem xit = load_x_item((const char*)G.x + (size_t)token * kBD * (L.x_bf16 ? 2 : 4), L.x_bf16 ? X_BF16 : X_F32, tid);
+  auto stage = [&]() __attribute__((always_inline)) {
+    int xi[8], sum;
+    const float s = group_ints(xit.v, xi, sum);
+    if ((tid & 15) == 0) {
+      G.XS[(size_t)token * kBGroups + (tid >> 4)] = s;
+      G.XSUM[(size_t)token * kBGroups + (tid >> 4)] = sum;
+    }
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = ((uint32_t)xi[2 * i] & 0xffffu) | ((uint32_t)xi[2 * i + 1] << 16);
+    ((uint4*)XI)[tid] = make_uint4(w[0], w[1], w[2], w[3]);
+  };
+  bool staged = false;
+  if (G.route_inline) {
+    for (int e0 = 0; e0 < E; e0 += 8) {
+      float4 w[8][2];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float* wr = G.Wr + (size_t)min(e0 + i, E - 1) * kBD + 8 * tid;     // rows past E repeat the last one
+        w[i][0] = *(const float4*)wr;
+        w[i][1] = *(const float4*)(wr + 4);
+      }
+      if (!staged) { stage(); staged = true; }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float acc = w[i][0].x * xit.v[0];
+        acc = fmaf(w[i][0].y, xit.v[1], acc); acc = fmaf(w[i][0].z, xit.v[2], acc); acc = fmaf(w[i][0].w, xit.v[3], acc);
+        acc = fmaf(w[i][1].x, xit.v[4], acc); acc = fmaf(w[i][1].y, xit.v[5], acc);
+        acc = fmaf(w[i][1].z, xit.v[6], acc); acc = fmaf(w[i][1].w, xit.v[7], acc);
+        acc = wave_sum(acc);
+        if (lane == 0 && e0 + i < E) rpart[wave * kBInlineMaxE + e0 + i] = acc;
+      }
+    }
+  }
+  if (!staged) stage();
+  __syncthreads();
+  if (G.route_inline && wave == 0) {
+    int* se = G.idx + (size_t)token * L.top_k;
+    float* sg = G.gate + (size_t)token * L.top_k;
+    if (lane < E) {
+      float t = rpart[lane];
+#pragma unroll
+      for (int wv = 1; wv < kBWaves; ++wv) t += rpart[wv * kBInlineMaxE + lane];
+      lg[lane] = t + (G.bias ? G.bias[lane] : 0.f);
+    }
+    if (E <= 8 && L.top_k <= 2) topk_tiny<8>(lg, E, L.top_k, L.renorm, lane, se, sg);
+    else if (E <= 16 && L.top_k <= 2) topk_tiny<16>(lg, E, L.top_k, L.renorm, lane, se, sg);
+    else topk_from_logits(lg, E, L.top_k, L.renorm, lane, se, sg, nullptr);
+  }
+  // the operand bytes: 256 pieces of 16 columns per bitwidth, both digits of a piece by one thread
+  auto pieces = [&](auto bits_tag) __attribute__((always_inline)) {
+    constexpr int BITS = decltype(bits_tag)::value;
+    uint8_t* out = G.XQ + ((size_t)bits_slot(G.bits_mask, BITS) * G.T + token) * (2 * kBD);
+    for (int pc = tid; pc < kBD / 16; pc += 512) {
+      const int g = pc >> 3, op = (pc >> 2) & 1, kb = pc & 3;
+      uint32_t lo[4] = {0u, 0u, 0u, 0u}, hi[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int v = XI[g * kBGroup + operand_col<BITS, false>(op, kb, j)];
+        lo[j >> 2] |= lo_byte(v) << (8 * (j & 3));
+        hi[j >> 2] |= hi_byte(v) << (8 * (j & 3));
+      }
+      uint4* dst = (uint4*)(out + (size_t)(g * 2 + op) * 128 + kb * 16);
+      dst[0] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+      dst[4] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    }
+  };
+  if (G.bits_mask & 2) pieces(std::integral_constant<int, 2>{});
+  if (G.bits_mask & 4) pieces(std::integral_constant<int, 4>{});
+  if (G.bits_mask & 8) pieces(std::integral_constant<int, 8>{});
+}
+
+// ---------------------------------------------------------------------------------------------
+// Groups the pairs of the call by expert into items (first come, first served; 16 pairs each), in LDS. Every thread of
+// a workgroup of 512 calls it. O(pairs) broadcast reads per pair: a call has at most kBatchMaxPairs of them.
+struct BatchLists {
+  int32_t pe[kBatchMaxPairs];
+  int32_t rank[kBatchMaxPairs];
+  int32_t it[kBatchMaxPairs];
+  int32_t wcnt[kBatchMaxPairs / 64];
+  BatchItem items[kBatchMaxPairs];
+};
+__device__ __forceinline__ int batch_items(const BatchArgs& G, BatchLists& S) {
+  const int p = threadIdx.x, P = G.T * G.k, E = G.L.n_experts;
+  const int lane = p & 63, wave = p >> 6;
+  int e = -1;
+  if (p < P) {
+    e = G.fixed_expert >= 0 ? G.fixed_expert : min(max(G.idx[p], 0), E - 1);
+    S.pe[p] = e;
+  }
+  __syncthreads();
+  int r = 0, total = 0;
+  if (p < P) {
+#pragma unroll 4
+    for (int q = 0; q < P; ++q) {
+      const int same = S.pe[q] == e ? 1 : 0;
+      total += same;
+      r += q < p ? same : 0;
+    }
+    S.rank[p] = r;
+  }
+  const bool first = p < P && (r & (kBTok - 1)) == 0;
+  const unsigned long long mask = __ballot(first);
+  if (lane == 0 && wave < kBatchMaxPairs / 64) S.wcnt[wave] = __popcll(mask);
+  __syncthreads();
+  int n_items = 0, before = 0;
+  for (int w = 0; w < kBatchMaxPairs / 64; ++w) {
+    before += w < wave ? S.wcnt[w] : 0;
+    n_items += S.wcnt[w];
+  }
+  if (first) {
+    const int i = before + __popcll(mask & ((1ull << lane) - 1ull));
+    S.it[p] = i;
+    S.items[i].e = e;
+    S.items[i].n = min(kBTok, total - r);
+    S.items[i].bits = G.table[e].bits;
+  }
+  __syncthreads();
+  if (p < P) {
+    int mine = 0;
+#pragma unroll 4
+    for (int q = 0; q < P; ++q)
+      if (S.pe[q] == e && S.rank[q] == (r & ~(kBTok - 1))) mine = q;
+    const int i = S.it[mine];
+    S.items[i].pair[r & (kBTok - 1)] = (uint8_t)p;
+  }
+  __syncthreads();
+  return n_items;
+}
+
+// A register set of k_batch_in: eight 16-byte loads (NH steps of 256 columns of NM matrices) and their scales.
+template <int BITS, int NM>
+struct BatchSet {
+  static constexpr int LPS = BITS / 2 * NM;        // loads per 256 columns
+  static constexpr int NH = 8 / LPS;               // 256-column steps
+  static constexpr int GS = 2 * NH;                // scale groups
+  static constexpr int NS = (GS + 3) / 4;          // scale words per matrix: lane (n, kb) holds group 4 i + kb of row n
+  static constexpr int SPU = kBD / 256 / NH;       // sets per row block
+  uint4 t[8];
+  uint32_t s[NM][NS];
+};
+
+struct BatchInLds {
+  uint4 A[kBGroups * 4][64];           // operand (g, op, digit): lane's 16 bytes
+  float XS[kBGroups][kBTok];
+  int32_t SX[kBGroups][kBTok];         // minus the code offset times the sum of x_int
+  float H[2][kBTok][kBGroup + 4];      // h of a unit's rows, two units in turn
+  BatchLists lists;
+};
+
+// Units [u0, u1) (128 rows of W_in / W_gate each) of one item. Wavefront w owns rows 16 w .. 16 w + 15 of a unit. Lane
+// (n, kb) loads the 16-byte pieces 4 h + kb of row n: 64 consecutive bytes of 16 rows per load, the other half of the
+// 128-byte lines with the next step's (5.6 TB/s as a bare access pattern with 16 loads per lane in flight, against 6.1
+// for whole 1 KB tiles, which would have to be transposed through LDS). A scale group is two pieces of all the row's
+// tiles: swapping half wavefronts between two loads puts a group's codes into all four kb.
+template <int BITS, int NM, bool SWIGLU>
+__device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S, const BatchItem& item, int u0, int u1) {
+  using Set = BatchSet<BITS, NM>;
+  constexpr int RB = 16 / BITS, TPR = BITS / 2;
+  constexpr uint32_t BB = 8192u + 64u * RB;
+  constexpr int LPM = BITS / 2;                    // loads of one matrix per 256 columns
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, kb = lane >> 4;
+  const DevExpert* ex = G.table + item.e;
+  const uint8_t* q[NM];
+  q[0] = uniform_ptr(ex->q_in);
+  if constexpr (NM == 2) q[1] = uniform_ptr(ex->q_gate);
+  const int NG = G.L.d_ff / kBGroup;
+  const uint8_t* xq = G.XQ + (size_t)bits_slot(G.bits_mask, BITS) * G.T * (2 * kBD);
+
+  __syncthreads();          // every wavefront is done with the previous item's operands
+  // the item's 16 activation rows into LDS, operand by operand (absent pairs repeat the first one; their results are dropped)
+  {
+    const int pm = item.pair[n < item.n ? n : 0];
+    const uint8_t* src = xq + (size_t)(pm / G.k) * (2 * kBD) + kb * 16;
+    const uint32_t a0 = (uint32_t)(uintptr_t)(MOEQ_LDS char*)&S.A[0][0];
+#pragma unroll 4
+    for (int i = 0; i < kBGroups * 4 / kBWaves; ++i) {
+      const int o = wave + i * kBWaves;
+      dma16(src + o * 64, a0 + (uint32_t)o * 1024u);
+    }
+  }
+  {
+    const int g = threadIdx.x >> 4, m = threadIdx.x & 15;         // 512 threads = 32 groups x 16 pairs
+    const int tok = item.pair[m < item.n ? m : 0] / G.k;
+    S.XS[g][m] = G.XS[(size_t)tok * kBGroups + g];
+    S.SX[g][m] = -code_offset<BITS>() * G.XSUM[(size_t)tok * kBGroups + g];
+  }
+  const int total = (u1 - u0) * Set::SPU;
+  auto issue = [&](Set& R, int s) __attribute__((always_inline)) {
+    const bool live = s < total;                   // past the end: cached bytes, so that every path issues the same loads
+    const uint32_t unit = (uint32_t)(u0 + s / Set::SPU), h0 = (uint32_t)(s % Set::SPU) * Set::NH;
+    const uint32_t row = unit * 128u + (uint32_t)(wave * 16 + n);
+    const uint32_t blk = row / RB, rr = row % RB;
+    const uint32_t off = live ? blk * BB + rr * (TPR * 1024u) + (uint32_t)kb * 16u + h0 * 64u : (uint32_t)lane * 16u;
+    const uint32_t sg = live ? blk * BB + 8192u + (rr / (RB > 1 ? (RB / 2) : 1)) * RB + ((rr % (RB / 2 > 0 ? RB / 2 : 1)) >> 1) * 4u : 0u;
+    // (8 bits: RB = 2, the word of group g holds both rows' scales; 2 and 4 bits: the half block's word)
+    const uint32_t soff = live ? (BITS == 8 ? blk * BB + 8192u : sg) + h0 * 2u * (2u * RB) : (uint32_t)lane * 4u;
+#pragma unroll
+    for (int hh = 0; hh < Set::NH; ++hh)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const uint8_t* b = live ? q[m] : xq;
+#pragma unroll
+        for (int part = 0; part < LPM; ++part)
+          R.t[(hh * NM + m) * LPM + part] = gload_u32x4(b + (off + (uint32_t)(part * 1024 + hh * 64)));
+      }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const uint8_t* b = live ? q[m] : xq;
+#pragma unroll
+      for (int i = 0; i < Set::NS; ++i) {
+        const uint32_t g = Set::GS >= 4 ? 4 * i + kb : (kb & (Set::GS - 1));
+        R.s[m][i] = gload_u32(b + (soff + (live ? g * (2u * RB) : 0u)));
+      }
+    }
+  };
+  // the A operands of a group, read from LDS while the group before it is multiplied
+  struct Operands { i32x4_t a[2][2], sx; float4 xs; };
+  auto read_a = [&](int g) __attribute__((always_inline)) {
+    Operands o;
+#pragma unroll
+    for (int op = 0; op < 2; ++op)
+#pragma unroll
+      for (int dg = 0; dg < 2; ++dg) o.a[op][dg] = __builtin_bit_cast(i32x4_t, S.A[(g * 2 + op) * 2 + dg][lane]);
+    o.sx = *(const i32x4_t*)&S.SX[g][4 * kb];
+    o.xs = *(const float4*)&S.XS[g][4 * kb];
+    return o;
+  };
+  Operands cur;
+  float acc[NM][4];
+  auto consume = [&](const Set& R, int s) __attribute__((always_inline)) {
+    const int h0 = (s % Set::SPU) * Set::NH;
+    if (s % Set::SPU == 0) {
+#pragma unroll
+      for (int m = 0; m < NM; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[m][i] = 0.f;
+    }
+    uint32_t sh[NM][Set::NS];
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int i = 0; i < Set::NS; ++i) sh[m][i] = R.s[m][i] >> (16 * (n & 1));
+#pragma unroll
+    for (int hh = 0; hh < Set::NH; ++hh) {
+      // B operands of the two groups of the step: [group][op] of every matrix
+      uint32_t w[NM][2][8];          // 2 bits: 2 words per group, 4 bits: 4, 8 bits: 8
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const uint4* t = &R.t[(hh * NM + m) * LPM];
+        if constexpr (BITS == 2) {
+          uint32_t a0 = t[0].x, a1 = t[0].y, a2 = t[0].z, a3 = t[0].w;
+          swap_halves(a0, a1);
+          swap_halves(a2, a3);
+          w[m][0][0] = a0; w[m][1][0] = a1; w[m][0][1] = a2; w[m][1][1] = a3;
+        } else if constexpr (BITS == 4) {
+          uint32_t a[4] = {t[0].x, t[0].y, t[0].z, t[0].w}, b[4] = {t[1].x, t[1].y, t[1].z, t[1].w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            swap_halves(a[j], b[j]);
+            w[m][0][j] = a[j]; w[m][1][j] = b[j];
+          }
+        } else {
+#pragma unroll
+          for (int pr = 0; pr < 2; ++pr) {
+            uint32_t a[4] = {t[2 * pr].x, t[2 * pr].y, t[2 * pr].z, t[2 * pr].w};
+            uint32_t b[4] = {t[2 * pr + 1].x, t[2 * pr + 1].y, t[2 * pr + 1].z, t[2 * pr + 1].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              swap_halves(a[j], b[j]);
+              w[m][0][4 * pr + j] = a[j]; w[m][1][4 * pr + j] = b[j];
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int gs = 0; gs < 2; ++gs) {
+        const int gl = 2 * hh + gs, g = 2 * h0 + gl;
+        __builtin_amdgcn_sched_barrier(0);        // one group's operands ahead, no more: bounds the live registers
+        const Operands next = read_a((g + 1) & (kBGroups - 1));
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          i32x4_t B[2];
+#pragma unroll
+          for (int op = 0; op < 2; ++op) {
+            if constexpr (BITS == 2) B[op] = codes16_2(w[m][gs][op]);
+            else if constexpr (BITS == 4) B[op] = codes16_4(w[m][gs][2 * op], w[m][gs][2 * op + 1]);
+            else B[op] = codes16_8(w[m][gs][4 * op], w[m][gs][4 * op + 1], w[m][gs][4 * op + 2], w[m][gs][4 * op + 3]);
+          }
+          i32x4_t dl = mfma_i8(cur.a[0][0], B[0], cur.sx);
+          i32x4_t dh = mfma_i8(cur.a[0][1], B[0], (i32x4_t){0, 0, 0, 0});
+          dl = mfma_i8(cur.a[1][0], B[1], dl);
+          dh = mfma_i8(cur.a[1][1], B[1], dh);
+          const float sc = f16_bits_to_f32((uint32_t)__builtin_amdgcn_ds_bpermute(4 * (n + 16 * (gl & 3)), (int)sh[m][gl >> 2]) & 0xffffu);
+          const float xf[4] = {cur.xs.x, cur.xs.y, cur.xs.z, cur.xs.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[m][i] = fmaf((float)(dl[i] + (dh[i] << 8)) * xf[i], sc, acc[m][i]);
+        }
+        cur = next;
+        // the sums are finished here: otherwise the compiler sinks them behind the loads and keeps every product alive
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(acc[m][i]));
+      }
+    }
+  };
+  Set R0, R1;
+  issue(R0, 0);
+  issue(R1, 1);
+  stage_wait<16>();                            // the operands have landed; the sixteen 16-byte loads behind them stay in flight
+  __syncthreads();
+  cur = read_a(0);
+  for (int s = 0; s < total; s += 2) {         // (SPU is even: a unit ends with a pair of sets)
+    consume(R0, s);
+    issue(R0, s + 2);
+    consume(R1, s + 1);
+    issue(R1, s + 3);
+    if ((s + 2) % Set::SPU == 0) {
+      // ---- the unit is complete: its 128 rows are scale group `unit` of h
+      const int unit = u0 + s / Set::SPU, hb = unit & 1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float a = acc[0][i];
+        float v;
+        if constexpr (SWIGLU) v = a / (1.0f + __expf(-a)) * acc[NM - 1][i];
+        else v = fmaxf(a, 0.f);
+        S.H[hb][4 * kb + i][wave * 16 + n] = v;
+      }
+      __syncthreads();
+      // half of the wavefronts, in turn, write the digits: 16 threads per pair, eight columns each
+      if ((wave >> 2) == hb) {
+        const int t8 = threadIdx.x & 255, m = t8 >> 4, seg = t8 & 15;
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = S.H[hb][m][8 * seg + i];
+        int xi[8], sum;
+        const float hs = group_ints(v, xi, sum);
+        uint32_t half[2][4];             // 2 bits: byte pairs (column q, q + 4 of the half word) of both digits
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+          half[0][qd] = lo_byte(xi[qd]) | lo_byte(xi[qd + 4]) << 8;
+          half[1][qd] = hi_byte(xi[qd]) | hi_byte(xi[qd + 4]) << 8;
+        }
+        uint32_t other[2][4];
+        if constexpr (BITS == 2) {
+#pragma unroll
+          for (int dg = 0; dg < 2; ++dg)
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) other[dg][qd] = (uint32_t)dppi<kDppXor1>((int)half[dg][qd]);
+        }
+        if (m < item.n) {
+          const size_t pair = item.pair[m];
+          if (seg == 0) {
+            G.HS[pair * NG + unit] = hs;
+            G.HSUM[pair * NG + unit] = sum;
+          }
+          uint8_t* dst = G.HQ + pair * (size_t)(2 * G.L.d_ff) + (size_t)unit * 256;
+#pragma unroll
+          for (int dg = 0; dg < 2; ++dg) {
+            uint32_t by[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) by[i] = dg ? hi_byte(xi[i]) : lo_byte(xi[i]);
+            if constexpr (BITS == 4) {           // the thread's columns are word `seg` of the group: op, half of the piece, kb
+              uint8_t* o = dst + ((seg >> 3) * 2 + dg) * 64 + (seg & 3) * 16 + ((seg >> 2) & 1) * 8;
+              *(uint2*)o = make_uint2(by[0] | by[2] << 8 | by[4] << 16 | by[6] << 24, by[1] | by[3] << 8 | by[5] << 16 | by[7] << 24);
+            } else if constexpr (BITS == 2) {    // half of word seg >> 1: the even thread writes dwords 0, 1, the odd one 2, 3
+              const int wd = seg >> 1, odd = seg & 1;
+              uint8_t* o = dst + ((wd >> 2) * 2 + dg) * 64 + (wd & 3) * 16 + odd * 8;
+              const uint32_t d0 = odd ? (other[dg][2] | half[dg][2] << 16) : (half[dg][0] | other[dg][0] << 16);
+              const uint32_t d1 = odd ? (other[dg][3] | half[dg][3] << 16) : (half[dg][1] | other[dg][1] << 16);
+              *(uint2*)o = make_uint2(d0, d1);
+            } else {                             // words 2 seg and 2 seg + 1
+#pragma unroll
+              for (int i = 0; i < 2; ++i) {
+                const int wd = 2 * seg + i;
+                uint8_t* o = dst + ((wd >> 4) * 2 + dg) * 64 + (wd & 3) * 16 + ((wd >> 2) & 3) * 4;
+                *(uint32_t*)o = by[4 * i] | by[4 * i + 1] << 8 | by[4 * i + 2] << 16 | by[4 * i + 3] << 24;
+              }
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
+// Grid: one workgroup per compute unit (the operands take most of its LDS). The units of all items form one list, cut
+// into ranges of equal weight (a unit costs its bytes: the bitwidth, plus the scales), one per workgroup; a workgroup's
+// range lies in one or two items.
+template <bool SWIGLU>
+__global__ __launch_bounds__(512) void k_batch_in(BatchArgs G) {
+  extern __shared__ __attribute__((aligned(16))) char bsmem[];
+  BatchInLds& S = *(BatchInLds*)bsmem;
+  constexpr int NM = SWIGLU ? 2 : 1;
+  const int n_items = batch_items(G, S.lists);
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < n_items * 2; i += 512) ((uint4*)G.items)[i] = ((const uint4*)S.lists.items)[i];
+    if (threadIdx.x == 0) *G.n_items = n_items;
+  }
+  const int NU = G.L.d_ff / kBGroup;
+  int64_t total = 0;
+  for (int i = 0; i < n_items; ++i) total += 8 * S.lists.items[i].bits + 1;
+  total *= NU;
+  const int64_t lo = total * blockIdx.x / gridDim.x, hi = total * (blockIdx.x + 1) / gridDim.x;
+  int64_t base = 0;
+  for (int i = 0; i < n_items; ++i) {
+    const int bits = __builtin_amdgcn_readfirstlane(S.lists.items[i].bits);
+    const int64_t c = 8 * bits + 1;
+    // units whose start weight lies in [lo, hi)
+    const int64_t a = lo > base ? (lo - base + c - 1) / c : 0, b = hi > base ? (hi - base + c - 1) / c : 0;
+    const int u0 = __builtin_amdgcn_readfirstlane((int)(a < NU ? a : NU)), u1 = __builtin_amdgcn_readfirstlane((int)(b < NU ? b : NU));
+    if (u0 < u1) {
+      const BatchItem& item = S.lists.items[i];
+      if (bits == 2) batch_in_units<2, NM, SWIGLU>(G, S, item, u0, u1);
+      else if (bits == 4) batch_in_units<4, NM, SWIGLU>(G, S, item, u0, u1);
+      else batch_in_units<8, NM, SWIGLU>(G, S, item, u0, u1);
+    }
+    base += c * NU;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// W_out in columns: word w of row r is the 32-bit word w * d_model + r. Lane (n, kb) loads word column 4 j + kb of the
+// rows 4 n .. 4 n + 3 of its wavefront's 64 rows (four runs of 256 consecutive bytes per load); operand i of a load
+// belongs to the rows 4 n + i.
+template <int BITS>
+struct BatchOutSet {
+  static constexpr int LPG = BITS;                 // loads per scale group (128 columns: 4 * BITS word columns)
+  static constexpr int GS = 8 / LPG;               // groups per set of eight loads
+  uint4 t[8];
+  uint2 s[GS];
+};
+
+struct BatchOutLds {
+  uint4 A[kBOutGroups * 4][64];
+  float XS[kBOutGroups][kBTok];
+  int32_t SX[kBOutGroups][kBTok];
+};
+
+template <int BITS>
+__device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, const BatchItem& item) {
+  using Set = BatchOutSet<BITS>;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, kb = lane >> 4;
+  const int NG = G.L.d_ff / kBGroup;
+  const int g0 = blockIdx.y * kBOutGroups, ng = min(kBOutGroups, NG - g0);
+  const int r0 = blockIdx.x * kBOutRows + wave * 64 + 4 * n;
+  const DevExpert* ex = G.table + item.e;
+  const uint8_t* q = uniform_ptr(ex->q_out);
+  const uint8_t* sc = (const uint8_t*)uniform_ptr(ex->s_out);
+  {
+    const int pm = item.pair[n < item.n ? n : 0];
+    const uint8_t* src = G.HQ + (size_t)pm * (size_t)(2 * G.L.d_ff) + (size_t)g0 * 256 + kb * 16;
+    const uint32_t a0 = (uint32_t)(uintptr_t)(MOEQ_LDS char*)&S.A[0][0];
+    for (int i = 0; i < kBOutGroups; ++i) {
+      const int o = wave + 4 * i;                  // operands of the groups that exist
+      if (o < ng * 4) dma16(src + o * 64, a0 + (uint32_t)o * 1024u);
+    }
+  }
+  if (threadIdx.x < kBOutGroups * kBTok) {
+    const int g = threadIdx.x >> 4, m = threadIdx.x & 15;
+    if (g < ng) {
+      const size_t at = (size_t)item.pair[m < item.n ? m : 0] * NG + g0 + g;
+      S.XS[g][m] = G.HS[at];
+      S.SX[g][m] = -code_offset<BITS>() * G.HSUM[at];
+    }
+  }
+  const int n_sets = (ng + Set::GS - 1) / Set::GS;
+  const uint32_t col = (uint32_t)kBD * 4u;         // bytes of a word column
+  const uint32_t lane_off = (uint32_t)kb * col + (uint32_t)r0 * 4u;
+  auto issue = [&](Set& R, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int gi = 0; gi < Set::GS; ++gi) {
+      const int g = min(g0 + s * Set::GS + gi, NG - 1);       // groups past the end: loaded again, not used
+      const uint8_t* qg = q + (size_t)g * (4 * BITS) * col;
+#pragma unroll
+      for (int j = 0; j < Set::LPG; ++j) R.t[gi * Set::LPG + j] = gload_u32x4(qg + (size_t)(4 * j) * col + lane_off);
+      R.s[gi] = gload_u32x2(sc + (size_t)g * (kBD * 2) + (uint32_t)r0 * 2u);
+    }
+  };
+  float acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+  auto consume = [&](const Set& R, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int gi = 0; gi < Set::GS; ++gi) {
+      const int g = s * Set::GS + gi;
+      if (g < ng) {
+        i32x4_t A[2][2];
+#pragma unroll
+        for (int op = 0; op < 2; ++op)
+#pragma unroll
+          for (int dg = 0; dg < 2; ++dg) A[op][dg] = __builtin_bit_cast(i32x4_t, S.A[(g * 2 + op) * 2 + dg][lane]);
+        const i32x4_t sx = *(const i32x4_t*)&S.SX[g][4 * kb];
+        const float4 xs = *(const float4*)&S.XS[g][4 * kb];
+        const float xf[4] = {xs.x, xs.y, xs.z, xs.w};
+        const uint32_t s4[4] = {R.s[gi].x & 0xffffu, R.s[gi].x >> 16, R.s[gi].y & 0xffffu, R.s[gi].y >> 16};
+        const uint4* t = &R.t[gi * Set::LPG];
+        auto word = [&](int j, int i) { return i == 0 ? t[j].x : i == 1 ? t[j].y : i == 2 ? t[j].z : t[j].w; };
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          i32x4_t B[2];
+#pragma unroll
+          for (int op = 0; op < 2; ++op) {
+            if constexpr (BITS == 2) B[op] = codes16_2(word(op, i));
+            else if constexpr (BITS == 4) B[op] = codes16_4(word(2 * op, i), word(2 * op + 1, i));
+            else B[op] = codes16_8(word(4 * op, i), word(4 * op + 1, i), word(4 * op + 2, i), word(4 * op + 3, i));
+          }
+          i32x4_t dl = mfma_i8(A[0][0], B[0], sx);
+          i32x4_t dh = mfma_i8(A[0][1], B[0], (i32x4_t){0, 0, 0, 0});
+          dl = mfma_i8(A[1][0], B[1], dl);
+          dh = mfma_i8(A[1][1], B[1], dh);
+          const float scf = f16_bits_to_f32(s4[i]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf((float)(dl[j] + (dh[j] << 8)) * xf[j], scf, acc[i][j]);
+        }
+      }
+    }
+  };
+  Set R0, R1;
+  issue(R0, 0);
+  issue(R1, 1);
+  stage_wait<16>();
+  __syncthreads();
+  for (int s = 0; s < n_sets; s += 2) {
+    consume(R0, s);
+    issue(R0, s + 2);
+    consume(R1, s + 1);
+    issue(R1, s + 3);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int m = 4 * kb + j;
+    if (m < item.n)
+      *(float4*)(G.part + ((size_t)blockIdx.y * (size_t)(G.T * G.k) + item.pair[m]) * kBD + r0) =
+          make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
+  }
+}
+
+// Grid (row chunks, chunks of d_ff, upper bound of the items).
+__global__ __launch_bounds__(256) void k_batch_out(BatchArgs G) {
+  __shared__ BatchOutLds S;
+  __shared__ BatchItem item;
+  if ((int)blockIdx.z >= *G.n_items) return;
+  if (threadIdx.x < 2) ((uint4*)&item)[threadIdx.x] = ((const uint4*)(G.items + blockIdx.z))[threadIdx.x];
+  __syncthreads();
+  const int bits = __builtin_amdgcn_readfirstlane(item.bits);
+  if (bits == 2) batch_out<2>(G, S, item);
+  else if (bits == 4) batch_out<4>(G, S, item);
+  else batch_out<8>(G, S, item);
+}
+
+// y[t][r] (+)= sum_j gate[t][j] * sum_c part[c][t k + j][r], chunks and choices in order. gate null: 1.
+__global__ __launch_bounds__(256) void k_batch_combine(const float* __restrict__ part, const float* __restrict__ gate,
+                                                       int n_chunks, int T, int k, int accumulate, float* __restrict__ y) {
+  const int t = blockIdx.y, r = (blockIdx.x * 256 + threadIdx.x) * 4;
+  float* o = y + (size_t)t * kBD + r;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  if (accumulate)
+    for (int i = 0; i < 4; ++i) v[i] = o[i];
+  for (int j = 0; j < k; ++j) {
+    const float* p = part + (size_t)(t * k + j) * kBD + r;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int c = 0; c < n_chunks; ++c) {
+      const float4 w = *(const float4*)(p + (size_t)c * T * k * kBD);
+      a.x += w.x; a.y += w.y; a.z += w.z; a.w += w.w;
+    }
+    const float g = gate ? gate[(size_t)t * k + j] : 1.0f;
+    v[0] = fmaf(g, a.x, v[0]); v[1] = fmaf(g, a.y, v[1]); v[2] = fmaf(g, a.z, v[2]); v[3] = fmaf(g, a.w, v[3]);
+  }
+  for (int i = 0; i < 4; ++i) o[i] = v[i];
+}
+
+inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
+
+int batch_cus() {
+  static const int cus = [] {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    return n;
+  }();
+  return cus;
+}
+
+}  // namespace
+
+// Byte offsets of the path's pieces in the workspace; k: choices per token (1 for a single expert's call).
+BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask) {
+  BatchWs w{};
+  const size_t P = (size_t)T * (size_t)k, NG = (size_t)L.d_ff / kBGroup;
+  size_t off = 0;
+  w.items = off;  off += up256(P * sizeof(BatchItem));
+  w.n_items = off; off += 256;
+  w.xq = off;     off += up256((size_t)__builtin_popcount((unsigned)bits_mask & 14u) * (size_t)T * 2 * kBD);
+  w.xs = off;     off += up256((size_t)T * kBGroups * 4);
+  w.xsum = off;   off += up256((size_t)T * kBGroups * 4);
+  w.hq = off;     off += up256(P * 2 * (size_t)L.d_ff);
+  w.hs = off;     off += up256(P * NG * 4);
+  w.hsum = off;   off += up256(P * NG * 4);
+  w.part = off;   off += up256((NG + kBOutGroups - 1) / kBOutGroups * P * kBD * 4);
+  w.total = off;
+  return w;
+}
+
+int batch_inline_router_max() { return kBInlineMaxE; }
+
+hipError_t init_attrs_decode_batch() {
+  (void)batch_cus();
+  if (hipError_t e = hipFuncSetAttribute((const void*)k_batch_in<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BatchInLds));
+      e != hipSuccess)
+    return e;
+  return hipFuncSetAttribute((const void*)k_batch_in<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BatchInLds));
+}
+
+hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
+                            bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T, int32_t* idx,
+                            float* gate, const float* gate_out, int32_t accumulate, char* ws, float* y, hipStream_t st) {
+  const int k = fixed_expert >= 0 ? 1 : L.top_k;
+  if (!stream_supported(L) || T < 1 || (int64_t)T * k > kBatchMaxPairs || !(bits_mask & 14)) return hipErrorInvalidValue;
+  if (route_inline && (fixed_expert >= 0 || L.n_experts > kBInlineMaxE)) return hipErrorInvalidValue;
+  if (fixed_expert < 0 && (!idx || !gate)) return hipErrorInvalidValue;
+  const BatchWs w = batch_ws(L, T, k, bits_mask);
+  BatchArgs G{L, table, router_w, router_bias, x, T, k, fixed_expert, bits_mask & 14, route_inline ? 1 : 0, idx, gate,
+              (uint8_t*)(ws + w.xq), (float*)(ws + w.xs), (int32_t*)(ws + w.xsum), (uint8_t*)(ws + w.hq),
+              (float*)(ws + w.hs), (int32_t*)(ws + w.hsum), (BatchItem*)(ws + w.items), (int32_t*)(ws + w.n_items),
+              (float*)(ws + w.part)};
+  const int P = T * k;
+  const int max_items = P < L.n_experts + P / kBTok ? P : L.n_experts + P / kBTok;
+  const int chunks = (L.d_ff / kBGroup + kBOutGroups - 1) / kBOutGroups;
+  hipLaunchKernelGGL(k_batch_prep, dim3(T), dim3(512), 0, st, G);
+  if (L.act == MOEQ_ACT_SWIGLU) hipLaunchKernelGGL(k_batch_in<true>, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
+  else hipLaunchKernelGGL(k_batch_in<false>, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
+  hipLaunchKernelGGL(k_batch_out, dim3(kBD / kBOutRows, chunks, max_items), dim3(256), 0, st, G);
+  hipLaunchKernelGGL(k_batch_combine, dim3(kBD / 1024, T), dim3(256), 0, st, G.part, gate_out, chunks, T, k, accumulate, y);
+  return hipGetLastError();
+}
+
+}  // namespace moeq

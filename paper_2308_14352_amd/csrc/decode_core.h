@@ -37,6 +37,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // FLAT loads, which count on the LDS counter as well, so that every wait for an LDS read would also wait
 // for all weight loads in flight.
 #define MOEQ_GLOBAL __attribute__((address_space(1)))
+#define MOEQ_LDS __attribute__((address_space(3)))
 // 16-byte load with the non-temporal hint: packed weights are read once per call and should not
 // displace the activations and scales that are reused from the caches.
 __device__ __forceinline__ uint4 load_stream16(const uint8_t* ptr) {
@@ -357,6 +358,8 @@ template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
+template <int CTRL>
+__device__ __forceinline__ int dppi(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
 constexpr int kDppXor1 = 0xB1;   // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;   // quad_perm [2,3,0,1]
 constexpr int kDppRor4 = 0x124;  // row_ror:4  (rotation inside a 16-lane row)
@@ -457,6 +460,25 @@ __device__ __forceinline__ const T* uniform_ptr(const T* ptr) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return (const T*)(((uint64_t)hi << 32) | lo);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Direct HBM -> LDS loads: lane l's 16 (4) bytes land at lds_base + 16 l (4 l); lds_base (an LDS byte address) is
+// wave-uniform and goes through M0. They are issued through asm statements: the compiler's wait-count pass would
+// otherwise make every later LDS read wait for all of them, which would serialise the ring. stage_wait states how
+// many of the wavefront's youngest loads may still be in flight. (M0 is a register the compiler reserves and never
+// keeps a value in across other code in these kernels, which use it nowhere else.)
+__device__ __forceinline__ void dma16(const uint8_t* g, uint32_t lds_base) {
+  const uint32_t base = __builtin_amdgcn_readfirstlane(lds_base);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(base) : "memory");
+}
+__device__ __forceinline__ void dma4(const uint8_t* g, uint32_t lds_base) {
+  const uint32_t base = __builtin_amdgcn_readfirstlane(lds_base);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(base) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void stage_wait() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
 // ---------------------------------------------------------------------------------------------

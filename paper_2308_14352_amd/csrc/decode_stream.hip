@@ -46,9 +46,6 @@ constexpr int kMaxBlocks = 8 * 12; // blocks of a wavefront's list: 8 experts x 
 __device__ __forceinline__ int sdot8(uint32_t a, uint32_t b, int c) { return __builtin_amdgcn_sdot8((int)a, (int)b, c, false); }
 __device__ __forceinline__ int sdot4(uint32_t a, uint32_t b, int c) { return __builtin_amdgcn_sdot4((int)a, (int)b, c, false); }
 
-template <int CTRL>
-__device__ __forceinline__ int dppi(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
-
 // Rows of one block of the stream layout: a block is eight tiles.
 __host__ __device__ constexpr int stream_rows_per_block(int bits) { return 16 / bits; }          // 8, 4, 2
 __host__ __device__ constexpr uint32_t stream_block_bytes(int bits) { return 8192u + 64u * (16u / (uint32_t)bits); }

@@ -35,8 +35,6 @@ constexpr int kItemTiles = 2;  // token tiles per GEMM work item (128 tokens)
 // row group); WV / kItemTiles row groups.
 __host__ __device__ constexpr int gemm_streams(int phase, int wv) { return (phase == 1 || wv == 16) ? 2 : 4; }
 
-#define MOEQ_LDS __attribute__((address_space(3)))
-
 // Staged operand of one GEMM (x for GEMM 1, h for GEMM 2; K = its length), per token tile (64 tokens of an expert):
 //   [K / 128 tiles of 16 KB]  tile = the 1 KB lines of one 128-column range: line (q, kb) holds, for each of the
 //                             64 tokens, the 16 bytes that are A operand q of k block kb (at 8 bits a K step is
@@ -200,24 +198,6 @@ struct GemmArgs {
   float* Hf;                // GEMM 1 out: h per pair, fp32 [pairs][d_ff]
   float* Y;                 // GEMM 2 out: [pairs][d_model]
 };
-
-// Direct HBM -> LDS loads: lane l's 16 (4) bytes land at lds_base + 16 l (4 l); lds_base (an LDS byte address) is
-// wave-uniform and goes through M0. They are issued through asm statements: the compiler's wait-count pass would
-// otherwise make every later LDS read wait for all of them, which would serialise the ring. stage_wait states how
-// many of the wavefront's youngest loads may still be in flight. (M0 is a register the compiler reserves and never
-// keeps a value in across other code in these kernels, which use it nowhere else.)
-__device__ __forceinline__ void dma16(const uint8_t* g, uint32_t lds_base) {
-  const uint32_t base = __builtin_amdgcn_readfirstlane(lds_base);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(base) : "memory");
-}
-__device__ __forceinline__ void dma4(const uint8_t* g, uint32_t lds_base) {
-  const uint32_t base = __builtin_amdgcn_readfirstlane(lds_base);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(base) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void stage_wait() {
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
 
 // COLS: GEMM 2 on a W_out in the dword-column-major layout. SIN: GEMM 1 on W_in / W_gate in the row-block stream
 // layout (blocks of RB = 16 / bits rows: 8 tiles of 1 KB, then 64 * RB bytes of scales; 16-byte piece c of row r is

@@ -1,0 +1,95 @@
+"""GPU parity of decode calls of a few tokens on stream layers (pairs grouped by expert, weights streamed once for up to
+16 pairs): the edges of its items, units and chunks."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+import gen
+import oracle
+import paper_2308_14352_amd as moeq
+from helpers import build_layer_pair, near_tie_tokens, oracle_layer, rel_err
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# x and h enter with one exponent per 128 values and 15 bits below it: an element is off by at most 2^-16 of its group's
+# largest (about 3.5 standard deviations), 6e-5 / sqrt(3) of a standard deviation, once for x and once for h; the largest
+# of 4096 outputs' errors (4 standard deviations) against the largest output (again about 4) stays near that figure. The
+# gate product and fp32 sums add less. 4e-4 leaves a factor of five.
+TOL = 4e-4
+
+
+@pytest.mark.parametrize("base,x_dtype,f,k,bits_table,tokens", [
+    ("c4", "bf16", 128, 2, [2, 4, 8], (2, 3, 16)),          # one unit, one chunk
+    ("c4", "f32", 1152, 2, [8, 2, 4, 4], (15, 17, 31)),     # nine scale groups: a last chunk of one
+    ("c4", "bf16", 1536, 2, [4, 2], (16, 31)),              # every token on both experts: two items of each
+    ("c1", "f32", 640, 1, [2, 8, 4], (7, 31)),              # ReLU, top-1
+    ("c4", "f32", 384, 5, [2, 2, 4, 8, 8, 4], (31,)),       # five choices: 155 pairs
+    ("c1", "bf16", 256, 2, [2 + 2 * (i % 2) for i in range(66)], (9,)),    # more experts than are routed in the kernel
+], ids=("one-unit", "nine-groups", "two-items", "relu", "top5", "66-experts"))
+def test_grouped_decode_calls(base, x_dtype, f, k, bits_table, tokens):
+    cfg = replace(gen.tiny_config(base, 4096, f, n_experts=len(bits_table), n_layers=1, group=128), top_k=k, x_dtype=x_dtype)
+    layer, orc_experts, Wr, bias = build_layer_pair(cfg, 0, DEV, bits_table, stream=True)
+    x = gen.hidden(cfg, 0, 0, max(tokens), DEV)
+    y_ref, idx_ref, gate_ref = oracle_layer(cfg, orc_experts, Wr, bias, x)
+    skip = set(near_tie_tokens(cfg, Wr, bias, x).tolist())
+    first = None
+    for T in tokens:
+        assert layer.path(T) == moeq.MOEQ_PATH_STREAM
+        y, idx, gate = moeq.moe_layer_forward(layer, x[:T], want_routing=True)
+        y_r = moeq.moe_layer_forward_routed(layer, x[:T], idx, gate)
+        torch.cuda.synchronize()
+        keep = [t for t in range(T) if t not in skip]
+        assert len(keep) >= T - 2
+        assert np.array_equal(idx.cpu().numpy()[keep], idx_ref[keep])
+        assert np.allclose(gate.cpu().numpy()[keep], gate_ref[keep], rtol=2e-5, atol=1e-7)
+        assert rel_err(y.cpu().numpy()[keep], y_ref[keep]).max() < TOL
+        assert torch.equal(y, y_r)
+        # a token's result does not depend on the tokens that share its call
+        first = y if first is None else first
+        n = min(T, first.shape[0])
+        assert torch.equal(y[:n], first[:n])
+    # the single-token kernel routes the same way, bit for bit
+    _, idx1, gate1 = moeq.moe_layer_forward(layer, x[:1], want_routing=True)
+    torch.cuda.synchronize()
+    assert torch.equal(idx1, idx[:1]) and torch.equal(gate1, gate[:1])
+
+
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("T", (2, 17, 33))
+def test_grouped_single_expert_call(bits, T):
+    cfg = replace(gen.tiny_config("c4", 4096, 1152, n_experts=2, n_layers=1, group=128), x_dtype="f32")
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits, bits], stream=True)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    gate = torch.linspace(0.2, 1.1, T, device=DEV)
+    y0 = gen.normal((T, cfg.d_model), 0.1, 7, DEV)
+    y = moeq.moe_expert_ffn_q(layer, 1, x, gate=gate)
+    y_acc = moeq.moe_expert_ffn_q(layer, 1, x, gate=gate, y=y0.clone(), accumulate=True)
+    torch.cuda.synchronize()
+    ref = gate.cpu().numpy()[:, None] * oracle.expert_ffn(orc_experts[1], cfg.d_model, cfg.d_ff, cfg.group, 1, x.cpu().numpy())
+    assert rel_err(y.cpu().numpy(), ref).max() < TOL
+    assert rel_err((y_acc - y0).cpu().numpy(), ref).max() < TOL + 1e-5
+
+
+def test_grouped_call_with_the_ungrouped_workspace():
+    """A workspace that only the ungrouped form of a call fits is still taken (a narrow layer with many choices)."""
+    cfg = replace(gen.tiny_config("c4", 4096, 128, n_experts=8, n_layers=1, group=128), top_k=8, x_dtype="f32")
+    layer, orc_experts, Wr, bias = build_layer_pair(cfg, 0, DEV, [4] * 8, stream=True)
+    T = 4
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    need = layer.workspace_bytes(T)
+    slices = cfg.d_ff // 64
+    small = need
+    y = moeq.moe_layer_forward(layer, x, ws=torch.empty(need, dtype=torch.uint8, device=DEV))
+    # the ungrouped form: routing, logits and T * slices partial vectors
+    part = T * slices * cfg.d_model * 4
+    up = lambda v: (v + 255) // 256 * 256
+    small = 2 * up(T * 8 * 4) + up(T * 8 * 4) + up(part)
+    assert small < need
+    y2 = moeq.moe_layer_forward(layer, x, ws=torch.empty(small, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    y_ref, _, _ = oracle_layer(cfg, orc_experts, Wr, bias, x)
+    assert rel_err(y.cpu().numpy(), y_ref).max() < TOL and rel_err(y2.cpu().numpy(), y_ref).max() < 2e-3
+    with pytest.raises(moeq.MoeqError):
+        moeq.moe_layer_forward(layer, x, ws=torch.empty(small - 1, dtype=torch.uint8, device=DEV))
