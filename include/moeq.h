@@ -156,8 +156,10 @@ size_t moe_workspace_bytes(const moeq_layer *layer, int32_t max_tokens);
  * caller or a test can know it beforehand). The three paths compute the same layer (Section 3.1, the
  * MoE layer: router, top-k experts, gate-weighted sum). Returns -1 for a null layer or n_tokens < 1.
  * Host-only. */
-#define MOEQ_PATH_TWO_KERNELS 0    /* canonical layout: router, phase-1 and phase-2 GEMV kernels          */
-#define MOEQ_PATH_ONE_KERNEL 1     /* columns layout: one streaming kernel per 32 tokens, vector instr.   */
+#define MOEQ_PATH_TWO_KERNELS 0    /* canonical layout: router, phase-1 and phase-2 GEMV kernels (ReLU layers from 32
+                                      tokens on: the pairs grouped by expert, each streamed once for 16 or 32 of them) */
+#define MOEQ_PATH_ONE_KERNEL 1     /* columns layout: one streaming kernel per 32 tokens, vector instr. (ReLU layers
+                                      from 32 tokens on: grouped, as above)                                */
 #define MOEQ_PATH_ONE_KERNEL_MX 2  /* columns layout: the same with matrix-core instructions              */
 #define MOEQ_PATH_GROUPED_GEMM 3   /* 32 tokens or more, either layout: pairs grouped by expert, GEMMs   */
 #define MOEQ_PATH_STREAM 4         /* stream + columns layouts: streaming kernels on integer dot products (one token: one

@@ -39,8 +39,9 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Workspace carving. Both paths keep idx, gate and logits; the two-kernel path adds the chosen experts'
 // records and h (fp32), the one-kernel path the partial output vectors.
 struct WsLayout {
-  size_t idx_off, gate_off, logits_off, sel_off, h_off, part_off, prefill_off, batch_off, total;
+  size_t idx_off, gate_off, logits_off, sel_off, h_off, part_off, prefill_off, batch_off, group_off, total;
   bool batch;      // the call runs the grouped streaming kernels (decode_batch.hip)
+  bool group;      // ... the grouped GEMMs of narrow layers (group_gemm.hip)
 };
 
 // Calls with at least this many tokens run as grouped GEMMs on the matrix cores (when the shape allows);
@@ -56,9 +57,14 @@ bool use_prefill(const moeq_layer* layer, int64_t T);
 constexpr int64_t kBatchMinTokens = 2;
 inline int64_t batch_tokens(int32_t k) { return kBatchMaxPairs / k; }
 
-// batch: whether calls on a stream layer may take the grouped form (its pieces share the place of the partial vectors).
+// Calls of at least this many tokens on a ReLU layer that use_prefill does not take group their pairs by expert as well;
+// they are taken in launches of at most group_max_pairs() pairs.
+constexpr int64_t kGroupMinTokens = 32;
+inline int64_t group_tokens(int32_t k) { return group_max_pairs() / k; }
+
+// grouped: whether a call may take a grouped form (its pieces share the place of the partial vectors, or lie behind h).
 // A call whose workspace holds the ungrouped form only runs that one.
-WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool batch = true) {
+WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true) {
   const LayerDims& L = layer->dims;
   WsLayout w{};
   const size_t slots = (size_t)T * L.top_k;
@@ -66,6 +72,10 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool batch = true) {
   w.gate_off = align_up(slots * sizeof(int32_t), 256);
   w.logits_off = w.gate_off + align_up(slots * sizeof(float), 256);
   const size_t tail = w.logits_off + align_up((size_t)T * (size_t)L.n_experts * sizeof(float), 256);
+  w.group = grouped_forms && T >= kGroupMinTokens && layer->in_layout == MOEQ_IN_CANONICAL && !use_prefill(layer, T) &&
+            group_supported(L);
+  w.group_off = tail;
+  const size_t group_total = w.group ? group_ws(L, (T < group_tokens(L.top_k) ? T : group_tokens(L.top_k)) * L.top_k).total : 0;
   if (layer->out_layout == MOEQ_OUT_COLUMNS) {
     const size_t chunk = (size_t)(T < kDecodeChunk ? T : kDecodeChunk);
     const size_t part = align_up(chunk * (size_t)layer->plan.n_slices * (size_t)L.d_model * sizeof(float), 256);
@@ -73,7 +83,7 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool batch = true) {
     w.prefill_off = tail;           // a call uses one of the two
     const size_t grouped = use_prefill(layer, T) ? prefill_ws(L, T).total : 0;
     size_t most = part > grouped ? part : grouped;
-    w.batch = batch && layer->in_layout == MOEQ_IN_STREAM && T >= kBatchMinTokens;
+    w.batch = grouped_forms && layer->in_layout == MOEQ_IN_STREAM && T >= kBatchMinTokens;
     if (w.batch) {
       // (the layer calls and, with one choice per token, the single-expert call)
       const int64_t nk = T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), n1 = T < batch_tokens(1) ? T : batch_tokens(1);
@@ -82,6 +92,7 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool batch = true) {
       if (bk > most) most = bk;
       if (b1 > most) most = b1;
     }
+    if (group_total > most) most = group_total;
     w.total = tail + most;
   } else {
     w.sel_off = tail;
@@ -91,6 +102,7 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool batch = true) {
       w.prefill_off = w.total;
       w.total = w.prefill_off + prefill_ws(L, T).total;
     }
+    if (tail + group_total > w.total) w.total = tail + group_total;      // (in the place of sel and h)
   }
   return w;
 }
@@ -115,7 +127,7 @@ int inline_router_max() {
 // The layout for a call with ws_bytes of workspace: without the grouped form where only that fits.
 WsLayout ws_layout_for(const moeq_layer* layer, int64_t T, size_t ws_bytes) {
   const WsLayout w = ws_layout(layer, T);
-  return w.batch && ws_bytes < w.total ? ws_layout(layer, T, false) : w;
+  return (w.batch || w.group) && ws_bytes < w.total ? ws_layout(layer, T, false) : w;
 }
 
 inline moeq_status dev(hipError_t e) { return e == hipSuccess ? MOEQ_OK : MOEQ_EDEVICE; }
@@ -142,6 +154,21 @@ void* static_scratch() {
   }
   __atomic_store_n(&g_scratch_ptr[devid], p, __ATOMIC_RELEASE);   // racing threads store the same value
   return p;
+}
+
+// Kernel attributes belong to the device, not to a layer: set once per device (about 3 us each, thirty of them; setting
+// them again from another thread does no harm).
+hipError_t init_kernel_attrs() {
+  static uint64_t done = 0;
+  int devid = -1;
+  if (hipGetDevice(&devid) != hipSuccess) return hipErrorInvalidDevice;
+  const uint64_t bit = devid >= 0 && devid < 64 ? 1ull << devid : 0ull;
+  if (__atomic_load_n(&done, __ATOMIC_ACQUIRE) & bit) return hipSuccess;
+  for (hipError_t (*init)() : {init_attrs_decode_fused, init_attrs_ffn_decode, init_attrs_prefill, init_attrs_decode_batch,
+                               init_attrs_group_gemm})
+    if (hipError_t e = init(); e != hipSuccess) return e;
+  __atomic_fetch_or(&done, bit, __ATOMIC_RELEASE);
+  return hipSuccess;
 }
 
 // Measurement aid (moe_layer_profile_kernel): records the layer's two events around one kernel launch.
@@ -243,8 +270,7 @@ moeq_status moe_layer_create(const moeq_layer_desc* desc, void* table_dev, size_
   L->in_layout = desc->in_layout;
   L->plan = plan;
   if (hipMemcpy(table_dev, tab.data(), tab.size() * sizeof(DevExpert), hipMemcpyHostToDevice) != hipSuccess ||
-      init_attrs_decode_fused() != hipSuccess || init_attrs_ffn_decode() != hipSuccess ||
-      init_attrs_prefill() != hipSuccess || init_attrs_decode_batch() != hipSuccess) {
+      init_kernel_attrs() != hipSuccess) {
     (void)hipGetLastError();
     delete L;
     return MOEQ_EDEVICE;
@@ -356,6 +382,22 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     const PrefillWs pw = prefill_ws(L, n_tokens);
     return dev(launch_prefill(L, layer->table, x, n_tokens, idx, gate, (char*)ws + w.prefill_off, pw, y,
                               layer->out_layout == MOEQ_OUT_COLUMNS, layer->in_layout == MOEQ_IN_STREAM, st));
+  }
+  if (w.group) {
+    if (!given && (launch_router_logits(L, layer->router_w, layer->router_bias, x, n_tokens, logits, st) != hipSuccess ||
+                   launch_topk(L, logits, n_tokens, idx, gate, nullptr, st) != hipSuccess))
+      return MOEQ_EDEVICE;
+    const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
+    const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
+    ScopedEvents ev(layer, cols ? MOEQ_KERNEL_FUSED : MOEQ_KERNEL_FFN_IN, st), ev2(layer, cols ? -1 : MOEQ_KERNEL_FFN_OUT, st);
+    for (int64_t t0 = 0; t0 < n_tokens; t0 += group_tokens(L.top_k)) {
+      const int32_t n = (int32_t)(n_tokens - t0 < group_tokens(L.top_k) ? n_tokens - t0 : group_tokens(L.top_k));
+      const size_t s0 = (size_t)t0 * (size_t)L.top_k;
+      if (launch_group(L, layer->table, (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, (char*)ws + w.group_off,
+                       cols, y + (size_t)t0 * L.d_model, st) != hipSuccess)
+        return MOEQ_EDEVICE;
+    }
+    return MOEQ_OK;
   }
   if (w.batch) {
     // the pairs grouped by expert; routed inside for few experts, else by the router kernels

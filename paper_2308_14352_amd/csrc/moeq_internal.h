@@ -113,6 +113,15 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
 hipError_t launch_relayout_in(const void* q, const void* s, int64_t rows, int bits, void* stream_buf, bool to_stream,
                               hipStream_t st);
 
+// ---- calls of many tokens on ReLU layers the prefill GEMMs do not take (group_gemm.hip): at most group_max_pairs() pairs
+struct GroupWs { size_t items, n_items, gpair, ginv, hq, hs, hk, part, total; };
+bool group_supported(const LayerDims& L);
+int group_max_pairs();
+GroupWs group_ws(const LayerDims& L, int64_t M);
+hipError_t init_attrs_group_gemm();
+hipError_t launch_group(const LayerDims& L, const DevExpert* table, const void* x, int32_t T, const int32_t* idx,
+                        const float* gate, char* ws, bool out_columns, float* y, hipStream_t st);
+
 // ---- batched (prefill) path: pairs grouped by expert, two quantized GEMMs on the matrix cores ----------
 // Byte offsets of the pieces of the prefill workspace (all 256-byte aligned).
 struct PrefillWs {

@@ -1,0 +1,79 @@
+"""GPU parity of calls of 32 tokens and more on ReLU layers whose scale groups the prefill GEMMs do not take: pairs grouped
+by expert, tiles of 16 and 32 pairs, ragged widths, every group size and both W_out layouts."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+import gen
+import oracle
+import paper_2308_14352_amd as moeq
+from helpers import build_layer_pair, near_tie_tokens, oracle_layer, rel_err
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TOL = 2e-3          # the decode bar: x and h enter with 11 bits, as in the kernels that serve fewer tokens
+
+
+@pytest.mark.parametrize("d,f,group,E,k,x_dtype,T", [
+    (256, 512, 32, 4, 1, "f32", 70),            # a block per scale group; items of 32 and a rest
+    (768, 3072, 32, 8, 1, "f32", 33),           # Switch-base, three chunks of d_ff
+    (1024, 1024, 64, 16, 2, "bf16", 40),        # two blocks per group
+    (640, 1152, 128, 3, 2, "f32", 100),         # (640 / 128) is odd: not the prefill GEMMs' shape; a last chunk of 128
+    (320, 192, 64, 2, 1, "f32", 128),           # widths that are no multiple of a load or of 128 columns
+    (384, 640, 32, 40, 1, "bf16", 32),          # more experts than tokens
+    (1536, 512, 32, 5, 1, "f32", 37),           # the widest the operand tile takes with groups of 32
+])
+@pytest.mark.parametrize("columns", (False, True), ids=("canonical", "columns"))
+def test_grouped_layer(d, f, group, E, k, x_dtype, T, columns):
+    cfg = replace(gen.tiny_config("c1", d, f, n_experts=E, n_layers=1, group=group), top_k=k, x_dtype=x_dtype)
+    bits_table = [(2, 4, 8)[i % 3] for i in range(E)]
+    layer, orc_experts, Wr, bias = build_layer_pair(cfg, 0, DEV, bits_table, columns=columns)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    y, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
+    torch.cuda.synchronize()
+    y_ref, idx_ref, gate_ref = oracle_layer(cfg, orc_experts, Wr, bias, x)
+    skip = set(near_tie_tokens(cfg, Wr, bias, x).tolist())
+    keep = [t for t in range(T) if t not in skip]
+    assert len(keep) >= T - 2
+    assert np.array_equal(idx.cpu().numpy()[keep], idx_ref[keep])
+    assert np.allclose(gate.cpu().numpy()[keep], gate_ref[keep], rtol=2e-5, atol=1e-7)
+    assert rel_err(y.cpu().numpy()[keep], y_ref[keep]).max() < TOL
+    y_r = moeq.moe_layer_forward_routed(layer, x, idx, gate)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y_r)
+    # every expert with exactly 1, 16, 17, 32 and 33 pairs, on tokens of very different scales
+    rng = np.random.default_rng(d + T)
+    counts = [1, 16, 17, 32, 33]
+    e_of = np.concatenate([np.full(c, i % E) for i, c in enumerate(counts)]).astype(np.int32)
+    rng.shuffle(e_of)
+    n = len(e_of)
+    idx_g = np.stack([(e_of + j) % E for j in range(k)], 1).astype(np.int32)
+    gate_g = rng.uniform(0.1, 1.0, (n, k)).astype(np.float32)
+    xs = gen.hidden(replace(cfg, x_dtype="f32"), 0, 1, n, DEV) * torch.from_numpy(2.0 ** rng.integers(-12, 13, (n, 1))).float().to(DEV)
+    xs = xs.to(torch.bfloat16) if x_dtype == "bf16" else xs
+    y_g = moeq.moe_layer_forward_routed(layer, xs, torch.from_numpy(idx_g).to(DEV), torch.from_numpy(gate_g).to(DEV))
+    torch.cuda.synchronize()
+    y_gr = oracle.layer_forward_routed(orc_experts, d, f, group, 0, k, xs.float().cpu().numpy(), idx_g, gate_g)
+    assert rel_err(y_g.cpu().numpy(), y_gr).max() < TOL
+
+
+@pytest.mark.parametrize("columns", (False, True), ids=("canonical", "columns"))
+def test_grouped_layer_per_channel_scales(columns):
+    """One scale per channel of each matrix (groups of 256 and 768 columns)."""
+    from helpers import pack_expert_gpu, pack_expert_oracle
+    cfg = gen.tiny_config("c1", 256, 768, n_experts=3, n_layers=1)
+    ws = [gen.expert_weights(cfg, 0, e, DEV) for e in range(3)]
+    bits = [2, 4, 8]
+    gpu = [pack_expert_gpu(w, b, 256, 768) for w, b in zip(ws, bits)]
+    if columns:
+        gpu = [e.with_out_columns(cfg.d_ff, 768) for e in gpu]
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(256, 768, 1, 32, moeq.MOEQ_ACT_RELU, False, moeq.MOEQ_F32, Wr, bias, gpu,
+                       moeq.MOEQ_OUT_COLUMNS if columns else moeq.MOEQ_OUT_CANONICAL, group_in=256, group_out=768)
+    x = gen.hidden(cfg, 0, 0, 50, DEV)
+    y, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
+    y1 = torch.cat([moeq.moe_layer_forward(layer, x[t:t + 1]) for t in range(50)])     # the decode kernels, token by token
+    torch.cuda.synchronize()
+    assert rel_err(y.cpu().numpy(), y1.cpu().numpy()).max() < TOL
