@@ -61,13 +61,22 @@ __device__ __forceinline__ uint2 gload_u32x2(const uint8_t* ptr) {
   return make_uint2(v.x, v.y);
 }
 
-// v / group for a per-lane v: a shift when the group size is a power of two (gsh = its log2, else -1), the
-// (40-instruction) division otherwise. gsh is uniform, so this is a branch, not a select.
+// a / b for 0 <= a < 2^21, b > 0: the quotient of the floats is off by less than 2^-21 of itself, the nearest integer
+// boundary of (a + 1/2) / b is 1 / (2 b) away. Five instructions. The kernels of the small layers execute almost every
+// instruction once per launch, and a launch finds the instruction caches cold: some 300 cycles per 64 bytes of code, so
+// that each of the compiler's 40-instruction divisions costs as much as a memory round trip.
+__device__ __forceinline__ int small_div(int a, int b) {
+  return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+}
+// v / group for v < 2^21: a shift when the group size is a power of two (gsh = its log2, else -1).
 __device__ __forceinline__ int group_shift(int group) { return (group & (group - 1)) == 0 ? __builtin_ctz(group) : -1; }
 __device__ __forceinline__ uint32_t div_group(uint32_t v, int group, int gsh) {
   if (gsh >= 0) return v >> gsh;
-  return v / (uint32_t)group;
+  return (uint32_t)small_div((int)v, group);
 }
+
+// log2 of the lanes that share a row of C chunks: the largest power of two that divides C, at most 64
+__device__ __forceinline__ int row_lanes_log2(int C) { return min(6, (int)__builtin_ctz((unsigned)C)); }
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 __device__ __forceinline__ uint32_t f32_to_f16_bits(float v) { return (uint32_t)__half_as_ushort(__float2half_rn(v)); }
@@ -279,7 +288,8 @@ __device__ __forceinline__ void offset_terms(const uint16_t* lin, int cols, int 
   constexpr int WPC = Fmt<BITS>::WPC;
   const int sub = group < WPC ? group : WPC;   // 16, 32 or 64 weights share a scale inside a chunk
   const uint4* lin4 = (const uint4*)lin;
-  for (int s = tid; s < cols / sub; s += nthreads) {
+  const int n_sub = sub == WPC ? cols / WPC : cols >> (sub == 16 ? 4 : 5);   // (sub is 16, 32 or the chunk)
+  for (int s = tid; s < n_sub; s += nthreads) {
     float acc = 0.f;
     for (int i = 0; i < sub / 8; ++i) {
       const uint4 v = lin4[s * (sub / 8) + i];
@@ -324,7 +334,7 @@ __device__ __forceinline__ void permute_x(const uint16_t* RAW, int cols, int gro
   if constexpr (BITS == 4) {
     // chunk = 32 activations = 4 reads; quad d = dword d of the codes: pairs (k, k+4), odd k pre-divided by 16
     for (int i = tid; i < 4 * C; i += nthreads) {
-      const int q = i / C, c = i - q * C;
+      const int q = small_div(i, C), c = i - q * C;
       const uint4 v = R4[c * 4 + q];
       X4[at(i)] = make_uint4(pair_lo(v.x, v.z), pair_scale(pair_hi(v.x, v.z), 0.0625f), pair_lo(v.y, v.w),
                              pair_scale(pair_hi(v.y, v.w), 0.0625f));
@@ -332,7 +342,7 @@ __device__ __forceinline__ void permute_x(const uint16_t* RAW, int cols, int gro
   } else if constexpr (BITS == 8) {
     // chunk = 16 activations = 2 reads; quad q = dwords 2q, 2q+1 of the codes: pairs (k, k+2)
     for (int i = tid; i < 2 * C; i += nthreads) {
-      const int q = i / C, c = i - q * C;
+      const int q = small_div(i, C), c = i - q * C;
       const uint4 v = R4[c * 2 + q];
       X4[at(i)] = make_uint4(pair_lo(v.x, v.y), pair_hi(v.x, v.y), pair_lo(v.z, v.w), pair_hi(v.z, v.w));
     }
@@ -340,7 +350,7 @@ __device__ __forceinline__ void permute_x(const uint16_t* RAW, int cols, int gro
     // chunk = 64 activations = 8 reads; dword d of the codes: pairs (j, j+8), j = 0..7, in the quads 2d
     // (j = 0..3, pre-divided by 1, 4, 16, 64) and 2d+1 (j = 4..7, pre-divided by 256, 1, 4, 16)
     for (int i = tid; i < 4 * C; i += nthreads) {
-      const int dd = i / C, c = i - dd * C;
+      const int dd = small_div(i, C), c = i - dd * C;
       const uint4 a = R4[c * 8 + 2 * dd], b = R4[c * 8 + 2 * dd + 1];
       X4[at((2 * dd) * C + c)] = make_uint4(pair_lo(a.x, b.x), pair_scale(pair_hi(a.x, b.x), 0.25f),
                                             pair_scale(pair_lo(a.y, b.y), 0.0625f), pair_scale(pair_hi(a.y, b.y), 0.015625f));
@@ -505,22 +515,22 @@ __device__ __forceinline__ void gemv_stream(const uint8_t* const (&q)[NM], const
   static_assert(NR <= kBlock && kBlock % NR == 0, "rows in flight must divide the block");
   constexpr int CPB = kBlock / NR;  // chunk steps per block
   const int C = cols / WPC;
-  int P = 1;
-  while (P < 64 && C % (P * 2) == 0) P *= 2;
-  const int RW = 64 / P;
-  const int p = lane % P, rsub = lane / P;
+  const int lp = row_lanes_log2(C), P = 1 << lp;
+  const int RW = 64 >> lp;
+  const int p = lane & (P - 1), rsub = lane >> lp;
   // The nwaves wavefronts form ks_parts teams; team `part` covers the chunk steps
   // [jb, jb + J) of every row, and its wavefronts share the tasks. epilogue gets partial sums then.
-  const int wpp = nwaves / ks_parts;            // wavefronts per team
-  const int part = wave / wpp, tw = wave - part * wpp;
-  const int Jfull = C / P;
-  const int jb = (part * Jfull) / ks_parts;
-  const int J = (wave < nwaves) ? ((part + 1) * Jfull) / ks_parts - jb : 0;
-  const int ng = cols / group;
+  const int ksh = __builtin_ctz((unsigned)ks_parts);   // ks_parts is 1, 2 or 4
+  const int wpp = nwaves >> ksh;                // wavefronts per team
+  const int part = small_div(wave, wpp), tw = wave - part * wpp;
+  const int Jfull = C >> lp;
+  const int jb = (part * Jfull) >> ksh;
+  const int J = (wave < nwaves) ? (((part + 1) * Jfull) >> ksh) - jb : 0;
   const int gsh = group_shift(group);
+  const int ng = (int)div_group((uint32_t)cols, group, gsh);
   const int task_rows = RW * NRM;
-  const int n_tasks = (row_end - row_begin + task_rows - 1) / task_rows;
-  const int n_my = (wave < nwaves && tw < n_tasks) ? (n_tasks - tw + wpp - 1) / wpp : 0;
+  const int n_tasks = (row_end - row_begin + task_rows - 1) >> (6 - lp + (NRM == 4 ? 2 : NRM == 2 ? 1 : 0));
+  const int n_my = (wave < nwaves && tw < n_tasks) ? small_div(n_tasks - tw + wpp - 1, wpp) : 0;
   const int S = n_my * J;  // chunk steps of this wavefront (0: it only takes part in stage())
   const uint4* XP4 = (const uint4*)XP;
   const uint32_t jstride = (uint32_t)P * 16u;
@@ -629,11 +639,7 @@ __device__ __forceinline__ void gemv_stream(const uint8_t* const (&q)[NM], const
   }
 }
 
-__host__ __device__ inline int lanes_per_row(int chunks) {
-  int P = 1;
-  while (P < 64 && chunks % (P * 2) == 0) P *= 2;
-  return P;
-}
+__host__ __device__ inline int lanes_per_row(int chunks) { return 1 << (__builtin_ctz((unsigned)chunks) < 6 ? __builtin_ctz((unsigned)chunks) : 6); }
 
 // Rows per lane group and matrix in one task: as many (up to nrm_max) as still leave every wavefront of
 // the workgroup a task, and never more than P (the fold needs NRM <= P).

@@ -81,42 +81,48 @@ __device__ __forceinline__ int layout_slot(int bits_mask, int bits) {
 // and row. The tiles (one 128-bit load per lane, plus its scale) of a wavefront are grouped in bursts
 // of RGB row groups x JC chunk steps x NM matrices (four tiles); a wavefront walks the bursts of its
 // row-group sets (J/JC bursts per set) with two register sets: the loads of
-// burst b+1 are issued before the arithmetic of burst b, so 4 to 8 loads per lane are always in flight.
+// burst b+1 are issued before the arithmetic of burst b, so 4 to 8 loads per lane are always in flight. stage() is called
+// once by every thread, behind the first burst's requests and before any activation is read: what it takes to get the
+// activations into LDS (barriers included) overlaps with the latency of the first weights.
 template <int BITS, int NM, int JC, int RGB>
 struct P1Burst {
   uint4 t[RGB][JC][NM];
   uint32_t sc[RGB][JC][NM];
 };
 
-template <int BITS, int NM, int JC, int RGB, typename Epilogue>
+template <int BITS, int NM, int JC, int RGB, typename Epilogue, typename Stage>
 __device__ __forceinline__ void p1_stream(const uint8_t* const (&q)[NM], const uint8_t* const (&s)[NM], int d,
-                                          int group, int row_begin, int n_rows, int P, int J, int lane, int wave,
-                                          int nwaves, const uint32_t* XP, const float* XK, Epilogue epilogue) {
+                                          int group, int row_begin, int n_rows, int lp, int J, int lane, int wave,
+                                          int nwaves, const uint32_t* XP, const float* XK, Epilogue epilogue,
+                                          Stage stage) {
   constexpr int WPC = Fmt<BITS>::WPC, PPC = Fmt<BITS>::PPC;
   using Burst = P1Burst<BITS, NM, JC, RGB>;
   const int C = d / WPC;
-  const int RW = 64 / P;
-  const int n_rg = (n_rows + RW - 1) / RW;
+  const int P = 1 << lp, RW = 64 >> lp;
+  const int n_rg = (n_rows + RW - 1) >> (6 - lp);
   const int n_sets = (n_rg + RGB - 1) / RGB;
   const int JB = J / JC;                                                     // bursts per row-group set
   // Wavefront w owns the contiguous run of sets [w*spw, (w+1)*spw) and starts at a position that depends
   // on the workgroup: at any moment the loads of a workgroup are spread over its whole block of rows, and
   // those of different workgroups over different parts of theirs, which keeps all memory channels busy
   // (workgroups walking their blocks in lockstep would otherwise hit the same few channels together).
-  const int spw = (n_sets + nwaves - 1) / nwaves;
+  const int spw = small_div(n_sets + nwaves - 1, nwaves);
   const int set_begin = wave * spw;
   const int my_sets = max(0, min(spw, n_sets - set_begin));
-  const int rot = my_sets > 0 ? (int)blockIdx.x % my_sets : 0;
+  const int rot = my_sets > 1 ? (int)blockIdx.x - my_sets * small_div((int)blockIdx.x, my_sets) : 0;
   const int nb = my_sets * JB;
-  const int p = lane & (P - 1), rsub = lane / P;
+  const int p = lane & (P - 1), rsub = lane >> lp;
   const uint32_t row_bytes = (uint32_t)C * 16u;
-  const uint32_t ng2 = (uint32_t)(d / group) * 2u;
   const int gsh = group_shift(group);
+  const uint32_t ng2 = div_group((uint32_t)d, group, gsh) * 2u;
   const bool two = (BITS == 2) && (group == 32);
   const uint4* XP4 = (const uint4*)XP;
 
-  auto issue = [&](Burst& B, int b) __attribute__((always_inline)) {
-    const int si = b / JB, j0 = (b - si * JB) * JC;
+  int is = 0, ij = 0, cs = 0, cj = 0;             // set and first chunk step of the next burst to request / to consume
+  auto issue = [&](Burst& B) __attribute__((always_inline)) {
+    const int si = is, j0 = ij;
+    ij += JC;
+    if (ij == J) { ij = 0; ++is; }
     const int sr = si + rot < my_sets ? si + rot : si + rot - my_sets;
     const int rg0 = (set_begin + sr) * RGB;
 #pragma unroll
@@ -140,8 +146,10 @@ __device__ __forceinline__ void p1_stream(const uint8_t* const (&q)[NM], const u
   };
 
   float tot[NM * RGB];
-  auto compute = [&](const Burst& B, int b) __attribute__((always_inline)) {
-    const int si = b / JB, j0 = (b - si * JB) * JC;
+  auto compute = [&](const Burst& B) __attribute__((always_inline)) {
+    const int si = cs, j0 = cj;
+    cj += JC;
+    if (cj == J) { cj = 0; ++cs; }
     const int sr = si + rot < my_sets ? si + rot : si + rot - my_sets;
     const int rg0 = (set_begin + sr) * RGB;
     if (j0 == 0) {
@@ -201,45 +209,47 @@ __device__ __forceinline__ void p1_stream(const uint8_t* const (&q)[NM], const u
   };
 
   Burst A, Bb;
-  if (nb > 0) issue(A, 0);
+  if (nb > 0) issue(A);
+  stage();
   for (int b = 0; b < nb; b += 2) {
-    if (b + 1 < nb) issue(Bb, b + 1);
-    compute(A, b);
-    if (b + 2 < nb) issue(A, b + 2);
-    if (b + 1 < nb) compute(Bb, b + 1);
+    if (b + 1 < nb) issue(Bb);
+    compute(A);
+    if (b + 2 < nb) issue(A);
+    if (b + 1 < nb) compute(Bb);
   }
 }
 
-// Phase 1 of one expert on the SW rows of its slice: the h values go to LDS as fp32 (HF); `up` undoes the
-// normalisation of the staged activations.
-template <int BITS, bool SWIGLU>
-__device__ __forceinline__ void fused_in(const DevExpert* ex, int tid, int nwaves, int d, int group, int row_begin,
-                                         int SW, float up, float* HF, const uint32_t* XP, const float* XK) {
+// Phase 1 of one expert on the SW rows of its slice: the h values go to LDS as fp32 (HF); *up (written by stage()) undoes
+// the normalisation of the staged activations. ex: uniform pointers.
+template <int BITS, bool SWIGLU, typename Stage>
+__device__ __forceinline__ void fused_in(const DevExpert& ex, int tid, int nwaves, int d, int group, int row_begin,
+                                         int SW, const float* upp, float* HF, const uint32_t* XP, const float* XK, Stage stage) {
   constexpr int NM = SWIGLU ? 2 : 1;
   const int C = d / Fmt<BITS>::WPC;
-  const int P = lanes_per_row(C), J = C / P;
+  const int lp = row_lanes_log2(C), P = 1 << lp, J = C >> lp;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto epi = [&](int row, const float (&r)[NM]) __attribute__((always_inline)) {
+    const float up = *upp;
     const float a = r[0] * up;
     float v;
     if constexpr (SWIGLU) v = a / (1.0f + __expf(-a)) * (r[NM - 1] * up);
     else v = fmaxf(a, 0.f);
     HF[row - row_begin] = v;
   };
-  const uint8_t* q0 = uniform_ptr(ex->q_in);
-  const uint8_t* s0 = (const uint8_t*)uniform_ptr(ex->s_in);
-  const uint8_t* q1 = SWIGLU ? uniform_ptr(ex->q_gate) : nullptr;
-  const uint8_t* s1 = SWIGLU ? (const uint8_t*)uniform_ptr(ex->s_gate) : nullptr;
+  const uint8_t* q0 = uniform_ptr(ex.q_in);
+  const uint8_t* s0 = (const uint8_t*)uniform_ptr(ex.s_in);
+  const uint8_t* q1 = SWIGLU ? uniform_ptr(ex.q_gate) : nullptr;
+  const uint8_t* s1 = SWIGLU ? (const uint8_t*)uniform_ptr(ex.s_gate) : nullptr;
   auto run = [&](auto jc_tag, auto rgb_tag) __attribute__((always_inline)) {
     constexpr int JC = decltype(jc_tag)::value, RGB = decltype(rgb_tag)::value;
     if constexpr (SWIGLU) {
       const uint8_t* const qq[2] = {q0, q1};
       const uint8_t* const ss[2] = {s0, s1};
-      p1_stream<BITS, 2, JC, RGB>(qq, ss, d, group, row_begin, SW, P, J, lane, wave, nwaves, XP, XK, epi);
+      p1_stream<BITS, 2, JC, RGB>(qq, ss, d, group, row_begin, SW, lp, J, lane, wave, nwaves, XP, XK, epi, stage);
     } else {
       const uint8_t* const qq[1] = {q0};
       const uint8_t* const ss[1] = {s0};
-      p1_stream<BITS, 1, JC, RGB>(qq, ss, d, group, row_begin, SW, P, J, lane, wave, nwaves, XP, XK, epi);
+      p1_stream<BITS, 1, JC, RGB>(qq, ss, d, group, row_begin, SW, lp, J, lane, wave, nwaves, XP, XK, epi, stage);
     }
   };
   // A burst is four tiles: two chunk steps when a row has an even number of them, and as many row groups
@@ -262,11 +272,11 @@ __device__ __forceinline__ void fused_in(const DevExpert* ex, int tid, int nwave
 // normalised by its own power of two (stage_normalised's rule, over the SW values of the slice), converted to
 // binary16 and stored linear (HL) and in the pair layout of the expert's bitwidth (HP); uph[j] receives the
 // factor that undoes the normalisation. One wavefront per expert, SW <= 256.
-__device__ __forceinline__ void stage_h_slices(const float* HF, int k, int SW, const DevExpert* tabp, const int* sel_e,
-                                               uint16_t* HLs, uint16_t* HPs, float* uph, int lane, int wave,
+template <typename BitsOf>
+__device__ __forceinline__ void stage_h_slices(const float* HF, int k, int SW, BitsOf bits_of, uint16_t* HLs, uint16_t* HPs, float* uph, int lane, int wave,
                                                int nwaves) {
   for (int j = wave; j < k; j += nwaves) {
-    const int bits = __builtin_amdgcn_readfirstlane(tabp[sel_e[j]].bits);
+    const int bits = bits_of(j);
     float v[4];
     float m = 0.f;
 #pragma unroll
@@ -340,7 +350,7 @@ __device__ __forceinline__ void fused_out(P2Burst<BITS, DWC>& first, const uint8
   const float K = hs * (Fmt<BITS>::OFF * 5.9604644775390625e-08f);
   const uint32_t* HPw = (const uint32_t*)HP;
   const int nrb = d / 4;
-  const int RB = (nrb + nthreads - 1) / nthreads;
+  const int RB = small_div(nrb + nthreads - 1, nthreads);
   auto consume = [&](const P2Burst<BITS, DWC>& cur, int wb, float (&acc)[RBC][4]) __attribute__((always_inline)) {
 #pragma unroll
     for (int w = 0; w < DWC; ++w) {
@@ -403,15 +413,15 @@ __device__ __forceinline__ void fused_out(P2Burst<BITS, DWC>& first, const uint8
 // flight across them. gate: the expert's gate times the factor that undoes the normalisation of its h,
 // read through a pointer because it is known only after the staging.
 template <int BITS, int DWC, typename Between>
-__device__ __forceinline__ void fused_expert_out(const DevExpert* ex, int tid, int nthreads, int d, int group,
+__device__ __forceinline__ void fused_expert_out(const DevExpert& ex, int tid, int nthreads, int d, int group,
                                                  int slice, int SW, float gate_j, const float* uph_j,
                                                  bool first_expert, const uint16_t* HL, const uint16_t* HP, float4* Y,
                                                  Between between) {
   // first_expert: the call that also waits for phase 1 (of every expert) to be complete
   constexpr int CPD = 32 / BITS;
   // this slice's first word column of the codes, and its scale group, as uniform pointers
-  const uint8_t* qT_s = uniform_ptr(ex->q_out) + (size_t)(slice * (SW / CPD)) * ((size_t)d * 4);
-  const uint8_t* sT_g = (const uint8_t*)uniform_ptr(ex->s_out) + (size_t)((slice * SW) / group) * ((size_t)d * 2);
+  const uint8_t* qT_s = uniform_ptr(ex.q_out) + (size_t)(slice * (SW / CPD)) * ((size_t)d * 4);
+  const uint8_t* sT_g = (const uint8_t*)uniform_ptr(ex.s_out) + (size_t)div_group((uint32_t)(slice * SW), group, group_shift(group)) * ((size_t)d * 2);
   P2Burst<BITS, DWC> first;
   p2_issue<BITS, DWC>(first, qT_s, sT_g, d, d / 4, tid, nthreads, 0, true);
   if (first_expert) {
@@ -719,10 +729,9 @@ __device__ __forceinline__ void mx2_compute(const MxSet2& S, const MxWalk2& w, i
   }
 }
 
-// MAXT: the largest workgroup the variant is launched with (small layers run 256 threads and then have four
-// times the registers per thread).
-template <bool SWIGLU, bool MX, int MAXT = 1024>
-__global__ __launch_bounds__(MAXT) void k_moe_decode(FusedParams P) {
+// The matrix-core variant.
+template <bool SWIGLU>
+__global__ __launch_bounds__(1024) void k_moe_decode_mx(FusedParams P) {
   extern __shared__ uint32_t smem[];
   __shared__ int sel_e[8];
   __shared__ float sel_g[8];
@@ -859,19 +868,18 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode(FusedParams P) {
     if (lane < k) sel_e[lane] = min(max(sel_e[lane], 0), E - 1);
   };
   auto stage_layouts = [&](int st, int sn) __attribute__((always_inline)) {
-    // behind the staged pairs of a bitwidth: its offset terms (matrix-core variant: negated, per range of
-    // a lane column)
+    // behind the staged pairs of a bitwidth: its offset terms (negated, per range of a lane column)
     if (P.bits_mask & 2) {
       uint32_t* XPs = LAY + layout_slot(P.bits_mask, 2) * lay_words;
-      permute_x<2, MX>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
+      permute_x<2, true>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
     }
     if (P.bits_mask & 4) {
       uint32_t* XPs = LAY + layout_slot(P.bits_mask, 4) * lay_words;
-      permute_x<4, MX>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
+      permute_x<4, true>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
     }
     if (P.bits_mask & 8) {
       uint32_t* XPs = LAY + layout_slot(P.bits_mask, 8) * lay_words;
-      permute_x<8, MX>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
+      permute_x<8, true>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
     }
   };
   auto publish_routing = [&]() __attribute__((always_inline)) {
@@ -881,7 +889,7 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode(FusedParams P) {
     }
   };
 
-  if constexpr (MX) {
+  {
     constexpr int NM = SWIGLU ? 2 : 1;
     if (wave == 0) {
       route();
@@ -1025,7 +1033,8 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode(FusedParams P) {
       MxSet2 A, B;
       issue2(A);                      // ns >= 1
       __syncthreads();                // the h slices of all chosen experts are complete in LDS (fp32)
-      stage_h_slices(HF, k, SW, tabp, sel_e, HLs, HPs, uph, lane, wave, nwaves);
+      stage_h_slices(HF, k, SW, [&](int j) { return __builtin_amdgcn_readfirstlane(tabp[sel_e[j]].bits); }, HLs, HPs, uph,
+                     lane, wave, nwaves);
       __syncthreads();                // ... and staged for phase 2
       // as in phase 1, a wavefront's priority falls with the sets it has left
       auto prio2 = [&](int left) __attribute__((always_inline)) {
@@ -1055,36 +1064,219 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode(FusedParams P) {
       __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();   // Y was written by the lanes that hold the instruction results, it is read by all
-  } else {
-  if (wave == 0) route();
-  else stage_layouts(threadIdx.x - 64, nthreads - 64);
-  __syncthreads();  // layouts, sel_e, sel_g are complete
-  publish_routing();
+  }
+  float4* out = (float4*)(P.part + ((size_t)token * gridDim.x + slice) * d);
+  for (int rb = threadIdx.x; rb < d / 4; rb += nthreads) out[rb] = Y[rb];
+}
+
+// The vector variant. For the small layers it serves, its duration is a chain of memory round trips, so the chain is kept
+// short: activations, router logits (or rows) and expert records are requested together; every wavefront routes for
+// itself and requests its first weights at once; the activations are normalised and put in pair order (for the chosen
+// experts' bitwidths only) while those are in flight.
+// MAXT: the largest workgroup the variant is launched with (small layers run 256 threads and then have four
+// times the registers per thread).
+template <bool SWIGLU, int MAXT>
+__global__ __launch_bounds__(MAXT) void k_moe_decode_vec(FusedParams P) {
+  extern __shared__ uint32_t smem[];
+  constexpr int MAXW = MAXT / 64;
+  __shared__ int sel_ew[MAXW][8];
+  __shared__ float sel_gw[MAXW][8];
+  __shared__ float lgw[MAXW][kInlineMaxE];
+  __shared__ float rpart[kInlineMaxE * kMaxSegs];         // router partial sums, unit u = e * n_seg + seg
+  __shared__ float red[16];                               // per-wavefront maxima of |x|
+  __shared__ float uph[8];                                // per chosen expert: undoes the normalisation of its h slice
+  __shared__ float s_up;                                  // undoes the normalisation of the activations
+  const LayerDims& L = P.L;
+  const int d = L.d_model, E = L.n_experts, SW = P.SW;
+  const int token = blockIdx.y;
+  const int slice = (gridDim.x & 7u) == 0 ? (int)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3))
+                                          : (int)blockIdx.x;      // as in k_moe_decode_mx
+  const int nthreads = blockDim.x, nwaves = nthreads >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k = P.fixed_expert >= 0 ? 1 : L.top_k;
+  const int lay_words = d / 2 + d / 16;
+  const bool bf16 = L.x_bf16 != 0;
+  uint16_t* RAW = (uint16_t*)smem;                 // the carve of k_moe_decode_mx
+  uint16_t* HLs = RAW + d;
+  uint16_t* HPs = HLs + k * SW;
+  float4* Y = (float4*)(HPs + k * SW);
+  float* HF = (float*)(Y + d / 4);
+  uint32_t* LAY = (uint32_t*)(HF + k * SW);
+  const char* xt = (const char*)P.x + (size_t)token * d * (bf16 ? 2 : 4);
+  const bool routed = P.fixed_expert < 0;
+  const bool given = routed && P.route_idx != nullptr;
+  const bool inline_router = routed && !P.logits && !given;
+  const int xkind = bf16 ? X_BF16 : X_F32;
+  const int n_items = d / 8;
+
+  // ---- requests that depend on nothing but the inputs: the activations (a thread's first 8 values stay in registers until
+  // the largest magnitude of the vector is known), and in lane e the record of expert e (up to 64 experts)
+  XItem xit;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) xit.v[q] = 0.f;
+  if ((int)threadIdx.x < n_items) xit = load_x_item(xt, xkind, threadIdx.x);
+  // (workgroups of more than 256 threads have no registers to spare for them)
+  const bool lane_recs = MAXT <= 256 && routed && E <= 64;
+  uint4 rec[4];
+  if constexpr (MAXT <= 256) {
+    const uint4* src = (const uint4*)(P.table + (lane_recs ? min(lane, E - 1) : 0));
+    rec[0] = src[0];
+    if constexpr (SWIGLU) rec[1] = src[1];
+    rec[2] = src[2];
+    rec[3] = src[3];
+  }
+  // router work unit = (expert, segment of seg_cols columns), one wavefront each; segments are sized so
+  // that the units about fill the wavefronts, at most eight 128-bit loads of the router row per lane
+  int n_seg = (d + 2047) / 2048;
+  if (inline_router) {
+    while (n_seg * 2 <= kMaxSegs && E * n_seg * 2 <= nwaves && d >= n_seg * 2 * 256) n_seg *= 2;
+    const int seg_cols = (small_div(d + n_seg - 1, n_seg) + 255) / 256 * 256;
+    for (int u = wave; u < E * n_seg; u += nwaves) {
+      const int e = small_div(u, n_seg), seg = u - e * n_seg;
+      const float* wr = P.Wr + (size_t)e * d;
+      const int c_end = min(d, (seg + 1) * seg_cols);
+      float4 w[8], v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int i = seg * seg_cols + q * 256 + lane * 4;
+        w[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        v[q] = w[q];
+        if (i < c_end) {
+          w[q] = *(const float4*)(wr + i);
+          if (bf16) {
+            const uint2 b = *(const uint2*)((const uint16_t*)xt + i);
+            v[q] = make_float4(bf16_bits_to_f32(b.x & 0xffffu), bf16_bits_to_f32(b.x >> 16),
+                               bf16_bits_to_f32(b.y & 0xffffu), bf16_bits_to_f32(b.y >> 16));
+          } else {
+            v[q] = *(const float4*)((const float*)xt + i);
+          }
+        }
+      }
+      float acc = 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        acc = fmaf(w[q].x, v[q].x, acc); acc = fmaf(w[q].y, v[q].y, acc);
+        acc = fmaf(w[q].z, v[q].z, acc); acc = fmaf(w[q].w, v[q].w, acc);
+      }
+      acc = wave_sum(acc);
+      if (lane == 0) rpart[u] = acc;
+    }
+  }
+  auto publish_max = [&]() __attribute__((always_inline)) {
+    float m = item_absmax(xit);
+    for (int i = threadIdx.x + nthreads; i < n_items; i += nthreads) m = fmaxf(m, item_absmax(load_x_item(xt, xkind, i)));
+    m = wave_max(m);
+    if (lane == 0) red[wave] = m;
+  };
+  if (inline_router) {
+    publish_max();
+    __syncthreads();  // red, rpart are complete
+  }
+
+  // ---- the routing, by every wavefront for itself (identical arithmetic, identical result)
+  int* sel_e = sel_ew[wave];
+  float* sel_g = sel_gw[wave];
+  if (given) {
+    if (lane < k) {
+      sel_e[lane] = P.route_idx[(size_t)token * k + lane];
+      sel_g[lane] = P.route_gate[(size_t)token * k + lane];
+    }
+  } else if (routed) {
+    if (inline_router) {
+      float* lg = lgw[wave];
+      if (lane < E) {
+        float t = 0.f;
+        for (int sg = 0; sg < n_seg; ++sg) t += rpart[lane * n_seg + sg];
+        lg[lane] = t + (P.bias ? P.bias[lane] : 0.f);
+      }
+      topk_from_logits(lg, E, k, L.renorm, lane, sel_e, sel_g, nullptr);
+    } else {
+      topk_from_logits(P.logits + (size_t)token * E, E, k, L.renorm, lane, sel_e, sel_g, nullptr);
+    }
+  } else if (lane == 0) {
+    sel_e[0] = P.fixed_expert;
+    sel_g[0] = P.gate_in ? P.gate_in[token] : 1.0f;
+  }
+  // the indices become addresses of expert records: whatever produced them, they stay inside the table
+  if (lane < k) sel_e[lane] = min(max(sel_e[lane], 0), E - 1);
+  if (routed && !given && slice == 0 && (int)threadIdx.x < k) {
+    if (P.idx_out) P.idx_out[(size_t)token * k + threadIdx.x] = sel_e[threadIdx.x];
+    if (P.gate_out) P.gate_out[(size_t)token * k + threadIdx.x] = sel_g[threadIdx.x];
+  }
+  // the record of choice j, as uniform values
+  auto record = [&](int j) __attribute__((always_inline)) {
+    const int e = __builtin_amdgcn_readfirstlane(sel_e[j]);
+    DevExpert ex;
+    if (MAXT <= 256 && lane_recs) {
+      auto rl = [&](uint32_t v) __attribute__((always_inline)) { return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)v, e); };
+      ex.q_in = (const uint8_t*)(rl(rec[0].x) | rl(rec[0].y) << 32);
+      ex.s_in = (const uint16_t*)(rl(rec[0].z) | rl(rec[0].w) << 32);
+      if constexpr (SWIGLU) {
+        ex.q_gate = (const uint8_t*)(rl(rec[1].x) | rl(rec[1].y) << 32);
+        ex.s_gate = (const uint16_t*)(rl(rec[1].z) | rl(rec[1].w) << 32);
+      }
+      ex.q_out = (const uint8_t*)(rl(rec[2].x) | rl(rec[2].y) << 32);
+      ex.s_out = (const uint16_t*)(rl(rec[2].z) | rl(rec[2].w) << 32);
+      ex.bits = (int)rl(rec[3].x);
+    } else {
+      ex = P.table[e];
+      ex.bits = __builtin_amdgcn_readfirstlane(ex.bits);
+    }
+    return ex;
+  };
+  // ---- behind the first weights' requests: the activations, normalised, in the pair order of every chosen bitwidth
+  auto stage_x = [&]() __attribute__((always_inline)) {
+    if (!inline_router) {
+      publish_max();
+      __syncthreads();  // red is complete
+    }
+    float M = 0.f;
+    for (int w = 0; w < nwaves; ++w) M = fmaxf(M, red[w]);
+    const int e = norm_exponent(M);
+    const float dn = pow2f(-e);
+    if (threadIdx.x == 0) s_up = pow2f(e);
+    uint4* RAW4 = (uint4*)RAW;
+    if ((int)threadIdx.x < n_items) RAW4[threadIdx.x] = item_to_f16(xit, dn);
+    for (int i = threadIdx.x + nthreads; i < n_items; i += nthreads) RAW4[i] = item_to_f16(load_x_item(xt, xkind, i), dn);
+    int want = 0;
+    for (int j = 0; j < k; ++j) want |= record(j).bits;
+    __syncthreads();  // RAW is complete
+    const int st = threadIdx.x;
+    if (want & 2) {
+      uint32_t* XPs = LAY + layout_slot(P.bits_mask, 2) * lay_words;
+      permute_x<2>(RAW, d, L.group, st, nthreads, XPs, (float*)(XPs + d / 2));
+    }
+    if (want & 4) {
+      uint32_t* XPs = LAY + layout_slot(P.bits_mask, 4) * lay_words;
+      permute_x<4>(RAW, d, L.group, st, nthreads, XPs, (float*)(XPs + d / 2));
+    }
+    if (want & 8) {
+      uint32_t* XPs = LAY + layout_slot(P.bits_mask, 8) * lay_words;
+      permute_x<8>(RAW, d, L.group, st, nthreads, XPs, (float*)(XPs + d / 2));
+    }
+    __syncthreads();  // the layouts and s_up are complete
+  };
   // ---- phase 1 of every chosen expert, back to back: no wavefront waits for another one here
   for (int j = 0; j < k; ++j) {
-    const int e = sel_e[j];
-    const DevExpert* ex = tab_in_lds ? &tab[e] : &P.table[e];
-    const int bits = __builtin_amdgcn_readfirstlane(ex->bits);
-    const uint32_t* XP = LAY + layout_slot(P.bits_mask, bits) * lay_words;
+    const DevExpert ex = record(j);
+    const uint32_t* XP = LAY + layout_slot(P.bits_mask, ex.bits) * lay_words;
     const float* XK = (const float*)(XP + d / 2);
+    auto stage = [&]() __attribute__((always_inline)) { if (j == 0) stage_x(); };
     int tid = threadIdx.x;  // opaque copy: keeps the per-bitwidth lane arithmetic inside this iteration
     asm volatile("" : "+v"(tid));
-    switch (bits) {
-      case 2: fused_in<2, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, up, HF + j * SW, XP, XK); break;
-      case 4: fused_in<4, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, up, HF + j * SW, XP, XK); break;
-      default: fused_in<8, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, up, HF + j * SW, XP, XK); break;
+    switch (ex.bits) {
+      case 2: fused_in<2, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, &s_up, HF + j * SW, XP, XK, stage); break;
+      case 4: fused_in<4, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, &s_up, HF + j * SW, XP, XK, stage); break;
+      default: fused_in<8, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, &s_up, HF + j * SW, XP, XK, stage); break;
     }
   }
   // ---- phase 2 of every chosen expert (the first one's call holds the barriers between the phases and the
   // staging of h between them)
-  const DevExpert* tabv = tab_in_lds ? tab : P.table;
   auto between = [&]() __attribute__((always_inline)) {
-    stage_h_slices(HF, k, SW, tabv, sel_e, HLs, HPs, uph, lane, wave, nwaves);
+    stage_h_slices(HF, k, SW, [&](int j) { return record(j).bits; }, HLs, HPs, uph, lane, wave, nwaves);
   };
   for (int j = 0; j < k; ++j) {
-    const int e = sel_e[j];
-    const DevExpert* ex = tab_in_lds ? &tab[e] : &P.table[e];
-    const int bits = __builtin_amdgcn_readfirstlane(ex->bits);
+    const DevExpert ex = record(j);
     const uint16_t* HL = HLs + j * SW;
     const uint16_t* HP = HPs + j * SW;
     const float gate = sel_g[j];
@@ -1098,16 +1290,13 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode(FusedParams P) {
       else if (DW == 2) fused_expert_out<BITS, 2>(ex, tid, nthreads, d, L.group_out, slice, SW, gate, uph + j, j == 0, HL, HP, Y, between);
       else fused_expert_out<BITS, 1>(ex, tid, nthreads, d, L.group_out, slice, SW, gate, uph + j, j == 0, HL, HP, Y, between);
     };
-    switch (bits) {
+    switch (ex.bits) {
       case 2: run(std::integral_constant<int, 2>{}); break;
       case 4: run(std::integral_constant<int, 4>{}); break;
       default: run(std::integral_constant<int, 8>{}); break;
     }
   }
-
-  }
-
-  // (vector path: every row block was accumulated by the thread that now writes it out)
+  // every row block was accumulated by the thread that now writes it out
   float4* out = (float4*)(P.part + ((size_t)token * gridDim.x + slice) * d);
   for (int rb = threadIdx.x; rb < d / 4; rb += nthreads) out[rb] = Y[rb];
 }
@@ -1243,9 +1432,9 @@ int fused_inline_router_max() { return kInlineMaxE; }
 
 hipError_t init_attrs_decode_fused() {
   (void)cu_count();
-  const void* ks[6] = {(const void*)k_moe_decode<false, false>, (const void*)k_moe_decode<true, false>,
-                       (const void*)k_moe_decode<false, true>, (const void*)k_moe_decode<true, true>,
-                       (const void*)k_moe_decode<false, false, 256>, (const void*)k_moe_decode<true, false, 256>};
+  const void* ks[6] = {(const void*)k_moe_decode_vec<false, 1024>, (const void*)k_moe_decode_vec<true, 1024>,
+                       (const void*)k_moe_decode_mx<false>, (const void*)k_moe_decode_mx<true>,
+                       (const void*)k_moe_decode_vec<false, 256>, (const void*)k_moe_decode_vec<true, 256>};
   for (const void* kf : ks)
     if (hipError_t e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBudget); e != hipSuccess)
       return e;
@@ -1267,9 +1456,9 @@ hipError_t launch_moe_decode(const LayerDims& L, const FusedPlan& plan, const De
                 idx_out, gate_out, plan.SW, bits_mask};
   const bool sw = L.act == MOEQ_ACT_SWIGLU, mx = plan.mx != 0;
   const bool small = !mx && plan.threads <= 256;
-  auto kernel = mx ? (sw ? k_moe_decode<true, true> : k_moe_decode<false, true>)
-                   : small ? (sw ? k_moe_decode<true, false, 256> : k_moe_decode<false, false, 256>)
-                           : (sw ? k_moe_decode<true, false> : k_moe_decode<false, false>);
+  auto kernel = mx ? (sw ? k_moe_decode_mx<true> : k_moe_decode_mx<false>)
+                   : small ? (sw ? k_moe_decode_vec<true, 256> : k_moe_decode_vec<false, 256>)
+                           : (sw ? k_moe_decode_vec<true, 1024> : k_moe_decode_vec<false, 1024>);
   if (lds > kFusedLdsBudget) return hipErrorInvalidValue;   // the ceiling init_attrs_decode_fused() asked for
   if (ev_start && ev_stop)
     hipExtLaunchKernelGGL(kernel, dim3(plan.n_slices, T), dim3(plan.threads), lds, st, ev_start, ev_stop, 0, P);

@@ -39,7 +39,7 @@ __device__ __forceinline__ void ffn_in_tasks(const DevExpert& ex, int tid, int n
                                              const uint32_t* XP, const float* XK, Stage stage) {
   constexpr int NM = SWIGLU ? 2 : 1;
   const int C = d / Fmt<BITS>::WPC;
-  const int P = lanes_per_row(C), RW = 64 / P;
+  const int lp = row_lanes_log2(C), P = 1 << lp, RW = 64 >> lp;
   const int lane = tid & 63, wave = tid >> 6;
   const int nrm = pick_nrm(row_end - row_begin, RW, nwaves, P, kBlock / NM);
   const bool two = (BITS == 2) && (group == 32);
@@ -209,10 +209,10 @@ __global__ __launch_bounds__(1024) void k_ffn_in(LayerDims L, const DevExpert* _
 // ---------------------------------------------------------------------------------------------
 // Number of wavefront teams that split every row of a phase-2 GEMV along its length: the rows a
 // workgroup owns are few and long, so without the split most wavefronts would have no task.
-__host__ __device__ inline int pick_ks(int rows_in_wg, int RW, int nwaves, int Jfull) {
-  const int tasks1 = (rows_in_wg + RW - 1) / RW;   // tasks at one row per lane group
+__device__ __forceinline__ int pick_ks(int rows_in_wg, int rw_log2, int nwaves, int Jfull) {
+  const int tasks1 = (rows_in_wg + (1 << rw_log2) - 1) >> rw_log2;   // tasks at one row per lane group
   int ks = 1;
-  while (ks < kMaxKs && tasks1 * ks * 2 <= nwaves && ks * 2 <= Jfull && nwaves % (ks * 2) == 0) ks *= 2;
+  while (ks < kMaxKs && tasks1 * ks * 2 <= nwaves && ks * 2 <= Jfull && (nwaves & (ks * 2 - 1)) == 0) ks *= 2;
   return ks;
 }
 
@@ -221,10 +221,10 @@ __device__ __forceinline__ void ffn_out_tasks(const DevExpert& ex, int tid, int 
                                               float g, const float* up, int row_begin, int row_end, int rows_per_wg,
                                               float* ybuf, const uint32_t* XP, const float* XK, Stage stage) {
   const int C = f / Fmt<BITS>::WPC;
-  const int P = lanes_per_row(C), RW = 64 / P;
+  const int lp = row_lanes_log2(C), P = 1 << lp, RW = 64 >> lp;
   const int lane = tid & 63, wave = tid >> 6;
-  const int ks = pick_ks(row_end - row_begin, RW, nwaves, C / P);
-  const int nrm = pick_nrm(row_end - row_begin, RW, nwaves / ks, P, kBlock);
+  const int ks = pick_ks(row_end - row_begin, 6 - lp, nwaves, C >> lp);
+  const int nrm = pick_nrm(row_end - row_begin, RW, nwaves >> __builtin_ctz((unsigned)ks), P, kBlock);
   const bool two = (BITS == 2) && (group == 32);
   const uint8_t* const qq[1] = {uniform_ptr(ex.q_out)};
   const uint16_t* const ss[1] = {uniform_ptr(ex.s_out)};
