@@ -219,17 +219,17 @@ __device__ __forceinline__ void p1_stream(const uint8_t* const (&q)[NM], const u
   }
 }
 
-// Phase 1 of one expert on the SW rows of its slice: the h values go to LDS as fp32 (HF); *up (written by stage()) undoes
-// the normalisation of the staged activations. ex: uniform pointers.
-template <int BITS, bool SWIGLU, typename Stage>
+// Phase 1 of one expert on the SW rows of its slice: the h values go to LDS as fp32 (HF); up_of() (known behind stage())
+// undoes the normalisation of the staged activations. ex: uniform pointers.
+template <int BITS, bool SWIGLU, typename UpOf, typename Stage>
 __device__ __forceinline__ void fused_in(const DevExpert& ex, int tid, int nwaves, int d, int group, int row_begin,
-                                         int SW, const float* upp, float* HF, const uint32_t* XP, const float* XK, Stage stage) {
+                                         int SW, UpOf up_of, float* HF, const uint32_t* XP, const float* XK, Stage stage) {
   constexpr int NM = SWIGLU ? 2 : 1;
   const int C = d / Fmt<BITS>::WPC;
   const int lp = row_lanes_log2(C), P = 1 << lp, J = C >> lp;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto epi = [&](int row, const float (&r)[NM]) __attribute__((always_inline)) {
-    const float up = *upp;
+    const float up = up_of();
     const float a = r[0] * up;
     float v;
     if constexpr (SWIGLU) v = a / (1.0f + __expf(-a)) * (r[NM - 1] * up);
@@ -273,8 +273,8 @@ __device__ __forceinline__ void fused_in(const DevExpert& ex, int tid, int nwave
 // binary16 and stored linear (HL) and in the pair layout of the expert's bitwidth (HP); uph[j] receives the
 // factor that undoes the normalisation. One wavefront per expert, SW <= 256.
 template <typename BitsOf>
-__device__ __forceinline__ void stage_h_slices(const float* HF, int k, int SW, BitsOf bits_of, uint16_t* HLs, uint16_t* HPs, float* uph, int lane, int wave,
-                                               int nwaves) {
+__device__ __forceinline__ void stage_h_slices(const float* HF, int k, int SW, BitsOf bits_of, uint16_t* HLs,
+                                               uint16_t* HPs, float* uph, int lane, int wave, int nwaves) {
   for (int j = wave; j < k; j += nwaves) {
     const int bits = bits_of(j);
     float v[4];
@@ -729,9 +729,10 @@ __device__ __forceinline__ void mx2_compute(const MxSet2& S, const MxWalk2& w, i
   }
 }
 
-// The matrix-core variant.
-template <bool SWIGLU>
-__global__ __launch_bounds__(1024) void k_moe_decode_mx(FusedParams P) {
+// Workgroups of up to 1024 threads: the matrix-core variant (MX), and the vector variant for the layers whose output
+// takes more than 256 threads.
+template <bool SWIGLU, bool MX>
+__global__ __launch_bounds__(1024) void k_moe_decode_wide(FusedParams P) {
   extern __shared__ uint32_t smem[];
   __shared__ int sel_e[8];
   __shared__ float sel_g[8];
@@ -868,18 +869,18 @@ __global__ __launch_bounds__(1024) void k_moe_decode_mx(FusedParams P) {
     if (lane < k) sel_e[lane] = min(max(sel_e[lane], 0), E - 1);
   };
   auto stage_layouts = [&](int st, int sn) __attribute__((always_inline)) {
-    // behind the staged pairs of a bitwidth: its offset terms (negated, per range of a lane column)
+    // behind the staged pairs of a bitwidth: its offset terms (matrix-core variant: negated, per range of a lane column)
     if (P.bits_mask & 2) {
       uint32_t* XPs = LAY + layout_slot(P.bits_mask, 2) * lay_words;
-      permute_x<2, true>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
+      permute_x<2, MX>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
     }
     if (P.bits_mask & 4) {
       uint32_t* XPs = LAY + layout_slot(P.bits_mask, 4) * lay_words;
-      permute_x<4, true>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
+      permute_x<4, MX>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
     }
     if (P.bits_mask & 8) {
       uint32_t* XPs = LAY + layout_slot(P.bits_mask, 8) * lay_words;
-      permute_x<8, true>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
+      permute_x<8, MX>(RAW, d, L.group, st, sn, XPs, (float*)(XPs + d / 2));
     }
   };
   auto publish_routing = [&]() __attribute__((always_inline)) {
@@ -889,7 +890,7 @@ __global__ __launch_bounds__(1024) void k_moe_decode_mx(FusedParams P) {
     }
   };
 
-  {
+  if constexpr (MX) {
     constexpr int NM = SWIGLU ? 2 : 1;
     if (wave == 0) {
       route();
@@ -1064,21 +1065,75 @@ __global__ __launch_bounds__(1024) void k_moe_decode_mx(FusedParams P) {
       __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();   // Y was written by the lanes that hold the instruction results, it is read by all
+  } else {
+  if (wave == 0) route();
+  else stage_layouts(threadIdx.x - 64, nthreads - 64);
+  __syncthreads();  // layouts, sel_e, sel_g are complete
+  publish_routing();
+  // ---- phase 1 of every chosen expert, back to back: no wavefront waits for another one here
+  for (int j = 0; j < k; ++j) {
+    const int e = sel_e[j];
+    const DevExpert& ex = tab_in_lds ? tab[e] : P.table[e];
+    const int bits = __builtin_amdgcn_readfirstlane(ex.bits);
+    const uint32_t* XP = LAY + layout_slot(P.bits_mask, bits) * lay_words;
+    const float* XK = (const float*)(XP + d / 2);
+    int tid = threadIdx.x;  // opaque copy: keeps the per-bitwidth lane arithmetic inside this iteration
+    asm volatile("" : "+v"(tid));
+    switch (bits) {
+      case 2: fused_in<2, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, [&] { return up; }, HF + j * SW, XP, XK, [] {}); break;
+      case 4: fused_in<4, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, [&] { return up; }, HF + j * SW, XP, XK, [] {}); break;
+      default: fused_in<8, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, [&] { return up; }, HF + j * SW, XP, XK, [] {}); break;
+    }
   }
+  // ---- phase 2 of every chosen expert (the first one's call holds the barriers between the phases and the
+  // staging of h between them)
+  const DevExpert* tabv = tab_in_lds ? tab : P.table;
+  auto between = [&]() __attribute__((always_inline)) {
+    stage_h_slices(HF, k, SW, [&](int j) { return __builtin_amdgcn_readfirstlane(tabv[sel_e[j]].bits); }, HLs, HPs, uph,
+                   lane, wave, nwaves);
+  };
+  for (int j = 0; j < k; ++j) {
+    const int e = sel_e[j];
+    const DevExpert& ex = tab_in_lds ? tab[e] : P.table[e];
+    const int bits = __builtin_amdgcn_readfirstlane(ex.bits);
+    const uint16_t* HL = HLs + j * SW;
+    const uint16_t* HP = HPs + j * SW;
+    const float gate = sel_g[j];
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    auto run = [&](auto bits_tag) __attribute__((always_inline)) {
+      constexpr int BITS = decltype(bits_tag)::value;
+      const int DW = SW * BITS / 32;
+      if (DW >= 8) fused_expert_out<BITS, 8>(ex, tid, nthreads, d, L.group_out, slice, SW, gate, uph + j, j == 0, HL, HP, Y, between);
+      else if (DW == 4) fused_expert_out<BITS, 4>(ex, tid, nthreads, d, L.group_out, slice, SW, gate, uph + j, j == 0, HL, HP, Y, between);
+      else if (DW == 2) fused_expert_out<BITS, 2>(ex, tid, nthreads, d, L.group_out, slice, SW, gate, uph + j, j == 0, HL, HP, Y, between);
+      else fused_expert_out<BITS, 1>(ex, tid, nthreads, d, L.group_out, slice, SW, gate, uph + j, j == 0, HL, HP, Y, between);
+    };
+    switch (bits) {
+      case 2: run(std::integral_constant<int, 2>{}); break;
+      case 4: run(std::integral_constant<int, 4>{}); break;
+      default: run(std::integral_constant<int, 8>{}); break;
+    }
+  }
+
+  }
+
+  // (vector path: every row block was accumulated by the thread that now writes it out)
   float4* out = (float4*)(P.part + ((size_t)token * gridDim.x + slice) * d);
   for (int rb = threadIdx.x; rb < d / 4; rb += nthreads) out[rb] = Y[rb];
 }
 
-// The vector variant. For the small layers it serves, its duration is a chain of memory round trips, so the chain is kept
-// short: activations, router logits (or rows) and expert records are requested together; every wavefront routes for
-// itself and requests its first weights at once; the activations are normalised and put in pair order (for the chosen
-// experts' bitwidths only) while those are in flight.
-// MAXT: the largest workgroup the variant is launched with (small layers run 256 threads and then have four
-// times the registers per thread).
-template <bool SWIGLU, int MAXT>
-__global__ __launch_bounds__(MAXT) void k_moe_decode_vec(FusedParams P) {
+// The vector variant for the layers that 256 threads cover (d_model up to 1024): its duration is a chain of memory round
+// trips, so the chain is kept short: activations, router logits (or rows) and expert records are requested together;
+// every wavefront routes for itself and requests its first weights at once; the activations are normalised and put in
+// pair order (for the chosen experts' bitwidths only) while those are in flight.
+// (Workgroups of more threads have no registers for a burst in flight beside the staging: with 1024 threads this order
+// spilled 144 bytes a lane and took 56 us instead of 45 for one token on a layer of d_ff 8192 with 4- and 8-bit experts.)
+constexpr int kVecThreads = 256;
+template <bool SWIGLU>
+__global__ __launch_bounds__(kVecThreads) void k_moe_decode_vec(FusedParams P) {
   extern __shared__ uint32_t smem[];
-  constexpr int MAXW = MAXT / 64;
+  constexpr int MAXW = kVecThreads / 64;
   __shared__ int sel_ew[MAXW][8];
   __shared__ float sel_gw[MAXW][8];
   __shared__ float lgw[MAXW][kInlineMaxE];
@@ -1090,13 +1145,13 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode_vec(FusedParams P) {
   const int d = L.d_model, E = L.n_experts, SW = P.SW;
   const int token = blockIdx.y;
   const int slice = (gridDim.x & 7u) == 0 ? (int)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3))
-                                          : (int)blockIdx.x;      // as in k_moe_decode_mx
+                                          : (int)blockIdx.x;      // as in k_moe_decode_wide
   const int nthreads = blockDim.x, nwaves = nthreads >> 6;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int k = P.fixed_expert >= 0 ? 1 : L.top_k;
   const int lay_words = d / 2 + d / 16;
   const bool bf16 = L.x_bf16 != 0;
-  uint16_t* RAW = (uint16_t*)smem;                 // the carve of k_moe_decode_mx
+  uint16_t* RAW = (uint16_t*)smem;                 // the carve of k_moe_decode_wide
   uint16_t* HLs = RAW + d;
   uint16_t* HPs = HLs + k * SW;
   float4* Y = (float4*)(HPs + k * SW);
@@ -1115,10 +1170,9 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode_vec(FusedParams P) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) xit.v[q] = 0.f;
   if ((int)threadIdx.x < n_items) xit = load_x_item(xt, xkind, threadIdx.x);
-  // (workgroups of more than 256 threads have no registers to spare for them)
-  const bool lane_recs = MAXT <= 256 && routed && E <= 64;
+  const bool lane_recs = routed && E <= 64;
   uint4 rec[4];
-  if constexpr (MAXT <= 256) {
+  {
     const uint4* src = (const uint4*)(P.table + (lane_recs ? min(lane, E - 1) : 0));
     rec[0] = src[0];
     if constexpr (SWIGLU) rec[1] = src[1];
@@ -1207,7 +1261,7 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode_vec(FusedParams P) {
   auto record = [&](int j) __attribute__((always_inline)) {
     const int e = __builtin_amdgcn_readfirstlane(sel_e[j]);
     DevExpert ex;
-    if (MAXT <= 256 && lane_recs) {
+    if (lane_recs) {
       auto rl = [&](uint32_t v) __attribute__((always_inline)) { return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)v, e); };
       ex.q_in = (const uint8_t*)(rl(rec[0].x) | rl(rec[0].y) << 32);
       ex.s_in = (const uint16_t*)(rl(rec[0].z) | rl(rec[0].w) << 32);
@@ -1219,8 +1273,11 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode_vec(FusedParams P) {
       ex.s_out = (const uint16_t*)(rl(rec[2].z) | rl(rec[2].w) << 32);
       ex.bits = (int)rl(rec[3].x);
     } else {
-      ex = P.table[e];
-      ex.bits = __builtin_amdgcn_readfirstlane(ex.bits);
+      const DevExpert* t = P.table + e;
+      ex.q_in = uniform_ptr(t->q_in); ex.s_in = uniform_ptr(t->s_in);
+      if constexpr (SWIGLU) { ex.q_gate = uniform_ptr(t->q_gate); ex.s_gate = uniform_ptr(t->s_gate); }
+      ex.q_out = uniform_ptr(t->q_out); ex.s_out = uniform_ptr(t->s_out);
+      ex.bits = __builtin_amdgcn_readfirstlane(t->bits);
     }
     return ex;
   };
@@ -1265,9 +1322,9 @@ __global__ __launch_bounds__(MAXT) void k_moe_decode_vec(FusedParams P) {
     int tid = threadIdx.x;  // opaque copy: keeps the per-bitwidth lane arithmetic inside this iteration
     asm volatile("" : "+v"(tid));
     switch (ex.bits) {
-      case 2: fused_in<2, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, &s_up, HF + j * SW, XP, XK, stage); break;
-      case 4: fused_in<4, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, &s_up, HF + j * SW, XP, XK, stage); break;
-      default: fused_in<8, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, &s_up, HF + j * SW, XP, XK, stage); break;
+      case 2: fused_in<2, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, [&] { return s_up; }, HF + j * SW, XP, XK, stage); break;
+      case 4: fused_in<4, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, [&] { return s_up; }, HF + j * SW, XP, XK, stage); break;
+      default: fused_in<8, SWIGLU>(ex, tid, nwaves, d, L.group, slice * SW, SW, [&] { return s_up; }, HF + j * SW, XP, XK, stage); break;
     }
   }
   // ---- phase 2 of every chosen expert (the first one's call holds the barriers between the phases and the
@@ -1432,9 +1489,9 @@ int fused_inline_router_max() { return kInlineMaxE; }
 
 hipError_t init_attrs_decode_fused() {
   (void)cu_count();
-  const void* ks[6] = {(const void*)k_moe_decode_vec<false, 1024>, (const void*)k_moe_decode_vec<true, 1024>,
-                       (const void*)k_moe_decode_mx<false>, (const void*)k_moe_decode_mx<true>,
-                       (const void*)k_moe_decode_vec<false, 256>, (const void*)k_moe_decode_vec<true, 256>};
+  const void* ks[6] = {(const void*)k_moe_decode_wide<false, false>, (const void*)k_moe_decode_wide<true, false>,
+                       (const void*)k_moe_decode_wide<false, true>, (const void*)k_moe_decode_wide<true, true>,
+                       (const void*)k_moe_decode_vec<false>, (const void*)k_moe_decode_vec<true>};
   for (const void* kf : ks)
     if (hipError_t e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBudget); e != hipSuccess)
       return e;
@@ -1455,10 +1512,10 @@ hipError_t launch_moe_decode(const LayerDims& L, const FusedPlan& plan, const De
   FusedParams P{L, table, router_w, router_bias, logits, fixed_expert, gate_in, route_idx, route_gate, x, part,
                 idx_out, gate_out, plan.SW, bits_mask};
   const bool sw = L.act == MOEQ_ACT_SWIGLU, mx = plan.mx != 0;
-  const bool small = !mx && plan.threads <= 256;
-  auto kernel = mx ? (sw ? k_moe_decode_mx<true> : k_moe_decode_mx<false>)
-                   : small ? (sw ? k_moe_decode_vec<true, 256> : k_moe_decode_vec<false, 256>)
-                           : (sw ? k_moe_decode_vec<true, 1024> : k_moe_decode_vec<false, 1024>);
+  const bool small = !mx && plan.threads <= kVecThreads;
+  auto kernel = mx ? (sw ? k_moe_decode_wide<true, true> : k_moe_decode_wide<false, true>)
+                   : small ? (sw ? k_moe_decode_vec<true> : k_moe_decode_vec<false>)
+                           : (sw ? k_moe_decode_wide<true, false> : k_moe_decode_wide<false, false>);
   if (lds > kFusedLdsBudget) return hipErrorInvalidValue;   // the ceiling init_attrs_decode_fused() asked for
   if (ev_start && ev_stop)
     hipExtLaunchKernelGGL(kernel, dim3(plan.n_slices, T), dim3(plan.threads), lds, st, ev_start, ev_stop, 0, P);
