@@ -1,5 +1,6 @@
 // Host side of the C ABI: argument validation, workspace carving, kernel dispatch.
 // Every check runs before the first HIP call, so the error paths work on a host without a GPU.
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -42,6 +43,7 @@ struct WsLayout {
   size_t idx_off, gate_off, logits_off, sel_off, h_off, part_off, prefill_off, batch_off, group_off, total;
   bool batch;      // the call runs the grouped streaming kernels (decode_batch.hip)
   bool group;      // ... the grouped GEMMs of narrow layers (group_gemm.hip)
+  bool grouped;    // room for a grouped form is included
 };
 
 // Calls with at least this many tokens run as grouped GEMMs on the matrix cores (when the shape allows);
@@ -51,10 +53,36 @@ constexpr int64_t kPrefillMinTokens = 32;
 // partial output vectors (tokens x slices x d_model floats) does not grow with the call.
 constexpr int32_t kDecodeChunk = 32;
 bool use_prefill(const moeq_layer* layer, int64_t T);
-// Calls of at least this many tokens on a layer in the stream layout group their pairs by expert (a single token has
-// nothing to share, and its one kernel is faster than the four of the grouped form); they are taken in launches of at
-// most kBatchMaxPairs pairs.
-constexpr int64_t kBatchMinTokens = 2;
+// Whether a call of T tokens with k choices each groups its pairs by expert (decode_batch.hip) on a layer that
+// batch_supported() takes, or runs the kernels that work token by token. Both sides as measured on layers of 4096 columns
+// (us; 2- and 4-bit experts unless stated):
+//   one workgroup per (slice, token), one workgroup per compute unit: 8 + rounds * (8 + 12 k), rounds = slices T / 256,
+//   at least 7 + 12 k (stream layout, 224 slices, k = 2: 65 / 93 / 122 / 221 / 828 for 2 / 3 / 4 / 8 / 31 tokens; 32
+//   slices: 32 for 6; columns, d_ff 3072 in 192 slices: 176 for 8)
+//   the two GEMV kernels of the canonical layout: 30 + rounds * (6 + 9 k) (0.4 + 0.2 bits), rounds = d_ff / 64 T / 256
+//   (78 / 136 / 114 / 197 / 658; d_ff 3072, 8 tokens: 70; one 4-bit expert, 3 tokens: 76)
+//   grouped: four kernels and every distinct expert once, 38 + 12.5 per expert of 14336 columns at 3 bits on average
+//   (79 / 90 / 111 / 134-150 / 161; d_ff 3072, 8 tokens: 60), 10 % more on canonical rows
+// The distinct experts are estimated as if every expert were equally likely; a hot set only makes grouping cheaper.
+bool batch_pays(const moeq_layer* layer, int64_t T, int32_t k, double experts, double bits) {
+  const LayerDims& L = layer->dims;
+  if (T < 2 || !batch_supported(L)) return false;
+  const bool canonical = layer->out_layout == MOEQ_OUT_CANONICAL;
+  const double rounds = (double)(canonical ? L.d_ff / 64 : layer->plan.n_slices) * (double)T / 256.0;
+  const double distinct = experts * (1.0 - std::pow(1.0 - std::fmin(1.0, k / experts), (double)T));
+  const double grouped = 38.0 + 12.5 * distinct * (L.d_ff / 14336.0) * (bits / 3.0);
+  // (256 / T workgroups a token split the rows evenly only for powers of two)
+  const double split = (T & (T - 1)) ? 1.25 : 1.0;
+  if (canonical) return T >= 3 && 1.1 * grouped < 30.0 + split * rounds * (6.0 + 9.0 * k) * (0.4 + 0.2 * bits);
+  return grouped < std::fmax(7.0 + 12.0 * k, 8.0 + rounds * (8.0 + 12.0 * k));
+}
+bool batch_pays_layer(const moeq_layer* layer, int64_t T) {
+  double bits = 0.0;
+  for (int32_t b : layer->bits) bits += b;
+  return batch_pays(layer, T, layer->dims.top_k, layer->dims.n_experts, bits / layer->dims.n_experts);
+}
+bool batch_pays_expert(const moeq_layer* layer, int64_t T, int32_t bits) { return batch_pays(layer, T, 1, 1.0, bits); }
+// Grouped calls are taken in launches of at most kBatchMaxPairs pairs.
 inline int64_t batch_tokens(int32_t k) { return kBatchMaxPairs / k; }
 
 // Calls of at least this many tokens on a ReLU layer that use_prefill does not take group their pairs by expert as well;
@@ -73,9 +101,20 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true
   w.logits_off = w.gate_off + align_up(slots * sizeof(float), 256);
   const size_t tail = w.logits_off + align_up((size_t)T * (size_t)L.n_experts * sizeof(float), 256);
   w.group = grouped_forms && T >= kGroupMinTokens && layer->in_layout == MOEQ_IN_CANONICAL && !use_prefill(layer, T) &&
-            group_supported(L);
+            !batch_supported(L) && group_supported(L);
   w.group_off = tail;
   const size_t group_total = w.group ? group_ws(L, (T < group_tokens(L.top_k) ? T : group_tokens(L.top_k)) * L.top_k).total : 0;
+  // (2-bit experts are the cheapest to group: whether any single-expert call of T tokens may be grouped)
+  w.batch = grouped_forms && batch_pays_layer(layer, T);
+  const bool one = grouped_forms && batch_pays_expert(layer, T, 2);
+  w.batch_off = tail;
+  size_t batch_total = 0;
+  if (w.batch) batch_total = batch_ws(L, T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), L.top_k, layer->bits_mask).total;
+  if (one) {
+    const size_t b1 = batch_ws(L, T < batch_tokens(1) ? T : batch_tokens(1), 1, layer->bits_mask).total;
+    if (b1 > batch_total) batch_total = b1;
+  }
+  w.grouped = w.batch || one || w.group;
   if (layer->out_layout == MOEQ_OUT_COLUMNS) {
     const size_t chunk = (size_t)(T < kDecodeChunk ? T : kDecodeChunk);
     const size_t part = align_up(chunk * (size_t)layer->plan.n_slices * (size_t)L.d_model * sizeof(float), 256);
@@ -83,15 +122,7 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true
     w.prefill_off = tail;           // a call uses one of the two
     const size_t grouped = use_prefill(layer, T) ? prefill_ws(L, T).total : 0;
     size_t most = part > grouped ? part : grouped;
-    w.batch = grouped_forms && layer->in_layout == MOEQ_IN_STREAM && T >= kBatchMinTokens;
-    if (w.batch) {
-      // (the layer calls and, with one choice per token, the single-expert call)
-      const int64_t nk = T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), n1 = T < batch_tokens(1) ? T : batch_tokens(1);
-      const size_t bk = batch_ws(L, nk, L.top_k, layer->bits_mask).total, b1 = batch_ws(L, n1, 1, layer->bits_mask).total;
-      w.batch_off = tail;
-      if (bk > most) most = bk;
-      if (b1 > most) most = b1;
-    }
+    if (batch_total > most) most = batch_total;
     if (group_total > most) most = group_total;
     w.total = tail + most;
   } else {
@@ -103,6 +134,7 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true
       w.total = w.prefill_off + prefill_ws(L, T).total;
     }
     if (tail + group_total > w.total) w.total = tail + group_total;      // (in the place of sel and h)
+    if (tail + batch_total > w.total) w.total = tail + batch_total;
   }
   return w;
 }
@@ -127,7 +159,7 @@ int inline_router_max() {
 // The layout for a call with ws_bytes of workspace: without the grouped form where only that fits.
 WsLayout ws_layout_for(const moeq_layer* layer, int64_t T, size_t ws_bytes) {
   const WsLayout w = ws_layout(layer, T);
-  return (w.batch || w.group) && ws_bytes < w.total ? ws_layout(layer, T, false) : w;
+  return w.grouped && ws_bytes < w.total ? ws_layout(layer, T, false) : w;
 }
 
 inline moeq_status dev(hipError_t e) { return e == hipSuccess ? MOEQ_OK : MOEQ_EDEVICE; }
@@ -315,13 +347,14 @@ moeq_status moe_expert_ffn_q(const moeq_layer* layer, int32_t expert, const void
   if (!ws || ws_bytes < w.total) return MOEQ_EWORKSPACE;
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  if (w.batch) {
+  if (w.grouped && batch_pays_expert(layer, n_tokens, layer->bits[(size_t)expert])) {
     const size_t x_row = (size_t)layer->dims.d_model * (layer->dims.x_bf16 ? 2 : 4);
     for (int64_t t0 = 0; t0 < n_tokens; t0 += batch_tokens(1)) {
       const int32_t n = (int32_t)(n_tokens - t0 < batch_tokens(1) ? n_tokens - t0 : batch_tokens(1));
       if (launch_moe_batch(layer->dims, layer->table, nullptr, nullptr, false, expert, layer->bits[(size_t)expert],
                            (const char*)x + (size_t)t0 * x_row, n, nullptr, nullptr, gate_opt ? gate_opt + t0 : nullptr,
-                           accumulate ? 1 : 0, (char*)ws + w.batch_off, y + (size_t)t0 * layer->dims.d_model, st) != hipSuccess)
+                           accumulate ? 1 : 0, layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS,
+                           (char*)ws + w.batch_off, y + (size_t)t0 * layer->dims.d_model, st) != hipSuccess)
         return MOEQ_EDEVICE;
     }
     return MOEQ_OK;
@@ -409,12 +442,14 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
         return MOEQ_EDEVICE;
     }
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
-    ScopedEvents ev(layer, MOEQ_KERNEL_FUSED, st);
+    const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
+    ScopedEvents ev(layer, cols ? MOEQ_KERNEL_FUSED : MOEQ_KERNEL_FFN_IN, st), ev2(layer, cols ? -1 : MOEQ_KERNEL_FFN_OUT, st);
     for (int64_t t0 = 0; t0 < n_tokens; t0 += batch_tokens(L.top_k)) {
       const int32_t n = (int32_t)(n_tokens - t0 < batch_tokens(L.top_k) ? n_tokens - t0 : batch_tokens(L.top_k));
       const size_t s0 = (size_t)t0 * (size_t)L.top_k;
       if (launch_moe_batch(L, layer->table, layer->router_w, layer->router_bias, route_inline, -1, layer->bits_mask,
-                           (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, gate + s0, 0, (char*)ws + w.batch_off,
+                           (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, gate + s0, 0,
+                           layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS, (char*)ws + w.batch_off,
                            y + (size_t)t0 * L.d_model, st) != hipSuccess)
         return MOEQ_EDEVICE;
     }

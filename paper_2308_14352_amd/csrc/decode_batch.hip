@@ -1,5 +1,5 @@
-// Decode calls of a few tokens on a layer in the stream + columns layouts (a batch of sequences decoded together):
-// the (token, choice) pairs are grouped by expert, and every expert's packed weights are streamed ONCE for up to 16 of
+// Decode calls of a few tokens on a layer of 4096-column experts with scale groups of 128, in any layout (a batch of
+// sequences decoded together): the (token, choice) pairs are grouped by expert, and every expert's packed weights are streamed ONCE for up to 16 of
 // its pairs, against all of them on the matrix cores (Section 2.1: only the chosen experts work on a token; Section
 // 3.2: the codes are decompressed by the mirror of the linear quantization - here they stay integers all the way into
 // the multiplier).
@@ -18,7 +18,7 @@
 // What bounds it: the bytes of the distinct experts. With one workgroup per (slice, token), as for a single token, a
 // call of T tokens pays T times the unpack arithmetic. Mixtral layer (8 experts, 2 / 4 bits, d_ff 14336): 8 tokens
 // 230 -> 130-150 us, 23 tokens 640 -> 157 us (550 MB: 3.5 TB/s over the whole call; k_batch_in 100, k_batch_out 47, the two
-// small kernels 6.5 and 6).
+// small kernels 6.5 and 6); canonical layout 197 -> 151 and 31 tokens 659 -> 178. Where grouping pays: batch_pays (api.cpp).
 #include <hip/hip_ext.h>
 
 #include "decode_core.h"
@@ -42,16 +42,23 @@ __device__ __forceinline__ i32x4_t mfma_i8(const i32x4_t& a, const i32x4_t& b, c
 }
 
 // The 128 columns of a scale group are two operands (op) of 64; lane (m or n = l % 16, kb = l / 16) holds 16 of an
-// operand's columns, byte j of them being column operand_col(..., j) of the group. W_in / W_gate in the stream layout:
-// the words that one swap of half wavefronts brings together (k_batch_in); W_out in columns: word columns 4 apart.
-template <int BITS, bool OUT>
+// operand's columns, byte j of them being column operand_col(..., j) of the group: W_in / W_gate in the stream layout, in
+// the canonical one; W_out in columns. Rows of W_out in the canonical layout are read like those of W_in. Two swapped
+// halves of a wavefront (swap_halves) stand behind the (kb & 1, kb >> 1) forms.
+enum BatchOrder { BO_STREAM = 0, BO_ROWS = 1, BO_COLUMNS = 2 };
+template <int BITS, int ORDER>
 __device__ __forceinline__ int operand_col(int op, int kb, int j) {
-  if constexpr (!OUT) {
-    if constexpr (BITS == 4) return 64 * (kb & 1) + 32 * (kb >> 1) + 16 * op + 8 * (j >> 3) + 2 * (j & 3) + ((j >> 2) & 1);
+  const int in8 = 2 * (j & 3) + ((j >> 2) & 1);                      // byte j of two words of eight 4-bit codes
+  if constexpr (ORDER == BO_STREAM) {
+    if constexpr (BITS == 4) return 64 * (kb & 1) + 32 * (kb >> 1) + 16 * op + 8 * (j >> 3) + in8;
     else if constexpr (BITS == 2) return 64 * (kb & 1) + 16 * (kb >> 1) + 32 * op + 4 * (j & 3) + (j >> 2);
     else return 64 * (kb & 1) + 16 * (kb >> 1) + 32 * op + j;
+  } else if constexpr (ORDER == BO_ROWS) {
+    if constexpr (BITS == 4) return 32 * kb + 16 * op + 8 * (j >> 3) + in8;
+    else if constexpr (BITS == 2) return 64 * (kb & 1) + 16 * (kb >> 1) + 32 * op + 4 * (j & 3) + (j >> 2);
+    else return 64 * op + 16 * kb + j;
   } else {
-    if constexpr (BITS == 4) return 64 * op + 32 * (j >> 3) + 8 * kb + 2 * (j & 3) + ((j >> 2) & 1);
+    if constexpr (BITS == 4) return 64 * op + 32 * (j >> 3) + 8 * kb + in8;
     else if constexpr (BITS == 2) return 64 * op + 16 * kb + 4 * (j & 3) + (j >> 2);
     else return 64 * op + 16 * (j >> 2) + 4 * kb + (j & 3);
   }
@@ -91,7 +98,7 @@ struct BatchArgs {
   const float* Wr;
   const float* bias;
   const void* x;
-  int32_t T, k, fixed_expert, bits_mask, route_inline;
+  int32_t T, k, fixed_expert, bits_mask, route_inline, in_stream, out_columns;
   int32_t* idx;          // [T][k] written by k_batch_prep (route_inline) or read (unused with a fixed expert)
   float* gate;           // [T][k] likewise
   uint8_t* XQ;           // [bitwidths][T][kBGroups][op][digit][kb][16]: x as operand bytes
@@ -206,15 +213,15 @@ __global__ __launch_bounds__(512) void k_batch_prep(BatchArgs G) {
     else topk_from_logits(lg, E, L.top_k, L.renorm, lane, se, sg, nullptr);
   }
   // the operand bytes: 256 pieces of 16 columns per bitwidth, both digits of a piece by one thread
-  auto pieces = [&](auto bits_tag) __attribute__((always_inline)) {
-    constexpr int BITS = decltype(bits_tag)::value;
+  auto pieces = [&](auto bits_tag, auto order_tag) __attribute__((always_inline)) {
+    constexpr int BITS = decltype(bits_tag)::value, ORDER = decltype(order_tag)::value;
     uint8_t* out = G.XQ + ((size_t)bits_slot(G.bits_mask, BITS) * G.T + token) * (2 * kBD);
     for (int pc = tid; pc < kBD / 16; pc += 512) {
       const int g = pc >> 3, op = (pc >> 2) & 1, kb = pc & 3;
       uint32_t lo[4] = {0u, 0u, 0u, 0u}, hi[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const int v = XI[g * kBGroup + operand_col<BITS, false>(op, kb, j)];
+        const int v = XI[g * kBGroup + operand_col<BITS, ORDER>(op, kb, j)];
         lo[j >> 2] |= lo_byte(v) << (8 * (j & 3));
         hi[j >> 2] |= hi_byte(v) << (8 * (j & 3));
       }
@@ -223,9 +230,13 @@ __global__ __launch_bounds__(512) void k_batch_prep(BatchArgs G) {
       dst[4] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
     }
   };
-  if (G.bits_mask & 2) pieces(std::integral_constant<int, 2>{});
-  if (G.bits_mask & 4) pieces(std::integral_constant<int, 4>{});
-  if (G.bits_mask & 8) pieces(std::integral_constant<int, 8>{});
+  auto all = [&](auto order_tag) __attribute__((always_inline)) {
+    if (G.bits_mask & 2) pieces(std::integral_constant<int, 2>{}, order_tag);
+    if (G.bits_mask & 4) pieces(std::integral_constant<int, 4>{}, order_tag);
+    if (G.bits_mask & 8) pieces(std::integral_constant<int, 8>{}, order_tag);
+  };
+  if (G.in_stream) all(std::integral_constant<int, BO_STREAM>{});
+  else all(std::integral_constant<int, BO_ROWS>{});
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -309,9 +320,10 @@ struct BatchInLds {
 // Units [u0, u1) (128 rows of W_in / W_gate each) of one item. Wavefront w owns rows 16 w .. 16 w + 15 of a unit. Lane
 // (n, kb) loads the 16-byte pieces 4 h + kb of row n: 64 consecutive bytes of 16 rows per load, the other half of the
 // 128-byte lines with the next step's (5.6 TB/s as a bare access pattern with 16 loads per lane in flight, against 6.1
-// for whole 1 KB tiles, which would have to be transposed through LDS). A scale group is two pieces of all the row's
-// tiles: swapping half wavefronts between two loads puts a group's codes into all four kb.
-template <int BITS, int NM, bool SWIGLU>
+// for whole 1 KB tiles, which would have to be transposed through LDS). Stream layout: a scale group is two pieces of all
+// the row's tiles, and swapping half wavefronts between two loads puts a group's codes into all four kb. Canonical rows:
+// the pieces of a row follow each other, 4 h' + kb with h' = (load of the row); only 2-bit codes (two groups a load) swap.
+template <int BITS, int NM, bool SWIGLU, bool STREAM>
 __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S, const BatchItem& item, int u0, int u1) {
   using Set = BatchSet<BITS, NM>;
   constexpr int RB = 16 / BITS, TPR = BITS / 2;
@@ -323,6 +335,9 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
   const uint8_t* q[NM];
   q[0] = uniform_ptr(ex->q_in);
   if constexpr (NM == 2) q[1] = uniform_ptr(ex->q_gate);
+  const uint8_t* sp[NM];                           // (the stream layout keeps the scales with the codes)
+  sp[0] = STREAM ? q[0] : (const uint8_t*)uniform_ptr(ex->s_in);
+  if constexpr (NM == 2) sp[1] = STREAM ? q[1] : (const uint8_t*)uniform_ptr(ex->s_gate);
   const int NG = G.L.d_ff / kBGroup;
   const uint8_t* xq = G.XQ + (size_t)bits_slot(G.bits_mask, BITS) * G.T * (2 * kBD);
 
@@ -350,10 +365,10 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
     const uint32_t unit = (uint32_t)(u0 + s / Set::SPU), h0 = (uint32_t)(s % Set::SPU) * Set::NH;
     const uint32_t row = unit * 128u + (uint32_t)(wave * 16 + n);
     const uint32_t blk = row / RB, rr = row % RB;
-    const uint32_t off = live ? blk * BB + rr * (TPR * 1024u) + (uint32_t)kb * 16u + h0 * 64u : (uint32_t)lane * 16u;
-    const uint32_t sg = live ? blk * BB + 8192u + (rr / (RB > 1 ? (RB / 2) : 1)) * RB + ((rr % (RB / 2 > 0 ? RB / 2 : 1)) >> 1) * 4u : 0u;
-    // (8 bits: RB = 2, the word of group g holds both rows' scales; 2 and 4 bits: the half block's word)
-    const uint32_t soff = live ? (BITS == 8 ? blk * BB + 8192u : sg) + h0 * 2u * (2u * RB) : (uint32_t)lane * 4u;
+    // stream: part `part` of step h at part * 1024 + h * 64 in the row's tiles; rows: load LPM h + part at 64 bytes each
+    const uint32_t off = !live ? (uint32_t)lane * 16u
+                       : STREAM ? blk * BB + rr * (TPR * 1024u) + (uint32_t)kb * 16u + h0 * 64u
+                                : row * (kBD * BITS / 8) + (uint32_t)kb * 16u + h0 * (64u * LPM);
 #pragma unroll
     for (int hh = 0; hh < Set::NH; ++hh)
 #pragma unroll
@@ -361,15 +376,21 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
         const uint8_t* b = live ? q[m] : xq;
 #pragma unroll
         for (int part = 0; part < LPM; ++part)
-          R.t[(hh * NM + m) * LPM + part] = gload_u32x4(b + (off + (uint32_t)(part * 1024 + hh * 64)));
+          R.t[(hh * NM + m) * LPM + part] = gload_u32x4(b + (off + (uint32_t)(STREAM ? part * 1024 + hh * 64 : (hh * LPM + part) * 64)));
       }
+    // scales: group g of the row. Stream layout: in the row's half of the block's scale area (8 bits: RB = 2, the word of a
+    // group holds both rows), the word's half n & 1; rows: one binary16 value
+    const uint32_t sg = blk * BB + 8192u + (BITS == 8 ? 0u : (rr / (RB > 1 ? RB / 2 : 1)) * RB + ((rr % (RB / 2 > 0 ? RB / 2 : 1)) >> 1) * 4u);
+    const uint32_t sstep = STREAM ? 2u * RB : 2u;
+    const uint32_t soff = !live ? (uint32_t)lane * 4u : (STREAM ? sg : row * (kBGroups * 2u)) + h0 * 2u * sstep;
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      const uint8_t* b = live ? q[m] : xq;
+      const uint8_t* b = live ? sp[m] : xq;
 #pragma unroll
       for (int i = 0; i < Set::NS; ++i) {
         const uint32_t g = Set::GS >= 4 ? 4 * i + kb : (kb & (Set::GS - 1));
-        R.s[m][i] = gload_u32(b + (soff + (live ? g * (2u * RB) : 0u)));
+        const uint8_t* a = b + (soff + (live ? g * sstep : 0u));
+        R.s[m][i] = STREAM ? gload_u32(a) : gload_u16(a);
       }
     }
   };
@@ -399,7 +420,7 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
 #pragma unroll
     for (int m = 0; m < NM; ++m)
 #pragma unroll
-      for (int i = 0; i < Set::NS; ++i) sh[m][i] = R.s[m][i] >> (16 * (n & 1));
+      for (int i = 0; i < Set::NS; ++i) sh[m][i] = STREAM ? R.s[m][i] >> (16 * (n & 1)) : R.s[m][i];
 #pragma unroll
     for (int hh = 0; hh < Set::NH; ++hh) {
       // B operands of the two groups of the step: [group][op] of every matrix
@@ -412,6 +433,13 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
           swap_halves(a0, a1);
           swap_halves(a2, a3);
           w[m][0][0] = a0; w[m][1][0] = a1; w[m][0][1] = a2; w[m][1][1] = a3;
+        } else if constexpr (!STREAM) {              // 4 bits: a load per group; 8 bits: two
+#pragma unroll
+          for (int part = 0; part < LPM; ++part) {
+            const uint4 v = t[part];
+            const int gs = part * 2 / LPM, at = (part % (LPM / 2 > 0 ? LPM / 2 : 1)) * 4;
+            w[m][gs][at] = v.x; w[m][gs][at + 1] = v.y; w[m][gs][at + 2] = v.z; w[m][gs][at + 3] = v.w;
+          }
         } else if constexpr (BITS == 4) {
           uint32_t a[4] = {t[0].x, t[0].y, t[0].z, t[0].w}, b[4] = {t[1].x, t[1].y, t[1].z, t[1].w};
 #pragma unroll
@@ -520,22 +548,26 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
             uint32_t by[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) by[i] = dg ? hi_byte(xi[i]) : lo_byte(xi[i]);
-            if constexpr (BITS == 4) {           // the thread's columns are word `seg` of the group: op, half of the piece, kb
-              uint8_t* o = dst + ((seg >> 3) * 2 + dg) * 64 + (seg & 3) * 16 + ((seg >> 2) & 1) * 8;
-              *(uint2*)o = make_uint2(by[0] | by[2] << 8 | by[4] << 16 | by[6] << 24, by[1] | by[3] << 8 | by[5] << 16 | by[7] << 24);
+            const uint32_t lo4 = by[0] | by[1] << 8 | by[2] << 16 | by[3] << 24, hi4 = by[4] | by[5] << 8 | by[6] << 16 | by[7] << 24;
+            const uint32_t even = by[0] | by[2] << 8 | by[4] << 16 | by[6] << 24, odds = by[1] | by[3] << 8 | by[5] << 16 | by[7] << 24;
+            const bool cols = G.out_columns != 0;
+            if constexpr (BITS == 4) {           // the thread's columns are word `seg` of the group: operand, kb, half of the piece
+              const int op = cols ? seg >> 3 : (seg >> 1) & 1, okb = cols ? seg & 3 : seg >> 2, hf = cols ? (seg >> 2) & 1 : seg & 1;
+              *(uint2*)(dst + (op * 2 + dg) * 64 + okb * 16 + hf * 8) = make_uint2(even, odds);
             } else if constexpr (BITS == 2) {    // half of word seg >> 1: the even thread writes dwords 0, 1, the odd one 2, 3
               const int wd = seg >> 1, odd = seg & 1;
-              uint8_t* o = dst + ((wd >> 2) * 2 + dg) * 64 + (wd & 3) * 16 + odd * 8;
+              const int op = cols ? wd >> 2 : (wd >> 1) & 1, okb = cols ? wd & 3 : (wd >> 2) | (wd & 1) << 1;
               const uint32_t d0 = odd ? (other[dg][2] | half[dg][2] << 16) : (half[dg][0] | other[dg][0] << 16);
               const uint32_t d1 = odd ? (other[dg][3] | half[dg][3] << 16) : (half[dg][1] | other[dg][1] << 16);
-              *(uint2*)o = make_uint2(d0, d1);
-            } else {                             // words 2 seg and 2 seg + 1
+              *(uint2*)(dst + (op * 2 + dg) * 64 + okb * 16 + odd * 8) = make_uint2(d0, d1);
+            } else if (cols) {                   // words 2 seg and 2 seg + 1
 #pragma unroll
               for (int i = 0; i < 2; ++i) {
                 const int wd = 2 * seg + i;
-                uint8_t* o = dst + ((wd >> 4) * 2 + dg) * 64 + (wd & 3) * 16 + ((wd >> 2) & 3) * 4;
-                *(uint32_t*)o = by[4 * i] | by[4 * i + 1] << 8 | by[4 * i + 2] << 16 | by[4 * i + 3] << 24;
+                *(uint32_t*)(dst + ((wd >> 4) * 2 + dg) * 64 + (wd & 3) * 16 + ((wd >> 2) & 3) * 4) = i ? hi4 : lo4;
               }
+            } else {                             // half of a piece of sixteen columns
+              *(uint2*)(dst + ((seg >> 3) * 2 + dg) * 64 + ((seg >> 1) & 3) * 16 + (seg & 1) * 8) = make_uint2(lo4, hi4);
             }
           }
         }
@@ -547,7 +579,7 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
 // Grid: one workgroup per compute unit (the operands take most of its LDS). The units of all items form one list, cut
 // into ranges of equal weight (a unit costs its bytes: the bitwidth, plus the scales), one per workgroup; a workgroup's
 // range lies in one or two items.
-template <bool SWIGLU>
+template <bool SWIGLU, bool STREAM>
 __global__ __launch_bounds__(512) void k_batch_in(BatchArgs G) {
   extern __shared__ __attribute__((aligned(16))) char bsmem[];
   BatchInLds& S = *(BatchInLds*)bsmem;
@@ -571,9 +603,9 @@ __global__ __launch_bounds__(512) void k_batch_in(BatchArgs G) {
     const int u0 = __builtin_amdgcn_readfirstlane((int)(a < NU ? a : NU)), u1 = __builtin_amdgcn_readfirstlane((int)(b < NU ? b : NU));
     if (u0 < u1) {
       const BatchItem& item = S.lists.items[i];
-      if (bits == 2) batch_in_units<2, NM, SWIGLU>(G, S, item, u0, u1);
-      else if (bits == 4) batch_in_units<4, NM, SWIGLU>(G, S, item, u0, u1);
-      else batch_in_units<8, NM, SWIGLU>(G, S, item, u0, u1);
+      if (bits == 2) batch_in_units<2, NM, SWIGLU, STREAM>(G, S, item, u0, u1);
+      else if (bits == 4) batch_in_units<4, NM, SWIGLU, STREAM>(G, S, item, u0, u1);
+      else batch_in_units<8, NM, SWIGLU, STREAM>(G, S, item, u0, u1);
     }
     base += c * NU;
   }
@@ -597,14 +629,16 @@ struct BatchOutLds {
   int32_t SX[kBOutGroups][kBTok];
 };
 
-template <int BITS>
+// Canonical rows: the wavefront's 64 rows are four blocks of 16; lane (n, kb) loads 16-byte piece 4 j + kb of row 16 i + n
+// (64 consecutive bytes of 16 rows: one scale group at 4 bits, two at 2, half of one at 8), operand i belongs to block i.
+template <int BITS, bool COLS>
 __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, const BatchItem& item) {
   using Set = BatchOutSet<BITS>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, kb = lane >> 4;
   const int NG = G.L.d_ff / kBGroup;
   const int g0 = blockIdx.y * kBOutGroups, ng = min(kBOutGroups, NG - g0);
-  const int r0 = blockIdx.x * kBOutRows + wave * 64 + 4 * n;
+  const int r0 = blockIdx.x * kBOutRows + wave * 64 + (COLS ? 4 * n : n);      // operand i: row r0 + i, or r0 + 16 i
   const DevExpert* ex = G.table + item.e;
   const uint8_t* q = uniform_ptr(ex->q_out);
   const uint8_t* sc = (const uint8_t*)uniform_ptr(ex->s_out);
@@ -628,16 +662,37 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
   const int n_sets = (ng + Set::GS - 1) / Set::GS;
   const uint32_t col = (uint32_t)kBD * 4u;         // bytes of a word column
   const uint32_t lane_off = (uint32_t)kb * col + (uint32_t)r0 * 4u;
+  const uint32_t row_bytes = (uint32_t)G.L.d_ff * BITS / 8u, pieces = row_bytes / 16u;
   auto issue = [&](Set& R, int s) __attribute__((always_inline)) {
+    if constexpr (COLS) {
 #pragma unroll
-    for (int gi = 0; gi < Set::GS; ++gi) {
-      const int g = min(g0 + s * Set::GS + gi, NG - 1);       // groups past the end: loaded again, not used
-      const uint8_t* qg = q + (size_t)g * (4 * BITS) * col;
+      for (int gi = 0; gi < Set::GS; ++gi) {
+        const int g = min(g0 + s * Set::GS + gi, NG - 1);       // groups past the end: loaded again, not used
+        const uint8_t* qg = q + (size_t)g * (4 * BITS) * col;
 #pragma unroll
-      for (int j = 0; j < Set::LPG; ++j) R.t[gi * Set::LPG + j] = gload_u32x4(qg + (size_t)(4 * j) * col + lane_off);
-      R.s[gi] = gload_u32x2(sc + (size_t)g * (kBD * 2) + (uint32_t)r0 * 2u);
+        for (int j = 0; j < Set::LPG; ++j) R.t[gi * Set::LPG + j] = gload_u32x4(qg + (size_t)(4 * j) * col + lane_off);
+        R.s[gi] = gload_u32x2(sc + (size_t)g * (kBD * 2) + (uint32_t)r0 * 2u);
+      }
+    } else {
+      // 64-byte steps of the rows: a set is two of them for the four blocks
+      const uint32_t step0 = (uint32_t)g0 * BITS / 4u + (uint32_t)s * 2u;
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          R.t[st * 4 + i] = gload_u32x4(q + ((size_t)(uint32_t)(r0 + 16 * i) * row_bytes + min((step0 + st) * 4u + kb, pieces - 1u) * 16u));
     }
   };
+  // canonical rows: lane (n, kb) holds the chunk's scales of row 16 kb + n, two groups to a register
+  uint32_t srow[kBOutGroups / 2];
+  if constexpr (!COLS) {
+    const int row = blockIdx.x * kBOutRows + wave * 64 + 16 * kb + n;
+#pragma unroll
+    for (int g = 0; g < kBOutGroups; g += 2) {
+      const uint32_t a = gload_u16(sc + ((size_t)row * NG + min(g0 + g, NG - 1)) * 2), b = gload_u16(sc + ((size_t)row * NG + min(g0 + g + 1, NG - 1)) * 2);
+      srow[g / 2] = a | b << 16;
+    }
+  }
   float acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -656,17 +711,44 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
         const i32x4_t sx = *(const i32x4_t*)&S.SX[g][4 * kb];
         const float4 xs = *(const float4*)&S.XS[g][4 * kb];
         const float xf[4] = {xs.x, xs.y, xs.z, xs.w};
-        const uint32_t s4[4] = {R.s[gi].x & 0xffffu, R.s[gi].x >> 16, R.s[gi].y & 0xffffu, R.s[gi].y >> 16};
-        const uint4* t = &R.t[gi * Set::LPG];
-        auto word = [&](int j, int i) { return i == 0 ? t[j].x : i == 1 ? t[j].y : i == 2 ? t[j].z : t[j].w; };
+        uint32_t s4[4];
+        if constexpr (COLS) {
+          s4[0] = R.s[gi].x & 0xffffu; s4[1] = R.s[gi].x >> 16; s4[2] = R.s[gi].y & 0xffffu; s4[3] = R.s[gi].y >> 16;
+        } else {
+          // (the group's register: s and gi select it; a set's groups have fixed places)
+          const int gp = g >> 1;
+          const uint32_t v = gp == 0 ? srow[0] : gp == 1 ? srow[1] : gp == 2 ? srow[2] : srow[3];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            s4[i] = ((uint32_t)__builtin_amdgcn_ds_bpermute(4 * (n + 16 * i), (int)v) >> (16 * (g & 1))) & 0xffffu;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           i32x4_t B[2];
+          if constexpr (COLS) {
+            const uint4* t = &R.t[gi * Set::LPG];
+            auto word = [&](int j) { return i == 0 ? t[j].x : i == 1 ? t[j].y : i == 2 ? t[j].z : t[j].w; };
 #pragma unroll
-          for (int op = 0; op < 2; ++op) {
-            if constexpr (BITS == 2) B[op] = codes16_2(word(op, i));
-            else if constexpr (BITS == 4) B[op] = codes16_4(word(2 * op, i), word(2 * op + 1, i));
-            else B[op] = codes16_8(word(4 * op, i), word(4 * op + 1, i), word(4 * op + 2, i), word(4 * op + 3, i));
+            for (int op = 0; op < 2; ++op) {
+              if constexpr (BITS == 2) B[op] = codes16_2(word(op));
+              else if constexpr (BITS == 4) B[op] = codes16_4(word(2 * op), word(2 * op + 1));
+              else B[op] = codes16_8(word(4 * op), word(4 * op + 1), word(4 * op + 2), word(4 * op + 3));
+            }
+          } else if constexpr (BITS == 2) {
+            const uint4 t = R.t[(gi >> 1) * 4 + i];
+            uint32_t a0 = t.x, a1 = t.y, a2 = t.z, a3 = t.w;
+            swap_halves(a0, a1);
+            swap_halves(a2, a3);
+            B[0] = codes16_2((gi & 1) ? a1 : a0);
+            B[1] = codes16_2((gi & 1) ? a3 : a2);
+          } else if constexpr (BITS == 4) {
+            const uint4 t = R.t[gi * 4 + i];
+            B[0] = codes16_4(t.x, t.y);
+            B[1] = codes16_4(t.z, t.w);
+          } else {
+            const uint4 t0 = R.t[i], t1 = R.t[4 + i];
+            B[0] = codes16_8(t0.x, t0.y, t0.z, t0.w);
+            B[1] = codes16_8(t1.x, t1.y, t1.z, t1.w);
           }
           i32x4_t dl = mfma_i8(A[0][0], B[0], sx);
           i32x4_t dh = mfma_i8(A[0][1], B[0], (i32x4_t){0, 0, 0, 0});
@@ -693,13 +775,20 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int m = 4 * kb + j;
-    if (m < item.n)
-      *(float4*)(G.part + ((size_t)blockIdx.y * (size_t)(G.T * G.k) + item.pair[m]) * kBD + r0) =
-          make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
+    if (m < item.n) {
+      float* o = G.part + ((size_t)blockIdx.y * (size_t)(G.T * G.k) + item.pair[m]) * kBD + r0;
+      if constexpr (COLS) {
+        *(float4*)o = make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[16 * i] = acc[i][j];
+      }
+    }
   }
 }
 
 // Grid (row chunks, chunks of d_ff, upper bound of the items).
+template <bool COLS>
 __global__ __launch_bounds__(256) void k_batch_out(BatchArgs G) {
   __shared__ BatchOutLds S;
   __shared__ BatchItem item;
@@ -707,9 +796,9 @@ __global__ __launch_bounds__(256) void k_batch_out(BatchArgs G) {
   if (threadIdx.x < 2) ((uint4*)&item)[threadIdx.x] = ((const uint4*)(G.items + blockIdx.z))[threadIdx.x];
   __syncthreads();
   const int bits = __builtin_amdgcn_readfirstlane(item.bits);
-  if (bits == 2) batch_out<2>(G, S, item);
-  else if (bits == 4) batch_out<4>(G, S, item);
-  else batch_out<8>(G, S, item);
+  if (bits == 2) batch_out<2, COLS>(G, S, item);
+  else if (bits == 4) batch_out<4, COLS>(G, S, item);
+  else batch_out<8, COLS>(G, S, item);
 }
 
 // y[t][r] (+)= sum_j gate[t][j] * sum_c part[c][t k + j][r], chunks and choices in order. gate null: 1.
@@ -765,25 +854,28 @@ BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask) {
   return w;
 }
 
+bool batch_supported(const LayerDims& L) { return L.d_model == kBD && L.group == kBGroup && L.group_out == kBGroup && L.top_k <= 8; }
 int batch_inline_router_max() { return kBInlineMaxE; }
 
 hipError_t init_attrs_decode_batch() {
   (void)batch_cus();
-  if (hipError_t e = hipFuncSetAttribute((const void*)k_batch_in<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BatchInLds));
-      e != hipSuccess)
-    return e;
-  return hipFuncSetAttribute((const void*)k_batch_in<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BatchInLds));
+  for (const void* kf : {(const void*)k_batch_in<true, true>, (const void*)k_batch_in<false, true>, (const void*)k_batch_in<true, false>,
+                         (const void*)k_batch_in<false, false>})
+    if (hipError_t e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BatchInLds)); e != hipSuccess) return e;
+  return hipSuccess;
 }
 
 hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
                             bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T, int32_t* idx,
-                            float* gate, const float* gate_out, int32_t accumulate, char* ws, float* y, hipStream_t st) {
+                            float* gate, const float* gate_out, int32_t accumulate, bool in_stream, bool out_columns, char* ws,
+                            float* y, hipStream_t st) {
   const int k = fixed_expert >= 0 ? 1 : L.top_k;
-  if (!stream_supported(L) || T < 1 || (int64_t)T * k > kBatchMaxPairs || !(bits_mask & 14)) return hipErrorInvalidValue;
+  if (!batch_supported(L) || L.d_ff % kBGroup || T < 1 || (int64_t)T * k > kBatchMaxPairs || !(bits_mask & 14)) return hipErrorInvalidValue;
   if (route_inline && (fixed_expert >= 0 || L.n_experts > kBInlineMaxE)) return hipErrorInvalidValue;
   if (fixed_expert < 0 && (!idx || !gate)) return hipErrorInvalidValue;
   const BatchWs w = batch_ws(L, T, k, bits_mask);
-  BatchArgs G{L, table, router_w, router_bias, x, T, k, fixed_expert, bits_mask & 14, route_inline ? 1 : 0, idx, gate,
+  BatchArgs G{L, table, router_w, router_bias, x, T, k, fixed_expert, bits_mask & 14, route_inline ? 1 : 0, in_stream ? 1 : 0,
+              out_columns ? 1 : 0, idx, gate,
               (uint8_t*)(ws + w.xq), (float*)(ws + w.xs), (int32_t*)(ws + w.xsum), (uint8_t*)(ws + w.hq),
               (float*)(ws + w.hs), (int32_t*)(ws + w.hsum), (BatchItem*)(ws + w.items), (int32_t*)(ws + w.n_items),
               (float*)(ws + w.part)};
@@ -791,9 +883,10 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
   const int max_items = P < L.n_experts + P / kBTok ? P : L.n_experts + P / kBTok;
   const int chunks = (L.d_ff / kBGroup + kBOutGroups - 1) / kBOutGroups;
   hipLaunchKernelGGL(k_batch_prep, dim3(T), dim3(512), 0, st, G);
-  if (L.act == MOEQ_ACT_SWIGLU) hipLaunchKernelGGL(k_batch_in<true>, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
-  else hipLaunchKernelGGL(k_batch_in<false>, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
-  hipLaunchKernelGGL(k_batch_out, dim3(kBD / kBOutRows, chunks, max_items), dim3(256), 0, st, G);
+  const bool sw = L.act == MOEQ_ACT_SWIGLU;
+  auto kin = in_stream ? (sw ? k_batch_in<true, true> : k_batch_in<false, true>) : (sw ? k_batch_in<true, false> : k_batch_in<false, false>);
+  hipLaunchKernelGGL(kin, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
+  hipLaunchKernelGGL(out_columns ? k_batch_out<true> : k_batch_out<false>, dim3(kBD / kBOutRows, chunks, max_items), dim3(256), 0, st, G);
   hipLaunchKernelGGL(k_batch_combine, dim3(kBD / 1024, T), dim3(256), 0, st, G.part, gate_out, chunks, T, k, accumulate, y);
   return hipGetLastError();
 }

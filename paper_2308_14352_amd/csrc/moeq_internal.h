@@ -96,19 +96,20 @@ hipError_t launch_moe_stream(const LayerDims& L, const DevExpert* table, const f
                              int32_t bits_mask, const void* x, int32_t T, float* part, int32_t* idx_out,
                              float* gate_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr);
-// ---- calls of a few tokens on the same layouts: pairs grouped by expert, every expert's weights streamed once for up
-// to 16 pairs (decode_batch.hip). At most kBatchMaxPairs (token, choice) pairs. route_inline: the router runs here and
+// ---- calls of a few tokens on layers of that shape in any layout: pairs grouped by expert, every expert's weights
+// streamed once for up to 16 pairs (decode_batch.hip). At most kBatchMaxPairs (token, choice) pairs. route_inline: the router runs here and
 // writes idx / gate (at most batch_inline_router_max() experts); else idx / gate hold the routing. fixed_expert >= 0:
 // that expert for every token (idx / gate unused). gate_out: the weights of the combine, [T][k] or null (= 1).
 constexpr int kBatchMaxPairs = 256;
 struct BatchWs { size_t items, n_items, xq, xs, xsum, hq, hs, hsum, part, total; };
 BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask);
+bool batch_supported(const LayerDims& L);
 int batch_inline_router_max();
 hipError_t init_attrs_decode_batch();
 hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
                             bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T,
-                            int32_t* idx, float* gate, const float* gate_out, int32_t accumulate, char* ws, float* y,
-                            hipStream_t st);
+                            int32_t* idx, float* gate, const float* gate_out, int32_t accumulate, bool in_stream,
+                            bool out_columns, char* ws, float* y, hipStream_t st);
 // canonical (q, s) <-> stream buffer of a [rows][4096] matrix, groups of 128 columns
 hipError_t launch_relayout_in(const void* q, const void* s, int64_t rows, int bits, void* stream_buf, bool to_stream,
                               hipStream_t st);

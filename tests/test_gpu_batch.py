@@ -1,5 +1,5 @@
-"""GPU parity of decode calls of a few tokens on stream layers (pairs grouped by expert, weights streamed once for up to
-16 pairs): the edges of its items, units and chunks."""
+"""GPU parity of decode calls of a few tokens on 4096-column layers (pairs grouped by expert, weights streamed once for up
+to 16 pairs), in every layout: the edges of its items, units and chunks."""
 from dataclasses import replace
 
 import numpy as np
@@ -21,22 +21,24 @@ TOL = 4e-4
 
 
 @pytest.mark.parametrize("base,x_dtype,f,k,bits_table,tokens", [
-    ("c4", "bf16", 128, 2, [2, 4, 8], (2, 3, 16)),          # one unit, one chunk
-    ("c4", "f32", 1152, 2, [8, 2, 4, 4], (15, 17, 31)),     # nine scale groups: a last chunk of one
-    ("c4", "bf16", 1536, 2, [4, 2], (16, 31)),              # every token on both experts: two items of each
-    ("c1", "f32", 640, 1, [2, 8, 4], (7, 31)),              # ReLU, top-1
-    ("c4", "f32", 384, 5, [2, 2, 4, 8, 8, 4], (31,)),       # five choices: 155 pairs
-    ("c1", "bf16", 256, 2, [2 + 2 * (i % 2) for i in range(66)], (9,)),    # more experts than are routed in the kernel
+    ("c4", "bf16", 128, 2, [2, 4, 8], (200,)),              # one unit, one chunk; two launches
+    ("c4", "f32", 1152, 2, [8, 2, 4, 4], (33, 50, 131)),    # nine scale groups: a last chunk of one
+    ("c4", "bf16", 1536, 2, [4, 2], (16, 17, 31)),          # every token on both experts: one and two items of each
+    ("c1", "f32", 640, 1, [2, 8, 4], (60, 129)),            # ReLU, top-1
+    ("c4", "f32", 384, 5, [2, 2, 4, 8, 8, 4], (60,)),       # five choices: launches of 51 tokens
+    ("c1", "bf16", 256, 2, [2 + 2 * (i % 2) for i in range(66)], (100,)),    # more experts than are routed in the kernel
 ], ids=("one-unit", "nine-groups", "two-items", "relu", "top5", "66-experts"))
-def test_grouped_decode_calls(base, x_dtype, f, k, bits_table, tokens):
+@pytest.mark.parametrize("layout", ("stream", "canonical", "columns"))
+def test_grouped_decode_calls(base, x_dtype, f, k, bits_table, tokens, layout):
     cfg = replace(gen.tiny_config(base, 4096, f, n_experts=len(bits_table), n_layers=1, group=128), top_k=k, x_dtype=x_dtype)
-    layer, orc_experts, Wr, bias = build_layer_pair(cfg, 0, DEV, bits_table, stream=True)
+    layer, orc_experts, Wr, bias = build_layer_pair(cfg, 0, DEV, bits_table, columns=layout == "columns", stream=layout == "stream")
     x = gen.hidden(cfg, 0, 0, max(tokens), DEV)
     y_ref, idx_ref, gate_ref = oracle_layer(cfg, orc_experts, Wr, bias, x)
     skip = set(near_tie_tokens(cfg, Wr, bias, x).tolist())
     first = None
     for T in tokens:
-        assert layer.path(T) == moeq.MOEQ_PATH_STREAM
+        assert layer.path(T) in {"stream": (moeq.MOEQ_PATH_STREAM,), "canonical": (moeq.MOEQ_PATH_TWO_KERNELS,),
+                                 "columns": (moeq.MOEQ_PATH_ONE_KERNEL, moeq.MOEQ_PATH_ONE_KERNEL_MX)}[layout]
         y, idx, gate = moeq.moe_layer_forward(layer, x[:T], want_routing=True)
         y_r = moeq.moe_layer_forward_routed(layer, x[:T], idx, gate)
         torch.cuda.synchronize()
@@ -46,10 +48,14 @@ def test_grouped_decode_calls(base, x_dtype, f, k, bits_table, tokens):
         assert np.allclose(gate.cpu().numpy()[keep], gate_ref[keep], rtol=2e-5, atol=1e-7)
         assert rel_err(y.cpu().numpy()[keep], y_ref[keep]).max() < TOL
         assert torch.equal(y, y_r)
+        # (the call was grouped: the kernels of a single token round differently)
+        assert not torch.equal(y[:1], moeq.moe_layer_forward(layer, x[:1]))
         # a token's result does not depend on the tokens that share its call
         first = y if first is None else first
         n = min(T, first.shape[0])
         assert torch.equal(y[:n], first[:n])
+    if layout != "stream" or len(bits_table) > 64:
+        return
     # the single-token kernel routes the same way, bit for bit
     _, idx1, gate1 = moeq.moe_layer_forward(layer, x[:1], want_routing=True)
     torch.cuda.synchronize()
@@ -57,10 +63,12 @@ def test_grouped_decode_calls(base, x_dtype, f, k, bits_table, tokens):
 
 
 @pytest.mark.parametrize("bits", (2, 4, 8))
-@pytest.mark.parametrize("T", (2, 17, 33))
-def test_grouped_single_expert_call(bits, T):
-    cfg = replace(gen.tiny_config("c4", 4096, 1152, n_experts=2, n_layers=1, group=128), x_dtype="f32")
-    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits, bits], stream=True)
+@pytest.mark.parametrize("f,T", [(2304, 20), (1152, 33), (384, 260)])
+@pytest.mark.parametrize("layout", ("stream", "canonical", "columns"))
+def test_grouped_single_expert_call(bits, f, T, layout):
+    cfg = replace(gen.tiny_config("c4", 4096, f, n_experts=2, n_layers=1, group=128), x_dtype="f32")
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits, bits], columns=layout == "columns",
+                                               stream=layout == "stream")
     x = gen.hidden(cfg, 0, 0, T, DEV)
     gate = torch.linspace(0.2, 1.1, T, device=DEV)
     y0 = gen.normal((T, cfg.d_model), 0.1, 7, DEV)
