@@ -205,7 +205,7 @@ class HipEvents:
 
 def dominant_kernel_events(stack, steps, idx):
     """Eager pass over `steps` steps with a HIP event pair the library attaches to the dominant kernel
-    of every layer call (begin and end of the kernel's execution on its stream): k_moe_decode (the whole layer
+    of every layer call (begin and end of the kernel's execution on its stream): k_moe_decode_* (the whole layer
     but the final sum of partial vectors) with W_out in columns, else k_ffn_in (phase 1, about two thirds
     of the bytes). Returns (mean duration in ms, mean algorithmic bytes of that kernel, and for single-token
     calls the same two figures grouped by the bitwidths of the chosen experts)."""
@@ -537,7 +537,7 @@ def main():
         "roofline": {"bound": "hbm",
                      "kernel": ("k_moe_stream (router + top-k + dequantize-fused FFN of every d_ff slice, integer dot "
                                 "products)" if layout == "stream" else
-                                "k_moe_decode (router + top-k + dequantize-fused FFN of every d_ff slice)" if columns
+                                "k_moe_decode_* (router + top-k + dequantize-fused FFN of every d_ff slice)" if columns
                                 else "k_ffn_in (phase 1: top-k + dequantize-fused W_in/W_gate GEMVs)"),
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "bytes_per_launch": res["kernel_bytes"], "avg_launch_ms": res["kernel_ms"],

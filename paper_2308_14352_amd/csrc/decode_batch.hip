@@ -1,8 +1,8 @@
 // Decode calls of a few tokens on a layer of 4096-column experts with scale groups of 128, in any layout (a batch of
-// sequences decoded together): the (token, choice) pairs are grouped by expert, and every expert's packed weights are streamed ONCE for up to 16 of
-// its pairs, against all of them on the matrix cores (Section 2.1: only the chosen experts work on a token; Section
-// 3.2: the codes are decompressed by the mirror of the linear quantization - here they stay integers all the way into
-// the multiplier).
+// sequences decoded together): the (token, choice) pairs are grouped by expert, and every expert's packed weights are
+// streamed ONCE for up to 16 of its pairs, against all of them on the matrix cores (Section 2.1: only the chosen experts
+// work on a token; Section 3.2: the codes are decompressed by the mirror of the linear quantization - here they stay
+// integers all the way into the multiplier).
 //
 // Arithmetic: that of decode_stream.hip. The activations of a scale group (128 columns) are block-floating-point
 // integers of up to 15 bits and a sign, split into two signed bytes x_int = lo + 256 hi; codes enter as bytes (2- and
