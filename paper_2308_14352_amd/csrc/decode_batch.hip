@@ -7,7 +7,8 @@
 // Arithmetic: that of decode_stream.hip. The activations of a scale group (128 columns) are block-floating-point
 // integers of up to 15 bits and a sign, split into two signed bytes x_int = lo + 256 hi; codes enter as bytes (2- and
 // 4-bit codes with their offset, which is taken off with the group's sum of x_int; 8-bit codes made signed by one XOR).
-// v_mfma_i32_16x16x64_i8 gives the exact integer sums of 16 tokens x 16 rows; per group sum * 2^e * scale in fp32.
+// v_mfma_i32_16x16x64_i8 gives the exact integer sums of 16 tokens x 16 rows; per group sum * scale * 2^e in fp32, 2^e last
+// and in the addition's fused multiply: sum * 2^e alone leaves fp32 from hidden states of about 2^108 on.
 //
 // Kernels (launch_moe_batch):
 //   k_batch_prep     per token: router + top-k, x as byte digits in the operand order of every bitwidth of the layer
@@ -481,7 +482,7 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
           const float sc = f16_bits_to_f32((uint32_t)__builtin_amdgcn_ds_bpermute(4 * (n + 16 * (gl & 3)), (int)sh[m][gl >> 2]) & 0xffffu);
           const float xf[4] = {cur.xs.x, cur.xs.y, cur.xs.z, cur.xs.w};
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[m][i] = fmaf((float)(dl[i] + (dh[i] << 8)) * xf[i], sc, acc[m][i]);
+          for (int i = 0; i < 4; ++i) acc[m][i] = fmaf((float)(dl[i] + (dh[i] << 8)) * sc, xf[i], acc[m][i]);
         }
         cur = next;
         // the sums are finished here: otherwise the compiler sinks them behind the loads and keeps every product alive
@@ -756,7 +757,7 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
           dh = mfma_i8(A[1][1], B[1], dh);
           const float scf = f16_bits_to_f32(s4[i]);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf((float)(dl[j] + (dh[j] << 8)) * xf[j], scf, acc[i][j]);
+          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf((float)(dl[j] + (dh[j] << 8)) * scf, xf[j], acc[i][j]);
         }
       }
     }

@@ -101,3 +101,21 @@ def test_grouped_call_with_the_ungrouped_workspace():
     assert rel_err(y.cpu().numpy(), y_ref).max() < TOL and rel_err(y2.cpu().numpy(), y_ref).max() < 2e-3
     with pytest.raises(moeq.MoeqError):
         moeq.moe_layer_forward(layer, x, ws=torch.empty(small - 1, dtype=torch.uint8, device=DEV))
+
+
+@pytest.mark.parametrize("layout", ("stream", "canonical", "columns"))
+def test_grouped_call_at_the_ends_of_the_hidden_states_range(layout):
+    """Largest magnitudes next to 2^124 and 2^-96, the range that the entry points state (ReLU: the exact result is then of
+    the size of the input)."""
+    cfg = replace(gen.tiny_config("c1", 4096, 640, n_experts=3, n_layers=1, group=128), top_k=1, x_dtype="f32")
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [2, 4, 8], columns=layout == "columns", stream=layout == "stream")
+    T = 66
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    x = x / x.abs().amax(1, keepdim=True)
+    idx = (torch.arange(T, device=DEV, dtype=torch.int32) % 3)[:, None].contiguous()
+    gate = torch.full((T, 1), 0.125, device=DEV)
+    y_ref = oracle.layer_forward_routed(orc_experts, 4096, 640, 128, 0, 1, x.cpu().numpy(), idx.cpu().numpy(), gate.cpu().numpy())
+    for e in (123, -95):
+        y = moeq.moe_layer_forward_routed(layer, x * 2.0 ** e, idx, gate)
+        torch.cuda.synchronize()
+        assert rel_err(y.cpu().numpy().astype(np.float64) * 2.0 ** -e, y_ref).max() < TOL
