@@ -109,9 +109,9 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true
   const bool one = grouped_forms && batch_pays_expert(layer, T, 2);
   w.batch_off = tail;
   size_t batch_total = 0;
-  if (w.batch) batch_total = batch_ws(L, T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), L.top_k, layer->bits_mask).total;
+  if (w.batch) batch_total = batch_ws(L, T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), L.top_k, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total;
   if (one) {
-    const size_t b1 = batch_ws(L, T < batch_tokens(1) ? T : batch_tokens(1), 1, layer->bits_mask).total;
+    const size_t b1 = batch_ws(L, T < batch_tokens(1) ? T : batch_tokens(1), 1, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total;
     if (b1 > batch_total) batch_total = b1;
   }
   w.grouped = w.batch || one || w.group;

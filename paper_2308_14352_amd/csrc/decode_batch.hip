@@ -1,14 +1,21 @@
 // Decode calls of a few tokens on a layer of 4096-column experts with scale groups of 128, in any layout (a batch of
 // sequences decoded together): the (token, choice) pairs are grouped by expert, and every expert's packed weights are
-// streamed ONCE for up to 16 of its pairs, against all of them on the matrix cores (Section 2.1: only the chosen experts
-// work on a token; Section 3.2: the codes are decompressed by the mirror of the linear quantization - here they stay
-// integers all the way into the multiplier).
+// streamed ONCE for up to 16 of its pairs (8 on layers that are not in the stream layout), against all of them on the
+// matrix cores (Section 2.1: only the chosen experts work on a token; Section 3.2: the codes are decompressed by the mirror
+// of the linear quantization - here they stay integers all the way into the multiplier).
 //
 // Arithmetic: that of decode_stream.hip. The activations of a scale group (128 columns) are block-floating-point
-// integers of up to 15 bits and a sign, split into two signed bytes x_int = lo + 256 hi; codes enter as bytes (2- and
-// 4-bit codes with their offset, which is taken off with the group's sum of x_int; 8-bit codes made signed by one XOR).
-// v_mfma_i32_16x16x64_i8 gives the exact integer sums of 16 tokens x 16 rows; per group sum * scale * 2^e in fp32, 2^e last
-// and in the addition's fused multiply: sum * 2^e alone leaves fp32 from hidden states of about 2^108 on.
+// integers, given as signed bytes; codes enter as bytes (2- and 4-bit codes with their offset, which is taken off with the
+// group's sum of x_int; 8-bit codes made signed by one XOR). v_mfma_i32_16x16x64_i8 gives the exact integer sums of 16
+// rows of activations x 16 rows of weights; per group sum * scale * 2^e in fp32, 2^e last and in the addition's fused
+// multiply: sum * 2^e alone leaves fp32 from hidden states of about 2^108 on.
+//   Stream layers: 15 bits below the group's largest and a sign, x_int = lo + 256 hi; an activation row per pair.
+//   Other layers: 30 bits and a sign, in two such parts that are two rows of the operand (x_int = low + 2^16 high), so 8
+//   pairs fill it. Their single-token kernels hold x and h as binary16, 11 bits of every element whatever its neighbours
+//   are, and 15 bits below the largest are not that: where a column with activations 2^10 times the others of its group
+//   meets zero weights, an output of 4-bit experts was off by 2.9e-2 (5.7e-4 token by token; now 8e-7, and 2.1e-7 instead
+//   of 7.7e-5 on normally distributed inputs). The price is a second pass over the weights of experts with 9 to 16 pairs:
+//   Mixtral layer in rows, 31 tokens 177 -> 232 us (669 token by token), 23 tokens 174 -> 180, up to 16 tokens within 3 %.
 //
 // Kernels (launch_moe_batch):
 //   k_batch_prep     per token: router + top-k, x as byte digits in the operand order of every bitwidth of the layer
@@ -19,7 +26,7 @@
 // What bounds it: the bytes of the distinct experts. With one workgroup per (slice, token), as for a single token, a
 // call of T tokens pays T times the unpack arithmetic. Mixtral layer (8 experts, 2 / 4 bits, d_ff 14336): 8 tokens
 // 230 -> 130-150 us, 23 tokens 640 -> 157 us (550 MB: 3.5 TB/s over the whole call; k_batch_in 100, k_batch_out 47, the two
-// small kernels 6.5 and 6); canonical layout 197 -> 151 and 31 tokens 659 -> 178. Where grouping pays: batch_pays (api.cpp).
+// small kernels 6.5 and 6); canonical layout 204 -> 170 and 23 tokens 846 -> 180. Where grouping pays: batch_pays (api.cpp).
 #include <hip/hip_ext.h>
 
 #include "decode_core.h"
@@ -30,7 +37,10 @@ namespace {
 constexpr int kBD = 4096;                 // d_model
 constexpr int kBGroup = 128;              // scale group of all matrices
 constexpr int kBGroups = kBD / kBGroup;   // scale groups of a row of W_in
-constexpr int kBTok = 16;                 // pairs of a work item (columns of the matrix instruction)
+constexpr int kBRows = 16;                // rows of an A operand (columns of the matrix instruction)
+// Pairs of a work item. Stream layers: one row per pair. Other layers: two, the low and the high half of its integers.
+__host__ __device__ constexpr int batch_parts(bool stream) { return stream ? 1 : 2; }
+__host__ __device__ constexpr int batch_tok(bool stream) { return kBRows / batch_parts(stream); }
 constexpr int kBWaves = 8;                // wavefronts of a k_batch_in workgroup
 constexpr int kBOutGroups = 8;            // scale groups of d_ff a k_batch_out workgroup takes
 constexpr int kBOutRows = 256;            // output rows a k_batch_out workgroup takes (64 per wavefront)
@@ -89,8 +99,8 @@ __device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
   b = r.y;
 }
 
-// A work item: up to kBTok pairs of one expert.
-struct BatchItem { int32_t e, n; uint8_t pair[kBTok]; int32_t bits, pad; };
+// A work item: up to batch_tok() pairs of one expert.
+struct alignas(16) BatchItem { int32_t e, n; uint8_t pair[kBRows]; int32_t bits, pad; };
 static_assert(sizeof(BatchItem) == 32, "two 16-byte pieces");
 
 struct BatchArgs {
@@ -99,15 +109,15 @@ struct BatchArgs {
   const float* Wr;
   const float* bias;
   const void* x;
-  int32_t T, k, fixed_expert, bits_mask, route_inline, in_stream, out_columns;
+  int32_t T, k, fixed_expert, bits_mask, route_inline, out_columns;
   int32_t* idx;          // [T][k] written by k_batch_prep (route_inline) or read (unused with a fixed expert)
   float* gate;           // [T][k] likewise
-  uint8_t* XQ;           // [bitwidths][T][kBGroups][op][digit][kb][16]: x as operand bytes
+  uint8_t* XQ;           // [bitwidths][T][kBGroups][op][part][digit][kb][16]: x as operand bytes
   float* XS;             // [T][kBGroups] 2^e of every group (NaN: the group holds a non-finite value)
-  int32_t* XSUM;         // [T][kBGroups] sum of x_int
-  uint8_t* HQ;           // [pairs][d_ff / 128][op][digit][kb][16]: h likewise, in the order of its expert's bitwidth
+  int32_t* XSUM;         // [T][kBGroups][part] sum of the part of x_int
+  uint8_t* HQ;           // [pairs][d_ff / 128][op][part][digit][kb][16]: h likewise, in the order of its expert's bitwidth
   float* HS;             // [pairs][d_ff / 128]
-  int32_t* HSUM;
+  int32_t* HSUM;         // [pairs][d_ff / 128][part]
   BatchItem* items;      // written by workgroup 0 of k_batch_in
   int32_t* n_items;
   float* part;           // [d_ff / 1024 rounded up][pairs][d_model]
@@ -117,9 +127,10 @@ __device__ __forceinline__ int bits_slot(int mask, int bits) {
   return __popc((unsigned)mask & ((unsigned)bits - 1u) & 14u);      // bitwidths 2, 4, 8 are the bits of the mask
 }
 
-// x_int of eight values of a scale group that the 16 lanes of a DPP row share; returns 2^e (NaN if a value of the
-// group is not finite, x_int = 0 then) and the group's sum of x_int.
-__device__ __forceinline__ float group_ints(const float (&v)[8], int (&xi)[8], int& sum) {
+// x_int of eight values of a scale group that the 16 lanes of a DPP row share, and what its parts hold of it; returns 2^e
+// (NaN if a value of the group is not finite, x_int = 0 then) and the group's sums of the parts.
+template <int PARTS>
+__device__ __forceinline__ float group_ints(const float (&v)[8], int (&part)[PARTS][8], int (&sum)[PARTS]) {
   float m = 0.f;
   bool bad = false;
 #pragma unroll
@@ -132,49 +143,63 @@ __device__ __forceinline__ float group_ints(const float (&v)[8], int (&xi)[8], i
   m = fmaxf(m, dpp<kDppXor2>(m));
   m = fmaxf(m, dpp<kDppRor4>(m));
   m = fmaxf(m, dpp<kDppRor8>(m));
-  // the largest magnitude m * 2^-e lies in [2^14, 32639], what a signed byte pair holds: one bit more than the digits of
-  // k_moe_stream, because h has one exponent per 128 values here and one per 64 there
+  // one part: the largest magnitude m * 2^-e lies in [2^14, 32639], what a signed byte pair holds: one bit more than the
+  // digits of k_moe_stream, because h has one exponent per 128 values here and one per 64 there. Two: in [2^29, 2^30), and
+  // the low part in [-32896, 32639]
   int e = 0;
   if (m > 0.f && m < INFINITY) {
-    e = __builtin_amdgcn_frexp_expf(m) - 15;
-    e += m * pow2f(min(max(-e, -120), 120)) > 32639.f ? 1 : 0;
+    e = __builtin_amdgcn_frexp_expf(m) - (PARTS == 1 ? 15 : 30);
+    if (PARTS == 1) e += m * pow2f(min(max(-e, -120), 120)) > 32639.f ? 1 : 0;
   }
   e = min(max(e, -120), 120);
   const float dn = pow2f(-e);
-  sum = 0;
+#pragma unroll
+  for (int p = 0; p < PARTS; ++p) sum[p] = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    xi[i] = m < INFINITY ? __float2int_rn(v[i] * dn) : 0;
-    sum += xi[i];
+    int xi = m < INFINITY ? __float2int_rn(v[i] * dn) : 0;
+    if constexpr (PARTS == 2) {
+      part[1][i] = (xi + 32896) >> 16;
+      sum[1] += part[1][i];
+      xi -= part[1][i] * 65536;
+    }
+    part[0][i] = xi;
+    sum[0] += xi;
   }
-  sum += dppi<kDppXor1>(sum);
-  sum += dppi<kDppXor2>(sum);
-  sum += dppi<kDppRor4>(sum);
-  sum += dppi<kDppRor8>(sum);
+#pragma unroll
+  for (int p = 0; p < PARTS; ++p) {
+    sum[p] += dppi<kDppXor1>(sum[p]);
+    sum[p] += dppi<kDppXor2>(sum[p]);
+    sum[p] += dppi<kDppRor4>(sum[p]);
+    sum[p] += dppi<kDppRor8>(sum[p]);
+  }
   return m < INFINITY ? pow2f(e) : __builtin_nanf("");
 }
 
 // ---------------------------------------------------------------------------------------------
 // Workgroup = one token, thread t holds columns 8 t .. 8 t + 7. The router's sums are those of k_moe_stream, term by
 // term, so a token's routing does not depend on how many tokens share its call.
+template <bool STREAM>
 __global__ __launch_bounds__(512) void k_batch_prep(BatchArgs G) {
-  __shared__ __align__(16) int16_t XI[kBD];
+  constexpr int PARTS = batch_parts(STREAM);
+  __shared__ __align__(16) int16_t XI[PARTS][kBD];
   __shared__ float rpart[kBWaves * kBInlineMaxE];
   __shared__ float lg[kBInlineMaxE];
   const LayerDims& L = G.L;
   const int token = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, E = L.n_experts;
   const XItem xit = load_x_item((const char*)G.x + (size_t)token * kBD * (L.x_bf16 ? 2 : 4), L.x_bf16 ? X_BF16 : X_F32, tid);
   auto stage = [&]() __attribute__((always_inline)) {
-    int xi[8], sum;
-    const float s = group_ints(xit.v, xi, sum);
-    if ((tid & 15) == 0) {
-      G.XS[(size_t)token * kBGroups + (tid >> 4)] = s;
-      G.XSUM[(size_t)token * kBGroups + (tid >> 4)] = sum;
-    }
-    uint32_t w[4];
+    int part[PARTS][8], sum[PARTS];
+    const float s = group_ints<PARTS>(xit.v, part, sum);
+    if ((tid & 15) == 0) G.XS[(size_t)token * kBGroups + (tid >> 4)] = s;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = ((uint32_t)xi[2 * i] & 0xffffu) | ((uint32_t)xi[2 * i + 1] << 16);
-    ((uint4*)XI)[tid] = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int p = 0; p < PARTS; ++p) {
+      if ((tid & 15) == 0) G.XSUM[((size_t)token * kBGroups + (tid >> 4)) * PARTS + p] = sum[p];
+      uint32_t w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = ((uint32_t)part[p][2 * i] & 0xffffu) | ((uint32_t)part[p][2 * i + 1] << 16);
+      ((uint4*)XI[p])[tid] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
   };
   bool staged = false;
   if (G.route_inline) {
@@ -213,35 +238,32 @@ __global__ __launch_bounds__(512) void k_batch_prep(BatchArgs G) {
     else if (E <= 16 && L.top_k <= 2) topk_tiny<16>(lg, E, L.top_k, L.renorm, lane, se, sg);
     else topk_from_logits(lg, E, L.top_k, L.renorm, lane, se, sg, nullptr);
   }
-  // the operand bytes: 256 pieces of 16 columns per bitwidth, both digits of a piece by one thread
-  auto pieces = [&](auto bits_tag, auto order_tag) __attribute__((always_inline)) {
-    constexpr int BITS = decltype(bits_tag)::value, ORDER = decltype(order_tag)::value;
-    uint8_t* out = G.XQ + ((size_t)bits_slot(G.bits_mask, BITS) * G.T + token) * (2 * kBD);
-    for (int pc = tid; pc < kBD / 16; pc += 512) {
+  // the operand bytes: 256 pieces of 16 columns per bitwidth and part, both digits of a piece by one thread
+  auto pieces = [&](auto bits_tag) __attribute__((always_inline)) {
+    constexpr int BITS = decltype(bits_tag)::value, ORDER = STREAM ? BO_STREAM : BO_ROWS;
+    uint8_t* out = G.XQ + ((size_t)bits_slot(G.bits_mask, BITS) * G.T + token) * (PARTS * 2 * kBD);
+    for (int i = tid; i < PARTS * (kBD / 16); i += 512) {
+      const int p = i / (kBD / 16), pc = i % (kBD / 16);
       const int g = pc >> 3, op = (pc >> 2) & 1, kb = pc & 3;
       uint32_t lo[4] = {0u, 0u, 0u, 0u}, hi[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const int v = XI[g * kBGroup + operand_col<BITS, ORDER>(op, kb, j)];
+        const int v = XI[p][g * kBGroup + operand_col<BITS, ORDER>(op, kb, j)];
         lo[j >> 2] |= lo_byte(v) << (8 * (j & 3));
         hi[j >> 2] |= hi_byte(v) << (8 * (j & 3));
       }
-      uint4* dst = (uint4*)(out + (size_t)(g * 2 + op) * 128 + kb * 16);
+      uint4* dst = (uint4*)(out + (size_t)((g * 2 + op) * PARTS + p) * 128 + kb * 16);
       dst[0] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
       dst[4] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
     }
   };
-  auto all = [&](auto order_tag) __attribute__((always_inline)) {
-    if (G.bits_mask & 2) pieces(std::integral_constant<int, 2>{}, order_tag);
-    if (G.bits_mask & 4) pieces(std::integral_constant<int, 4>{}, order_tag);
-    if (G.bits_mask & 8) pieces(std::integral_constant<int, 8>{}, order_tag);
-  };
-  if (G.in_stream) all(std::integral_constant<int, BO_STREAM>{});
-  else all(std::integral_constant<int, BO_ROWS>{});
+  if (G.bits_mask & 2) pieces(std::integral_constant<int, 2>{});
+  if (G.bits_mask & 4) pieces(std::integral_constant<int, 4>{});
+  if (G.bits_mask & 8) pieces(std::integral_constant<int, 8>{});
 }
 
 // ---------------------------------------------------------------------------------------------
-// Groups the pairs of the call by expert into items (first come, first served; 16 pairs each), in LDS. Every thread of
+// Groups the pairs of the call by expert into items (first come, first served; TOK pairs each), in LDS. Every thread of
 // a workgroup of 512 calls it. O(pairs) broadcast reads per pair: a call has at most kBatchMaxPairs of them.
 struct BatchLists {
   int32_t pe[kBatchMaxPairs];
@@ -250,6 +272,7 @@ struct BatchLists {
   int32_t wcnt[kBatchMaxPairs / 64];
   BatchItem items[kBatchMaxPairs];
 };
+template <int TOK>
 __device__ __forceinline__ int batch_items(const BatchArgs& G, BatchLists& S) {
   const int p = threadIdx.x, P = G.T * G.k, E = G.L.n_experts;
   const int lane = p & 63, wave = p >> 6;
@@ -269,7 +292,7 @@ __device__ __forceinline__ int batch_items(const BatchArgs& G, BatchLists& S) {
     }
     S.rank[p] = r;
   }
-  const bool first = p < P && (r & (kBTok - 1)) == 0;
+  const bool first = p < P && (r & (TOK - 1)) == 0;
   const unsigned long long mask = __ballot(first);
   if (lane == 0 && wave < kBatchMaxPairs / 64) S.wcnt[wave] = __popcll(mask);
   __syncthreads();
@@ -282,7 +305,7 @@ __device__ __forceinline__ int batch_items(const BatchArgs& G, BatchLists& S) {
     const int i = before + __popcll(mask & ((1ull << lane) - 1ull));
     S.it[p] = i;
     S.items[i].e = e;
-    S.items[i].n = min(kBTok, total - r);
+    S.items[i].n = min(TOK, total - r);
     S.items[i].bits = G.table[e].bits;
   }
   __syncthreads();
@@ -290,9 +313,9 @@ __device__ __forceinline__ int batch_items(const BatchArgs& G, BatchLists& S) {
     int mine = 0;
 #pragma unroll 4
     for (int q = 0; q < P; ++q)
-      if (S.pe[q] == e && S.rank[q] == (r & ~(kBTok - 1))) mine = q;
+      if (S.pe[q] == e && S.rank[q] == (r & ~(TOK - 1))) mine = q;
     const int i = S.it[mine];
-    S.items[i].pair[r & (kBTok - 1)] = (uint8_t)p;
+    S.items[i].pair[r & (TOK - 1)] = (uint8_t)p;
   }
   __syncthreads();
   return n_items;
@@ -312,9 +335,9 @@ struct BatchSet {
 
 struct BatchInLds {
   uint4 A[kBGroups * 4][64];           // operand (g, op, digit): lane's 16 bytes
-  float XS[kBGroups][kBTok];
-  int32_t SX[kBGroups][kBTok];         // minus the code offset times the sum of x_int
-  float H[2][kBTok][kBGroup + 4];      // h of a unit's rows, two units in turn
+  float XS[kBGroups][kBRows];          // 2^e of every row (a high part's is 2^16 times its low part's)
+  int32_t SX[kBGroups][kBRows];        // minus the code offset times the sum of the row's integers
+  float H[2][kBRows][kBGroup + 4];     // h of a unit's rows, two units in turn
   BatchLists lists;
 };
 
@@ -327,7 +350,7 @@ struct BatchInLds {
 template <int BITS, int NM, bool SWIGLU, bool STREAM>
 __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S, const BatchItem& item, int u0, int u1) {
   using Set = BatchSet<BITS, NM>;
-  constexpr int RB = 16 / BITS, TPR = BITS / 2;
+  constexpr int RB = 16 / BITS, TPR = BITS / 2, TOK = batch_tok(STREAM), PARTS = batch_parts(STREAM);
   constexpr uint32_t BB = 8192u + 64u * RB;
   constexpr int LPM = BITS / 2;                    // loads of one matrix per 256 columns
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -340,25 +363,26 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
   sp[0] = STREAM ? q[0] : (const uint8_t*)uniform_ptr(ex->s_in);
   if constexpr (NM == 2) sp[1] = STREAM ? q[1] : (const uint8_t*)uniform_ptr(ex->s_gate);
   const int NG = G.L.d_ff / kBGroup;
-  const uint8_t* xq = G.XQ + (size_t)bits_slot(G.bits_mask, BITS) * G.T * (2 * kBD);
+  const uint8_t* xq = G.XQ + (size_t)bits_slot(G.bits_mask, BITS) * G.T * (PARTS * 2 * kBD);
 
   __syncthreads();          // every wavefront is done with the previous item's operands
-  // the item's 16 activation rows into LDS, operand by operand (absent pairs repeat the first one; their results are dropped)
+  // the item's 16 activation rows into LDS, operand by operand (row m: pair m % TOK, part m / TOK; absent pairs repeat the
+  // first one, their results are dropped)
   {
-    const int pm = item.pair[n < item.n ? n : 0];
-    const uint8_t* src = xq + (size_t)(pm / G.k) * (2 * kBD) + kb * 16;
+    const int pm = item.pair[n % TOK < item.n ? n % TOK : 0];
+    const uint8_t* src = xq + (size_t)(pm / G.k) * (PARTS * 2 * kBD) + (n / TOK) * 128 + kb * 16;
     const uint32_t a0 = (uint32_t)(uintptr_t)(MOEQ_LDS char*)&S.A[0][0];
 #pragma unroll 4
     for (int i = 0; i < kBGroups * 4 / kBWaves; ++i) {
-      const int o = wave + i * kBWaves;
-      dma16(src + o * 64, a0 + (uint32_t)o * 1024u);
+      const int o = wave + i * kBWaves;              // (operand op of a group, digit) = (o / 2, o % 2)
+      dma16(src + (o >> 1) * (PARTS * 128) + (o & 1) * 64, a0 + (uint32_t)o * 1024u);
     }
   }
   {
-    const int g = threadIdx.x >> 4, m = threadIdx.x & 15;         // 512 threads = 32 groups x 16 pairs
-    const int tok = item.pair[m < item.n ? m : 0] / G.k;
-    S.XS[g][m] = G.XS[(size_t)tok * kBGroups + g];
-    S.SX[g][m] = -code_offset<BITS>() * G.XSUM[(size_t)tok * kBGroups + g];
+    const int g = threadIdx.x >> 4, m = threadIdx.x & 15;         // 512 threads = 32 groups x 16 rows
+    const size_t at = (size_t)(item.pair[m % TOK < item.n ? m % TOK : 0] / G.k) * kBGroups + g;
+    S.XS[g][m] = G.XS[at] * (m < TOK ? 1.f : 65536.f);
+    S.SX[g][m] = -code_offset<BITS>() * G.XSUM[at * PARTS + m / TOK];
   }
   const int total = (u1 - u0) * Set::SPU;
   auto issue = [&](Set& R, int s) __attribute__((always_inline)) {
@@ -509,6 +533,10 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
       const int unit = u0 + s / Set::SPU, hb = unit & 1;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
+        if constexpr (PARTS == 2) {                // low and high part of a pair: lanes kb and kb + 2
+#pragma unroll
+          for (int m = 0; m < NM; ++m) acc[m][i] += __shfl_xor(acc[m][i], 32);
+        }
         const float a = acc[0][i];
         float v;
         if constexpr (SWIGLU) v = a / (1.0f + __expf(-a)) * acc[NM - 1][i];
@@ -522,28 +550,29 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
         float v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = S.H[hb][m][8 * seg + i];
-        int xi[8], sum;
-        const float hs = group_ints(v, xi, sum);
-        uint32_t half[2][4];             // 2 bits: byte pairs (column q, q + 4 of the half word) of both digits
+        int part[PARTS][8], sum[PARTS];
+        const float hs = group_ints<PARTS>(v, part, sum);
+        const size_t pair = item.pair[m < item.n ? m : 0];
+        if (m < item.n && seg == 0) G.HS[pair * NG + unit] = hs;
 #pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          half[0][qd] = lo_byte(xi[qd]) | lo_byte(xi[qd + 4]) << 8;
-          half[1][qd] = hi_byte(xi[qd]) | hi_byte(xi[qd + 4]) << 8;
-        }
-        uint32_t other[2][4];
-        if constexpr (BITS == 2) {
+        for (int p = 0; p < PARTS; ++p) {
+          const int (&xi)[8] = part[p];
+          uint32_t half[2][4];             // 2 bits: byte pairs (column q, q + 4 of the half word) of both digits
 #pragma unroll
-          for (int dg = 0; dg < 2; ++dg)
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) other[dg][qd] = (uint32_t)dppi<kDppXor1>((int)half[dg][qd]);
-        }
-        if (m < item.n) {
-          const size_t pair = item.pair[m];
-          if (seg == 0) {
-            G.HS[pair * NG + unit] = hs;
-            G.HSUM[pair * NG + unit] = sum;
+          for (int qd = 0; qd < 4; ++qd) {
+            half[0][qd] = lo_byte(xi[qd]) | lo_byte(xi[qd + 4]) << 8;
+            half[1][qd] = hi_byte(xi[qd]) | hi_byte(xi[qd + 4]) << 8;
           }
-          uint8_t* dst = G.HQ + pair * (size_t)(2 * G.L.d_ff) + (size_t)unit * 256;
+          uint32_t other[2][4];
+          if constexpr (BITS == 2) {
+#pragma unroll
+            for (int dg = 0; dg < 2; ++dg)
+#pragma unroll
+              for (int qd = 0; qd < 4; ++qd) other[dg][qd] = (uint32_t)dppi<kDppXor1>((int)half[dg][qd]);
+          }
+          if (m >= item.n) continue;
+          if (seg == 0) G.HSUM[(pair * NG + unit) * PARTS + p] = sum[p];
+          uint8_t* dst = G.HQ + (pair * (size_t)(2 * G.L.d_ff) + (size_t)unit * 256) * PARTS + p * 128;
 #pragma unroll
           for (int dg = 0; dg < 2; ++dg) {
             uint32_t by[8];
@@ -551,24 +580,25 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
             for (int i = 0; i < 8; ++i) by[i] = dg ? hi_byte(xi[i]) : lo_byte(xi[i]);
             const uint32_t lo4 = by[0] | by[1] << 8 | by[2] << 16 | by[3] << 24, hi4 = by[4] | by[5] << 8 | by[6] << 16 | by[7] << 24;
             const uint32_t even = by[0] | by[2] << 8 | by[4] << 16 | by[6] << 24, odds = by[1] | by[3] << 8 | by[5] << 16 | by[7] << 24;
-            const bool cols = G.out_columns != 0;
+            const bool cols = STREAM || G.out_columns != 0;
+            // a piece (op, digit dg, kb) of the group lies at op * 128 * PARTS + dg * 64 + kb * 16
             if constexpr (BITS == 4) {           // the thread's columns are word `seg` of the group: operand, kb, half of the piece
               const int op = cols ? seg >> 3 : (seg >> 1) & 1, okb = cols ? seg & 3 : seg >> 2, hf = cols ? (seg >> 2) & 1 : seg & 1;
-              *(uint2*)(dst + (op * 2 + dg) * 64 + okb * 16 + hf * 8) = make_uint2(even, odds);
+              *(uint2*)(dst + op * (128 * PARTS) + dg * 64 + okb * 16 + hf * 8) = make_uint2(even, odds);
             } else if constexpr (BITS == 2) {    // half of word seg >> 1: the even thread writes dwords 0, 1, the odd one 2, 3
               const int wd = seg >> 1, odd = seg & 1;
               const int op = cols ? wd >> 2 : (wd >> 1) & 1, okb = cols ? wd & 3 : (wd >> 2) | (wd & 1) << 1;
               const uint32_t d0 = odd ? (other[dg][2] | half[dg][2] << 16) : (half[dg][0] | other[dg][0] << 16);
               const uint32_t d1 = odd ? (other[dg][3] | half[dg][3] << 16) : (half[dg][1] | other[dg][1] << 16);
-              *(uint2*)(dst + (op * 2 + dg) * 64 + okb * 16 + odd * 8) = make_uint2(d0, d1);
+              *(uint2*)(dst + op * (128 * PARTS) + dg * 64 + okb * 16 + odd * 8) = make_uint2(d0, d1);
             } else if (cols) {                   // words 2 seg and 2 seg + 1
 #pragma unroll
               for (int i = 0; i < 2; ++i) {
                 const int wd = 2 * seg + i;
-                *(uint32_t*)(dst + ((wd >> 4) * 2 + dg) * 64 + (wd & 3) * 16 + ((wd >> 2) & 3) * 4) = i ? hi4 : lo4;
+                *(uint32_t*)(dst + (wd >> 4) * (128 * PARTS) + dg * 64 + (wd & 3) * 16 + ((wd >> 2) & 3) * 4) = i ? hi4 : lo4;
               }
             } else {                             // half of a piece of sixteen columns
-              *(uint2*)(dst + ((seg >> 3) * 2 + dg) * 64 + ((seg >> 1) & 3) * 16 + (seg & 1) * 8) = make_uint2(lo4, hi4);
+              *(uint2*)(dst + (seg >> 3) * (128 * PARTS) + dg * 64 + ((seg >> 1) & 3) * 16 + (seg & 1) * 8) = make_uint2(lo4, hi4);
             }
           }
         }
@@ -585,7 +615,7 @@ __global__ __launch_bounds__(512) void k_batch_in(BatchArgs G) {
   extern __shared__ __attribute__((aligned(16))) char bsmem[];
   BatchInLds& S = *(BatchInLds*)bsmem;
   constexpr int NM = SWIGLU ? 2 : 1;
-  const int n_items = batch_items(G, S.lists);
+  const int n_items = batch_items<batch_tok(STREAM)>(G, S.lists);
   if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i < n_items * 2; i += 512) ((uint4*)G.items)[i] = ((const uint4*)S.lists.items)[i];
     if (threadIdx.x == 0) *G.n_items = n_items;
@@ -626,15 +656,16 @@ struct BatchOutSet {
 
 struct BatchOutLds {
   uint4 A[kBOutGroups * 4][64];
-  float XS[kBOutGroups][kBTok];
-  int32_t SX[kBOutGroups][kBTok];
+  float XS[kBOutGroups][kBRows];
+  int32_t SX[kBOutGroups][kBRows];
 };
 
 // Canonical rows: the wavefront's 64 rows are four blocks of 16; lane (n, kb) loads 16-byte piece 4 j + kb of row 16 i + n
 // (64 consecutive bytes of 16 rows: one scale group at 4 bits, two at 2, half of one at 8), operand i belongs to block i.
-template <int BITS, bool COLS>
+template <int BITS, bool COLS, bool STREAM>
 __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, const BatchItem& item) {
   using Set = BatchOutSet<BITS>;
+  constexpr int TOK = batch_tok(STREAM), PARTS = batch_parts(STREAM);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, kb = lane >> 4;
   const int NG = G.L.d_ff / kBGroup;
@@ -644,20 +675,20 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
   const uint8_t* q = uniform_ptr(ex->q_out);
   const uint8_t* sc = (const uint8_t*)uniform_ptr(ex->s_out);
   {
-    const int pm = item.pair[n < item.n ? n : 0];
-    const uint8_t* src = G.HQ + (size_t)pm * (size_t)(2 * G.L.d_ff) + (size_t)g0 * 256 + kb * 16;
+    const int pm = item.pair[n % TOK < item.n ? n % TOK : 0];
+    const uint8_t* src = G.HQ + ((size_t)pm * (size_t)(2 * G.L.d_ff) + (size_t)g0 * 256) * PARTS + (n / TOK) * 128 + kb * 16;
     const uint32_t a0 = (uint32_t)(uintptr_t)(MOEQ_LDS char*)&S.A[0][0];
     for (int i = 0; i < kBOutGroups; ++i) {
       const int o = wave + 4 * i;                  // operands of the groups that exist
-      if (o < ng * 4) dma16(src + o * 64, a0 + (uint32_t)o * 1024u);
+      if (o < ng * 4) dma16(src + (o >> 1) * (PARTS * 128) + (o & 1) * 64, a0 + (uint32_t)o * 1024u);
     }
   }
-  if (threadIdx.x < kBOutGroups * kBTok) {
+  if (threadIdx.x < kBOutGroups * kBRows) {
     const int g = threadIdx.x >> 4, m = threadIdx.x & 15;
     if (g < ng) {
-      const size_t at = (size_t)item.pair[m < item.n ? m : 0] * NG + g0 + g;
-      S.XS[g][m] = G.HS[at];
-      S.SX[g][m] = -code_offset<BITS>() * G.HSUM[at];
+      const size_t at = (size_t)item.pair[m % TOK < item.n ? m % TOK : 0] * NG + g0 + g;
+      S.XS[g][m] = G.HS[at] * (m < TOK ? 1.f : 65536.f);
+      S.SX[g][m] = -code_offset<BITS>() * G.HSUM[at * PARTS + m / TOK];
     }
   }
   const int n_sets = (ng + Set::GS - 1) / Set::GS;
@@ -775,7 +806,11 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int m = 4 * kb + j;
+    if constexpr (PARTS == 2) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i][j] += __shfl_xor(acc[i][j], 32);
+    }
+    const int m = 4 * kb + j;                      // (the lanes of the high parts' rows, 8 .. 15, write nothing: item.n <= TOK)
     if (m < item.n) {
       float* o = G.part + ((size_t)blockIdx.y * (size_t)(G.T * G.k) + item.pair[m]) * kBD + r0;
       if constexpr (COLS) {
@@ -789,7 +824,7 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
 }
 
 // Grid (row chunks, chunks of d_ff, upper bound of the items).
-template <bool COLS>
+template <bool COLS, bool STREAM>
 __global__ __launch_bounds__(256) void k_batch_out(BatchArgs G) {
   __shared__ BatchOutLds S;
   __shared__ BatchItem item;
@@ -797,9 +832,9 @@ __global__ __launch_bounds__(256) void k_batch_out(BatchArgs G) {
   if (threadIdx.x < 2) ((uint4*)&item)[threadIdx.x] = ((const uint4*)(G.items + blockIdx.z))[threadIdx.x];
   __syncthreads();
   const int bits = __builtin_amdgcn_readfirstlane(item.bits);
-  if (bits == 2) batch_out<2, COLS>(G, S, item);
-  else if (bits == 4) batch_out<4, COLS>(G, S, item);
-  else batch_out<8, COLS>(G, S, item);
+  if (bits == 2) batch_out<2, COLS, STREAM>(G, S, item);
+  else if (bits == 4) batch_out<4, COLS, STREAM>(G, S, item);
+  else batch_out<8, COLS, STREAM>(G, S, item);
 }
 
 // y[t][r] (+)= sum_j gate[t][j] * sum_c part[c][t k + j][r], chunks and choices in order. gate null: 1.
@@ -838,18 +873,18 @@ int batch_cus() {
 }  // namespace
 
 // Byte offsets of the path's pieces in the workspace; k: choices per token (1 for a single expert's call).
-BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask) {
+BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask, bool in_stream) {
   BatchWs w{};
-  const size_t P = (size_t)T * (size_t)k, NG = (size_t)L.d_ff / kBGroup;
+  const size_t parts = batch_parts(in_stream), P = (size_t)T * (size_t)k, NG = (size_t)L.d_ff / kBGroup;
   size_t off = 0;
   w.items = off;  off += up256(P * sizeof(BatchItem));
   w.n_items = off; off += 256;
-  w.xq = off;     off += up256((size_t)__builtin_popcount((unsigned)bits_mask & 14u) * (size_t)T * 2 * kBD);
+  w.xq = off;     off += up256((size_t)__builtin_popcount((unsigned)bits_mask & 14u) * (size_t)T * parts * 2 * kBD);
   w.xs = off;     off += up256((size_t)T * kBGroups * 4);
-  w.xsum = off;   off += up256((size_t)T * kBGroups * 4);
-  w.hq = off;     off += up256(P * 2 * (size_t)L.d_ff);
+  w.xsum = off;   off += up256((size_t)T * kBGroups * parts * 4);
+  w.hq = off;     off += up256(P * parts * 2 * (size_t)L.d_ff);
   w.hs = off;     off += up256(P * NG * 4);
-  w.hsum = off;   off += up256(P * NG * 4);
+  w.hsum = off;   off += up256(P * NG * parts * 4);
   w.part = off;   off += up256((NG + kBOutGroups - 1) / kBOutGroups * P * kBD * 4);
   w.total = off;
   return w;
@@ -871,23 +906,24 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
                             float* gate, const float* gate_out, int32_t accumulate, bool in_stream, bool out_columns, char* ws,
                             float* y, hipStream_t st) {
   const int k = fixed_expert >= 0 ? 1 : L.top_k;
-  if (!batch_supported(L) || L.d_ff % kBGroup || T < 1 || (int64_t)T * k > kBatchMaxPairs || !(bits_mask & 14)) return hipErrorInvalidValue;
+  if (!batch_supported(L) || L.d_ff % kBGroup || T < 1 || (int64_t)T * k > kBatchMaxPairs || !(bits_mask & 14) || (in_stream && !out_columns))
+    return hipErrorInvalidValue;
   if (route_inline && (fixed_expert >= 0 || L.n_experts > kBInlineMaxE)) return hipErrorInvalidValue;
   if (fixed_expert < 0 && (!idx || !gate)) return hipErrorInvalidValue;
-  const BatchWs w = batch_ws(L, T, k, bits_mask);
-  BatchArgs G{L, table, router_w, router_bias, x, T, k, fixed_expert, bits_mask & 14, route_inline ? 1 : 0, in_stream ? 1 : 0,
-              out_columns ? 1 : 0, idx, gate,
+  const BatchWs w = batch_ws(L, T, k, bits_mask, in_stream);
+  BatchArgs G{L, table, router_w, router_bias, x, T, k, fixed_expert, bits_mask & 14, route_inline ? 1 : 0, out_columns ? 1 : 0, idx, gate,
               (uint8_t*)(ws + w.xq), (float*)(ws + w.xs), (int32_t*)(ws + w.xsum), (uint8_t*)(ws + w.hq),
               (float*)(ws + w.hs), (int32_t*)(ws + w.hsum), (BatchItem*)(ws + w.items), (int32_t*)(ws + w.n_items),
               (float*)(ws + w.part)};
   const int P = T * k;
-  const int max_items = P < L.n_experts + P / kBTok ? P : L.n_experts + P / kBTok;
+  const int tok = batch_tok(in_stream), max_items = P < L.n_experts + P / tok ? P : L.n_experts + P / tok;
   const int chunks = (L.d_ff / kBGroup + kBOutGroups - 1) / kBOutGroups;
-  hipLaunchKernelGGL(k_batch_prep, dim3(T), dim3(512), 0, st, G);
+  hipLaunchKernelGGL(in_stream ? k_batch_prep<true> : k_batch_prep<false>, dim3(T), dim3(512), 0, st, G);
   const bool sw = L.act == MOEQ_ACT_SWIGLU;
   auto kin = in_stream ? (sw ? k_batch_in<true, true> : k_batch_in<false, true>) : (sw ? k_batch_in<true, false> : k_batch_in<false, false>);
   hipLaunchKernelGGL(kin, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
-  hipLaunchKernelGGL(out_columns ? k_batch_out<true> : k_batch_out<false>, dim3(kBD / kBOutRows, chunks, max_items), dim3(256), 0, st, G);
+  auto kout = in_stream ? k_batch_out<true, true> : out_columns ? k_batch_out<true, false> : k_batch_out<false, false>;
+  hipLaunchKernelGGL(kout, dim3(kBD / kBOutRows, chunks, max_items), dim3(256), 0, st, G);
   hipLaunchKernelGGL(k_batch_combine, dim3(kBD / 1024, T), dim3(256), 0, st, G.part, gate_out, chunks, T, k, accumulate, y);
   return hipGetLastError();
 }

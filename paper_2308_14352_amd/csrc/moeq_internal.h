@@ -97,12 +97,12 @@ hipError_t launch_moe_stream(const LayerDims& L, const DevExpert* table, const f
                              float* gate_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr);
 // ---- calls of a few tokens on layers of that shape in any layout: pairs grouped by expert, every expert's weights
-// streamed once for up to 16 pairs (decode_batch.hip). At most kBatchMaxPairs (token, choice) pairs. route_inline: the router runs here and
+// streamed once for up to 16 pairs (8 on layers that are not in the stream layout; decode_batch.hip). At most kBatchMaxPairs (token, choice) pairs. route_inline: the router runs here and
 // writes idx / gate (at most batch_inline_router_max() experts); else idx / gate hold the routing. fixed_expert >= 0:
 // that expert for every token (idx / gate unused). gate_out: the weights of the combine, [T][k] or null (= 1).
 constexpr int kBatchMaxPairs = 256;
 struct BatchWs { size_t items, n_items, xq, xs, xsum, hq, hs, hsum, part, total; };
-BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask);
+BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask, bool in_stream);
 bool batch_supported(const LayerDims& L);
 int batch_inline_router_max();
 hipError_t init_attrs_decode_batch();

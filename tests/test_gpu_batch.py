@@ -9,14 +9,14 @@ import torch
 import gen
 import oracle
 import paper_2308_14352_amd as moeq
-from helpers import build_layer_pair, near_tie_tokens, oracle_layer, rel_err
+from helpers import build_layer_pair, near_tie_tokens, oracle_layer, pack_expert_gpu, pack_expert_oracle, rel_err
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-# x and h enter with one exponent per 128 values and 15 bits below it: an element is off by at most 2^-16 of its group's
+# On layers in the stream layout x and h enter with one exponent per 128 values and 15 bits below it: an element is off by at most 2^-16 of its group's
 # largest (about 3.5 standard deviations), 6e-5 / sqrt(3) of a standard deviation, once for x and once for h; the largest
 # of 4096 outputs' errors (4 standard deviations) against the largest output (again about 4) stays near that figure. The
-# gate product and fp32 sums add less. 4e-4 leaves a factor of five.
+# gate product and fp32 sums add less. 4e-4 leaves a factor of five. (On other layers they enter with 30 bits below it.)
 TOL = 4e-4
 
 
@@ -119,3 +119,27 @@ def test_grouped_call_at_the_ends_of_the_hidden_states_range(layout):
         y = moeq.moe_layer_forward_routed(layer, x * 2.0 ** e, idx, gate)
         torch.cuda.synchronize()
         assert rel_err(y.cpu().numpy().astype(np.float64) * 2.0 ** -e, y_ref).max() < TOL
+
+
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("layout", ("canonical", "columns"))
+def test_grouped_call_with_outlier_columns_that_meet_zero_weights(bits, layout):
+    """An element 2^10 times the others in every scale group, on weights of zero: the results are those of the other
+    elements, which keep at least the 11 bits that the single-token kernels give every element. (Layers in the stream layout
+    hold 14 bits below the largest of a scale group on every path.)"""
+    d, f, g, T = 4096, 1152, 128, 40
+    cfg = replace(gen.tiny_config("c4", d, f, n_experts=1, n_layers=1, group=g), top_k=1, x_dtype="f32")
+    w = gen.expert_weights(cfg, 0, 0, DEV)
+    w["w_in"][:, 5::g] = 0.0
+    w["w_gate"][:, 5::g] = 0.0
+    ex = pack_expert_gpu(w, bits, g)
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    columns = layout == "columns"
+    layer = moeq.Layer(d, f, 1, g, moeq.MOEQ_ACT_SWIGLU, True, moeq.MOEQ_F32, Wr, bias, [ex.with_out_columns(f, g) if columns else ex],
+                       moeq.MOEQ_OUT_COLUMNS if columns else moeq.MOEQ_OUT_CANONICAL)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    x[:, 5::g] *= 1024.0
+    y = moeq.moe_expert_ffn_q(layer, 0, x)
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn(pack_expert_oracle(w, bits, g), d, f, g, 1, x.cpu().numpy())
+    assert rel_err(y.cpu().numpy(), ref).max() < TOL
