@@ -9,7 +9,9 @@
 // group's sum of x_int; 8-bit codes made signed by one XOR). v_mfma_i32_16x16x64_i8 gives the exact integer sums of 16
 // rows of activations x 16 rows of weights; per group sum * scale * 2^e in fp32, 2^e last and in the addition's fused
 // multiply: sum * 2^e alone leaves fp32 from hidden states of about 2^108 on.
-//   Stream layers: 15 bits below the group's largest and a sign, x_int = lo + 256 hi; an activation row per pair.
+//   Stream layers: 15 bits below the largest and a sign, x_int = lo + 256 hi; an activation row per pair. h has one exponent
+//   per 64 columns (an operand), as in k_moe_stream: with one per 128 an output of which the larger half met zero weights
+//   was off by 8.5e-2 instead of 2e-4 when the halves differed by 2^10.
 //   Other layers: 30 bits and a sign, in two such parts that are two rows of the operand (x_int = low + 2^16 high), so 8
 //   pairs fill it. Their single-token kernels hold x and h as binary16, 11 bits of every element whatever its neighbours
 //   are, and 15 bits below the largest are not that: where a column with activations 2^10 times the others of its group
@@ -116,8 +118,8 @@ struct BatchArgs {
   float* XS;             // [T][kBGroups] 2^e of every group (NaN: the group holds a non-finite value)
   int32_t* XSUM;         // [T][kBGroups][part] sum of the part of x_int
   uint8_t* HQ;           // [pairs][d_ff / 128][op][part][digit][kb][16]: h likewise, in the order of its expert's bitwidth
-  float* HS;             // [pairs][d_ff / 128]
-  int32_t* HSUM;         // [pairs][d_ff / 128][part]
+  float* HS;             // [pairs][d_ff / 128][2]: of both halves of the group's columns (other than stream layers: the same)
+  int32_t* HSUM;         // [pairs][d_ff / 128][2]: of both halves; other than stream layers: of both parts
   BatchItem* items;      // written by workgroup 0 of k_batch_in
   int32_t* n_items;
   float* part;           // [d_ff / 1024 rounded up][pairs][d_model]
@@ -127,9 +129,26 @@ __device__ __forceinline__ int bits_slot(int mask, int bits) {
   return __popc((unsigned)mask & ((unsigned)bits - 1u) & 14u);      // bitwidths 2, 4, 8 are the bits of the mask
 }
 
-// x_int of eight values of a scale group that the 16 lanes of a DPP row share, and what its parts hold of it; returns 2^e
-// (NaN if a value of the group is not finite, x_int = 0 then) and the group's sums of the parts.
-template <int PARTS>
+// Maximum / sum over the LANES (16: a DPP row, or 8) that share an exponent, in every one of them.
+template <int LANES>
+__device__ __forceinline__ float lanes_max(float m) {
+  m = fmaxf(m, dpp<kDppXor1>(m));
+  m = fmaxf(m, dpp<kDppXor2>(m));
+  if constexpr (LANES == 8) return fmaxf(m, dpp<kDppHalfMirror>(m));
+  m = fmaxf(m, dpp<kDppRor4>(m));
+  return fmaxf(m, dpp<kDppRor8>(m));
+}
+template <int LANES>
+__device__ __forceinline__ int lanes_sum(int v) {
+  v += dppi<kDppXor1>(v);
+  v += dppi<kDppXor2>(v);
+  if constexpr (LANES == 8) return v + dppi<kDppHalfMirror>(v);
+  v += dppi<kDppRor4>(v);
+  return v + dppi<kDppRor8>(v);
+}
+// x_int of eight values of the columns that LANES lanes share, and what its parts hold of it; returns 2^e (NaN if a value of
+// these columns is not finite, x_int = 0 then) and the sums of the parts over them.
+template <int PARTS, int LANES>
 __device__ __forceinline__ float group_ints(const float (&v)[8], int (&part)[PARTS][8], int (&sum)[PARTS]) {
   float m = 0.f;
   bool bad = false;
@@ -138,14 +157,9 @@ __device__ __forceinline__ float group_ints(const float (&v)[8], int (&part)[PAR
     m = fmaxf(m, fabsf(v[i]));
     bad = bad || !(fabsf(v[i]) < INFINITY);
   }
-  m = bad ? INFINITY : m;
-  m = fmaxf(m, dpp<kDppXor1>(m));
-  m = fmaxf(m, dpp<kDppXor2>(m));
-  m = fmaxf(m, dpp<kDppRor4>(m));
-  m = fmaxf(m, dpp<kDppRor8>(m));
-  // one part: the largest magnitude m * 2^-e lies in [2^14, 32639], what a signed byte pair holds: one bit more than the
-  // digits of k_moe_stream, because h has one exponent per 128 values here and one per 64 there. Two: in [2^29, 2^30), and
-  // the low part in [-32896, 32639]
+  m = lanes_max<LANES>(bad ? INFINITY : m);
+  // one part: the largest magnitude m * 2^-e lies in [2^14, 32639], what a signed byte pair holds (one bit more than the
+  // digits of k_moe_stream). Two: in [2^29, 2^30), and the low part in [-32896, 32639]
   int e = 0;
   if (m > 0.f && m < INFINITY) {
     e = __builtin_amdgcn_frexp_expf(m) - (PARTS == 1 ? 15 : 30);
@@ -167,12 +181,7 @@ __device__ __forceinline__ float group_ints(const float (&v)[8], int (&part)[PAR
     sum[0] += xi;
   }
 #pragma unroll
-  for (int p = 0; p < PARTS; ++p) {
-    sum[p] += dppi<kDppXor1>(sum[p]);
-    sum[p] += dppi<kDppXor2>(sum[p]);
-    sum[p] += dppi<kDppRor4>(sum[p]);
-    sum[p] += dppi<kDppRor8>(sum[p]);
-  }
+  for (int p = 0; p < PARTS; ++p) sum[p] = lanes_sum<LANES>(sum[p]);
   return m < INFINITY ? pow2f(e) : __builtin_nanf("");
 }
 
@@ -190,7 +199,7 @@ __global__ __launch_bounds__(512) void k_batch_prep(BatchArgs G) {
   const XItem xit = load_x_item((const char*)G.x + (size_t)token * kBD * (L.x_bf16 ? 2 : 4), L.x_bf16 ? X_BF16 : X_F32, tid);
   auto stage = [&]() __attribute__((always_inline)) {
     int part[PARTS][8], sum[PARTS];
-    const float s = group_ints<PARTS>(xit.v, part, sum);
+    const float s = group_ints<PARTS, 16>(xit.v, part, sum);
     if ((tid & 15) == 0) G.XS[(size_t)token * kBGroups + (tid >> 4)] = s;
 #pragma unroll
     for (int p = 0; p < PARTS; ++p) {
@@ -551,9 +560,10 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = S.H[hb][m][8 * seg + i];
         int part[PARTS][8], sum[PARTS];
-        const float hs = group_ints<PARTS>(v, part, sum);
+        const float hs = group_ints<PARTS, STREAM ? 8 : 16>(v, part, sum);
         const size_t pair = item.pair[m < item.n ? m : 0];
-        if (m < item.n && seg == 0) G.HS[pair * NG + unit] = hs;
+        const size_t at = (pair * NG + unit) * 2;           // of HS and HSUM
+        if (m < item.n && (seg & 7) == 0) G.HS[at + (seg >> 3)] = hs;
 #pragma unroll
         for (int p = 0; p < PARTS; ++p) {
           const int (&xi)[8] = part[p];
@@ -571,7 +581,7 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
               for (int qd = 0; qd < 4; ++qd) other[dg][qd] = (uint32_t)dppi<kDppXor1>((int)half[dg][qd]);
           }
           if (m >= item.n) continue;
-          if (seg == 0) G.HSUM[(pair * NG + unit) * PARTS + p] = sum[p];
+          if (STREAM ? (seg & 7) == 0 : seg == 0) G.HSUM[at + (STREAM ? seg >> 3 : p)] = sum[p];
           uint8_t* dst = G.HQ + (pair * (size_t)(2 * G.L.d_ff) + (size_t)unit * 256) * PARTS + p * 128;
 #pragma unroll
           for (int dg = 0; dg < 2; ++dg) {
@@ -656,8 +666,8 @@ struct BatchOutSet {
 
 struct BatchOutLds {
   uint4 A[kBOutGroups * 4][64];
-  float XS[kBOutGroups][kBRows];
-  int32_t SX[kBOutGroups][kBRows];
+  float XS[kBOutGroups][2][kBRows];        // [half of the group's columns] (other than stream layers: the first)
+  int32_t SX[kBOutGroups][2][kBRows];
 };
 
 // Canonical rows: the wavefront's 64 rows are four blocks of 16; lane (n, kb) loads 16-byte piece 4 j + kb of row 16 i + n
@@ -683,12 +693,12 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
       if (o < ng * 4) dma16(src + (o >> 1) * (PARTS * 128) + (o & 1) * 64, a0 + (uint32_t)o * 1024u);
     }
   }
-  if (threadIdx.x < kBOutGroups * kBRows) {
-    const int g = threadIdx.x >> 4, m = threadIdx.x & 15;
+  {
+    const int g = threadIdx.x >> 5, half = (threadIdx.x >> 4) & 1, m = threadIdx.x & 15;      // 256 threads = 8 groups x 2 x 16 rows
     if (g < ng) {
-      const size_t at = (size_t)item.pair[m % TOK < item.n ? m % TOK : 0] * NG + g0 + g;
-      S.XS[g][m] = G.HS[at] * (m < TOK ? 1.f : 65536.f);
-      S.SX[g][m] = -code_offset<BITS>() * G.HSUM[at * PARTS + m / TOK];
+      const size_t at = ((size_t)item.pair[m % TOK < item.n ? m % TOK : 0] * NG + g0 + g) * 2;
+      S.XS[g][half][m] = G.HS[at + half] * (m < TOK ? 1.f : 65536.f);
+      S.SX[g][half][m] = -code_offset<BITS>() * G.HSUM[at + (STREAM ? half : m / TOK)];
     }
   }
   const int n_sets = (ng + Set::GS - 1) / Set::GS;
@@ -740,9 +750,13 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
         for (int op = 0; op < 2; ++op)
 #pragma unroll
           for (int dg = 0; dg < 2; ++dg) A[op][dg] = __builtin_bit_cast(i32x4_t, S.A[(g * 2 + op) * 2 + dg][lane]);
-        const i32x4_t sx = *(const i32x4_t*)&S.SX[g][4 * kb];
-        const float4 xs = *(const float4*)&S.XS[g][4 * kb];
+        const i32x4_t sx = *(const i32x4_t*)&S.SX[g][0][4 * kb];
+        const float4 xs = *(const float4*)&S.XS[g][0][4 * kb];
         const float xf[4] = {xs.x, xs.y, xs.z, xs.w};
+        // (stream layers: the second operand's columns have an exponent of their own, as in k_moe_stream)
+        const i32x4_t sx1 = STREAM ? *(const i32x4_t*)&S.SX[g][1][4 * kb] : (i32x4_t){0, 0, 0, 0};
+        const float4 xs1 = STREAM ? *(const float4*)&S.XS[g][1][4 * kb] : xs;
+        const float xf1[4] = {xs1.x, xs1.y, xs1.z, xs1.w};
         uint32_t s4[4];
         if constexpr (COLS) {
           s4[0] = R.s[gi].x & 0xffffu; s4[1] = R.s[gi].x >> 16; s4[2] = R.s[gi].y & 0xffffu; s4[3] = R.s[gi].y >> 16;
@@ -784,11 +798,14 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
           }
           i32x4_t dl = mfma_i8(A[0][0], B[0], sx);
           i32x4_t dh = mfma_i8(A[0][1], B[0], (i32x4_t){0, 0, 0, 0});
-          dl = mfma_i8(A[1][0], B[1], dl);
-          dh = mfma_i8(A[1][1], B[1], dh);
+          const i32x4_t dl1 = mfma_i8(A[1][0], B[1], STREAM ? sx1 : dl);
+          const i32x4_t dh1 = mfma_i8(A[1][1], B[1], STREAM ? (i32x4_t){0, 0, 0, 0} : dh);
           const float scf = f16_bits_to_f32(s4[i]);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf((float)(dl[j] + (dh[j] << 8)) * scf, xf[j], acc[i][j]);
+          for (int j = 0; j < 4; ++j) {
+            if constexpr (STREAM) acc[i][j] = fmaf((float)(dl[j] + (dh[j] << 8)) * scf, xf[j], acc[i][j]);
+            acc[i][j] = fmaf((float)(dl1[j] + (dh1[j] << 8)) * scf, xf1[j], acc[i][j]);
+          }
         }
       }
     }
@@ -883,8 +900,8 @@ BatchWs batch_ws(const LayerDims& L, int64_t T, int32_t k, int32_t bits_mask, bo
   w.xs = off;     off += up256((size_t)T * kBGroups * 4);
   w.xsum = off;   off += up256((size_t)T * kBGroups * parts * 4);
   w.hq = off;     off += up256(P * parts * 2 * (size_t)L.d_ff);
-  w.hs = off;     off += up256(P * NG * 4);
-  w.hsum = off;   off += up256(P * NG * parts * 4);
+  w.hs = off;     off += up256(P * NG * 8);
+  w.hsum = off;   off += up256(P * NG * 8);
   w.part = off;   off += up256((NG + kBOutGroups - 1) / kBOutGroups * P * kBD * 4);
   w.total = off;
   return w;

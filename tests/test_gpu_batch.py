@@ -143,3 +143,28 @@ def test_grouped_call_with_outlier_columns_that_meet_zero_weights(bits, layout):
     torch.cuda.synchronize()
     ref = oracle.expert_ffn(pack_expert_oracle(w, bits, g), d, f, g, 1, x.cpu().numpy())
     assert rel_err(y.cpu().numpy(), ref).max() < TOL
+
+
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("layout", ("stream", "canonical", "columns"))
+def test_grouped_call_whose_larger_half_of_h_meets_zero_weights(bits, layout):
+    """64 of the 128 columns of h that share a scale are 2^10 times the others and meet weights of zero: the results are
+    those of the others."""
+    d, f, g, T = 4096, 1152, 128, 60
+    cfg = replace(gen.tiny_config("c4", d, f, n_experts=1, n_layers=1, group=g), top_k=1, x_dtype="f32")
+    w = gen.expert_weights(cfg, 0, 0, DEV)
+    big = torch.arange(f, device=DEV) % 128 < 64
+    w["w_gate"][big] *= 1024.0
+    w["w_out"][:, big] = 0.0
+    ex = pack_expert_gpu(w, bits, g)
+    if layout != "canonical":
+        ex = ex.with_stream_layout(d, f, g) if layout == "stream" else ex.with_out_columns(f, g)
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(d, f, 1, g, moeq.MOEQ_ACT_SWIGLU, True, moeq.MOEQ_F32, Wr, bias, [ex],
+                       moeq.MOEQ_OUT_CANONICAL if layout == "canonical" else moeq.MOEQ_OUT_COLUMNS,
+                       moeq.MOEQ_IN_STREAM if layout == "stream" else moeq.MOEQ_IN_CANONICAL)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    y = moeq.moe_expert_ffn_q(layer, 0, x)
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn(pack_expert_oracle(w, bits, g), d, f, g, 1, x.cpu().numpy())
+    assert rel_err(y.cpu().numpy(), ref).max() < TOL
