@@ -149,13 +149,26 @@ __device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {    // odd qua
   const u32x2s_t r = __builtin_bit_cast(u32x2s_t, __builtin_amdgcn_permlane16_swap(a, b, false, false));
   a = r.x; b = r.y;
 }
-// 2-bit codes: eight of the word's sixteen, by quarter, two bits higher than they lie in a byte. The matrix instruction
-// aligns its products by the exponents of its operands, subnormal ones as they stand, and what it drops below the largest
-// weighs most against fields that begin at bit 0. Error of 500 tokens on 2-bit Switch-base experts against 64 bits: two
-// bits up 2.95e-4, as they lie 3.05e-4 (the kernels that work token by token: 2.98e-4).
+// Code fields two bits higher than they lie in a byte. The matrix instruction aligns its products by the exponents of its
+// operands, subnormal ones as they stand, and what it drops below the largest weighs most against fields that begin at bit
+// 0. Error of 500 tokens on 2-bit Switch-base experts against 64 bits: two bits up 2.95e-4, as they lie 3.05e-4 (the kernels
+// that work token by token: 2.98e-4). It grows where a column of large activations meets zero weights: 60 tokens, an
+// element 2^13 times the others, largest error of 4- / 8-bit experts 8.1e-4 / 5.7e-4 (as they lie 2.2e-3 / 2.6e-3, token by token
+// 2.1e-3 / 2.1e-3).
+// 2 bits: eight of the word's sixteen, by quarter; 4 and 8 bits: as codes8. The masks leave the rotations' wrapped bits out.
 __device__ __forceinline__ half8_t codes8_2(uint32_t w, int kb) {
-  const uint32_t v = __builtin_amdgcn_alignbit(w, w, kb & 2 ? 6u : 30u);     // rotated; the masks leave the wrapped bits out
+  const uint32_t v = __builtin_amdgcn_alignbit(w, w, kb & 2 ? 6u : 30u);
   const u32x4v_t r = {v & 0x000c000cu, v & 0x00300030u, v & 0x00c000c0u, v & 0x03000300u};
+  return __builtin_bit_cast(half8_t, r);
+}
+__device__ __forceinline__ half8_t codes8_4(uint32_t w) {
+  const uint32_t v = __builtin_amdgcn_alignbit(w, w, 30u), u = __builtin_amdgcn_alignbit(w, w, 6u);
+  const u32x4v_t r = {v & 0x003c003cu, v & 0x03c003c0u, u & 0x003c003cu, u & 0x03c003c0u};
+  return __builtin_bit_cast(half8_t, r);
+}
+__device__ __forceinline__ half8_t codes8_8(uint32_t w0, uint32_t w1) {
+  const u32x4v_t r = {__builtin_amdgcn_alignbit(w0, w0, 30u) & 0x03fc03fcu, __builtin_amdgcn_alignbit(w0, w0, 6u) & 0x03fc03fcu,
+                      __builtin_amdgcn_alignbit(w1, w1, 30u) & 0x03fc03fcu, __builtin_amdgcn_alignbit(w1, w1, 6u) & 0x03fc03fcu};
   return __builtin_bit_cast(half8_t, r);
 }
 
@@ -171,8 +184,8 @@ __device__ __forceinline__ void b_operands(uint4 v, int kb, half8_t (&B)[load_bl
   if constexpr (BITS == 8) {
     swap32(w[0], w[2]);
     swap32(w[1], w[3]);
-    B[0] = codes8<8, 0>(w[0], w[1]);
-    B[1] = codes8<8, 0>(w[2], w[3]);
+    B[0] = codes8_8(w[0], w[1]);
+    B[1] = codes8_8(w[2], w[3]);
   } else {
     // quarters x words transposed: word j then holds, in quarter kb, word kb of the load's piece j
     swap32(w[0], w[2]);
@@ -182,7 +195,7 @@ __device__ __forceinline__ void b_operands(uint4 v, int kb, half8_t (&B)[load_bl
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if constexpr (BITS == 4) {
-        B[j] = codes8<4, 0>(w[j], 0u);
+        B[j] = codes8_4(w[j]);
       } else {
         uint32_t a = w[j], b = w[j];
         swap32(a, b);                    // (words 0, 1, 0, 1) and (words 2, 3, 2, 3) of the piece
@@ -194,8 +207,8 @@ __device__ __forceinline__ void b_operands(uint4 v, int kb, half8_t (&B)[load_bl
 }
 
 // What turns the results of the instructions into sums of code * activation, and the offset of a code in their unit.
-template <int BITS> constexpr float code_unit() { return BITS == 2 ? 4194304.0f : 16777216.0f; }     // 2^22, 2^24
-template <int BITS> constexpr float code_half() { return (float)(1 << (BITS - 1)) / code_unit<BITS>(); }
+constexpr float kCodeUnit = 4194304.0f;     // 2^22
+template <int BITS> constexpr float code_half() { return (float)(1 << (BITS - 1)) / kCodeUnit; }
 
 struct GrpLds {             // byte offsets of the pieces of a workgroup's LDS
   int a, ks, up, scales, h, total;
@@ -409,7 +422,7 @@ __device__ __forceinline__ void grp_in(const GrpArgs& G, const GrpItem& item, ch
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int m = 16 * t + 4 * kb + i;
-        const float v = u * kGUnit + wave * 16 + n < f ? fmaxf(inner[t][i] * code_unit<BITS>() * UP[t < nt ? m : 0], 0.f) : 0.f;
+        const float v = u * kGUnit + wave * 16 + n < f ? fmaxf(inner[t][i] * kCodeUnit * UP[t < nt ? m : 0], 0.f) : 0.f;
         if (t < nt) H[m * (kGUnit + 4) + wave * 16 + n] = v;
       }
     __syncthreads();
@@ -585,7 +598,7 @@ __device__ __forceinline__ void grp_out(const GrpArgs& G, const GrpItem& item, c
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int m = 16 * t + 4 * kb + i;
-          if (m < item.n && row < d) part[(size_t)(item.g0 + m) * d + row] = acc[t][i] * code_unit<BITS>();
+          if (m < item.n && row < d) part[(size_t)(item.g0 + m) * d + row] = acc[t][i] * kCodeUnit;
         }
     }
   } else {
@@ -645,9 +658,9 @@ __device__ __forceinline__ void grp_out(const GrpArgs& G, const GrpItem& item, c
         half8_t B[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          if constexpr (BITS == 4) B[r] = codes8<4, 0>(word(0, r), 0u);
+          if constexpr (BITS == 4) B[r] = codes8_4(word(0, r));
           else if constexpr (BITS == 2) B[r] = codes8_2(word(0, r), kb);
-          else B[r] = codes8<8, 0>(word(0, r), word(LPB - 1, r));
+          else B[r] = codes8_8(word(0, r), word(LPB - 1, r));
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -682,7 +695,7 @@ __device__ __forceinline__ void grp_out(const GrpArgs& G, const GrpItem& item, c
                 const int m = 16 * t + 4 * kb + j;
                 if (m < item.n && row < row_end)
                   *(float4*)(part + (size_t)(item.g0 + m) * d + row) =
-                      make_float4(acc[0][t][j] * code_unit<BITS>(), acc[1][t][j] * code_unit<BITS>(), acc[2][t][j] * code_unit<BITS>(), acc[3][t][j] * code_unit<BITS>());
+                      make_float4(acc[0][t][j] * kCodeUnit, acc[1][t][j] * kCodeUnit, acc[2][t][j] * kCodeUnit, acc[3][t][j] * kCodeUnit);
               }
           }
         }

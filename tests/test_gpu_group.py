@@ -77,3 +77,26 @@ def test_grouped_layer_per_channel_scales(columns):
     y1 = torch.cat([moeq.moe_layer_forward(layer, x[t:t + 1]) for t in range(50)])     # the decode kernels, token by token
     torch.cuda.synchronize()
     assert rel_err(y.cpu().numpy(), y1.cpu().numpy()).max() < TOL
+
+
+@pytest.mark.parametrize("bits", (4, 8))
+@pytest.mark.parametrize("columns", (False, True), ids=("canonical", "columns"))
+def test_grouped_layer_with_outlier_columns_that_meet_zero_weights(bits, columns):
+    """Elements 2^13 times the others, on weights of zero: the results are those of the others, to the decode bar (the matrix
+    instruction drops what lies far below its largest operands, zero products included)."""
+    from helpers import pack_expert_gpu, pack_expert_oracle
+    d, f, g, T = 768, 3072, 32, 60
+    cfg = gen.tiny_config("c1", d, f, n_experts=1, n_layers=1, group=g)
+    w = gen.expert_weights(cfg, 0, 0, DEV)
+    w["w_in"][:, 5::128] = 0.0
+    ex = pack_expert_gpu(w, bits, g)
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(d, f, 1, g, moeq.MOEQ_ACT_RELU, False, moeq.MOEQ_F32, Wr, bias, [ex.with_out_columns(f, g) if columns else ex],
+                       moeq.MOEQ_OUT_COLUMNS if columns else moeq.MOEQ_OUT_CANONICAL)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    x[:, 5::128] *= 8192.0
+    idx, gate = torch.zeros((T, 1), dtype=torch.int32, device=DEV), torch.ones((T, 1), device=DEV)
+    y = moeq.moe_layer_forward_routed(layer, x, idx, gate)
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn(pack_expert_oracle(w, bits, g), d, f, g, 0, x.cpu().numpy())
+    assert rel_err(y.cpu().numpy(), ref).max() < TOL
