@@ -104,9 +104,10 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true
             !batch_supported(L) && group_supported(L);
   w.group_off = tail;
   const size_t group_total = w.group ? group_ws(L, (T < group_tokens(L.top_k) ? T : group_tokens(L.top_k)) * L.top_k).total : 0;
-  // (2-bit experts are the cheapest to group: whether any single-expert call of T tokens may be grouped)
+  // whether a call of T tokens of any one expert may be grouped, by the bitwidths that the layer holds
   w.batch = grouped_forms && batch_pays_layer(layer, T);
-  const bool one = grouped_forms && batch_pays_expert(layer, T, 2);
+  bool one = false;
+  for (int32_t b : {2, 4, 8}) one = one || (grouped_forms && (layer->bits_mask & b) && batch_pays_expert(layer, T, b));
   w.batch_off = tail;
   size_t batch_total = 0;
   if (w.batch) batch_total = batch_ws(L, T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), L.top_k, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total;

@@ -1,0 +1,27 @@
+"""What a call computes does not depend on how large a workspace it is given beyond its need, nor on what else its layer
+holds: grouped and ungrouped kernels round differently, so the choice shows in the bits."""
+from dataclasses import replace
+
+import pytest
+import torch
+
+import gen
+import paper_2308_14352_amd as moeq
+from helpers import build_layer_pair
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("layout", ("canonical", "columns"))
+@pytest.mark.parametrize("f", (1024, 4096))
+def test_an_experts_call_does_not_depend_on_the_other_experts(f, layout):
+    cfg = replace(gen.tiny_config("c4", 4096, f, n_experts=4, n_layers=1, group=128), x_dtype="f32")
+    kw = dict(want_oracle=False, columns=layout == "columns")
+    mixed, _, Wr, bias = build_layer_pair(cfg, 0, DEV, [8, 2, 2, 4], **kw)
+    alone = moeq.Layer(4096, f, 1, 128, moeq.MOEQ_ACT_SWIGLU, True, moeq.MOEQ_F32, Wr[:1].contiguous(), bias if bias is None else bias[:1].contiguous(),
+                       mixed.experts[:1], mixed.out_layout, mixed.in_layout)
+    x = gen.hidden(cfg, 0, 0, 40, DEV)
+    for T in list(range(2, 18)) + [24, 31, 32, 40]:
+        a, b = moeq.moe_expert_ffn_q(mixed, 0, x[:T]), moeq.moe_expert_ffn_q(alone, 0, x[:T])
+        assert torch.equal(a, b), T
