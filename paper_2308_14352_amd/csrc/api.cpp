@@ -1,5 +1,6 @@
 // Host side of the C ABI: argument validation, workspace carving, kernel dispatch.
 // Every check runs before the first HIP call, so the error paths work on a host without a GPU.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -20,6 +21,8 @@ struct moeq_layer {
   int32_t out_layout;              // layout of W_out (MOEQ_OUT_CANONICAL or MOEQ_OUT_COLUMNS)
   int32_t in_layout;               // layout of W_in / W_gate (MOEQ_IN_CANONICAL or MOEQ_IN_STREAM)
   FusedPlan plan;                  // split of the one-kernel path (out_layout == MOEQ_OUT_COLUMNS)
+  double mean_bits;                // of the bitwidth table
+  int64_t batch_from, one_from;    // the smallest layer / single-expert call that groups its pairs (batch_pays)
   // measurement aid (moe_layer_profile_kernel): events to record around one kernel of this layer's calls
   int32_t prof_which = 0;
   hipEvent_t prof_start = nullptr, prof_stop = nullptr;
@@ -77,11 +80,17 @@ bool batch_pays(const moeq_layer* layer, int64_t T, int32_t k, double experts, d
   return grouped < std::fmax(7.0 + 12.0 * k, 8.0 + rounds * (8.0 + 12.0 * k));
 }
 bool batch_pays_layer(const moeq_layer* layer, int64_t T) {
-  double bits = 0.0;
-  for (int32_t b : layer->bits) bits += b;
-  return batch_pays(layer, T, layer->dims.top_k, layer->dims.n_experts, bits / layer->dims.n_experts);
+  return batch_pays(layer, T, layer->dims.top_k, layer->dims.n_experts, layer->mean_bits);
 }
 bool batch_pays_expert(const moeq_layer* layer, int64_t T, int32_t bits) { return batch_pays(layer, T, 1, 1.0, bits); }
+// The smallest T for which pays(T) holds. (It holds for some: the ungrouped time grows with T, the grouped one is bounded by
+// that of all experts. A thousand tokens are about the most it takes; beyond the limits of a call none matters.)
+template <typename Pays>
+int64_t first_paying(const LayerDims& L, Pays pays) {
+  for (int64_t T = 2; batch_supported(L) && T <= 65535; ++T)
+    if (pays(T)) return T;
+  return (int64_t)1 << 40;
+}
 // Grouped calls are taken in launches of at most kBatchMaxPairs pairs.
 inline int64_t batch_tokens(int32_t k) { return kBatchMaxPairs / k; }
 
@@ -104,18 +113,16 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true
             !batch_supported(L) && group_supported(L);
   w.group_off = tail;
   const size_t group_total = w.group ? group_ws(L, (T < group_tokens(L.top_k) ? T : group_tokens(L.top_k)) * L.top_k).total : 0;
-  // whether a call of T tokens of any one expert may be grouped, by the bitwidths that the layer holds
-  w.batch = grouped_forms && batch_pays_layer(layer, T);
-  bool one = false;
-  for (int32_t b : {2, 4, 8}) one = one || (grouped_forms && (layer->bits_mask & b) && batch_pays_expert(layer, T, b));
+  // (every piece grows with T and room is made for the grouped form of any smaller call that has one: a workspace for T
+  // tokens serves all calls of fewer tokens in the same way)
+  w.batch = grouped_forms && !use_prefill(layer, T) && batch_pays_layer(layer, T);
   w.batch_off = tail;
+  auto bytes = [&](int64_t n, int32_t k) { return batch_ws(L, n, k, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total; };
   size_t batch_total = 0;
-  if (w.batch) batch_total = batch_ws(L, T < batch_tokens(L.top_k) ? T : batch_tokens(L.top_k), L.top_k, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total;
-  if (one) {
-    const size_t b1 = batch_ws(L, T < batch_tokens(1) ? T : batch_tokens(1), 1, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total;
-    if (b1 > batch_total) batch_total = b1;
-  }
-  w.grouped = w.batch || one || w.group;
+  const int64_t Tb = use_prefill(layer, T) ? kPrefillMinTokens - 1 : T;     // the largest layer call that may be grouped so
+  if (grouped_forms && Tb >= layer->batch_from) batch_total = bytes(std::min(Tb, batch_tokens(L.top_k)), L.top_k);
+  if (grouped_forms && T >= layer->one_from) batch_total = std::max(batch_total, bytes(std::min(T, batch_tokens(1)), 1));
+  w.grouped = batch_total > 0 || w.group;
   if (layer->out_layout == MOEQ_OUT_COLUMNS) {
     const size_t chunk = (size_t)(T < kDecodeChunk ? T : kDecodeChunk);
     const size_t part = align_up(chunk * (size_t)layer->plan.n_slices * (size_t)L.d_model * sizeof(float), 256);
@@ -302,6 +309,14 @@ moeq_status moe_layer_create(const moeq_layer_desc* desc, void* table_dev, size_
   L->out_layout = desc->out_layout;
   L->in_layout = desc->in_layout;
   L->plan = plan;
+  L->mean_bits = 0.0;
+  for (int32_t b : L->bits) L->mean_bits += (double)b / E;
+  L->batch_from = first_paying(dims, [&](int64_t T) { return batch_pays_layer(L, T); });
+  L->one_from = first_paying(dims, [&](int64_t T) {
+    for (int32_t b : {2, 4, 8})
+      if ((L->bits_mask & b) && batch_pays_expert(L, T, b)) return true;
+    return false;
+  });
   if (hipMemcpy(table_dev, tab.data(), tab.size() * sizeof(DevExpert), hipMemcpyHostToDevice) != hipSuccess ||
       init_kernel_attrs() != hipSuccess) {
     (void)hipGetLastError();

@@ -13,6 +13,22 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+@pytest.mark.parametrize("layout", ("stream", "canonical", "columns"))
+def test_workspace_made_for_more_tokens_gives_the_same_bits(layout):
+    cfg = replace(gen.tiny_config("c4", 4096, 2048, n_experts=8, n_layers=1, group=128), x_dtype="f32")
+    layer, _, _, _ = build_layer_pair(cfg, 0, DEV, [2, 4] * 4, want_oracle=False, columns=layout == "columns", stream=layout == "stream")
+    x = gen.hidden(cfg, 0, 0, 34, DEV)
+    sizes = (2, 3, 4, 5, 6, 7, 8, 9, 12, 13, 16, 17, 23, 31, 32, 33, 34)
+    assert all(layer.workspace_bytes(a) <= layer.workspace_bytes(a + 1) for a in range(1, 300))
+    for T in sizes:
+        fresh = lambda n: torch.empty(layer.workspace_bytes(n), dtype=torch.uint8, device=DEV)
+        want = moeq.moe_layer_forward(layer, x[:T], ws=fresh(T))
+        want_e = moeq.moe_expert_ffn_q(layer, 3, x[:T], ws=fresh(T))
+        for N in [n for n in sizes if n > T]:
+            assert torch.equal(moeq.moe_layer_forward(layer, x[:T], ws=fresh(N)), want), (T, N)
+            assert torch.equal(moeq.moe_expert_ffn_q(layer, 3, x[:T], ws=fresh(N)), want_e), (T, N)
+
+
 @pytest.mark.parametrize("layout", ("canonical", "columns"))
 @pytest.mark.parametrize("f", (1024, 4096))
 def test_an_experts_call_does_not_depend_on_the_other_experts(f, layout):
