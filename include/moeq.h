@@ -76,7 +76,7 @@ typedef enum {
   MOEQ_OK = 0,
   MOEQ_EINVAL = 1,       /* malformed argument (null pointer, bad shape, bad bitwidth ...)   */
   MOEQ_EUNSUPPORTED = 2, /* well-formed but outside what the kernels cover                    */
-  MOEQ_EWORKSPACE = 3,   /* ws is NULL or smaller than moe_workspace_bytes() for this call    */
+  MOEQ_EWORKSPACE = 3,   /* ws is NULL or too small for this call (see moe_workspace_bytes)   */
   MOEQ_EDEVICE = 4       /* a HIP call failed (no device, launch error); see hipGetLastError  */
 } moeq_status;
 
@@ -148,7 +148,9 @@ void moe_layer_destroy(moeq_layer *layer);
 
 /* Workspace bytes needed by any compute call on `layer` with up to max_tokens tokens (the routing, the router
  * logits, and what the path of Section 2.1 needs between its kernels: h, or the partial output vectors, or
- * the grouped path's staging). Host-only arithmetic. */
+ * the grouped paths' staging). A call's results do not depend on how much more it is given than it needs. Calls that
+ * group their pairs are also taken with less, down to the size of their token-by-token form: they run in more launches
+ * then, with the same results (where not even one token's pieces fit: token by token). Host-only arithmetic. */
 size_t moe_workspace_bytes(const moeq_layer *layer, int32_t max_tokens);
 
 /* Which kernels moe_layer_forward / moe_layer_forward_routed run for a call with n_tokens tokens on
@@ -201,10 +203,10 @@ moeq_status moe_layer_forward(const moeq_layer *layer, const void *x, int32_t n_
  * capture, tight serving loops, harnesses that forbid hipMalloc. Same computation, same kernels, same
  * results; the scratch that `ws` brings in elsewhere is a fixed array inside the library's device code
  * (moe_static_scratch_bytes() bytes, 8 MiB, held on every GPU the library runs on until the process ends).
- * The call allocates nothing and frees nothing. Returns MOEQ_EWORKSPACE when
- * moe_workspace_bytes(layer, n_tokens) exceeds that size (e.g. more than 2 tokens per call on a
- * Mixtral-sized layer in the columns layout: split the call), MOEQ_EDEVICE when the array's address cannot be
- * obtained. All calls on one GPU share the one array, which keeps the previous call's contents (nothing in
+ * The call allocates nothing and frees nothing. Calls whose grouped form exceeds that size run it in several launches
+ * (see moe_workspace_bytes). Returns MOEQ_EWORKSPACE when what every launch of the call needs exceeds it (e.g. more than
+ * 2 tokens per call on a Mixtral-sized layer in the columns layout: split the call), MOEQ_EDEVICE when the array's
+ * address cannot be obtained. All calls on one GPU share the one array, which keeps the previous call's contents (nothing in
  * it needs clearing: every piece is written before it is read): calls that overlap on one GPU - two streams,
  * two threads - race; order them on one stream. x, y, topk_*_opt, stream as for moe_layer_forward. */
 size_t moe_static_scratch_bytes(void);

@@ -43,10 +43,12 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Workspace carving. Both paths keep idx, gate and logits; the two-kernel path adds the chosen experts'
 // records and h (fp32), the one-kernel path the partial output vectors.
 struct WsLayout {
-  size_t idx_off, gate_off, logits_off, sel_off, h_off, part_off, prefill_off, batch_off, group_off, total;
-  bool batch;      // the call runs the grouped streaming kernels (decode_batch.hip)
-  bool group;      // ... the grouped GEMMs of narrow layers (group_gemm.hip)
-  bool grouped;    // room for a grouped form is included
+  size_t idx_off, gate_off, logits_off, sel_off, h_off, part_off, prefill_off;
+  size_t group_off;  // the grouped forms of decode_batch.hip and group_gemm.hip: in the place of what lies behind the logits
+  size_t least;      // what every call needs: the form that works token by token (or the prefill GEMMs)
+  size_t total;      // ... and room for the grouped form of any call of up to T tokens in the fewest launches
+  bool batch;        // a layer call of T tokens runs the grouped streaming kernels (decode_batch.hip)
+  bool group;        // ... the grouped GEMMs of narrow layers (group_gemm.hip)
 };
 
 // Calls with at least this many tokens run as grouped GEMMs on the matrix cores (when the shape allows);
@@ -99,9 +101,25 @@ inline int64_t batch_tokens(int32_t k) { return kBatchMaxPairs / k; }
 constexpr int64_t kGroupMinTokens = 32;
 inline int64_t group_tokens(int32_t k) { return group_max_pairs() / k; }
 
-// grouped: whether a call may take a grouped form (its pieces share the place of the partial vectors, or lie behind h).
-// A call whose workspace holds the ungrouped form only runs that one.
-WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true) {
+// Bytes of a grouped form's pieces for launches of n tokens with k choices each.
+size_t batch_bytes(const moeq_layer* layer, int64_t n, int32_t k) {
+  return batch_ws(layer->dims, n, k, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total;
+}
+size_t group_bytes(const moeq_layer* layer, int64_t n) { return group_ws(layer->dims, n * layer->dims.top_k).total; }
+// Tokens per launch of a grouped call: `most`, or as many as fit into `room` bytes (0: not one).
+template <typename Bytes>
+int64_t launch_tokens(int64_t most, size_t room, Bytes bytes) {
+  if (bytes(most) <= room) return most;
+  int64_t lo = 0;
+  for (int64_t hi = most; hi - lo > 1;) {
+    const int64_t mid = (lo + hi) / 2;
+    (bytes(mid) <= room ? lo : hi) = mid;
+  }
+  return lo;
+}
+
+// Every piece grows with T, so a workspace for T tokens serves all calls of fewer tokens in the same way.
+WsLayout ws_layout(const moeq_layer* layer, int64_t T) {
   const LayerDims& L = layer->dims;
   WsLayout w{};
   const size_t slots = (size_t)T * L.top_k;
@@ -109,41 +127,30 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T, bool grouped_forms = true
   w.gate_off = align_up(slots * sizeof(int32_t), 256);
   w.logits_off = w.gate_off + align_up(slots * sizeof(float), 256);
   const size_t tail = w.logits_off + align_up((size_t)T * (size_t)L.n_experts * sizeof(float), 256);
-  w.group = grouped_forms && T >= kGroupMinTokens && layer->in_layout == MOEQ_IN_CANONICAL && !use_prefill(layer, T) &&
-            !batch_supported(L) && group_supported(L);
+  const bool prefill = use_prefill(layer, T);
   w.group_off = tail;
-  const size_t group_total = w.group ? group_ws(L, (T < group_tokens(L.top_k) ? T : group_tokens(L.top_k)) * L.top_k).total : 0;
-  // (every piece grows with T and room is made for the grouped form of any smaller call that has one: a workspace for T
-  // tokens serves all calls of fewer tokens in the same way)
-  w.batch = grouped_forms && !use_prefill(layer, T) && batch_pays_layer(layer, T);
-  w.batch_off = tail;
-  auto bytes = [&](int64_t n, int32_t k) { return batch_ws(L, n, k, layer->bits_mask, layer->in_layout == MOEQ_IN_STREAM).total; };
-  size_t batch_total = 0;
-  const int64_t Tb = use_prefill(layer, T) ? kPrefillMinTokens - 1 : T;     // the largest layer call that may be grouped so
-  if (grouped_forms && Tb >= layer->batch_from) batch_total = bytes(std::min(Tb, batch_tokens(L.top_k)), L.top_k);
-  if (grouped_forms && T >= layer->one_from) batch_total = std::max(batch_total, bytes(std::min(T, batch_tokens(1)), 1));
-  w.grouped = batch_total > 0 || w.group;
+  w.batch = !prefill && batch_pays_layer(layer, T);
+  w.group = !prefill && T >= kGroupMinTokens && layer->in_layout == MOEQ_IN_CANONICAL && !batch_supported(L) && group_supported(L);
+  size_t most = w.group ? group_bytes(layer, std::min(T, group_tokens(L.top_k))) : 0;
+  const int64_t Tb = prefill ? kPrefillMinTokens - 1 : T;         // the largest layer call that may run decode_batch.hip
+  if (Tb >= layer->batch_from) most = std::max(most, batch_bytes(layer, std::min(Tb, batch_tokens(L.top_k)), L.top_k));
+  if (T >= layer->one_from) most = std::max(most, batch_bytes(layer, std::min(T, batch_tokens(1)), 1));
   if (layer->out_layout == MOEQ_OUT_COLUMNS) {
     const size_t chunk = (size_t)(T < kDecodeChunk ? T : kDecodeChunk);
     const size_t part = align_up(chunk * (size_t)layer->plan.n_slices * (size_t)L.d_model * sizeof(float), 256);
     w.part_off = tail;
     w.prefill_off = tail;           // a call uses one of the two
-    const size_t grouped = use_prefill(layer, T) ? prefill_ws(L, T).total : 0;
-    size_t most = part > grouped ? part : grouped;
-    if (batch_total > most) most = batch_total;
-    if (group_total > most) most = group_total;
-    w.total = tail + most;
+    w.least = tail + std::max(part, prefill ? prefill_ws(L, T).total : (size_t)0);
   } else {
     w.sel_off = tail;
     w.h_off = w.sel_off + align_up(slots * sizeof(DevExpert), 256);
-    w.total = w.h_off + align_up(slots * (size_t)L.d_ff * sizeof(float), 256);
-    if (use_prefill(layer, T)) {      // moe_layer_forward takes the grouped path; the single-expert call keeps h
-      w.prefill_off = w.total;
-      w.total = w.prefill_off + prefill_ws(L, T).total;
+    w.least = w.h_off + align_up(slots * (size_t)L.d_ff * sizeof(float), 256);
+    if (prefill) {                  // moe_layer_forward takes the grouped path; the single-expert call keeps h
+      w.prefill_off = w.least;
+      w.least = w.prefill_off + prefill_ws(L, T).total;
     }
-    if (tail + group_total > w.total) w.total = tail + group_total;      // (in the place of sel and h)
-    if (tail + batch_total > w.total) w.total = tail + batch_total;
   }
+  w.total = std::max(w.least, tail + most);
   return w;
 }
 
@@ -162,12 +169,6 @@ int inline_router_max() {
     return want < cap ? want : cap;
   }();
   return v;
-}
-
-// The layout for a call with ws_bytes of workspace: without the grouped form where only that fits.
-WsLayout ws_layout_for(const moeq_layer* layer, int64_t T, size_t ws_bytes) {
-  const WsLayout w = ws_layout(layer, T);
-  return w.grouped && ws_bytes < w.total ? ws_layout(layer, T, false) : w;
 }
 
 inline moeq_status dev(hipError_t e) { return e == hipSuccess ? MOEQ_OK : MOEQ_EDEVICE; }
@@ -341,8 +342,8 @@ moeq_status moe_router_topk(const moeq_layer* layer, const void* x, int32_t n_to
   if (n_tokens == 0) return MOEQ_OK;
   if (!x || !topk_idx || !topk_gate || ((uintptr_t)x & 15u)) return MOEQ_EINVAL;
   if (n_tokens > 65535) return MOEQ_EUNSUPPORTED;
-  const WsLayout w = ws_layout_for(layer, n_tokens, ws_bytes);
-  if (!ws || ws_bytes < w.total) return MOEQ_EWORKSPACE;
+  const WsLayout w = ws_layout(layer, n_tokens);
+  if (!ws || ws_bytes < w.least) return MOEQ_EWORKSPACE;
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   float* logits = (float*)((char*)ws + w.logits_off);
   hipStream_t st = (hipStream_t)stream;
@@ -359,18 +360,21 @@ moeq_status moe_expert_ffn_q(const moeq_layer* layer, int32_t expert, const void
   if (n_tokens == 0) return MOEQ_OK;
   if (!x || !y || ((uintptr_t)x & 15u) || ((uintptr_t)y & 3u)) return MOEQ_EINVAL;
   if (n_tokens > 65535) return MOEQ_EUNSUPPORTED;
-  const WsLayout w = ws_layout_for(layer, n_tokens, ws_bytes);
-  if (!ws || ws_bytes < w.total) return MOEQ_EWORKSPACE;
+  const WsLayout w = ws_layout(layer, n_tokens);
+  if (!ws || ws_bytes < w.least) return MOEQ_EWORKSPACE;
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  if (w.grouped && batch_pays_expert(layer, n_tokens, layer->bits[(size_t)expert])) {
+  const int32_t bits = layer->bits[(size_t)expert];
+  const int64_t per = !batch_pays_expert(layer, n_tokens, bits) ? 0
+      : launch_tokens(std::min<int64_t>(n_tokens, batch_tokens(1)), ws_bytes - w.group_off, [&](int64_t n) { return batch_bytes(layer, n, 1); });
+  if (per > 0) {
     const size_t x_row = (size_t)layer->dims.d_model * (layer->dims.x_bf16 ? 2 : 4);
-    for (int64_t t0 = 0; t0 < n_tokens; t0 += batch_tokens(1)) {
-      const int32_t n = (int32_t)(n_tokens - t0 < batch_tokens(1) ? n_tokens - t0 : batch_tokens(1));
-      if (launch_moe_batch(layer->dims, layer->table, nullptr, nullptr, false, expert, layer->bits[(size_t)expert],
-                           (const char*)x + (size_t)t0 * x_row, n, nullptr, nullptr, gate_opt ? gate_opt + t0 : nullptr,
-                           accumulate ? 1 : 0, layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS,
-                           (char*)ws + w.batch_off, y + (size_t)t0 * layer->dims.d_model, st) != hipSuccess)
+    for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
+      const int32_t n = (int32_t)std::min<int64_t>(n_tokens - t0, per);
+      if (launch_moe_batch(layer->dims, layer->table, nullptr, nullptr, false, expert, bits, (const char*)x + (size_t)t0 * x_row, n,
+                           nullptr, nullptr, gate_opt ? gate_opt + t0 : nullptr, accumulate ? 1 : 0,
+                           layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS, (char*)ws + w.group_off,
+                           y + (size_t)t0 * layer->dims.d_model, st) != hipSuccess)
         return MOEQ_EDEVICE;
     }
     return MOEQ_OK;
@@ -385,7 +389,7 @@ moeq_status moe_expert_ffn_q(const moeq_layer* layer, int32_t expert, const void
                               gate_opt ? gate_opt + t0 : nullptr, nullptr, nullptr, layer->bits_mask,
                               (const char*)x + (size_t)t0 * x_row, n, part, nullptr, nullptr, st)
           : launch_moe_decode(layer->dims, layer->plan, layer->table, nullptr, nullptr, nullptr, expert,
-                              gate_opt ? gate_opt + t0 : nullptr, nullptr, nullptr, layer->bits[(size_t)expert],
+                              gate_opt ? gate_opt + t0 : nullptr, nullptr, nullptr, bits,
                               (const char*)x + (size_t)t0 * x_row, n, part, nullptr, nullptr, st);
       if (le != hipSuccess) return MOEQ_EDEVICE;
       if (launch_reduce_partials(part, layer->plan.n_slices, layer->dims.d_model, n, accumulate ? 1 : 0,
@@ -411,8 +415,8 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
   if (!x || !y || ((uintptr_t)x & 15u) || ((uintptr_t)y & 3u)) return MOEQ_EINVAL;
   if ((int64_t)n_tokens * layer->dims.top_k > 65535) return MOEQ_EUNSUPPORTED;
   const LayerDims& L = layer->dims;
-  const WsLayout w = ws_layout_for(layer, n_tokens, ws_bytes);
-  if (!ws || ws_bytes < w.total) return MOEQ_EWORKSPACE;
+  const WsLayout w = ws_layout(layer, n_tokens);
+  if (!ws || ws_bytes < w.least) return MOEQ_EWORKSPACE;
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   const bool given = given_idx != nullptr;
   int32_t* idx = topk_idx_opt ? topk_idx_opt : (int32_t*)((char*)ws + w.idx_off);
@@ -432,15 +436,21 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     return dev(launch_prefill(L, layer->table, x, n_tokens, idx, gate, (char*)ws + w.prefill_off, pw, y,
                               layer->out_layout == MOEQ_OUT_COLUMNS, layer->in_layout == MOEQ_IN_STREAM, st));
   }
-  if (w.group) {
+  // a grouped call's tokens per launch; a workspace too small for a single token's takes the token-by-token form
+  const int64_t per = w.group ? launch_tokens(std::min<int64_t>(n_tokens, group_tokens(L.top_k)), ws_bytes - w.group_off,
+                                              [&](int64_t n) { return group_bytes(layer, n); })
+                    : w.batch ? launch_tokens(std::min<int64_t>(n_tokens, batch_tokens(L.top_k)), ws_bytes - w.group_off,
+                                              [&](int64_t n) { return batch_bytes(layer, n, L.top_k); })
+                              : 0;
+  if (w.group && per > 0) {
     if (!given && (launch_router_logits(L, layer->router_w, layer->router_bias, x, n_tokens, logits, st) != hipSuccess ||
                    launch_topk(L, logits, n_tokens, idx, gate, nullptr, st) != hipSuccess))
       return MOEQ_EDEVICE;
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
     const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
     ScopedEvents ev(layer, cols ? MOEQ_KERNEL_FUSED : MOEQ_KERNEL_FFN_IN, st), ev2(layer, cols ? -1 : MOEQ_KERNEL_FFN_OUT, st);
-    for (int64_t t0 = 0; t0 < n_tokens; t0 += group_tokens(L.top_k)) {
-      const int32_t n = (int32_t)(n_tokens - t0 < group_tokens(L.top_k) ? n_tokens - t0 : group_tokens(L.top_k));
+    for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
+      const int32_t n = (int32_t)std::min<int64_t>(n_tokens - t0, per);
       const size_t s0 = (size_t)t0 * (size_t)L.top_k;
       if (launch_group(L, layer->table, (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, (char*)ws + w.group_off,
                        cols, y + (size_t)t0 * L.d_model, st) != hipSuccess)
@@ -448,7 +458,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     }
     return MOEQ_OK;
   }
-  if (w.batch) {
+  if (w.batch && per > 0) {
     // the pairs grouped by expert; routed inside for few experts, else by the router kernels
     const bool route_inline = !given && L.n_experts <= (inline_router_max() < batch_inline_router_max() ? inline_router_max()
                                                                                                         : batch_inline_router_max());
@@ -460,12 +470,12 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
     const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
     ScopedEvents ev(layer, cols ? MOEQ_KERNEL_FUSED : MOEQ_KERNEL_FFN_IN, st), ev2(layer, cols ? -1 : MOEQ_KERNEL_FFN_OUT, st);
-    for (int64_t t0 = 0; t0 < n_tokens; t0 += batch_tokens(L.top_k)) {
-      const int32_t n = (int32_t)(n_tokens - t0 < batch_tokens(L.top_k) ? n_tokens - t0 : batch_tokens(L.top_k));
+    for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
+      const int32_t n = (int32_t)std::min<int64_t>(n_tokens - t0, per);
       const size_t s0 = (size_t)t0 * (size_t)L.top_k;
       if (launch_moe_batch(L, layer->table, layer->router_w, layer->router_bias, route_inline, -1, layer->bits_mask,
                            (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, gate + s0, 0,
-                           layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS, (char*)ws + w.batch_off,
+                           layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS, (char*)ws + w.group_off,
                            y + (size_t)t0 * L.d_model, st) != hipSuccess)
         return MOEQ_EDEVICE;
     }
@@ -542,7 +552,7 @@ moeq_status moe_layer_forward_static(const moeq_layer* layer, const void* x, int
                                      int32_t* topk_idx_opt, float* topk_gate_opt, void* stream) {
   if (!layer || n_tokens < 0) return MOEQ_EINVAL;
   if (n_tokens == 0) return MOEQ_OK;
-  if (ws_layout_for(layer, n_tokens, kStaticScratchBytes).total > kStaticScratchBytes) return MOEQ_EWORKSPACE;   // beyond the fixed scratch
+  if (ws_layout(layer, n_tokens).least > kStaticScratchBytes) return MOEQ_EWORKSPACE;   // beyond the fixed scratch
   void* ws = static_scratch();
   if (!ws) return MOEQ_EDEVICE;
   return layer_forward_impl(layer, x, n_tokens, y, topk_idx_opt, topk_gate_opt, nullptr, nullptr, ws,

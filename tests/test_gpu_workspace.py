@@ -7,6 +7,7 @@ import torch
 
 import gen
 import paper_2308_14352_amd as moeq
+from paper_2308_14352_amd import binding
 from helpers import build_layer_pair
 
 pytestmark = pytest.mark.gpu
@@ -27,6 +28,21 @@ def test_workspace_made_for_more_tokens_gives_the_same_bits(layout):
         for N in [n for n in sizes if n > T]:
             assert torch.equal(moeq.moe_layer_forward(layer, x[:T], ws=fresh(N)), want), (T, N)
             assert torch.equal(moeq.moe_expert_ffn_q(layer, 3, x[:T], ws=fresh(N)), want_e), (T, N)
+
+
+@pytest.mark.parametrize("base,d,f,E,group,T", [
+    ("c4", 4096, 8192, 4, 128, 31),     # grouped decode kernels: 31 tokens in one launch take more than the fixed scratch
+    ("c1", 768, 3072, 8, 32, 620),      # grouped GEMMs of narrow layers
+])
+def test_static_entry_runs_the_grouped_kernels_in_smaller_launches(base, d, f, E, group, T):
+    cfg = replace(gen.tiny_config(base, d, f, n_experts=E, n_layers=1, group=group), x_dtype="f32")
+    layer, _, _, _ = build_layer_pair(cfg, 0, DEV, [2, 4] * (E // 2), want_oracle=False)
+    assert layer.workspace_bytes(T) > binding.moe_static_scratch_bytes()
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    want = moeq.moe_layer_forward(layer, x, want_routing=True)
+    got = binding.moe_layer_forward_static(layer, x, want_routing=True)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
 @pytest.mark.parametrize("layout", ("canonical", "columns"))
