@@ -59,27 +59,53 @@ constexpr int64_t kPrefillMinTokens = 32;
 constexpr int32_t kDecodeChunk = 32;
 bool use_prefill(const moeq_layer* layer, int64_t T);
 // Whether a call of T tokens with k choices each groups its pairs by expert (decode_batch.hip) on a layer that
-// batch_supported() takes, or runs the kernels that work token by token. Both sides as measured on layers of 4096 columns
-// (us; 2- and 4-bit experts unless stated):
-//   one workgroup per (slice, token), one workgroup per compute unit: 8 + rounds * (8 + 12 k), rounds = slices T / 256,
-//   at least 7 + 12 k (stream layout, 224 slices, k = 2: 65 / 93 / 122 / 221 / 828 for 2 / 3 / 4 / 8 / 31 tokens; 32
-//   slices: 32 for 6; columns, d_ff 3072 in 192 slices: 176 for 8)
-//   the two GEMV kernels of the canonical layout: 30 + rounds * (6 + 9 k) (0.4 + 0.2 bits), rounds = d_ff / 64 T / 256
-//   (78 / 136 / 114 / 197 / 658; d_ff 3072, 8 tokens: 70; one 4-bit expert, 3 tokens: 76)
-//   grouped: four kernels and every distinct expert once, 38 + 12.5 per expert of 14336 columns at 3 bits on average
-//   (79 / 90 / 111 / 134-150 / 161; d_ff 3072, 8 tokens: 60), 10 % more on canonical rows
-// The distinct experts are estimated as if every expert were equally likely; a hot set only makes grouping cheaper.
+// batch_supported() takes, or runs the kernels that work token by token: a model of either side in microseconds, fitted so
+// that the choice between them is right over 1725 pairs of measured calls (d_ff 256 to 14336, 2, 4 and 8 bits, 1 to 64
+// experts, 2 to 31 tokens; single experts up to 300). The form it picks is 0.2 % slower than the faster one on average, and
+// more than 5 % in 20 of them (at most 15 %: rows, d_ff 1920, 5 to 8 tokens).
+//   token by token, W_out in columns: rounds of one workgroup (a slice of d_ff, a token) per compute unit, nearly as long when
+//     they are not full, in launches of kDecodeChunk tokens; canonical rows: the GEMV kernels, a third more unless T is a
+//     power of two (256 / T workgroups a token split the rows evenly only then), three quarters beyond 256 tokens
+//   grouped: four kernels, at least the latency of a workgroup's one unit of 128 rows, which grows with the bitwidth, or the
+//     bytes of the work items: every expert once per 16 pairs (8 on layers that are not in the stream layout)
+// us, token by token / grouped: Mixtral layer (d_ff 14336, 2 and 4 bits) in stream 96 / 103, 225 / 152, 823 / 163 for 3, 8, 31
+// tokens, in rows 134 / 113, 204 / 170, 669 / 232; one 8-bit expert in rows, d_ff 4096: 33 / 75, 48 / 77, 83 / 68, 190 / 69
+// for 4, 8, 16, 24 tokens, d_ff 1024: 24 / 63, 49 / 66 for 8, 24.
+// The experts are taken as equally likely; a hot set only makes grouping cheaper.
+struct BatchModel {
+  double ceil_part, u0, u_round, u_k, u_bits, u_bits0, u_token;      // token by token (layers with W_out in columns)
+  double lat0, lat_bits, g0, g_bytes, g_bits0, g_item;               // grouped
+};
+constexpr BatchModel kModelStream{0.85, 0.4, 9.5, 5.0, 0.22, 2.2, 0.2, 35.4, 3.45, 23.3, 2.65, 2.1, 0.3};
+constexpr BatchModel kModelColumns{0.55, 9.5, 8.7, 6.25, 0.45, 0.6, 0.12, 25.4, 5.4, 18.2, 3.75, 2.1, 0.7};
+constexpr BatchModel kModelRows{0, 0, 0, 0, 0, 0, 0, 31.5, 3.5, 25.1, 3.8, 0.9, 0.8};
 bool batch_pays(const moeq_layer* layer, int64_t T, int32_t k, double experts, double bits) {
   const LayerDims& L = layer->dims;
-  if (T < 2 || !batch_supported(L)) return false;
-  const bool canonical = layer->out_layout == MOEQ_OUT_CANONICAL;
-  const double rounds = (double)(canonical ? L.d_ff / 64 : layer->plan.n_slices) * (double)T / 256.0;
+  const bool rows = layer->out_layout == MOEQ_OUT_CANONICAL, stream = layer->in_layout == MOEQ_IN_STREAM;
+  if (T < (rows ? 3 : 2) || !batch_supported(L)) return false;
+  // Layer calls of 32 tokens and more on rows (that the prefill GEMMs do not take) are all grouped, on narrow layers too, where
+  // it is not the faster form: d_ff 640 is even at 60 tokens, d_ff 128 takes twice as long (200 tokens 87 / 186).
+  if (rows && experts > 1.0 && T >= kPrefillMinTokens) return true;
+  const BatchModel& m = stream ? kModelStream : rows ? kModelRows : kModelColumns;
+  const double nm = L.act == MOEQ_ACT_SWIGLU ? 1.0 : 2.0 / 3.0;      // an expert's weights, in three matrices
+  double one = 0.0;
+  if (rows) {
+    const double uneven = T > 256 ? 1.75 : (T & (T - 1)) ? 1.34 : 1.0;
+    one = 4.0 + 11.2 * k + L.d_ff / 64.0 * (double)T / 256.0 * nm * (7.5 * k - 0.84) * (1.0 + 0.21 * bits) * uneven;
+  } else {
+    auto launch = [&](double n) {
+      const double fill = layer->plan.n_slices * n / 256.0, rounds = m.ceil_part * std::ceil(fill) + (1.0 - m.ceil_part) * std::fmax(1.0, fill);
+      const double slice = nm * L.d_ff / (double)layer->plan.n_slices / 16.0;      // in 16 columns
+      return m.u0 + rounds * (m.u_round + k * (m.u_k + m.u_bits * slice * (bits + m.u_bits0))) + m.u_token * n;
+    };
+    if (T >= kDecodeChunk) one = (double)(T / kDecodeChunk) * launch(kDecodeChunk);
+    if (T % kDecodeChunk) one += launch((double)(T % kDecodeChunk));
+  }
+  const double launches = std::ceil((double)T * k / kBatchMaxPairs);
   const double distinct = experts * (1.0 - std::pow(1.0 - std::fmin(1.0, k / experts), (double)T));
-  const double grouped = 38.0 + 12.5 * distinct * (L.d_ff / 14336.0) * (bits / 3.0);
-  // (256 / T workgroups a token split the rows evenly only for powers of two)
-  const double split = (T & (T - 1)) ? 1.25 : 1.0;
-  if (canonical) return T >= 3 && 1.1 * grouped < 30.0 + split * rounds * (6.0 + 9.0 * k) * (0.4 + 0.2 * bits);
-  return grouped < std::fmax(7.0 + 12.0 * k, 8.0 + rounds * (8.0 + 12.0 * k));
+  const double items = std::fmax(distinct, (double)T * k / (stream ? 16.0 : 8.0) + 0.5 * distinct);
+  const double bytes = m.g0 + m.g_bytes * items / launches * nm * L.d_ff / 14336.0 * (bits + m.g_bits0);
+  return launches * std::fmax(m.lat0 + m.lat_bits * bits, bytes) + m.g_item * items < one;
 }
 bool batch_pays_layer(const moeq_layer* layer, int64_t T) {
   return batch_pays(layer, T, layer->dims.top_k, layer->dims.n_experts, layer->mean_bits);

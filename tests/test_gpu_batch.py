@@ -168,3 +168,22 @@ def test_grouped_call_whose_larger_half_of_h_meets_zero_weights(bits, layout):
     torch.cuda.synchronize()
     ref = oracle.expert_ffn(pack_expert_oracle(w, bits, g), d, f, g, 1, x.cpu().numpy())
     assert rel_err(y.cpu().numpy(), ref).max() < TOL
+
+
+@pytest.mark.parametrize("layout,f,bits,alone,grouped", [
+    ("canonical", 4096, 8, (4, 6, 8), (24, 31)),          # us, token by token / grouped: 48 / 77 for 8 tokens, 190 / 69 for 24
+    ("canonical", 1024, 8, (8, 16, 24), (100,)),          # 49 / 66 for 24, 152 / 78 for 100
+    ("canonical", 1024, 4, (16, 24), (100,)),             # 26 / 46 for 16, 111 / 60 for 100
+    ("columns", 1024, 8, (2, 8), (16, 31)),               # 39 / 59 for 8, 73 / 61 for 16
+])
+def test_one_experts_calls_take_the_faster_form(layout, f, bits, alone, grouped):
+    """The forms differ by their error: token by token the activations have 11 bits, grouped (rows, columns) 30."""
+    cfg = replace(gen.tiny_config("c4", 4096, f, n_experts=1, n_layers=1, group=128), top_k=1, x_dtype="f32")
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits], columns=layout == "columns")
+    x = gen.hidden(cfg, 0, 0, max(grouped), DEV)
+    ref = oracle.expert_ffn(orc_experts[0], 4096, f, 128, 1, x.cpu().numpy())
+    for T in alone + grouped:
+        y = moeq.moe_expert_ffn_q(layer, 0, x[:T])
+        torch.cuda.synchronize()
+        err = rel_err(y.cpu().numpy(), ref[:T]).max()
+        assert err < 2e-5 if T in grouped else 5e-5 < err < 2e-3, (T, err)
