@@ -100,3 +100,17 @@ def test_grouped_layer_with_outlier_columns_that_meet_zero_weights(bits, columns
     torch.cuda.synchronize()
     ref = oracle.expert_ffn(pack_expert_oracle(w, bits, g), d, f, g, 0, x.cpu().numpy())
     assert rel_err(y.cpu().numpy(), ref).max() < TOL
+
+
+@pytest.mark.parametrize("E,T,grouped", [(128, 32, False), (64, 40, False), (8, 48, True), (64, 128, True)])
+def test_grouped_only_where_the_tokens_share_experts(E, T, grouped):
+    """Switch-base layers in rows: few tokens on many experts run token by token (128 experts, 32 tokens 36 us, grouped 51).
+    That shows against calls of 24 tokens, which are never grouped: the same kernels differ by the order of fp32 sums (1e-7),
+    the grouped ones round x and h apart from them (1e-4)."""
+    cfg = gen.tiny_config("c1", 768, 3072, n_experts=E, n_layers=1, group=32)
+    layer, _, _, _ = build_layer_pair(cfg, 0, DEV, [(2, 4, 8)[i % 3] for i in range(E)], want_oracle=False)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    y = moeq.moe_layer_forward(layer, x)
+    few = torch.cat([moeq.moe_layer_forward(layer, x[t:t + 24]) for t in range(0, T, 24)])
+    torch.cuda.synchronize()
+    assert (float((y - few).abs().max() / few.abs().max()) > 5e-6) == grouped
