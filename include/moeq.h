@@ -265,8 +265,10 @@ moeq_status moe_unprepare_in(const void *stream_buf, int64_t rows, int64_t cols,
 /* Measurement aid, per layer. While `which` names a kernel, every moe_layer_forward call on THIS
  * layer records start_event just before and stop_event just after that kernel on the call's stream
  * (hipEvent_t handles created by the caller with timing enabled, which must outlive the setting),
- * so a benchmark can time the dominant kernel alone. For MOEQ_KERNEL_FUSED the two events bracket the kernels of
- * a call of several tokens on a stream layer; elsewhere they are
+ * so a benchmark can time the dominant kernel alone (W_out in columns: MOEQ_KERNEL_FUSED; rows: the other two; calls that
+ * run the prefill GEMMs record nothing). Calls that group their pairs (moe_layer_path) record them in their first launch:
+ * FFN_IN around the kernel of W_in / W_gate, FFN_OUT from the kernel of W_out to the combine, FUSED around all kernels but
+ * the combine. For MOEQ_KERNEL_FUSED on the other calls the two events are
  * attached to the kernel launch itself and receive the begin and end of the kernel's execution
  * (what a kernel trace reports), without the dispatch before it. which = 0 turns it off (the
  * default). The setting is part of the layer handle: change it only while no other thread is

@@ -484,18 +484,23 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
                     : w.batch ? launch_tokens(std::min<int64_t>(n_tokens, batch_tokens(L.top_k)), ws_bytes - w.group_off,
                                               [&](int64_t n) { return batch_bytes(layer, n, L.top_k); })
                               : 0;
+  // the profiling events of its first launch (FFN_IN / FFN_OUT on rows, FUSED on columns, as for the ungrouped kernels)
+  auto prof = [&](int64_t t0) {
+    const bool here = t0 == 0 && layer->prof_start && layer->prof_stop &&
+                      (layer->prof_which == MOEQ_KERNEL_FUSED) == (layer->out_layout == MOEQ_OUT_COLUMNS);
+    return Prof{here ? layer->prof_which : 0, layer->prof_start, layer->prof_stop};
+  };
   if (w.group && per > 0) {
     if (!given && (launch_router_logits(L, layer->router_w, layer->router_bias, x, n_tokens, logits, st) != hipSuccess ||
                    launch_topk(L, logits, n_tokens, idx, gate, nullptr, st) != hipSuccess))
       return MOEQ_EDEVICE;
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
     const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
-    ScopedEvents ev(layer, cols ? MOEQ_KERNEL_FUSED : MOEQ_KERNEL_FFN_IN, st), ev2(layer, cols ? -1 : MOEQ_KERNEL_FFN_OUT, st);
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
       const int32_t n = (int32_t)std::min<int64_t>(n_tokens - t0, per);
       const size_t s0 = (size_t)t0 * (size_t)L.top_k;
       if (launch_group(L, layer->table, (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, (char*)ws + w.group_off,
-                       cols, y + (size_t)t0 * L.d_model, st) != hipSuccess)
+                       cols, y + (size_t)t0 * L.d_model, st, prof(t0)) != hipSuccess)
         return MOEQ_EDEVICE;
     }
     return MOEQ_OK;
@@ -510,15 +515,13 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
         return MOEQ_EDEVICE;
     }
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
-    const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
-    ScopedEvents ev(layer, cols ? MOEQ_KERNEL_FUSED : MOEQ_KERNEL_FFN_IN, st), ev2(layer, cols ? -1 : MOEQ_KERNEL_FFN_OUT, st);
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
       const int32_t n = (int32_t)std::min<int64_t>(n_tokens - t0, per);
       const size_t s0 = (size_t)t0 * (size_t)L.top_k;
       if (launch_moe_batch(L, layer->table, layer->router_w, layer->router_bias, route_inline, -1, layer->bits_mask,
                            (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, gate + s0, 0,
                            layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS, (char*)ws + w.group_off,
-                           y + (size_t)t0 * L.d_model, st) != hipSuccess)
+                           y + (size_t)t0 * L.d_model, st, prof(t0)) != hipSuccess)
         return MOEQ_EDEVICE;
     }
     return MOEQ_OK;

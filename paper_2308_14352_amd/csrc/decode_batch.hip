@@ -921,7 +921,7 @@ hipError_t init_attrs_decode_batch() {
 hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
                             bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T, int32_t* idx,
                             float* gate, const float* gate_out, int32_t accumulate, bool in_stream, bool out_columns, char* ws,
-                            float* y, hipStream_t st) {
+                            float* y, hipStream_t st, const Prof& prof) {
   const int k = fixed_expert >= 0 ? 1 : L.top_k;
   if (!batch_supported(L) || L.d_ff % kBGroup || T < 1 || (int64_t)T * k > kBatchMaxPairs || !(bits_mask & 14) || (in_stream && !out_columns))
     return hipErrorInvalidValue;
@@ -935,13 +935,19 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
   const int P = T * k;
   const int tok = batch_tok(in_stream), max_items = P < L.n_experts + P / tok ? P : L.n_experts + P / tok;
   const int chunks = (L.d_ff / kBGroup + kBOutGroups - 1) / kBOutGroups;
+  prof_start(prof, MOEQ_KERNEL_FUSED, st);
   hipLaunchKernelGGL(in_stream ? k_batch_prep<true> : k_batch_prep<false>, dim3(T), dim3(512), 0, st, G);
   const bool sw = L.act == MOEQ_ACT_SWIGLU;
   auto kin = in_stream ? (sw ? k_batch_in<true, true> : k_batch_in<false, true>) : (sw ? k_batch_in<true, false> : k_batch_in<false, false>);
+  prof_start(prof, MOEQ_KERNEL_FFN_IN, st);
   hipLaunchKernelGGL(kin, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
+  prof_stop(prof, MOEQ_KERNEL_FFN_IN, st);
+  prof_start(prof, MOEQ_KERNEL_FFN_OUT, st);
   auto kout = in_stream ? k_batch_out<true, true> : out_columns ? k_batch_out<true, false> : k_batch_out<false, false>;
   hipLaunchKernelGGL(kout, dim3(kBD / kBOutRows, chunks, max_items), dim3(256), 0, st, G);
+  prof_stop(prof, MOEQ_KERNEL_FUSED, st);
   hipLaunchKernelGGL(k_batch_combine, dim3(kBD / 1024, T), dim3(256), 0, st, G.part, gate_out, chunks, T, k, accumulate, y);
+  prof_stop(prof, MOEQ_KERNEL_FFN_OUT, st);
   return hipGetLastError();
 }
 

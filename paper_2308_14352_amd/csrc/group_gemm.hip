@@ -796,7 +796,7 @@ hipError_t init_attrs_group_gemm() {
 }
 
 hipError_t launch_group(const LayerDims& L, const DevExpert* table, const void* x, int32_t T, const int32_t* idx,
-                        const float* gate, char* ws, bool out_columns, float* y, hipStream_t st) {
+                        const float* gate, char* ws, bool out_columns, float* y, hipStream_t st, const Prof& prof) {
   const int M = T * L.top_k;
   if (!group_supported(L) || T < 1 || M > kGMaxPairs) return hipErrorInvalidValue;
   const GroupWs w = group_ws(L, M);
@@ -806,6 +806,7 @@ hipError_t launch_group(const LayerDims& L, const DevExpert* table, const void* 
             (int32_t*)(ws + w.gpair), (int32_t*)(ws + w.ginv), (uint8_t*)(ws + w.hq), (float*)(ws + w.hs), (float*)(ws + w.hk),
             (float*)(ws + w.part), 16 * nt, 0};
   const int max_items = M < L.n_experts + M / (16 * nt) ? M : L.n_experts + M / (16 * nt);
+  prof_start(prof, MOEQ_KERNEL_FUSED, st);
   hipLaunchKernelGGL(k_grp_plan, dim3(L.n_experts), dim3(256), 0, st, G);
   // rows per workgroup: enough workgroups for the chip (three per compute unit), no more: each stages the item's activations
   constexpr int lds_want = kGLdsMost / 2;      // two workgroups on a compute unit (their registers allow no third)
@@ -815,8 +816,10 @@ hipError_t launch_group(const LayerDims& L, const DevExpert* table, const void* 
   while (rows > kGUnit && grp_in_lds(L, nt, rows) > lds_want) rows -= kGUnit;
   gx = (L.d_ff + rows - 1) / rows;
   G.rows_per_wg = rows;
+  prof_start(prof, MOEQ_KERNEL_FFN_IN, st);
   hipLaunchKernelGGL(nt == 1 ? grp_in_kernel<1>(g4_of(L.group)) : grp_in_kernel<2>(g4_of(L.group)), dim3(gx, max_items), dim3(kGThreads),
                      grp_in_lds(L, nt, rows), st, G);
+  prof_stop(prof, MOEQ_KERNEL_FFN_IN, st);
   const int unit = out_columns ? 64 * kGWaves : kGUnit, nu2 = (L.d_model + unit - 1) / unit;
   const int want2 = (768 + max_items * chunks - 1) / (max_items * chunks);
   gx = want2 < nu2 ? want2 : nu2;
@@ -824,9 +827,12 @@ hipError_t launch_group(const LayerDims& L, const DevExpert* table, const void* 
   while (rows > unit && grp_out_lds(L, nt, rows, out_columns) > lds_want) rows -= unit;
   gx = (L.d_model + rows - 1) / rows;
   G.rows_per_wg = rows;
+  prof_start(prof, MOEQ_KERNEL_FFN_OUT, st);
   hipLaunchKernelGGL(nt == 1 ? grp_out_kernel<1>(g4_of(L.group_out), out_columns) : grp_out_kernel<2>(g4_of(L.group_out), out_columns),
                      dim3(gx, max_items, chunks), dim3(kGThreads), grp_out_lds(L, nt, rows, out_columns), st, G);
+  prof_stop(prof, MOEQ_KERNEL_FUSED, st);
   hipLaunchKernelGGL(k_grp_combine, dim3(T), dim3(256), 0, st, G.part, G.ginv, gate, chunks, M, L.top_k, L.d_model, y);
+  prof_stop(prof, MOEQ_KERNEL_FFN_OUT, st);
   return hipGetLastError();
 }
 

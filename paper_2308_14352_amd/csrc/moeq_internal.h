@@ -25,6 +25,12 @@ struct LayerDims {
   int32_t d_model, d_ff, n_experts, top_k, group, act, renorm, x_bf16, group_out;
 };
 
+// Measurement aid of the calls that are several kernels (moe_layer_profile_kernel): the events to record around the kernels
+// that `which` names; 0: none.
+struct Prof { int32_t which; hipEvent_t start, stop; };
+inline void prof_start(const Prof& p, int32_t which, hipStream_t st) { if (p.which == which) (void)hipEventRecord(p.start, st); }
+inline void prof_stop(const Prof& p, int32_t which, hipStream_t st) { if (p.which == which) (void)hipEventRecord(p.stop, st); }
+
 // Launchers (defined in the .hip files). All enqueue on `st` and return the launch status.
 
 // logits[t][e] = router_w[e] . x[t] (+ bias[e])
@@ -109,7 +115,7 @@ hipError_t init_attrs_decode_batch();
 hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
                             bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T,
                             int32_t* idx, float* gate, const float* gate_out, int32_t accumulate, bool in_stream,
-                            bool out_columns, char* ws, float* y, hipStream_t st);
+                            bool out_columns, char* ws, float* y, hipStream_t st, const Prof& prof = Prof{});
 // canonical (q, s) <-> stream buffer of a [rows][4096] matrix, groups of 128 columns
 hipError_t launch_relayout_in(const void* q, const void* s, int64_t rows, int bits, void* stream_buf, bool to_stream,
                               hipStream_t st);
@@ -121,7 +127,7 @@ int group_max_pairs();
 GroupWs group_ws(const LayerDims& L, int64_t M);
 hipError_t init_attrs_group_gemm();
 hipError_t launch_group(const LayerDims& L, const DevExpert* table, const void* x, int32_t T, const int32_t* idx,
-                        const float* gate, char* ws, bool out_columns, float* y, hipStream_t st);
+                        const float* gate, char* ws, bool out_columns, float* y, hipStream_t st, const Prof& prof = Prof{});
 
 // ---- batched (prefill) path: pairs grouped by expert, two quantized GEMMs on the matrix cores ----------
 // Byte offsets of the pieces of the prefill workspace (all 256-byte aligned).

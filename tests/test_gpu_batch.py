@@ -9,6 +9,7 @@ import torch
 import gen
 import oracle
 import paper_2308_14352_amd as moeq
+from paper_2308_14352_amd import binding
 from helpers import build_layer_pair, near_tie_tokens, oracle_layer, pack_expert_gpu, pack_expert_oracle, rel_err
 
 pytestmark = pytest.mark.gpu
@@ -187,3 +188,34 @@ def test_one_experts_calls_take_the_faster_form(layout, f, bits, alone, grouped)
         torch.cuda.synchronize()
         err = rel_err(y.cpu().numpy(), ref[:T]).max()
         assert err < 2e-5 if T in grouped else 5e-5 < err < 2e-3, (T, err)
+
+
+@pytest.mark.parametrize("base,d,f,group,T", [("c4", 4096, 8192, 128, 12), ("c1", 768, 3072, 32, 500)])
+def test_profile_events_of_grouped_calls_bracket_their_phase(base, d, f, group, T):
+    """On rows FFN_IN and FFN_OUT time the two phases, not the whole call twice."""
+    cfg = gen.tiny_config(base, d, f, n_experts=8, n_layers=1, group=group)
+    layer, _, _, _ = build_layer_pair(cfg, 0, DEV, [4] * 8, want_oracle=False)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    ws = torch.empty(layer.workspace_bytes(T), dtype=torch.uint8, device=DEV)
+    y = torch.empty((T, d), device=DEV)
+
+    def median_us(which):
+        times = []
+        for _ in range(15):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record(), b.record()
+            if which:
+                binding.moe_layer_profile_kernel(layer, which, a.cuda_event, b.cuda_event)
+            else:
+                a.record()
+            moeq.moe_layer_forward(layer, x, y=y, ws=ws)
+            if not which:
+                b.record()
+            binding.moe_layer_profile_kernel(layer, 0)
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3)
+        return sorted(times)[7]
+
+    median_us(0)
+    whole, t_in, t_out = median_us(0), median_us(binding.MOEQ_KERNEL_FFN_IN), median_us(binding.MOEQ_KERNEL_FFN_OUT)
+    assert t_in > 5 and t_out > 5 and t_in + t_out < 1.4 * whole, (whole, t_in, t_out)
