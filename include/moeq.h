@@ -23,14 +23,20 @@
  *   - Calls that share a workspace, and all compute calls on one layer handle, must be ordered on
  *     one stream (or otherwise serialised).
  *   - Range of the hidden states (Section 4.1, "Baselines": the decompressed weights are used in FP32
- *     arithmetic, so the path's range is fp32's). The kernels multiply in binary16 x integer code and
- *     accumulate in fp32; before that, every token's hidden state - and every intermediate vector h -
- *     is multiplied by a power of two of its own that brings its largest magnitude to about 2^14, and
- *     the result is scaled back in fp32. Accuracy therefore does not depend on the scale of a token as
- *     long as its largest magnitude lies in [2^-96, 2^124] and the exact results fit fp32; elements more
- *     than 2^29 times smaller than the token's largest one lose relative precision. A token that holds
- *     a NaN or an infinity gets the experts 0 .. top_k-1, NaN gates and a non-finite output; other tokens
- *     of the call are not affected and no invalid address is formed.
+ *     arithmetic, so the path's range is fp32's). The kernels multiply x and every intermediate vector h, normalised by
+ *     powers of two, with the integer codes, accumulate in fp32 and scale back in fp32. Accuracy therefore does not depend
+ *     on the scale of a token as long as its largest magnitude lies in [2^-96, 2^124] and the exact results fit fp32. What
+ *     an element keeps beside larger ones:
+ *       binary16, one power of two per token and h vector (or slice of it): single tokens and calls that run token by token on
+ *         layers with W_in in rows, and all grouped GEMMs (MOEQ_PATH_GROUPED_GEMM, and the grouped calls of narrow ReLU
+ *         layers): 11 bits, in the stored value down to 2^-29 of the token's largest element. The multipliers add up what
+ *         shares an instruction relative to its largest operands, zero weights included, so that less than 11 bits remain of
+ *         a sum beside operands some 2^10 times its own.
+ *       integers of 30 bits and sign per 128 columns: calls of a few tokens that group their pairs, W_in in rows (see moe_layer_path)
+ *       integers of 14 bits and sign per 128 columns of x and 64 of h: layers in the stream layout, single tokens; 15 bits
+ *         where a call groups its pairs
+ *     A token that holds a NaN or an infinity gets the experts 0 .. top_k-1, NaN gates and a non-finite output; other
+ *     tokens of the call are not affected and no invalid address is formed.
  *   - Token limits: moe_router_topk and moe_expert_ffn_q take at most 65535 tokens per call,
  *     moe_layer_forward(_routed) at most 65535 / top_k (else MOEQ_EUNSUPPORTED).
  *
@@ -138,9 +144,9 @@ size_t moe_layer_table_bytes(int32_t n_experts);
  * n_experts <= 1024; d_model, d_ff <= 32768. With out_layout = MOEQ_OUT_COLUMNS also: group and d_ff
  * multiples of 16, d_model <= 8192 (else MOEQ_EUNSUPPORTED). With in_layout = MOEQ_IN_STREAM also: out_layout =
  * MOEQ_OUT_COLUMNS, d_model = 4096, group = 128, d_ff a multiple of 64 (else MOEQ_EUNSUPPORTED); calls on such a
- * layer run the streaming kernel below 32 tokens and the grouped GEMMs from 32 tokens on where their shape rules
- * hold (d_ff a multiple of 256 with d_ff / 128 a multiple of 4; else the streaming kernel, 32 tokens per launch):
- * one copy of the weights serves decode and prefill.
+ * layer run the streaming kernels (moe_layer_path) below 32 tokens and the grouped GEMMs from 32 tokens on where their
+ * shape rules hold (d_ff a multiple of 256 with d_ff / 128 a multiple of 4; else the streaming kernels): one copy of the
+ * weights serves decode and prefill.
  * Errors: MOEQ_EINVAL, MOEQ_EUNSUPPORTED, MOEQ_EDEVICE (copy failed). */
 moeq_status moe_layer_create(const moeq_layer_desc *desc, void *table_dev, size_t table_bytes,
                              moeq_layer **out);
@@ -153,19 +159,21 @@ void moe_layer_destroy(moeq_layer *layer);
  * then, with the same results (where not even one token's pieces fit: token by token). Host-only arithmetic. */
 size_t moe_workspace_bytes(const moeq_layer *layer, int32_t max_tokens);
 
-/* Which kernels moe_layer_forward / moe_layer_forward_routed run for a call with n_tokens tokens on
- * `layer` (the choice depends on the layer's shape and W_out layout and on the token count only, so a
- * caller or a test can know it beforehand). The three paths compute the same layer (Section 3.1, the
- * MoE layer: router, top-k experts, gate-weighted sum). Returns -1 for a null layer or n_tokens < 1.
- * Host-only. */
-#define MOEQ_PATH_TWO_KERNELS 0    /* canonical layout: router, phase-1 and phase-2 GEMV kernels (ReLU layers from 32
-                                      tokens on: the pairs grouped by expert, each streamed once for 16 or 32 of them) */
-#define MOEQ_PATH_ONE_KERNEL 1     /* columns layout: one streaming kernel per 32 tokens, vector instr. (ReLU layers
-                                      from 32 tokens on: grouped, as above)                                */
+/* Which path moe_layer_forward / moe_layer_forward_routed take for a call with n_tokens tokens on `layer` (by the layer's
+ * shape and layouts and the token count, so a caller or a test can know it beforehand). The paths compute the same layer
+ * (Section 3.1, the MoE layer: router, top-k experts, gate-weighted sum). Returns -1 for a null layer or n_tokens < 1.
+ * Host-only.
+ * The paths 0, 1, 2 and 4 have a second form, which groups the call's (token, choice) pairs by expert and streams every
+ * expert once for several of them, like moe_expert_ffn_q on the first kind of layer:
+ *   d_model 4096, scale groups of 128: 2 tokens on (rows: 3), up to the 31 of a layer that the grouped GEMMs take beyond;
+ *   ReLU layers with W_in in rows that neither these kernels nor the grouped GEMMs take: 32 tokens on.
+ * It runs where it is faster by a rule on the sizes, the mean bitwidth and the token count; a workspace that holds less than
+ * its least launch keeps the first form (moe_workspace_bytes). The forms round differently (see "Range" above). */
+#define MOEQ_PATH_TWO_KERNELS 0    /* W_out in rows: router, phase-1 and phase-2 GEMV kernels             */
+#define MOEQ_PATH_ONE_KERNEL 1     /* columns layout: one streaming kernel per 32 tokens, vector instr.   */
 #define MOEQ_PATH_ONE_KERNEL_MX 2  /* columns layout: the same with matrix-core instructions              */
-#define MOEQ_PATH_GROUPED_GEMM 3   /* 32 tokens or more, either layout: pairs grouped by expert, GEMMs   */
-#define MOEQ_PATH_STREAM 4         /* stream + columns layouts: streaming kernels on integer dot products (one token: one
-                                      kernel; more: the pairs grouped by expert, every expert streamed once for 16 pairs) */
+#define MOEQ_PATH_GROUPED_GEMM 3   /* 32 tokens or more, any layout: pairs grouped by expert, GEMMs       */
+#define MOEQ_PATH_STREAM 4         /* stream + columns layouts: one streaming kernel per 32 tokens on integer dot products */
 int32_t moe_layer_path(const moeq_layer *layer, int32_t n_tokens);
 
 /* Codes bytes of a packed [rows][cols] matrix; *scale_bytes_opt receives the bytes of its scales.
