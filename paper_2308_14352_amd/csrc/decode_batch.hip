@@ -57,7 +57,7 @@ __device__ __forceinline__ i32x4_t mfma_i8(const i32x4_t& a, const i32x4_t& b, c
 // The 128 columns of a scale group are two operands (op) of 64; lane (m or n = l % 16, kb = l / 16) holds 16 of an
 // operand's columns, byte j of them being column operand_col(..., j) of the group: W_in / W_gate in the stream layout, in
 // the canonical one; W_out in columns. Rows of W_out in the canonical layout are read like those of W_in. Two swapped
-// halves of a wavefront (swap_halves) stand behind the (kb & 1, kb >> 1) forms.
+// halves of a wavefront (swap32) stand behind the (kb & 1, kb >> 1) forms.
 enum BatchOrder { BO_STREAM = 0, BO_ROWS = 1, BO_COLUMNS = 2 };
 template <int BITS, int ORDER>
 __device__ __forceinline__ int operand_col(int op, int kb, int j) {
@@ -92,14 +92,6 @@ template <int BITS> constexpr int code_offset() { return BITS == 8 ? 0 : 1 << (B
 
 __device__ __forceinline__ uint32_t lo_byte(int v) { return (uint32_t)v & 255u; }
 __device__ __forceinline__ uint32_t hi_byte(int v) { return (uint32_t)((v + 128) >> 8) & 255u; }
-
-// Lanes 32..63 of a against lanes 0..31 of b: a = (a.lower, b.lower), b = (a.upper, b.upper).
-__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
-  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(a, b, false, false));
-  a = r.x;
-  b = r.y;
-}
 
 // A work item: up to batch_tok() pairs of one expert.
 struct alignas(16) BatchItem { int32_t e, n; uint8_t pair[kBRows]; int32_t bits, pad; };
@@ -464,8 +456,8 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
         const uint4* t = &R.t[(hh * NM + m) * LPM];
         if constexpr (BITS == 2) {
           uint32_t a0 = t[0].x, a1 = t[0].y, a2 = t[0].z, a3 = t[0].w;
-          swap_halves(a0, a1);
-          swap_halves(a2, a3);
+          swap32(a0, a1);
+          swap32(a2, a3);
           w[m][0][0] = a0; w[m][1][0] = a1; w[m][0][1] = a2; w[m][1][1] = a3;
         } else if constexpr (!STREAM) {              // 4 bits: a load per group; 8 bits: two
 #pragma unroll
@@ -478,7 +470,7 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
           uint32_t a[4] = {t[0].x, t[0].y, t[0].z, t[0].w}, b[4] = {t[1].x, t[1].y, t[1].z, t[1].w};
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            swap_halves(a[j], b[j]);
+            swap32(a[j], b[j]);
             w[m][0][j] = a[j]; w[m][1][j] = b[j];
           }
         } else {
@@ -488,7 +480,7 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
             uint32_t b[4] = {t[2 * pr + 1].x, t[2 * pr + 1].y, t[2 * pr + 1].z, t[2 * pr + 1].w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              swap_halves(a[j], b[j]);
+              swap32(a[j], b[j]);
               w[m][0][4 * pr + j] = a[j]; w[m][1][4 * pr + j] = b[j];
             }
           }
@@ -783,8 +775,8 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
           } else if constexpr (BITS == 2) {
             const uint4 t = R.t[(gi >> 1) * 4 + i];
             uint32_t a0 = t.x, a1 = t.y, a2 = t.z, a3 = t.w;
-            swap_halves(a0, a1);
-            swap_halves(a2, a3);
+            swap32(a0, a1);
+            swap32(a2, a3);
             B[0] = codes16_2((gi & 1) ? a1 : a0);
             B[1] = codes16_2((gi & 1) ? a3 : a2);
           } else if constexpr (BITS == 4) {
@@ -875,8 +867,6 @@ __global__ __launch_bounds__(256) void k_batch_combine(const float* __restrict__
   }
   for (int i = 0; i < 4; ++i) o[i] = v[i];
 }
-
-inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 int batch_cus() {
   static const int cus = [] {

@@ -61,8 +61,9 @@ __device__ __forceinline__ uint2 gload_u32x2(const uint8_t* ptr) {
   return make_uint2(v.x, v.y);
 }
 
-// a / b for 0 <= a < 2^21, b > 0: the quotient of the floats is off by less than 2^-21 of itself, the nearest integer
-// boundary of (a + 1/2) / b is 1 / (2 b) away. Five instructions. The kernels of the small layers execute almost every
+// a / b for 0 <= a < 2^21, b > 0: the quotient of the floats is off by less than 1.5 * 2^-23 of itself (a reciprocal of one
+// unit in the last place and one rounding; a + 1/2 is exact), and the nearest integer lies 1 / (2 a + 1) of (a + 1/2) / b
+// away, more than 2^-22.01. Five instructions. The kernels of the small layers execute almost every
 // instruction once per launch, and a launch finds the instruction caches cold: some 300 cycles per 64 bytes of code, so
 // that each of the compiler's 40-instruction divisions costs as much as a memory round trip.
 __device__ __forceinline__ int small_div(int a, int b) {
@@ -461,6 +462,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32));
   const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48));
   return (r0 + r1) + (r2 + r3);
+}
+
+// Halves of a wavefront, and quarters: two registers' halves (quarters) exchanged crosswise.
+typedef unsigned u32x2s_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {    // a = (a.lower, b.lower), b = (a.upper, b.upper)
+  const u32x2s_t r = __builtin_bit_cast(u32x2s_t, __builtin_amdgcn_permlane32_swap(a, b, false, false));
+  a = r.x; b = r.y;
+}
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {    // odd quarters of a against even quarters of b
+  const u32x2s_t r = __builtin_bit_cast(u32x2s_t, __builtin_amdgcn_permlane16_swap(a, b, false, false));
+  a = r.x; b = r.y;
 }
 
 // A pointer that is the same in every lane, moved to scalar registers so that loads can use the

@@ -31,8 +31,8 @@ constexpr int kGRing = 4;                  // 16-byte loads per lane in flight
 constexpr int kGMaxPairs = 8192;           // pairs grouped at a time
 constexpr int kGMaxBlocks = 64;            // blocks of 32 columns of d_model
 
-struct alignas(16) GrpItem {   // pairs gpair[g0 .. g0 + n) of expert e, and what the kernels need of the expert's record
-  int32_t e, n, g0, bits;
+struct alignas(16) GrpItem {   // pairs gpair[g0 .. g0 + n) of an expert, and what the kernels need of the expert's record
+  int32_t n, g0, bits, pad;
   const uint8_t* q_in;
   const uint16_t* s_in;
   const uint8_t* q_out;
@@ -45,7 +45,7 @@ struct GrpArgs {
   const DevExpert* table;
   const void* x;
   const int32_t* idx;       // [M]
-  int32_t M, k, out_columns;
+  int32_t M, k;
   GrpItem* items;
   int32_t* n_items;
   int32_t* gpair;           // [M] pairs in expert order
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256) void k_grp_plan(GrpArgs G) {
   const int ibase = red[0][1] + red[1][1] + red[2][1] + red[3][1];
   const int n = h[e], mine = (n + kGTok - 1) / kGTok;
   for (int i = tid; i < mine; i += 256)
-    G.items[ibase + i] = GrpItem{e, min(kGTok, n - i * kGTok), base + i * kGTok, G.table[e].bits,
+    G.items[ibase + i] = GrpItem{min(kGTok, n - i * kGTok), base + i * kGTok, G.table[e].bits, 0,
                                  G.table[e].q_in, G.table[e].s_in, G.table[e].q_out, G.table[e].s_out};
   if (e == E - 1 && tid == 0) *G.n_items = ibase + mine;
   if (n == 0) return;
@@ -140,15 +140,6 @@ __device__ __forceinline__ uint4 block_operand(const float (&a)[4], const float 
   return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
-typedef unsigned u32x2s_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {    // a = (a.lower, b.lower), b = (a.upper, b.upper)
-  const u32x2s_t r = __builtin_bit_cast(u32x2s_t, __builtin_amdgcn_permlane32_swap(a, b, false, false));
-  a = r.x; b = r.y;
-}
-__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {    // odd quarters of a against even quarters of b
-  const u32x2s_t r = __builtin_bit_cast(u32x2s_t, __builtin_amdgcn_permlane16_swap(a, b, false, false));
-  a = r.x; b = r.y;
-}
 // Code fields two bits higher than they lie in a byte. The matrix instruction aligns its products by the exponents of its
 // operands, subnormal ones as they stand, and what it drops below the largest weighs most against fields that begin at bit
 // 0. Error of 500 tokens on 2-bit Switch-base experts against 64 bits: two bits up 2.95e-4, as they lie 3.05e-4 (the kernels
@@ -465,7 +456,6 @@ __device__ __forceinline__ GrpItem load_item(const GrpArgs& G) {
   const int count = *G.n_items;
   GrpItem it = G.items[blockIdx.y];
   it.n = (int)blockIdx.y < count ? it.n : 0;
-  it.e = __builtin_amdgcn_readfirstlane(it.e);
   it.n = __builtin_amdgcn_readfirstlane(it.n);
   it.g0 = __builtin_amdgcn_readfirstlane(it.g0);
   it.bits = __builtin_amdgcn_readfirstlane(it.bits);
@@ -741,7 +731,6 @@ __global__ __launch_bounds__(256) void k_grp_combine(const float* __restrict__ p
   }
 }
 
-inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr int kGLdsMost = 160 * 1024;
 
 int grp_in_lds(const LayerDims& L, int nt, int rows) { return grp_lds(nt, padded_blocks(L.d_model), rows, L.d_model / L.group, true).total; }
@@ -802,7 +791,7 @@ hipError_t launch_group(const LayerDims& L, const DevExpert* table, const void* 
   const GroupWs w = group_ws(L, M);
   const int nt = tiles_of(L, M);
   const int NU = (L.d_ff + kGUnit - 1) / kGUnit, chunks = (L.d_ff + kGChunk - 1) / kGChunk;
-  GrpArgs G{L, table, x, idx, M, L.top_k, out_columns ? 1 : 0, (GrpItem*)(ws + w.items), (int32_t*)(ws + w.n_items),
+  GrpArgs G{L, table, x, idx, M, L.top_k, (GrpItem*)(ws + w.items), (int32_t*)(ws + w.n_items),
             (int32_t*)(ws + w.gpair), (int32_t*)(ws + w.ginv), (uint8_t*)(ws + w.hq), (float*)(ws + w.hs), (float*)(ws + w.hk),
             (float*)(ws + w.part), 16 * nt, 0};
   const int max_items = M < L.n_experts + M / (16 * nt) ? M : L.n_experts + M / (16 * nt);

@@ -31,6 +31,9 @@ struct Prof { int32_t which; hipEvent_t start, stop; };
 inline void prof_start(const Prof& p, int32_t which, hipStream_t st) { if (p.which == which) (void)hipEventRecord(p.start, st); }
 inline void prof_stop(const Prof& p, int32_t which, hipStream_t st) { if (p.which == which) (void)hipEventRecord(p.stop, st); }
 
+// Pieces of a workspace are 256-byte aligned.
+inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
+
 // Launchers (defined in the .hip files). All enqueue on `st` and return the launch status.
 
 // logits[t][e] = router_w[e] . x[t] (+ bias[e])

@@ -582,7 +582,6 @@ __global__ __launch_bounds__(256) void k_combine(const float* __restrict__ Ypair
   }
 }
 
-inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 }  // namespace
 

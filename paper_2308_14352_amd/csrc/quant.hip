@@ -1,7 +1,7 @@
 // Compression primitives on the device (Section 3.2): group-wise linear quantization with float16
 // scales, packing into the boundary format, and the two mirror maps (packed -> signed codes,
-// packed -> fp32). These are the offline side of the path; they are written for exactness, and
-// only coalesced enough to quantize tens of gigabytes of synthetic weights in seconds.
+// packed -> fp32). These are the offline side of the path; they are written for exactness first. The usual group sizes and
+// row widths have kernels bound by their fp32 reads or stores, the others simpler ones.
 #include <type_traits>
 
 #include "moeq_internal.h"

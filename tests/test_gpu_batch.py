@@ -1,5 +1,6 @@
 """GPU parity of decode calls of a few tokens on 4096-column layers (pairs grouped by expert, weights streamed once for up
-to 16 pairs), in every layout: the edges of its items, units and chunks."""
+to 16 pairs, 8 in rows and columns), in every layout: the edges of its items, units and chunks, inputs at the ends of their
+range and with outliers, and which calls are grouped."""
 from dataclasses import replace
 
 import numpy as np
@@ -14,9 +15,9 @@ from helpers import build_layer_pair, near_tie_tokens, oracle_layer, pack_expert
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-# On layers in the stream layout x and h enter with one exponent per 128 values and 15 bits below it: an element is off by at most 2^-16 of its group's
-# largest (about 3.5 standard deviations), 6e-5 / sqrt(3) of a standard deviation, once for x and once for h; the largest
-# of 4096 outputs' errors (4 standard deviations) against the largest output (again about 4) stays near that figure. The
+# On layers in the stream layout x and h enter with 15 bits below the largest of 128 (h: 64) values: an element is off by at
+# most 2^-16 of that (about 3.5 standard deviations), 6e-5 / sqrt(3) of a standard deviation, once for x and once for h; the
+# largest of 4096 outputs' errors (4 standard deviations) against the largest output (again about 4) stays near that figure. The
 # gate product and fp32 sums add less. 4e-4 leaves a factor of five. (On other layers they enter with 30 bits below it.)
 TOL = 4e-4
 
@@ -89,7 +90,6 @@ def test_grouped_call_with_the_ungrouped_workspace():
     x = gen.hidden(cfg, 0, 0, T, DEV)
     need = layer.workspace_bytes(T)
     slices = cfg.d_ff // 64
-    small = need
     y = moeq.moe_layer_forward(layer, x, ws=torch.empty(need, dtype=torch.uint8, device=DEV))
     # the ungrouped form: routing, logits and T * slices partial vectors
     part = T * slices * cfg.d_model * 4

@@ -1,5 +1,6 @@
 """GPU parity of calls of 32 tokens and more on ReLU layers whose scale groups the prefill GEMMs do not take: pairs grouped
-by expert, tiles of 16 and 32 pairs, ragged widths, every group size and both W_out layouts."""
+by expert, tiles of 16 and 32 pairs, ragged widths, every group size and both W_out layouts, outliers, calls in several
+launches, and which calls are grouped."""
 from dataclasses import replace
 
 import numpy as np
@@ -23,7 +24,9 @@ TOL = 2e-3          # the decode bar: x and h enter with 11 bits, as in the kern
     (640, 1152, 128, 3, 2, "f32", 100),         # (640 / 128) is odd: not the prefill GEMMs' shape; a last chunk of 128
     (320, 192, 64, 2, 1, "f32", 128),           # widths that are no multiple of a load or of 128 columns
     (384, 640, 32, 40, 1, "bf16", 32),          # more experts than tokens
-    (1536, 512, 32, 5, 1, "f32", 37),           # the widest the operand tile takes with groups of 32
+    (1536, 512, 32, 5, 1, "f32", 37),           # wide
+    (1792, 512, 32, 4, 1, "f32", 66),           # the widest the operand tile takes with groups of 32 ...
+    (2048, 1152, 128, 3, 1, "f32", 60),         # ... and with groups of 128
 ])
 @pytest.mark.parametrize("columns", (False, True), ids=("canonical", "columns"))
 def test_grouped_layer(d, f, group, E, k, x_dtype, T, columns):
@@ -114,3 +117,16 @@ def test_grouped_only_where_the_tokens_share_experts(E, T, grouped):
     few = torch.cat([moeq.moe_layer_forward(layer, x[t:t + 24]) for t in range(0, T, 24)])
     torch.cuda.synchronize()
     assert (float((y - few).abs().max() / few.abs().max()) > 5e-6) == grouped
+
+
+@pytest.mark.parametrize("k", (1, 2))
+def test_grouped_calls_of_more_pairs_than_a_launch_takes(k):
+    """8192 pairs are grouped at a time: a call of more is a call of those tokens and one of the rest."""
+    cfg = replace(gen.tiny_config("c1", 256, 384, n_experts=5, n_layers=1, group=32), top_k=k)
+    layer, _, _, _ = build_layer_pair(cfg, 0, DEV, [2, 4, 8, 4, 2], want_oracle=False)
+    first, T = 8192 // k, 8192 // k + 700
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    y, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
+    parts = [moeq.moe_layer_forward(layer, x[a:b], want_routing=True) for a, b in ((0, first), (first, T))]
+    torch.cuda.synchronize()
+    assert all(torch.equal(w, torch.cat([p[i] for p in parts])) for i, w in enumerate((y, idx, gate)))
