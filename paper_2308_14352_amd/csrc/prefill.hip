@@ -23,6 +23,8 @@
 // Every operand of the main loop travels HBM -> LDS directly (global_load_lds: no registers in between), into
 // rings of two or three stages, so that the loads of the next steps are in flight while a step is multiplied; the loop
 // holds no other memory instruction, and its waits are the hand-written s_waitcnt of stage_wait.
+#include <algorithm>
+
 #include "decode_core.h"
 
 namespace moeq {
@@ -52,9 +54,14 @@ __host__ __device__ inline Staged staged_layout(int K) {
 
 // ---------------------------------------------------------------------------------------------
 // grouping
+
+// A work item of k_gemm_small: expert, block of its pairs, bitwidth of the expert.
+__device__ __forceinline__ uint32_t small_item(int e, int tb, int bits) { return (uint32_t)e | (uint32_t)tb << 10 | (uint32_t)bits << 24; }
+
 __global__ __launch_bounds__(1024) void k_count_pairs(const int32_t* __restrict__ idx, int M, int E,
                                                       int32_t* __restrict__ poff, int32_t* __restrict__ boff,
-                                                      int2* __restrict__ blocks, int32_t* __restrict__ n_blocks) {
+                                                      int2* __restrict__ blocks, int32_t* __restrict__ n_blocks,
+                                                      const DevExpert* __restrict__ table, int small) {
   __shared__ int h[1024];
   for (int e = threadIdx.x; e < E; e += blockDim.x) h[e] = 0;
   __syncthreads();
@@ -66,7 +73,11 @@ __global__ __launch_bounds__(1024) void k_count_pairs(const int32_t* __restrict_
       poff[e] = off;
       boff[e] = nt;                 // token tile tb of expert e is tile number boff[e] + tb
       const int c = h[e];
-      for (int tb = 0; tb * (kTB * kItemTiles) < c; ++tb) blocks[nb++] = make_int2(e, tb);
+      if (small) {
+        for (int tb = 0; tb * small < c; ++tb) ((uint32_t*)blocks)[nb++] = small_item(e, tb, table[e].bits);
+      } else {
+        for (int tb = 0; tb * (kTB * kItemTiles) < c; ++tb) blocks[nb++] = make_int2(e, tb);
+      }
       nt += (c + kTB - 1) / kTB;
       off += c;
     }
@@ -104,6 +115,86 @@ __global__ __launch_bounds__(256) void k_scatter_pairs(const int32_t* __restrict
   }
 }
 
+// Both for calls of up to kPlanPairs pairs on up to kPlanExperts experts, by one workgroup (two dependent kernels cost two
+// launches of 4.7 us each for little work): a wavefront ranks 64 consecutive pairs at a time inside their experts by ballots,
+// then the counts of the 64-pair segments are summed per expert. Items of small_tok pairs (0: of 128), wide experts first:
+// their units last longest.
+constexpr int kPlanPairs = 4096, kPlanExperts = 64;
+__global__ __launch_bounds__(1024) void k_plan_pairs(const int32_t* __restrict__ idx, int M, int E, int32_t* __restrict__ poff,
+                                                     int32_t* __restrict__ boff, int2* __restrict__ blocks, int32_t* __restrict__ n_blocks,
+                                                     int32_t* __restrict__ gpair, int32_t* __restrict__ ginv, int32_t* __restrict__ gexp,
+                                                     const DevExpert* __restrict__ table, int small_tok) {
+  constexpr int SEGS = kPlanPairs / 64, PER = SEGS / 16;
+  __shared__ uint16_t cnt[SEGS][kPlanExperts];   // pairs of the segment, then the pairs of the segments before it
+  __shared__ int off[kPlanExperts];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int e[PER], rank[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int p = (i * 16 + wave) * 64 + lane;
+    e[i] = p < M ? min(max(idx[p], 0), E - 1) : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int seg = i * 16 + wave;
+    rank[i] = 0;
+    if (seg * 64 < M) {
+      int mine = 0;
+      for (int x = 0; x < E; ++x) {
+        const unsigned long long mask = __ballot(e[i] == x);
+        rank[i] = e[i] == x ? __popcll(mask & ((1ull << lane) - 1ull)) : rank[i];
+        mine = lane == x ? __popcll(mask) : mine;
+      }
+      cnt[seg][lane] = (uint16_t)mine;
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int segs = (M + 63) / 64, bits = lane < E ? table[lane].bits : 0;
+    int c = 0;
+#pragma unroll 8
+    for (int sg = 0; sg < segs; ++sg) {
+      const int v = cnt[sg][lane];
+      cnt[sg][lane] = (uint16_t)c;
+      c += v;
+    }
+    if (lane >= E) c = 0;
+    // exclusive sums over the experts: pairs, token tiles, and items, those in the order of the bitwidths
+    const int tiles = (c + kTB - 1) / kTB, per = small_tok ? small_tok : kTB * kItemTiles, items = (c + per - 1) / per;
+    const int own = items << (bits == 8 ? 0 : bits == 4 ? 10 : 20);      // (at most 192 items of one bitwidth)
+    int po = c, to = tiles, io = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int a = __shfl_up(po, d), b = __shfl_up(to, d), f = __shfl_up(io, d);
+      if (lane >= d) { po += a; to += b; io += f; }
+    }
+    const int all = __builtin_amdgcn_readlane(io, 63), n8 = all & 1023, n4 = (all >> 10) & 1023, n2 = all >> 20;
+    io -= own;
+    if (lane < E) {
+      off[lane] = po - c;
+      poff[lane] = po - c;
+      boff[lane] = to - tiles;
+      int at = bits == 8 ? io & 1023 : bits == 4 ? n8 + ((io >> 10) & 1023) : n8 + n4 + (io >> 20);
+      for (int tb = 0; tb < items; ++tb, ++at) {
+        if (small_tok) ((uint32_t*)blocks)[at] = small_item(lane, tb, bits);
+        else blocks[at] = make_int2(lane, tb);
+      }
+    }
+    if (lane == 0) { poff[E] = M; *n_blocks = n8 + n4 + n2; }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int seg = i * 16 + wave, p = seg * 64 + lane;
+    if (p < M) {
+      const int g = off[e[i]] + cnt[seg][e[i]] + rank[i];
+      gpair[g] = p;
+      ginv[p] = g;
+      gexp[g] = e[i];
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Staging of the activation vector of one pair for a GEMM, into the tiles of its work item (see Staged).
 // FROM_H = false: the pair's token row of x (GEMM 1); true: row g of the fp32 h that GEMM 1 wrote (GEMM 2).
@@ -132,12 +223,12 @@ struct TilePlace {
 };
 
 template <bool FROM_H>
-__global__ __launch_bounds__(256) void k_stage(LayerDims L, const DevExpert* __restrict__ table,
+__global__ __launch_bounds__(1024) void k_stage(LayerDims L, const DevExpert* __restrict__ table,
                                                const void* __restrict__ src, const int32_t* __restrict__ gpair,
                                                const int32_t* __restrict__ gexp, const int32_t* __restrict__ poff,
                                                const int32_t* __restrict__ boff, char* __restrict__ OUT, int M) {
   extern __shared__ uint32_t smem[];
-  __shared__ float red[4];
+  __shared__ float red[16];
   const int cols = FROM_H ? L.d_ff : L.d_model;
   uint16_t* RAW = (uint16_t*)smem;
   // consecutive pairs go to workgroups on the same XCD (workgroup i runs on XCD i % 8), so that the 16-byte pieces
@@ -567,15 +658,375 @@ __global__ __launch_bounds__(WV * 64) void k_gemm_q(GemmArgs G, int n_rb) {
   }
 }
 
-// y[t][r] = sum_j gate[t][j] * Ypair[ginv[t*k + j]][r], j in top-k order
+
+// ---------------------------------------------------------------------------------------------
+// The GEMMs of calls whose experts hold a few dozen pairs each (prompts of a hundred tokens or two). The 128-token items
+// above multiply mostly padding there; here an item is up to 32 pairs, and the call is bound by the packed bytes of the experts:
+//   - Workgroup = 8 wavefronts, two workgroups per compute unit (one's barriers and epilogue beside the other's loads). A
+//     wavefront owns 32 rows of weights (two streams of 16: with two matrices 16 rows of both) and reads them into registers
+//     in sets of four 16-byte loads per lane (W_out in columns: eight of 8 bytes), two sets ahead, 128 KB in flight per
+//     compute unit; every operand is unpacked once for the item's tokens. No other wavefront needs its bytes, so they do
+//     not pass through LDS.
+//   - The activations come in chunks of 512 columns (32 KB), double buffered in LDS, from the tiles k_stage wrote; a chunk's
+//     loads are issued with the sets of the chunk before it. One barrier per chunk, passed with the weights in flight.
+//   - GEMM 2 is cut along d_ff into `split` ranges whose partial outputs k_combine adds in order (an item has few rows of
+//     output, and all compute units are needed to reach the memory's rate). The cut depends on the layer's sizes alone.
+// Operands, instructions and scaling are those of k_gemm_q; a lane finds its A operand in the line of the staged tile that
+// holds the columns of its codes, so that every layout of the weights reads the same tiles.
+// Mixtral layer (8 experts, 2 and 4 bits, stream layout), us: 117 tokens GEMM 1 205 -> 129-139, GEMM 2 111 -> 59-64; 32 tokens
+// 341 -> 178 for the whole call (with the kernels around it). What is left of GEMM 1: with the multiplications taken out it
+// takes as long at 4 bits (160 us; 700 MB, experts of more than 32 pairs being read twice), so its loads bound it: 64 bytes of
+// 16 rows each, 4.4 TB/s, where 128 bytes of eight rows would reach 5.6 but leave the codes in the wrong lanes.
+// Tried: four streams a wavefront and half the wavefronts (137), items of 64 pairs on one workgroup of 8 wavefronts
+// (238: two wavefronts per SIMD do not hide the latencies), persistent workgroups (150: registers spill).
+constexpr int kSTok = 32;                        // pairs of an item, at most
+constexpr int kSCols = 512;                      // columns of a chunk
+constexpr int kSWaves = 8;
+constexpr int kSStreams = 2;                     // streams of 16 rows per wavefront
+constexpr int kSRows = 16 * kSStreams;
+constexpr int kSGroups = kSCols / 128;           // scale groups of a chunk
+enum SmallOrder { SO_ROWS = 0, SO_STREAM = 1, SO_COLUMNS = 2 };
+
+struct SmallLds {
+  uint4 A[2][kSGroups * 16][kSTok];              // [buffer][line of the staged tile][token]
+  float KS[2][kSGroups][kSTok];                  // negated offset terms
+  uint16_t SC[2][kSWaves][kSRows * kSGroups];    // rows, stream: [row][group], columns: [group][row]
+};
+
+template <int BITS, int NM, int PHASE, int ORDER>
+__device__ __forceinline__ void small_gemm_body(const GemmArgs& G, const DevExpert& ex, int e, int tb, int rb, int c0, int c1,
+                                                float* out, SmallLds& S) {
+  constexpr int NS = kSStreams, TT = kSTok / 16, RBW = NS / NM;
+  constexpr bool COLS = ORDER == SO_COLUMNS;
+  constexpr int GS = 8 / BITS;                   // scale groups of a set (stream layout, 8 bits: half of two)
+  constexpr int SPC = kSGroups / GS;             // sets of a chunk: 1, 2, 4
+  constexpr int AL = 32 / kSWaves, APS = AL / SPC; // a wavefront's loads of the next chunk's activations per set
+  constexpr int U = SPC < 2 ? 2 : SPC;           // sets per round of the loop
+  const int K = PHASE == 0 ? G.L.d_model : G.L.d_ff;
+  const int N = PHASE == 0 ? G.L.d_ff : G.L.d_model;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, kb = lane >> 4;
+  const int g0 = G.poff[e] + tb * kSTok;
+  const int ntok = min(kSTok, G.poff[e + 1] - g0);
+  const int R0 = (rb * kSWaves + wave) * (RBW * 16);             // (whole: N is a multiple of 256)
+  const Staged lay = staged_layout(K);
+  constexpr int IPT = kTB / kSTok;               // items per staged tile
+  const uint8_t* tile = (const uint8_t*)G.A + (size_t)(G.boff[e] + tb / IPT) * lay.block_bytes;
+  const int t0 = (tb % IPT) * kSTok;             // the item's first token in the tile
+
+  // ---- weights: stream s = (matrix s / RBW, row block s % RBW)
+  const uint8_t* q[NM];
+  const uint8_t* sq[NM];
+  if constexpr (PHASE == 0) {
+    q[0] = uniform_ptr(ex.q_in);
+    sq[0] = ORDER == SO_STREAM ? q[0] : (const uint8_t*)uniform_ptr(ex.s_in);
+    if constexpr (NM == 2) {
+      q[1] = uniform_ptr(ex.q_gate);
+      sq[1] = ORDER == SO_STREAM ? q[1] : (const uint8_t*)uniform_ptr(ex.s_gate);
+    }
+  } else {
+    q[0] = uniform_ptr(ex.q_out);
+    sq[0] = (const uint8_t*)uniform_ptr(ex.s_out);
+  }
+  constexpr uint32_t RB = 16 / BITS, TPR = BITS / 2, BB = 8192u + 64u * RB;      // stream layout: rows, tiles of a row, bytes of a block
+  const uint32_t row_bytes = (uint32_t)K * BITS / 8u, col_bytes = (uint32_t)N * 4u;
+  uint32_t loff[RBW];                            // the lane's first piece of every row block
+#pragma unroll
+  for (int r = 0; r < RBW; ++r) {
+    const uint32_t row = (uint32_t)(R0 + r * 16 + n);
+    if (ORDER == SO_STREAM) loff[r] = row / RB * BB + row % RB * (TPR * 1024u) + (uint32_t)kb * 16u;
+    else loff[r] = row * row_bytes + (uint32_t)kb * 16u;
+  }
+  if (COLS) loff[0] = (uint32_t)(R0 + NS * n) * 4u + (uint32_t)kb * (BITS == 8 ? 2u : 1u) * col_bytes;
+  using Piece = typename std::conditional<COLS, uint2, uint4>::type;
+  constexpr int NL = COLS ? 8 : 2 * NS;          // loads of a set
+  struct Set { Piece t[NL]; };
+  auto issue = [&](Set& R, int st) __attribute__((always_inline)) {
+    if constexpr (COLS) {
+      // load j of a group: word column 4 j + kb (8 bits: 8 (j / 2) + 2 kb + j % 2) of two rows
+      const uint8_t* b = q[0] + (size_t)(uint32_t)st * ((size_t)(GS * 4 * BITS) * col_bytes);
+#pragma unroll
+      for (int i = 0; i < NL; ++i) R.t[i] = gload_u32x2(b + (size_t)(BITS == 8 ? 8 * (i >> 1) + (i & 1) : 4 * i) * col_bytes + loff[0]);
+    } else {
+#pragma unroll
+      for (int p = 0; p < 2; ++p)                // 64-byte step of the rows (stream layout: part of their tiles)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          uint32_t o;
+          if (ORDER == SO_STREAM && BITS == 4) o = (uint32_t)st * 64u + p * 1024u;
+          else if (ORDER == SO_STREAM && BITS == 8) o = (uint32_t)(st >> 1) * 64u + (uint32_t)((st & 1) * 2 + p) * 1024u;
+          else o = (uint32_t)(st * 2 + p) * 64u;
+          R.t[p * NS + s] = gload_u32x4(q[s / RBW] + o + loff[s % RBW]);
+        }
+    }
+  };
+  // ---- a chunk's scales, two values per lane. Rows, stream: half a wavefront covers the 128 bytes of a stream's 16 rows x 4
+  // groups; columns: lane (n, kb) takes group kb of its rows
+  const uint32_t so = (uint32_t)(lane & 31) * 4u;                // byte of the stream's
+  const uint32_t srow = (uint32_t)(R0 + (lane >> 5) % RBW * 16);
+  const uint8_t* const sbase = NM == 2 && lane >= 32 ? sq[NM - 1] : sq[0];
+  // (stream layout: blocks of RB rows, whose 4 groups are 8 RB consecutive bytes, [group][row])
+  const uint32_t soff = ORDER == SO_STREAM ? (srow + so / (8u * RB) * RB) / RB * BB + 8192u + so % (8u * RB)
+                      : ORDER == SO_ROWS ? (srow + so / 8u) * (uint32_t)(K / 128 * 2) + so % 8u
+                                         : (uint32_t)kb * (uint32_t)N * 2u + (uint32_t)(R0 + NS * n) * 2u;
+  auto load_scales = [&](int c) __attribute__((always_inline)) {
+    return gload_u32(sbase + (uint32_t)c * (ORDER == SO_STREAM ? 8u * RB : ORDER == SO_ROWS ? 8u : (uint32_t)N * 8u) + soff);
+  };
+  auto store_scales = [&](int buf, uint32_t v) __attribute__((always_inline)) {
+    uint16_t* d = S.SC[buf][wave];
+    if constexpr (ORDER == SO_STREAM) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t o = so / 2u + i, blk = o / (4u * RB), u = o % (4u * RB);      // in values
+        d[((uint32_t)(lane >> 5) * 16u + blk * RB + u % RB) * kSGroups + u / RB] = (uint16_t)(v >> (16 * i));
+      }
+    } else {
+      *(uint32_t*)(d + lane * 2) = v;            // (columns: lane n + 16 kb, so [group][row])
+    }
+  };
+  // ---- a chunk's activations and offset terms
+  const uint8_t* asrc = tile + (uint32_t)((lane / kSTok) * 1024 + (lane % kSTok + t0) * 16);
+  constexpr int LPL = 64 / kSTok;                // lines a load covers
+  auto load_a = [&](int c, int i) __attribute__((always_inline)) {
+    return gload_u32x4(asrc + ((size_t)(uint32_t)c * (kSGroups * 16384u) + (uint32_t)((wave * AL + i) * LPL) * 1024u));
+  };
+  auto store_a = [&](int buf, int i, const uint4& v) __attribute__((always_inline)) {
+    ((uint4*)S.A[buf])[(wave * AL + i) * 64 + lane] = v;
+  };
+  auto load_k = [&](int c) __attribute__((always_inline)) {
+    const int i = tid & (kSGroups * kSTok - 1), g = c * kSGroups + i / kSTok, t = i % kSTok + t0;
+    const float* ks = (const float*)(tile + lay.ks_off);
+    return BITS == 8 ? ks[(2 * g) * kTB + t] + ks[(2 * g + 1) * kTB + t] : ks[g * kTB + t];
+  };
+  auto store_k = [&](int buf, float v) __attribute__((always_inline)) { (&S.KS[buf][0][0])[tid & (kSGroups * kSTok - 1)] = v; };
+
+  // ---- the line of operand q of a lane: lbase + lstep(q)
+  const int lbase = COLS ? (BITS == 4 ? 4 * kb : BITS == 2 ? 8 * (kb & 1) + (kb >> 1) : 4 * (kb & 1) + (kb >> 1))
+                  : BITS == 2 ? 8 * (kb >> 1) + 2 * (kb & 1)
+                  : ORDER == SO_STREAM ? (BITS == 4 ? 2 * (kb & 1) + (kb >> 1) : 8 * (kb & 1) + (kb >> 1)) : kb;
+  auto lstep = [](int i) {
+    if (COLS) return BITS == 4 ? i : BITS == 2 ? 4 * (i & 1) + 2 * (i >> 1) : 8 * (i >> 1) + 2 * (i & 1);
+    if (BITS == 2) return 4 * (i & 1) + (i >> 1);
+    if (ORDER == SO_STREAM && BITS == 8) return 4 * (i & 1) + 2 * (i >> 1);
+    return 4 * i;
+  };
+
+  float4_t acc[NS][TT];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[s][t] = (float4_t){0.f, 0.f, 0.f, 0.f};
+  // the chunk's scales: [stream] four groups, or [group] the streams
+  uint2 scv[COLS ? kSGroups : NS];
+  // operands Q0 .. Q0 + NQ - 1 of group g of the chunk, whose codes B(s, i) gives
+  auto multiply = [&](int buf, int g, auto q0_tag, auto nq_tag, auto B) __attribute__((always_inline)) {
+    constexpr int Q0 = decltype(q0_tag)::value, NQ = decltype(nq_tag)::value;
+    const uint4* A = &S.A[buf][g * 16 + lbase][n];
+    float4_t D[NS][TT];
+    uint4 a[2][TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      a[0][t] = A[lstep(Q0) * kSTok + 16 * t];
+      float4_t kv = {0.f, 0.f, 0.f, 0.f};
+      if (Q0 == 0) {
+        const float4 k4 = *(const float4*)&S.KS[buf][g][16 * t + 4 * kb];
+        kv = (float4_t){k4.x, k4.y, k4.z, k4.w};
+      }
+#pragma unroll
+      for (int s = 0; s < NS; ++s) D[s][t] = kv;
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      if (i + 1 < NQ) {
+#pragma unroll
+        for (int t = 0; t < TT; ++t) a[(i + 1) & 1][t] = A[lstep(Q0 + i + 1) * kSTok + 16 * t];
+      }
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const half8_t b = B(s, i);
+#pragma unroll
+        for (int t = 0; t < TT; ++t) D[s][t] = mfma16(as_half8(a[i & 1][t]), b, D[s][t]);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint2 v = COLS ? scv[g] : scv[s];
+      const int at = COLS ? s : g;
+      const uint32_t h = (at & 2) ? v.y : v.x;
+      const float sc = f16_bits_to_f32((at & 1) ? h >> 16 : h & 0xffffu);
+#pragma unroll
+      for (int t = 0; t < TT; ++t) acc[s][t] += sc * D[s][t];
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I2 = std::integral_constant<int, 2>;
+  using I4 = std::integral_constant<int, 4>;
+  auto consume = [&](Set& R, int buf, int sp) __attribute__((always_inline)) {       // set sp of the chunk
+    if constexpr (COLS) {
+#pragma unroll
+      for (int gi = 0; gi < GS; ++gi)
+        multiply(buf, sp * GS + gi, I0{}, I4{}, [&](int s, int i) __attribute__((always_inline)) {
+          auto word = [&](int j) { const Piece& v = R.t[gi * BITS + j]; return s == 0 ? v.x : v.y; };
+          if constexpr (BITS == 2) return (i & 1) ? codes8<2, 1>(word(i >> 1), 0u) : codes8<2, 0>(word(i >> 1), 0u);
+          else if constexpr (BITS == 4) return codes8<4, 0>(word(i), 0u);
+          else return codes8<8, 0>(word(2 * i), word(2 * i + 1));
+        });
+    } else if constexpr (BITS == 2) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) { swap32(R.t[i].x, R.t[i].y); swap32(R.t[i].z, R.t[i].w); }
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi)
+        multiply(buf, gi, I0{}, I4{}, [&](int s, int i) __attribute__((always_inline)) {
+          const uint4& v = R.t[(gi >> 1) * NS + s];
+          const uint32_t w = (i >> 1) ? ((gi & 1) ? v.w : v.z) : ((gi & 1) ? v.y : v.x);
+          return (i & 1) ? codes8<2, 1>(w, 0u) : codes8<2, 0>(w, 0u);
+        });
+    } else if constexpr (BITS == 4) {
+      if constexpr (ORDER == SO_STREAM) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          swap32(R.t[s].x, R.t[NS + s].x); swap32(R.t[s].y, R.t[NS + s].y);
+          swap32(R.t[s].z, R.t[NS + s].z); swap32(R.t[s].w, R.t[NS + s].w);
+        }
+      }
+#pragma unroll
+      for (int gi = 0; gi < 2; ++gi)
+        multiply(buf, sp * 2 + gi, I0{}, I4{}, [&](int s, int i) __attribute__((always_inline)) {
+          const uint4& v = R.t[gi * NS + s];
+          return codes8<4, 0>(i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w, 0u);
+        });
+    } else if constexpr (ORDER == SO_ROWS) {
+      multiply(buf, sp, I0{}, I4{}, [&](int s, int i) __attribute__((always_inline)) {
+        const uint4& v = R.t[(i >> 1) * NS + s];
+        return (i & 1) ? codes8<8, 0>(v.z, v.w) : codes8<8, 0>(v.x, v.y);
+      });
+    } else {
+      // a set holds parts 2 pr and 2 pr + 1 of two groups: operands 2 pr and 2 pr + 1 of both
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        swap32(R.t[s].x, R.t[NS + s].x); swap32(R.t[s].y, R.t[NS + s].y);
+        swap32(R.t[s].z, R.t[NS + s].z); swap32(R.t[s].w, R.t[NS + s].w);
+      }
+#pragma unroll
+      for (int gi = 0; gi < 2; ++gi) {
+        auto B = [&](int s, int i) __attribute__((always_inline)) {
+          const uint4& v = R.t[gi * NS + s];
+          return i ? codes8<8, 0>(v.z, v.w) : codes8<8, 0>(v.x, v.y);
+        };
+        if (sp & 1) multiply(buf, (sp >> 1) * 2 + gi, I2{}, I2{}, B);
+        else multiply(buf, (sp >> 1) * 2 + gi, I0{}, I2{}, B);
+      }
+    }
+  };
+
+  const int n_sets = (c1 - c0) * SPC, s0 = c0 * SPC;
+  Set R[2];
+  {
+    uint4 a[AL];
+#pragma unroll
+    for (int i = 0; i < AL; ++i) a[i] = load_a(c0, i);
+    const float kv = load_k(c0);
+    const uint32_t sv = load_scales(c0);
+    issue(R[0], s0);
+    issue(R[1], s0 + (n_sets > 1 ? 1 : 0));
+#pragma unroll
+    for (int i = 0; i < AL; ++i) store_a(0, i, a[i]);
+    store_k(0, kv);
+    store_scales(0, sv);
+  }
+  __syncthreads();
+  for (int b = 0; b < n_sets; b += U) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int st = b + i, sp = i % SPC;
+      if (SPC == 1 && st >= n_sets) break;       // (an odd number of one-set chunks)
+      const int c = c0 + st / SPC, buf = (st / SPC) & 1;
+      if (sp == 0) {
+        const uint16_t* sc = S.SC[buf][wave];
+#pragma unroll
+        for (int j = 0; j < (COLS ? kSGroups : NS); ++j) {
+          if constexpr (COLS) scv[j] = make_uint2(*(const uint32_t*)(sc + (j * 16 + n) * NS), 0u);
+          else scv[j] = *(const uint2*)(sc + (j * 16 + n) * 4);
+        }
+      }
+      const int cn = c + 1 < c1 ? c + 1 : c;     // (past the last chunk: loaded again, not used)
+      uint4 a[APS];
+#pragma unroll
+      for (int j = 0; j < APS; ++j) a[j] = load_a(cn, sp * APS + j);
+      float kv = 0.f;
+      uint32_t sv = 0u;
+      if (sp == 0) { kv = load_k(cn); sv = load_scales(cn); }
+      consume(R[i & 1], buf, sp);
+      issue(R[i & 1], s0 + (st + 2 < n_sets ? st + 2 : st));
+#pragma unroll
+      for (int j = 0; j < APS; ++j) store_a(buf ^ 1, sp * APS + j, a[j]);
+      if (sp == 0) { store_k(buf ^ 1, kv); store_scales(buf ^ 1, sv); }
+      if (sp == SPC - 1) __syncthreads();
+    }
+  }
+
+  // ---- D element i of lane (n, kb): token 16 t + 4 kb + i, row n of the stream (columns: row 2 n + stream)
+  const float* UP = (const float*)(tile + lay.up_off) + t0;
+#pragma unroll
+  for (int t = 0; t < TT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int tok = 16 * t + 4 * kb + i;
+      if (tok < ntok) {
+        const float up = UP[tok];
+        float* o = out + (size_t)(g0 + tok) * N + R0;
+        if constexpr (PHASE == 0) {
+#pragma unroll
+          for (int r = 0; r < RBW; ++r) {
+            const float a = acc[r][t][i] * 16777216.0f * up;
+            float v;
+            if constexpr (NM == 2) v = a / (1.0f + __expf(-a)) * (acc[RBW + r][t][i] * 16777216.0f * up);
+            else v = fmaxf(a, 0.f);
+            o[r * 16 + n] = v;
+          }
+        } else if constexpr (COLS) {
+          *(float2*)(o + NS * n) = make_float2(acc[0][t][i] * 16777216.0f * up, acc[1][t][i] * 16777216.0f * up);
+        } else {
+#pragma unroll
+          for (int s = 0; s < NS; ++s) o[s * 16 + n] = acc[s][t][i] * 16777216.0f * up;
+        }
+      }
+    }
+}
+
+// Grid (row blocks x ranges of K, upper bound of the items); items: small_item.
+template <int NM, int PHASE, int ORDER>
+__global__ __launch_bounds__(kSWaves * 64, 4) void k_gemm_small(GemmArgs G, int n_rb, int split) {
+  extern __shared__ __attribute__((aligned(16))) char gsmem[];
+  if ((int)blockIdx.y >= *G.n_blocks) return;
+  const uint32_t it = ((const uint32_t*)G.blocks)[blockIdx.y];
+  const int e = (int)(it & 1023u), tb = (int)((it >> 10) & 0x3fffu), bits = (int)(it >> 24);
+  const int rb = (int)blockIdx.x % n_rb, ks = (int)blockIdx.x / n_rb;
+  const int chunks = (PHASE == 0 ? G.L.d_model : G.L.d_ff) / kSCols;
+  const int c0 = chunks * ks / split, c1 = chunks * (ks + 1) / split;
+  float* out = PHASE == 0 ? G.Hf : G.Y + (size_t)ks * (size_t)G.poff[G.L.n_experts] * (size_t)G.L.d_model;
+  SmallLds& S = *(SmallLds*)gsmem;
+  const DevExpert& ex = G.table[e];
+  if (bits == 2) small_gemm_body<2, NM, PHASE, ORDER>(G, ex, e, tb, rb, c0, c1, out, S);
+  else if (bits == 4) small_gemm_body<4, NM, PHASE, ORDER>(G, ex, e, tb, rb, c0, c1, out, S);
+  else small_gemm_body<8, NM, PHASE, ORDER>(G, ex, e, tb, rb, c0, c1, out, S);
+}
+
+// y[t][r] = sum_j gate[t][j] * sum_s Ypair[s][ginv[t*k + j]][r], s and j in order
 __global__ __launch_bounds__(256) void k_combine(const float* __restrict__ Ypair, const int32_t* __restrict__ ginv,
-                                                 const float* __restrict__ gate, int k, int d, float* __restrict__ y) {
-  const int t = blockIdx.x;
-  for (int r = threadIdx.x * 4; r < d; r += blockDim.x * 4) {
+                                                 const float* __restrict__ gate, int k, int d, int split, float* __restrict__ y) {
+  const int t = blockIdx.y, r = (int)(blockIdx.x * 256 + threadIdx.x) * 4;
+  const size_t stride = (size_t)gridDim.y * k * d;
+  if (r < d) {
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int j = 0; j < k; ++j) {
       const float g = gate[(size_t)t * k + j];
-      const float4 v = *(const float4*)(Ypair + (size_t)ginv[(size_t)t * k + j] * d + r);
+      const float* p = Ypair + (size_t)ginv[(size_t)t * k + j] * d + r;
+      float4 v = *(const float4*)p;
+      for (int s = 1; s < split; ++s) {
+        const float4 w = *(const float4*)(p + s * stride);
+        v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+      }
       a.x = fmaf(g, v.x, a.x); a.y = fmaf(g, v.y, a.y); a.z = fmaf(g, v.z, a.z); a.w = fmaf(g, v.w, a.w);
     }
     *(float4*)(y + (size_t)t * d + r) = a;
@@ -603,6 +1054,9 @@ hipError_t init_attrs_prefill() {
   if (hipError_t e = hipFuncSetAttribute((const void*)k_stage<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       e != hipSuccess)
     return e;
+  for (const void* kf : {(const void*)k_gemm_small<1, 0, SO_ROWS>, (const void*)k_gemm_small<2, 0, SO_ROWS>, (const void*)k_gemm_small<1, 0, SO_STREAM>,
+                         (const void*)k_gemm_small<2, 0, SO_STREAM>, (const void*)k_gemm_small<1, 1, SO_ROWS>, (const void*)k_gemm_small<1, 1, SO_COLUMNS>})
+    if (hipError_t e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SmallLds)); e != hipSuccess) return e;
   // the GEMMs' rings
   if (hipError_t e = hipFuncSetAttribute((const void*)k_gemm_q<2, 0, false, kWaves1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                          gemm_lds_bytes<0, false, kWaves1>());
@@ -651,6 +1105,19 @@ PrefillWs prefill_ws(const LayerDims& L, int64_t T) {
   return w;
 }
 
+// The list of k_gemm_small's items (one word each) starts behind the count of the items.
+constexpr int kSmallList = 64;
+// Calls of up to 72 pairs per expert take k_gemm_small. us, items of 32 / of 128 pairs, Mixtral layer of 8 experts, 170, 230, 300
+// and 350 tokens (42, 57, 75, 87 pairs per expert): 2 and 4 bits in stream 256 / 377, 307 / 391, 357 / 427, 405 / 479; 4 and 8
+// bits in rows 381 / 533, 451 / 541, 520 / 551, 586 / 557; 4 bits in columns 284 / 348, 336 / 373, 394 / 416, 444 / 494.
+bool small_items(const LayerDims& L, int64_t M, const PrefillWs& w) {
+  return M <= 72 * (int64_t)L.n_experts && L.group == 128 && L.group_out == 128 && L.d_model % kSCols == 0 && L.d_ff % kSCols == 0 &&
+         (size_t)(M / kSTok + L.n_experts) * 4 <= w.gpair - w.nblk - kSmallList;
+}
+// Ranges of d_ff of their GEMM 2: as many as fit into the place of h and of the pairs' outputs, up to four (117 tokens, 4 and 8
+// bits in rows: one range 376 us, two 354, three 346, four 339).
+int small_split(const LayerDims& L) { return std::min(4, std::min((L.d_ff + L.d_model) / L.d_model, L.d_ff / kSCols)); }
+
 hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void* x, int32_t T, const int32_t* idx,
                           const float* gate, char* ws, const PrefillWs& w, float* y, bool out_columns, bool in_stream,
                           hipStream_t st) {
@@ -665,14 +1132,35 @@ hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void
   char* XA = ws + w.xa;
   char* HA = ws + w.ha;
   float* Ypair = (float*)(ws + w.ypair);
-  hipLaunchKernelGGL(k_count_pairs, dim3(1), dim3(1024), 0, st, idx, M, L.n_experts, poff, boff, blocks, nblk);
-  hipLaunchKernelGGL(k_scatter_pairs, dim3(L.n_experts), dim3(256), 0, st, idx, M, poff, gpair, ginv, gexp);
+  const bool small = small_items(L, M, w);
+  if (small) blocks = (int2*)(ws + w.nblk + kSmallList);
+  if (M <= kPlanPairs && L.n_experts <= kPlanExperts) {
+    hipLaunchKernelGGL(k_plan_pairs, dim3(1), dim3(1024), 0, st, idx, M, L.n_experts, poff, boff, blocks, nblk, gpair, ginv, gexp, table, small ? kSTok : 0);
+  } else {
+    hipLaunchKernelGGL(k_count_pairs, dim3(1), dim3(1024), 0, st, idx, M, L.n_experts, poff, boff, blocks, nblk, table, small ? kSTok : 0);
+    hipLaunchKernelGGL(k_scatter_pairs, dim3(L.n_experts), dim3(256), 0, st, idx, M, poff, gpair, ginv, gexp);
+  }
   float* Hf = (float*)(ws + w.hf);
   auto stage_lds = [](int cols) { return (size_t)cols * 2 + (size_t)cols / 16 * 4 + 64; };
+  const unsigned h_threads = M <= 1024 ? 1024 : 256;
   const unsigned stage_grid = (unsigned)((M + 7) / 8 * 8);
   hipLaunchKernelGGL(k_stage<false>, dim3(stage_grid), dim3(256), stage_lds(L.d_model), st, L, table, x, gpair, gexp,
                      poff, boff, XA, M);
   GemmArgs G{L, table, blocks, nblk, poff, boff, XA, Hf, Ypair};
+  if (small) {
+    const unsigned items = (unsigned)std::min<int64_t>(M, M / kSTok + L.n_experts);
+    const bool sw = L.act == MOEQ_ACT_SWIGLU;
+    const int n_rb = L.d_ff / (kSWaves * (sw ? kSRows / 2 : kSRows)), n_rb2 = L.d_model / (kSWaves * kSRows), split = small_split(L);
+    auto kin = in_stream ? (sw ? k_gemm_small<2, 0, SO_STREAM> : k_gemm_small<1, 0, SO_STREAM>) : (sw ? k_gemm_small<2, 0, SO_ROWS> : k_gemm_small<1, 0, SO_ROWS>);
+    hipLaunchKernelGGL(kin, dim3(n_rb, items), dim3(kSWaves * 64), sizeof(SmallLds), st, G, n_rb, 1);
+    hipLaunchKernelGGL(k_stage<true>, dim3(stage_grid), dim3(h_threads), stage_lds(L.d_ff), st, L, table, (const void*)Hf, gpair, gexp, poff, boff, HA, M);
+    G.A = HA;
+    G.Y = Hf;                      // h is staged: its place and the pairs' outputs behind it take the partial outputs
+    auto kout = out_columns ? k_gemm_small<1, 1, SO_COLUMNS> : k_gemm_small<1, 1, SO_ROWS>;
+    hipLaunchKernelGGL(kout, dim3(n_rb2 * split, items), dim3(kSWaves * 64), sizeof(SmallLds), st, G, n_rb2, split);
+    hipLaunchKernelGGL(k_combine, dim3((L.d_model + 1023) / 1024, T), dim3(256), 0, st, Hf, ginv, gate, L.top_k, L.d_model, split, y);
+    return hipGetLastError();
+  }
   const unsigned nb = (unsigned)w.max_blocks;
   constexpr int lds1 = gemm_lds_bytes<0, false, kWaves1>(), lds2 = gemm_lds_bytes<1, false, kWaves2>(),
                 lds2c = gemm_lds_bytes<1, true, 8>();
@@ -690,7 +1178,7 @@ hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void
     if (in_stream) hipLaunchKernelGGL((k_gemm_q<1, 0, false, kWaves1, true>), grid, block, lds1s, st, G, n_rb);
     else hipLaunchKernelGGL((k_gemm_q<1, 0, false, kWaves1>), grid, block, lds1, st, G, n_rb);
   }
-  hipLaunchKernelGGL(k_stage<true>, dim3(stage_grid), dim3(256), stage_lds(L.d_ff), st, L, table, (const void*)Hf, gpair,
+  hipLaunchKernelGGL(k_stage<true>, dim3(stage_grid), dim3(h_threads), stage_lds(L.d_ff), st, L, table, (const void*)Hf, gpair,
                      gexp, poff, boff, HA, M);
   G.A = HA;
   if (out_columns) {
@@ -702,7 +1190,7 @@ hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void
     const int n_rb = (L.d_model + BN - 1) / BN;
     hipLaunchKernelGGL((k_gemm_q<1, 1, false, kWaves2>), dim3((unsigned)n_rb * nb), dim3(kWaves2 * 64), lds2, st, G, n_rb);
   }
-  hipLaunchKernelGGL(k_combine, dim3(T), dim3(256), 0, st, Ypair, ginv, gate, L.top_k, L.d_model, y);
+  hipLaunchKernelGGL(k_combine, dim3((L.d_model + 1023) / 1024, T), dim3(256), 0, st, Ypair, ginv, gate, L.top_k, L.d_model, 1, y);
   return hipGetLastError();
 }
 

@@ -1,13 +1,53 @@
-"""GPU parity of the kernel that routes calls of many tokens, through the C ABI against the oracle."""
+"""GPU parity of prompts whose experts hold a few dozen pairs each (GEMMs on items of 32 pairs), and of the kernels that route
+and group the tokens of such calls, through the C ABI against the oracle."""
+import gen
 import numpy as np
 import oracle
 import paper_2308_14352_amd as moeq
 import pytest
 import torch
-from helpers import pack_expert_gpu
+from helpers import build_layer_pair, pack_expert_gpu, rel_err
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
+# Activations enter the multipliers rounded to 11 bits, twice: 2.4e-4 each of the output's scale where the signs are random,
+# worst single elements of hundreds of tokens three to four times their root sum.
+TOL = 2e-3
+
+
+@pytest.mark.parametrize("base,d,f,layout", [
+    ("c5", 512, 512, "canonical"),      # one chunk, one range of W_out
+    ("c5", 1024, 1536, "columns"),      # an odd number of chunks
+    ("c1", 512, 1536, "canonical"),     # ReLU: four rows of a matrix where SwiGLU has two of both
+    ("c1", 512, 2048, "columns"),       # ranges of W_out
+    ("c5", 4096, 1024, "stream"),
+    ("c1", 4096, 512, "stream"),
+])
+@pytest.mark.parametrize("bits", (2, 4, 8))
+def test_items_at_their_edges(base, d, f, layout, bits):
+    """0, 1, 15..17, 31..33, 63..65 and 129 pairs per expert, and an index outside [0, E)."""
+    counts = [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 129]
+    E = len(counts)
+    cfg = gen.tiny_config(base, d, f, n_experts=E, n_layers=1, group=128)
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits] * E, columns=layout == "columns", stream=layout == "stream")
+    pairs = np.concatenate([np.full(c, e, dtype=np.int32) for e, c in enumerate(counts)])
+    rng = np.random.default_rng(7 + bits)
+    rng.shuffle(pairs)
+    k = cfg.top_k
+    pairs = np.concatenate([pairs, np.full(k - len(pairs) % k, E, dtype=np.int32)])
+    idx = pairs.reshape(-1, k)
+    T = idx.shape[0]
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    gate = rng.uniform(0.1, 1.0, size=(T, k)).astype(np.float32)
+    args = layer, x, torch.from_numpy(idx).to(DEV), torch.from_numpy(gate).to(DEV)
+    y = moeq.moe_layer_forward_routed(*args)
+    again = moeq.moe_layer_forward_routed(*args)
+    torch.cuda.synchronize()
+    assert torch.equal(y, again)
+    y_ref = oracle.layer_forward_routed(orc_experts, d, f, 128, int(cfg.swiglu), k, x.float().cpu().numpy(), idx, gate)
+    live = np.abs(y_ref).max(axis=1) > 0
+    assert rel_err(y.cpu().numpy()[live], y_ref[live]).max() < TOL
+    assert not y.cpu().numpy()[~live].any()
 
 
 @pytest.mark.parametrize("d,f,E,k,x_dtype,T", [
