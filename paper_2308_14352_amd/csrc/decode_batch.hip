@@ -369,6 +369,11 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
   __syncthreads();          // every wavefront is done with the previous item's operands
   // the item's 16 activation rows into LDS, operand by operand (row m: pair m % TOK, part m / TOK; absent pairs repeat the
   // first one, their results are dropped)
+  // (their factors are requested first and stored behind the first weights' requests, which wait for nothing)
+  const int sg = threadIdx.x >> 4, sm = threadIdx.x & 15;         // 512 threads = 32 groups x 16 rows
+  const size_t sat = (size_t)(item.pair[sm % TOK < item.n ? sm % TOK : 0] / G.k) * kBGroups + sg;
+  const float sxs = G.XS[sat];
+  const int32_t sxsum = G.XSUM[sat * PARTS + sm / TOK];
   {
     const int pm = item.pair[n % TOK < item.n ? n % TOK : 0];
     const uint8_t* src = xq + (size_t)(pm / G.k) * (PARTS * 2 * kBD) + (n / TOK) * 128 + kb * 16;
@@ -378,12 +383,6 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
       const int o = wave + i * kBWaves;              // (operand op of a group, digit) = (o / 2, o % 2)
       dma16(src + (o >> 1) * (PARTS * 128) + (o & 1) * 64, a0 + (uint32_t)o * 1024u);
     }
-  }
-  {
-    const int g = threadIdx.x >> 4, m = threadIdx.x & 15;         // 512 threads = 32 groups x 16 rows
-    const size_t at = (size_t)(item.pair[m % TOK < item.n ? m % TOK : 0] / G.k) * kBGroups + g;
-    S.XS[g][m] = G.XS[at] * (m < TOK ? 1.f : 65536.f);
-    S.SX[g][m] = -code_offset<BITS>() * G.XSUM[at * PARTS + m / TOK];
   }
   const int total = (u1 - u0) * Set::SPU;
   auto issue = [&](Set& R, int s) __attribute__((always_inline)) {
@@ -521,6 +520,8 @@ __device__ __forceinline__ void batch_in_units(const BatchArgs& G, BatchInLds& S
   Set R0, R1;
   issue(R0, 0);
   issue(R1, 1);
+  S.XS[sg][sm] = sxs * (sm < TOK ? 1.f : 65536.f);
+  S.SX[sg][sm] = -code_offset<BITS>() * sxsum;
   stage_wait<16>();                            // the operands have landed; the sixteen 16-byte loads behind them stay in flight
   __syncthreads();
   cur = read_a(0);
@@ -623,24 +624,29 @@ __global__ __launch_bounds__(512) void k_batch_in(BatchArgs G) {
     if (threadIdx.x == 0) *G.n_items = n_items;
   }
   const int NU = G.L.d_ff / kBGroup;
-  int64_t total = 0;
-  for (int i = 0; i < n_items; ++i) total += 8 * S.lists.items[i].bits + 1;
-  total *= NU;
-  const int64_t lo = total * blockIdx.x / gridDim.x, hi = total * (blockIdx.x + 1) / gridDim.x;
-  int64_t base = 0;
-  for (int i = 0; i < n_items; ++i) {
+  // 32 bits and a division only for the items the range meets: 64-bit ones for every item were 1-2 us ahead of the first load.
+  // (256 items of weight 65: no overflow below d_ff 2^24)
+  uint32_t total = 0;
+  for (int i = 0; i < n_items; ++i) total += 8u * (uint32_t)S.lists.items[i].bits + 1u;
+  total *= (uint32_t)NU;
+  const uint32_t whole = total / gridDim.x, rest = total % gridDim.x;        // total * blockIdx.x / gridDim.x
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(whole * blockIdx.x + rest * blockIdx.x / gridDim.x);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(whole * (blockIdx.x + 1) + rest * (blockIdx.x + 1) / gridDim.x);
+  uint32_t base = 0, end = 0;
+  for (int i = 0; i < n_items && base < hi; ++i, base = end) {
     const int bits = __builtin_amdgcn_readfirstlane(S.lists.items[i].bits);
-    const int64_t c = 8 * bits + 1;
+    const uint32_t c = 8u * (uint32_t)bits + 1u;
+    end = base + c * (uint32_t)NU;
+    if (end <= lo) continue;
     // units whose start weight lies in [lo, hi)
-    const int64_t a = lo > base ? (lo - base + c - 1) / c : 0, b = hi > base ? (hi - base + c - 1) / c : 0;
-    const int u0 = __builtin_amdgcn_readfirstlane((int)(a < NU ? a : NU)), u1 = __builtin_amdgcn_readfirstlane((int)(b < NU ? b : NU));
+    const uint32_t a = lo > base ? (lo - base + c - 1) / c : 0, b = (hi - base + c - 1) / c;
+    const int u0 = __builtin_amdgcn_readfirstlane((int)min(a, (uint32_t)NU)), u1 = __builtin_amdgcn_readfirstlane((int)min(b, (uint32_t)NU));
     if (u0 < u1) {
       const BatchItem& item = S.lists.items[i];
       if (bits == 2) batch_in_units<2, NM, SWIGLU, STREAM>(G, S, item, u0, u1);
       else if (bits == 4) batch_in_units<4, NM, SWIGLU, STREAM>(G, S, item, u0, u1);
       else batch_in_units<8, NM, SWIGLU, STREAM>(G, S, item, u0, u1);
     }
-    base += c * NU;
   }
 }
 
