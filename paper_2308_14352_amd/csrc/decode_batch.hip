@@ -27,8 +27,8 @@
 //
 // What bounds it: the bytes of the distinct experts. With one workgroup per (slice, token), as for a single token, a
 // call of T tokens pays T times the unpack arithmetic. Mixtral layer (8 experts, 2 / 4 bits, d_ff 14336): 8 tokens
-// 230 -> 130-150 us, 23 tokens 640 -> 157 us (550 MB: 3.5 TB/s over the whole call; k_batch_in 100, k_batch_out 47, the two
-// small kernels 6.5 and 6); canonical layout 204 -> 170 and 23 tokens 846 -> 180. Where grouping pays: batch_pays (api.cpp).
+// 230 -> 128-146 us, 23 tokens 640 -> 150 us (550 MB: 3.7 TB/s over the whole call; k_batch_in 96, k_batch_out 45-47, the two
+// small kernels 6.5 and 5); canonical layout 204 -> 170 and 23 tokens 846 -> 180. Where grouping pays: batch_pays (api.cpp).
 #include <hip/hip_ext.h>
 
 #include "decode_core.h"
@@ -668,20 +668,30 @@ struct BatchOutLds {
   int32_t SX[kBOutGroups][2][kBRows];
 };
 
+// A workgroup takes `blocks` blocks of 256 rows with the same activations, its requests running on from one to the next. What
+// lies past its end asks for a cached line: the next chunk's words, requested and dropped, were half as many bytes again at 4
+// bits. W_out in columns is read with the non-temporal hint (4 bits, d_ff 14336, 23 tokens: 64 us at first, 56 without it, 54
+// with it, 4.5 TB/s; the loads alone take 51 without it, the arithmetic alone 36; 8 bits 104 -> 96; 2 bits 38 -> 44, bound by
+// its arithmetic, which more workgroups hid better; 2 and 4 bits mixed 50 -> 45-47).
 // Canonical rows: the wavefront's 64 rows are four blocks of 16; lane (n, kb) loads 16-byte piece 4 j + kb of row 16 i + n
 // (64 consecutive bytes of 16 rows: one scale group at 4 bits, two at 2, half of one at 8), operand i belongs to block i.
 template <int BITS, bool COLS, bool STREAM>
-__device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, const BatchItem& item) {
+__device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, const BatchItem& item, int blocks) {
   using Set = BatchOutSet<BITS>;
   constexpr int TOK = batch_tok(STREAM), PARTS = batch_parts(STREAM);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, kb = lane >> 4;
   const int NG = G.L.d_ff / kBGroup;
   const int g0 = blockIdx.y * kBOutGroups, ng = min(kBOutGroups, NG - g0);
-  const int r0 = blockIdx.x * kBOutRows + wave * 64 + (COLS ? 4 * n : n);      // operand i: row r0 + i, or r0 + 16 i
+  const int r0 = blockIdx.x * blocks * kBOutRows + wave * 64 + (COLS ? 4 * n : n);   // of the first block: operand i is row r0 + i, or r0 + 16 i
   const DevExpert* ex = G.table + item.e;
   const uint8_t* q = uniform_ptr(ex->q_out);
   const uint8_t* sc = (const uint8_t*)uniform_ptr(ex->s_out);
+  // 256 threads = 8 groups x 2 halves x 16 rows: the operands' factors, stored behind the first weights' requests
+  const int fg = threadIdx.x >> 5, fhalf = (threadIdx.x >> 4) & 1, fm = threadIdx.x & 15;
+  const size_t fat = ((size_t)item.pair[fm % TOK < item.n ? fm % TOK : 0] * NG + min(g0 + fg, NG - 1)) * 2;
+  const float fxs = G.HS[fat + fhalf];
+  const int32_t fsum = G.HSUM[fat + (STREAM ? fhalf : fm / TOK)];
   {
     const int pm = item.pair[n % TOK < item.n ? n % TOK : 0];
     const uint8_t* src = G.HQ + ((size_t)pm * (size_t)(2 * G.L.d_ff) + (size_t)g0 * 256) * PARTS + (n / TOK) * 128 + kb * 16;
@@ -691,54 +701,58 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
       if (o < ng * 4) dma16(src + (o >> 1) * (PARTS * 128) + (o & 1) * 64, a0 + (uint32_t)o * 1024u);
     }
   }
-  {
-    const int g = threadIdx.x >> 5, half = (threadIdx.x >> 4) & 1, m = threadIdx.x & 15;      // 256 threads = 8 groups x 2 x 16 rows
-    if (g < ng) {
-      const size_t at = ((size_t)item.pair[m % TOK < item.n ? m % TOK : 0] * NG + g0 + g) * 2;
-      S.XS[g][half][m] = G.HS[at + half] * (m < TOK ? 1.f : 65536.f);
-      S.SX[g][half][m] = -code_offset<BITS>() * G.HSUM[at + (STREAM ? half : m / TOK)];
-    }
-  }
-  const int n_sets = (ng + Set::GS - 1) / Set::GS;
+  // sets of a block, an even number (the two register sets take turns); one past the chunk's groups is loaded from its last group
+  const int n_sets = ((ng + Set::GS - 1) / Set::GS + 1) & ~1;
   const uint32_t col = (uint32_t)kBD * 4u;         // bytes of a word column
   const uint32_t lane_off = (uint32_t)kb * col + (uint32_t)r0 * 4u;
-  const uint32_t row_bytes = (uint32_t)G.L.d_ff * BITS / 8u, pieces = row_bytes / 16u;
-  auto issue = [&](Set& R, int s) __attribute__((always_inline)) {
+  const uint32_t row_bytes = (uint32_t)G.L.d_ff * BITS / 8u;
+  // canonical rows: lane (n, kb) holds the chunk's scales of row 16 kb + n, two groups to a register
+  uint32_t srow[kBOutGroups / 2] = {}, snext[kBOutGroups / 2] = {};
+  int is = 0, ib = 0;                              // set and block the next request is for
+  auto issue = [&](Set& R) __attribute__((always_inline)) {
+    const bool live = ib < blocks;                 // past the end: cached bytes, so that every path issues the same loads
+    const uint32_t rows = (uint32_t)ib * kBOutRows;
+    const uint8_t* dead = G.HQ + lane * 16;
     if constexpr (COLS) {
 #pragma unroll
       for (int gi = 0; gi < Set::GS; ++gi) {
-        const int g = min(g0 + s * Set::GS + gi, NG - 1);       // groups past the end: loaded again, not used
-        const uint8_t* qg = q + (size_t)g * (4 * BITS) * col;
+        const int g = min(g0 + is * Set::GS + gi, g0 + ng - 1);
+        const uint8_t* qg = q + (size_t)g * (4 * BITS) * col + (size_t)rows * 4u;
 #pragma unroll
-        for (int j = 0; j < Set::LPG; ++j) R.t[gi * Set::LPG + j] = gload_u32x4(qg + (size_t)(4 * j) * col + lane_off);
-        R.s[gi] = gload_u32x2(sc + (size_t)g * (kBD * 2) + (uint32_t)r0 * 2u);
+        for (int j = 0; j < Set::LPG; ++j) R.t[gi * Set::LPG + j] = load_stream16(live ? qg + (size_t)(4 * j) * col + lane_off : dead);
+        R.s[gi] = gload_u32x2(live ? sc + (size_t)g * (kBD * 2) + (rows + (uint32_t)r0) * 2u : dead);
       }
     } else {
-      // 64-byte steps of the rows: a set is two of them for the four blocks
-      const uint32_t step0 = (uint32_t)g0 * BITS / 4u + (uint32_t)s * 2u;
+      // 64-byte steps of the rows: a set is two of them for the four blocks of 16
+      const uint32_t step0 = (uint32_t)g0 * BITS / 4u + (uint32_t)is * 2u, last = (uint32_t)(g0 + ng) * BITS - 1u;
 #pragma unroll
       for (int st = 0; st < 2; ++st)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          R.t[st * 4 + i] = gload_u32x4(q + ((size_t)(uint32_t)(r0 + 16 * i) * row_bytes + min((step0 + st) * 4u + kb, pieces - 1u) * 16u));
+          R.t[st * 4 + i] = gload_u32x4(live ? q + ((size_t)(rows + (uint32_t)(r0 + 16 * i)) * row_bytes + min((step0 + st) * 4u + kb, last) * 16u) : dead);
+      if (is == 0) {
+        const uint32_t row = live ? rows + (uint32_t)(blockIdx.x * blocks * kBOutRows + wave * 64 + 16 * kb + n) : 0u;
+#pragma unroll
+        for (int g = 0; g < kBOutGroups; g += 2) {
+          const uint32_t a = gload_u16(sc + ((size_t)row * NG + min(g0 + g, NG - 1)) * 2), b = gload_u16(sc + ((size_t)row * NG + min(g0 + g + 1, NG - 1)) * 2);
+          snext[g / 2] = a | b << 16;
+        }
+      }
     }
+    if (++is == n_sets) { is = 0; ++ib; }
   };
-  // canonical rows: lane (n, kb) holds the chunk's scales of row 16 kb + n, two groups to a register
-  uint32_t srow[kBOutGroups / 2];
-  if constexpr (!COLS) {
-    const int row = blockIdx.x * kBOutRows + wave * 64 + 16 * kb + n;
-#pragma unroll
-    for (int g = 0; g < kBOutGroups; g += 2) {
-      const uint32_t a = gload_u16(sc + ((size_t)row * NG + min(g0 + g, NG - 1)) * 2), b = gload_u16(sc + ((size_t)row * NG + min(g0 + g + 1, NG - 1)) * 2);
-      srow[g / 2] = a | b << 16;
-    }
-  }
   float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
   auto consume = [&](const Set& R, int s) __attribute__((always_inline)) {
+    if (s == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+      if constexpr (!COLS) {
+#pragma unroll
+        for (int g = 0; g < kBOutGroups / 2; ++g) srow[g] = snext[g];
+      }
+    }
 #pragma unroll
     for (int gi = 0; gi < Set::GS; ++gi) {
       const int g = s * Set::GS + gi;
@@ -809,70 +823,90 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
     }
   };
   Set R0, R1;
-  issue(R0, 0);
-  issue(R1, 1);
+  issue(R0);
+  issue(R1);
+  S.XS[fg][fhalf][fm] = fxs * (fm < TOK ? 1.f : 65536.f);
+  S.SX[fg][fhalf][fm] = -code_offset<BITS>() * fsum;
   stage_wait<16>();
   __syncthreads();
-  for (int s = 0; s < n_sets; s += 2) {
-    consume(R0, s);
-    issue(R0, s + 2);
-    consume(R1, s + 1);
-    issue(R1, s + 3);
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if constexpr (PARTS == 2) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i][j] += __shfl_xor(acc[i][j], 32);
+  for (int blk = 0; blk < blocks; ++blk) {
+    for (int s = 0; s < n_sets; s += 2) {
+      consume(R0, s);
+      issue(R0);
+      consume(R1, s + 1);
+      issue(R1);
     }
-    const int m = 4 * kb + j;                      // (the lanes of the high parts' rows, 8 .. 15, write nothing: item.n <= TOK)
-    if (m < item.n) {
-      float* o = G.part + ((size_t)blockIdx.y * (size_t)(G.T * G.k) + item.pair[m]) * kBD + r0;
-      if constexpr (COLS) {
-        *(float4*)o = make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
-      } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[16 * i] = acc[i][j];
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (PARTS == 2) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][j] += __shfl_xor(acc[i][j], 32);
+      }
+      const int m = 4 * kb + j;                    // (the lanes of the high parts' rows, 8 .. 15, write nothing: item.n <= TOK)
+      if (m < item.n) {
+        float* o = G.part + ((size_t)blockIdx.y * (size_t)(G.T * G.k) + item.pair[m]) * kBD + blk * kBOutRows + r0;
+        if constexpr (COLS) {
+          *(float4*)o = make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[16 * i] = acc[i][j];
+        }
       }
     }
   }
 }
 
-// Grid (row chunks, chunks of d_ff, upper bound of the items).
+// Grid (d_model / (blocks * 256), chunks of d_ff, upper bound of the items).
 template <bool COLS, bool STREAM>
-__global__ __launch_bounds__(256) void k_batch_out(BatchArgs G) {
+__global__ __launch_bounds__(256) void k_batch_out(BatchArgs G, int blocks) {
   __shared__ BatchOutLds S;
   __shared__ BatchItem item;
   if ((int)blockIdx.z >= *G.n_items) return;
   if (threadIdx.x < 2) ((uint4*)&item)[threadIdx.x] = ((const uint4*)(G.items + blockIdx.z))[threadIdx.x];
   __syncthreads();
   const int bits = __builtin_amdgcn_readfirstlane(item.bits);
-  if (bits == 2) batch_out<2, COLS, STREAM>(G, S, item);
-  else if (bits == 4) batch_out<4, COLS, STREAM>(G, S, item);
-  else batch_out<8, COLS, STREAM>(G, S, item);
+  if (bits == 2) batch_out<2, COLS, STREAM>(G, S, item, blocks);
+  else if (bits == 4) batch_out<4, COLS, STREAM>(G, S, item, blocks);
+  else batch_out<8, COLS, STREAM>(G, S, item, blocks);
 }
 
-// y[t][r] (+)= sum_j gate[t][j] * sum_c part[c][t k + j][r], chunks and choices in order. gate null: 1.
-__global__ __launch_bounds__(256) void k_batch_combine(const float* __restrict__ part, const float* __restrict__ gate,
+// y[t][r] (+)= sum_j gate[t][j] * sum_c part[c][t k + j][r], chunks and choices in order. gate null: 1. Wavefront j sums the
+// chunks of choice j, sixteen requested together; the first one adds the choices.
+__global__ __launch_bounds__(512) void k_batch_combine(const float* __restrict__ part, const float* __restrict__ gate,
                                                        int n_chunks, int T, int k, int accumulate, float* __restrict__ y) {
-  const int t = blockIdx.y, r = (blockIdx.x * 256 + threadIdx.x) * 4;
+  __shared__ float4 sums[8][64];
+  const int t = blockIdx.y, lane = threadIdx.x & 63, j = threadIdx.x >> 6, r = (blockIdx.x * 64 + lane) * 4;
+  const float* p = part + (size_t)(t * k + j) * kBD + r;
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int c0 = 0; c0 < n_chunks; c0 += 16) {
+    float4 w[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = *(const float4*)(p + (size_t)min(c0 + i, n_chunks - 1) * T * k * kBD);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const bool in = c0 + i < n_chunks;
+      a.x += in ? w[i].x : 0.f; a.y += in ? w[i].y : 0.f; a.z += in ? w[i].z : 0.f; a.w += in ? w[i].w : 0.f;
+    }
+  }
+  sums[j][lane] = a;
+  __syncthreads();
+  if (j) return;
   float* o = y + (size_t)t * kBD + r;
   float v[4] = {0.f, 0.f, 0.f, 0.f};
   if (accumulate)
     for (int i = 0; i < 4; ++i) v[i] = o[i];
-  for (int j = 0; j < k; ++j) {
-    const float* p = part + (size_t)(t * k + j) * kBD + r;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-    for (int c = 0; c < n_chunks; ++c) {
-      const float4 w = *(const float4*)(p + (size_t)c * T * k * kBD);
-      a.x += w.x; a.y += w.y; a.z += w.z; a.w += w.w;
-    }
-    const float g = gate ? gate[(size_t)t * k + j] : 1.0f;
-    v[0] = fmaf(g, a.x, v[0]); v[1] = fmaf(g, a.y, v[1]); v[2] = fmaf(g, a.z, v[2]); v[3] = fmaf(g, a.w, v[3]);
+  for (int q = 0; q < k; ++q) {
+    const float g = gate ? gate[(size_t)t * k + q] : 1.0f;
+    const float4 w = sums[q][lane];
+    v[0] = fmaf(g, w.x, v[0]); v[1] = fmaf(g, w.y, v[1]); v[2] = fmaf(g, w.z, v[2]); v[3] = fmaf(g, w.w, v[3]);
   }
   for (int i = 0; i < 4; ++i) o[i] = v[i];
 }
+
+// Blocks of 256 rows that a k_batch_out workgroup takes one after the other, for so many (chunk, item) pairs of a call: two
+// where that leaves more workgroups than are resident (three per compute unit). Mixtral layer (2 and 4 bits, stream), one / two /
+// four blocks, us: d_ff 14336, 6 tokens 37.0 / 35.6 / 44, 23 tokens 50.2 / 45.4 / 47; d_ff 4096, 23 tokens 17.4 / 17.8 / 26.7.
+int out_blocks(int64_t pairs) { return pairs * (kBD / kBOutRows / 2) > 768 ? 2 : 1; }
 
 int batch_cus() {
   static const int cus = [] {
@@ -940,9 +974,10 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
   prof_stop(prof, MOEQ_KERNEL_FFN_IN, st);
   prof_start(prof, MOEQ_KERNEL_FFN_OUT, st);
   auto kout = in_stream ? k_batch_out<true, true> : out_columns ? k_batch_out<true, false> : k_batch_out<false, false>;
-  hipLaunchKernelGGL(kout, dim3(kBD / kBOutRows, chunks, max_items), dim3(256), 0, st, G);
+  const int blocks = out_blocks((int64_t)chunks * max_items);
+  hipLaunchKernelGGL(kout, dim3(kBD / kBOutRows / blocks, chunks, max_items), dim3(256), 0, st, G, blocks);
   prof_stop(prof, MOEQ_KERNEL_FUSED, st);
-  hipLaunchKernelGGL(k_batch_combine, dim3(kBD / 1024, T), dim3(256), 0, st, G.part, gate_out, chunks, T, k, accumulate, y);
+  hipLaunchKernelGGL(k_batch_combine, dim3(kBD / 256, T), dim3(64 * k), 0, st, G.part, gate_out, chunks, T, k, accumulate, y);
   prof_stop(prof, MOEQ_KERNEL_FFN_OUT, st);
   return hipGetLastError();
 }

@@ -82,6 +82,22 @@ def test_grouped_single_expert_call(bits, f, T, layout):
     assert rel_err((y_acc - y0).cpu().numpy(), ref).max() < TOL + 1e-5
 
 
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("layout,f", [("stream", 5504), ("canonical", 2432), ("columns", 2432)])
+def test_output_blocks_taken_in_turn(bits, layout, f):
+    """Enough items and chunks that a workgroup of the output kernel takes two blocks of rows; a last chunk of three groups."""
+    cfg = replace(gen.tiny_config("c4", 4096, f, n_experts=2, n_layers=1, group=128), x_dtype="f32")
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits, bits], columns=layout == "columns", stream=layout == "stream")
+    x = gen.hidden(cfg, 0, 0, 256, DEV)
+    gate = torch.linspace(0.2, 1.1, 256, device=DEV)
+    y = moeq.moe_expert_ffn_q(layer, 1, x, gate=gate)
+    few = moeq.moe_expert_ffn_q(layer, 1, x[:20], gate=gate[:20])
+    torch.cuda.synchronize()
+    assert torch.equal(y[:20], few)
+    y_ref = oracle.expert_ffn(orc_experts[1], 4096, f, cfg.group, int(cfg.swiglu), x[:20].cpu().numpy())
+    assert rel_err(few.cpu().numpy(), gate[:20].cpu().numpy()[:, None] * y_ref).max() < TOL
+
+
 def test_grouped_call_with_the_ungrouped_workspace():
     """A workspace that only the ungrouped form of a call fits is still taken (a narrow layer with many choices)."""
     cfg = replace(gen.tiny_config("c4", 4096, 128, n_experts=8, n_layers=1, group=128), top_k=8, x_dtype="f32")
