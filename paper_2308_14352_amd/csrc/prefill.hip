@@ -58,32 +58,40 @@ __host__ __device__ inline Staged staged_layout(int K) {
 // A work item of k_gemm_small: expert, block of its pairs, bitwidth of the expert.
 __device__ __forceinline__ uint32_t small_item(int e, int tb, int bits) { return (uint32_t)e | (uint32_t)tb << 10 | (uint32_t)bits << 24; }
 
+// Histogram of the pairs, offsets of every expert's pairs and token tiles, and the list of work items, by one workgroup with a
+// thread per expert (E <= 1024). small: pairs of an item of k_gemm_small, or 0. A thread that walks all experts, as here before,
+// pays an LDS round trip per expert (and for small_item a load of the bitwidth per expert that holds pairs): a call of 128 tokens
+// on 128 / 1024 experts of 1024 x 512 took 90 / 235 us, now 55 / 82.
 __global__ __launch_bounds__(1024) void k_count_pairs(const int32_t* __restrict__ idx, int M, int E,
                                                       int32_t* __restrict__ poff, int32_t* __restrict__ boff,
                                                       int2* __restrict__ blocks, int32_t* __restrict__ n_blocks,
                                                       const DevExpert* __restrict__ table, int small) {
-  __shared__ int h[1024];
-  for (int e = threadIdx.x; e < E; e += blockDim.x) h[e] = 0;
+  __shared__ int h[1024], sums[16][3];
+  const int e = threadIdx.x, lane = e & 63, wave = e >> 6;
+  const int bits = small && e < E ? table[e].bits : 0;
+  h[e] = 0;
   __syncthreads();
-  for (int p = threadIdx.x; p < M; p += blockDim.x) atomicAdd(&h[min(max(idx[p], 0), E - 1)], 1);
+  for (int p = threadIdx.x; p < M; p += 1024) atomicAdd(&h[min(max(idx[p], 0), E - 1)], 1);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int off = 0, nb = 0, nt = 0;
-    for (int e = 0; e < E; ++e) {
-      poff[e] = off;
-      boff[e] = nt;                 // token tile tb of expert e is tile number boff[e] + tb
-      const int c = h[e];
-      if (small) {
-        for (int tb = 0; tb * small < c; ++tb) ((uint32_t*)blocks)[nb++] = small_item(e, tb, table[e].bits);
-      } else {
-        for (int tb = 0; tb * (kTB * kItemTiles) < c; ++tb) blocks[nb++] = make_int2(e, tb);
-      }
-      nt += (c + kTB - 1) / kTB;
-      off += c;
-    }
-    poff[E] = off;
-    *n_blocks = nb;
+  const int c = h[e], tiles = (c + kTB - 1) / kTB, per = small ? small : kTB * kItemTiles, items = (c + per - 1) / per;
+  int po = c, to = tiles, io = items;              // inclusive sums over the experts
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int a = __shfl_up(po, d), b = __shfl_up(to, d), f = __shfl_up(io, d);
+    if (lane >= d) { po += a; to += b; io += f; }
   }
+  if (lane == 63) { sums[wave][0] = po; sums[wave][1] = to; sums[wave][2] = io; }
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) { po += sums[w][0]; to += sums[w][1]; io += sums[w][2]; }
+  if (e < E) {
+    poff[e] = po - c;
+    boff[e] = to - tiles;           // token tile tb of expert e is tile number boff[e] + tb
+    for (int tb = 0, at = io - items; tb < items; ++tb, ++at) {
+      if (small) ((uint32_t*)blocks)[at] = small_item(e, tb, bits);
+      else blocks[at] = make_int2(e, tb);
+    }
+  }
+  if (e == E - 1) { poff[E] = po; *n_blocks = io; }
 }
 
 // Workgroup e writes the pairs routed to expert e, in increasing pair order, behind poff[e].

@@ -50,6 +50,36 @@ def test_items_at_their_edges(base, d, f, layout, bits):
     assert not y.cpu().numpy()[~live].any()
 
 
+@pytest.mark.parametrize("base,E,T", [
+    ("c5", 97, 64),        # more experts than one workgroup plans, 32-pair items
+    ("c5", 64, 2048),      # 4096 pairs on 64 experts: the most that one workgroup plans
+    ("c5", 64, 2049),      # ... and two pairs more
+    ("c5", 3, 2049),       # the same with items of 128 pairs
+    ("c1", 70, 5100),      # more experts, items of 128 pairs, one choice a token
+])
+def test_planning_of_many_pairs_and_experts(base, E, T):
+    """Pairs grouped by one workgroup (up to 4096 pairs, 64 experts) or by two kernels, for either size of item."""
+    d = f = 512
+    cfg = gen.tiny_config(base, d, f, n_experts=E, n_layers=1, group=128)
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [(2, 4, 8)[e % 3] for e in range(E)])
+    rng = np.random.default_rng(E + T)
+    k = cfg.top_k
+    idx = rng.integers(0, E, size=(T, k)).astype(np.int32)
+    idx[: T // 3, 0] = 1                                     # an expert with a third of the tokens
+    idx[5, 0], idx[T - 1, k - 1] = -1, E                     # outside [0, E): weighted 0
+    gate = rng.uniform(0.1, 1.0, size=(T, k)).astype(np.float32)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    y = moeq.moe_layer_forward_routed(layer, x, torch.from_numpy(idx).to(DEV), torch.from_numpy(gate).to(DEV))
+    torch.cuda.synchronize()
+    some = np.unique(np.concatenate([[5, T - 1], rng.integers(0, T, size=300)]))
+    y_ref = oracle.layer_forward_routed(orc_experts, d, f, 128, int(cfg.swiglu), k, x[some].float().cpu().numpy(), idx[some], gate[some])
+    y = y.cpu().numpy()
+    assert np.isfinite(y).all()
+    live = np.abs(y_ref).max(axis=1) > 0
+    assert rel_err(y[some][live], y_ref[live]).max() < TOL
+    assert not y[some][~live].any()
+
+
 @pytest.mark.parametrize("d,f,E,k,x_dtype,T", [
     (768, 1024, 64, 1, "f32", 300),     # a block of eight experts per wavefront, two tokens a workgroup
     (800, 1024, 9, 3, "bf16", 37),      # two blocks, ranges of columns that do not divide
