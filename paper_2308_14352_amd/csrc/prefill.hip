@@ -123,11 +123,10 @@ __global__ __launch_bounds__(256) void k_scatter_pairs(const int32_t* __restrict
   }
 }
 
-// Both for calls of up to kPlanPairs pairs on up to kPlanExperts experts, by one workgroup (two dependent kernels cost two
-// launches of 4.7 us each for little work): a wavefront ranks 64 consecutive pairs at a time inside their experts by ballots,
-// then the counts of the 64-pair segments are summed per expert. Items of small_tok pairs (0: of 128), wide experts first:
-// their units last longest.
-constexpr int kPlanPairs = 4096, kPlanExperts = 64;
+// Both for calls of not too many pairs and experts (plan_in_one), by one workgroup (two dependent kernels cost two launches for
+// little work): a wavefront ranks 64 consecutive pairs at a time inside their experts by ballots, then the counts of the 64-pair
+// segments are summed per expert. Items of small_tok pairs (0: of 128), wide experts first: their units last longest.
+constexpr int kPlanPairs = 4096, kPlanExperts = 64;      // at most; a lane per expert
 __global__ __launch_bounds__(1024) void k_plan_pairs(const int32_t* __restrict__ idx, int M, int E, int32_t* __restrict__ poff,
                                                      int32_t* __restrict__ boff, int2* __restrict__ blocks, int32_t* __restrict__ n_blocks,
                                                      int32_t* __restrict__ gpair, int32_t* __restrict__ ginv, int32_t* __restrict__ gexp,
@@ -1126,6 +1125,11 @@ bool small_items(const LayerDims& L, int64_t M, const PrefillWs& w) {
 // bits in rows: one range 376 us, two 354, three 346, four 339).
 int small_split(const LayerDims& L) { return std::min(4, std::min((L.d_ff + L.d_model) / L.d_model, L.d_ff / kSCols)); }
 
+// One workgroup's time grows with both, a ballot per expert and 64 pairs. us, whole call of 512 x 512 experts, k_plan_pairs /
+// two kernels: 8 experts 30 / 32 (128 pairs) and 60 / 65 (4096), 32 experts 46 / 46.5 (2048) and 66 / 65 (4096), 48 experts 41 / 41.5
+// (1024) and 48.5 / 47 (2048), 64 experts 33.5 / 33 (128) and 80 / 69 (4096).
+bool plan_in_one(int64_t M, int E) { return M <= kPlanPairs && E <= 48 && M * E <= 96 * 1024; }
+
 hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void* x, int32_t T, const int32_t* idx,
                           const float* gate, char* ws, const PrefillWs& w, float* y, bool out_columns, bool in_stream,
                           hipStream_t st) {
@@ -1142,7 +1146,7 @@ hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void
   float* Ypair = (float*)(ws + w.ypair);
   const bool small = small_items(L, M, w);
   if (small) blocks = (int2*)(ws + w.nblk + kSmallList);
-  if (M <= kPlanPairs && L.n_experts <= kPlanExperts) {
+  if (plan_in_one(M, L.n_experts)) {
     hipLaunchKernelGGL(k_plan_pairs, dim3(1), dim3(1024), 0, st, idx, M, L.n_experts, poff, boff, blocks, nblk, gpair, ginv, gexp, table, small ? kSTok : 0);
   } else {
     hipLaunchKernelGGL(k_count_pairs, dim3(1), dim3(1024), 0, st, idx, M, L.n_experts, poff, boff, blocks, nblk, table, small ? kSTok : 0);

@@ -51,14 +51,16 @@ def test_items_at_their_edges(base, d, f, layout, bits):
 
 
 @pytest.mark.parametrize("base,E,T", [
-    ("c5", 97, 64),        # more experts than one workgroup plans, 32-pair items
-    ("c5", 64, 2048),      # 4096 pairs on 64 experts: the most that one workgroup plans
-    ("c5", 64, 2049),      # ... and two pairs more
-    ("c5", 3, 2049),       # the same with items of 128 pairs
-    ("c1", 70, 5100),      # more experts, items of 128 pairs, one choice a token
+    ("c5", 97, 64),        # two kernels: many experts, 32-pair items
+    ("c5", 24, 2048),      # 4096 pairs on 24 experts, the most that one workgroup plans, in items of 128
+    ("c5", 24, 2049),      # ... and two pairs more
+    ("c5", 48, 1024),      # its most experts, in items of 32
+    ("c5", 49, 1024),      # ... and one more
+    ("c5", 3, 2049),       # many pairs on few experts
+    ("c1", 70, 5100),      # more experts, one choice a token
 ])
 def test_planning_of_many_pairs_and_experts(base, E, T):
-    """Pairs grouped by one workgroup (up to 4096 pairs, 64 experts) or by two kernels, for either size of item."""
+    """Pairs grouped by one workgroup or by two kernels, for either size of item."""
     d = f = 512
     cfg = gen.tiny_config(base, d, f, n_experts=E, n_layers=1, group=128)
     layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [(2, 4, 8)[e % 3] for e in range(E)])
