@@ -472,7 +472,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, st) != hipSuccess) return MOEQ_EDEVICE;
     const PrefillWs pw = prefill_ws(L, n_tokens);
     return dev(launch_prefill(L, layer->table, x, n_tokens, idx, gate, (char*)ws + w.prefill_off, pw, y,
-                              layer->out_layout == MOEQ_OUT_COLUMNS, layer->in_layout == MOEQ_IN_STREAM, st));
+                              layer->out_layout == MOEQ_OUT_COLUMNS, layer->in_layout == MOEQ_IN_STREAM, layer->mean_bits, st));
   }
   // a grouped call's tokens per launch; a workspace too small for a single token's takes the token-by-token form
   const int64_t per = w.group ? launch_tokens(std::min<int64_t>(n_tokens, group_tokens(L.top_k)), ws_bytes - w.group_off,

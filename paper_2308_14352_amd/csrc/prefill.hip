@@ -24,6 +24,7 @@
 // rings of two or three stages, so that the loads of the next steps are in flight while a step is multiplied; the loop
 // holds no other memory instruction, and its waits are the hand-written s_waitcnt of stage_wait.
 #include <algorithm>
+#include <cmath>
 
 #include "decode_core.h"
 
@@ -1114,16 +1115,39 @@ PrefillWs prefill_ws(const LayerDims& L, int64_t T) {
 
 // The list of k_gemm_small's items (one word each) starts behind the count of the items.
 constexpr int kSmallList = 64;
-// Calls of up to 72 pairs per expert take k_gemm_small. us, items of 32 / of 128 pairs, Mixtral layer of 8 experts, 170, 230, 300
-// and 350 tokens (42, 57, 75, 87 pairs per expert): 2 and 4 bits in stream 256 / 377, 307 / 391, 357 / 427, 405 / 479; 4 and 8
-// bits in rows 381 / 533, 451 / 541, 520 / 551, 586 / 557; 4 bits in columns 284 / 348, 336 / 373, 394 / 416, 444 / 494.
-bool small_items(const LayerDims& L, int64_t M, const PrefillWs& w) {
-  return M <= 72 * (int64_t)L.n_experts && L.group == 128 && L.group_out == 128 && L.d_model % kSCols == 0 && L.d_ff % kSCols == 0 &&
-         (size_t)(M / kSTok + L.n_experts) * 4 <= w.gpair - w.nblk - kSmallList;
-}
 // Ranges of d_ff of their GEMM 2: as many as fit into the place of h and of the pairs' outputs, up to four (117 tokens, 4 and 8
 // bits in rows: one range 376 us, two 354, three 346, four 339).
 int small_split(const LayerDims& L) { return std::min(4, std::min((L.d_ff + L.d_model) / L.d_model, L.d_ff / kSCols)); }
+// Which calls take k_gemm_small: where their experts hold up to 72 pairs on average and a model of the call's time with either
+// kind of item says so, fitted to both sides of 35000 measured calls (d_model 512 to 4096, d_ff 512 to 14336, 2 to 128 experts of
+// every bitwidth and layout, 3 to 140 pairs per expert, evenly and unevenly spread). An item of 32 pairs costs less, but an expert
+// of more reads and unpacks its weights again, which does not pay where items of 128 fill the compute units anyway: many experts,
+// narrow ones, 8 bits. us, items of 32 / of 128: Mixtral layer (8 experts, 2 and 4 bits, stream) of 30 / 72 pairs per expert
+// 228 / 364 and 402 / 485; 128 experts of 1024 x 3072 (4 bits, columns) of 30 / 60 pairs 343 / 373 and 531 / 445; 64 ReLU experts of
+// 1024 x 2048 (4 bits, rows) of 30 / 60 pairs 107 / 103 and 158 / 131. Of the calls of up to 72 pairs 1.2 % are more than 5 % slower
+// for the model's choice than with items of 128, at most 33 % (two or three of many experts holding most pairs, which the host
+// cannot see); with the line at 72 pairs alone 5.9 % were, at most 57 %.
+struct ItemModel { double ceil_part, wg, in0, in_bits, out0, out_bits, out_cols, base, pair; };
+constexpr ItemModel kItems128{0.556, 0.0, 0.996, 0.1374, 1.185, 0.0488, 0.65, 24.7, 5.64e-6};
+constexpr ItemModel kItems32{0.982, 6.64, 1.583, 0.5636, 1.501, 0.7761, 0.739, 11.7, 5.13e-6};
+bool small_items(const LayerDims& L, int64_t M, const PrefillWs& w, double bits, bool out_columns) {
+  if (M > 72 * (int64_t)L.n_experts || L.group != 128 || L.group_out != 128 || L.d_model % kSCols || L.d_ff % kSCols ||
+      (size_t)(M / kSTok + L.n_experts) * 4 > w.gpair - w.nblk - kSmallList)
+    return false;
+  const double m = (double)M, E = L.n_experts, distinct = E * (1.0 - std::exp(-m / E)), d = L.d_model, f = L.d_ff;
+  // both GEMMs in rounds of the workgroups that are resident together, each `in` and `out` units of K long
+  auto us = [&](const ItemModel& q, double in_wgs, double out_wgs, double resident, double in, double out) {
+    auto rounds = [&](double n) { return q.ceil_part * std::ceil(n / resident) + (1.0 - q.ceil_part) * std::fmax(1.0, n / resident); };
+    return q.base + q.pair * m * (d + f) + rounds(in_wgs) * (q.wg + in * (q.in0 + q.in_bits * bits)) +
+           rounds(out_wgs) * (q.wg + out * (q.out0 + q.out_bits * bits) * (out_columns ? q.out_cols : 1.0));
+  };
+  auto items = [&](double n) { return std::fmax(distinct, m / n + 0.5 * distinct); };
+  const double rows = L.act == MOEQ_ACT_SWIGLU ? 128.0 : 256.0, split = small_split(L);
+  const double by32 = us(kItems32, items(kSTok) * f / rows, items(kSTok) * d / 256.0 * split, 512.0, d / kSCols, f / kSCols / split);
+  const double by128 = us(kItems128, items(kTB * kItemTiles) * f / rows, items(kTB * kItemTiles) * d / (out_columns ? 128.0 : 256.0), 256.0,
+                          d / 128.0, f / 128.0);
+  return by32 < 0.95 * by128;
+}
 
 // One workgroup's time grows with both, a ballot per expert and 64 pairs. us, whole call of 512 x 512 experts, k_plan_pairs /
 // two kernels: 8 experts 30 / 32 (128 pairs) and 60 / 65 (4096), 32 experts 46 / 46.5 (2048) and 66 / 65 (4096), 48 experts 41 / 41.5
@@ -1132,7 +1156,7 @@ bool plan_in_one(int64_t M, int E) { return M <= kPlanPairs && E <= 48 && M * E 
 
 hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void* x, int32_t T, const int32_t* idx,
                           const float* gate, char* ws, const PrefillWs& w, float* y, bool out_columns, bool in_stream,
-                          hipStream_t st) {
+                          double mean_bits, hipStream_t st) {
   const int M = T * L.top_k;
   int32_t* poff = (int32_t*)(ws + w.poff);
   int32_t* boff = (int32_t*)(ws + w.boff);
@@ -1144,7 +1168,7 @@ hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void
   char* XA = ws + w.xa;
   char* HA = ws + w.ha;
   float* Ypair = (float*)(ws + w.ypair);
-  const bool small = small_items(L, M, w);
+  const bool small = small_items(L, M, w, mean_bits, out_columns);
   if (small) blocks = (int2*)(ws + w.nblk + kSmallList);
   if (plan_in_one(M, L.n_experts)) {
     hipLaunchKernelGGL(k_plan_pairs, dim3(1), dim3(1024), 0, st, idx, M, L.n_experts, poff, boff, blocks, nblk, gpair, ginv, gexp, table, small ? kSTok : 0);

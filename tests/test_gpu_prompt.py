@@ -82,6 +82,39 @@ def test_planning_of_many_pairs_and_experts(base, E, T):
     assert not y[some][~live].any()
 
 
+def test_one_chunk_of_8_bit_codes():
+    """The shortest GEMMs (one chunk of columns, one range of W_out) on 8-bit rows, 0 to 65 pairs per expert."""
+    d = f = 512
+    counts = [0, 1, 15, 16, 17, 31, 65, 0]
+    cfg = gen.tiny_config("c5", d, f, n_experts=len(counts), n_layers=1, group=128)
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [8] * len(counts))
+    pairs = np.concatenate([np.full(c, e, dtype=np.int32) for e, c in enumerate(counts)] + [[6]]).astype(np.int32)
+    np.random.default_rng(5).shuffle(pairs)
+    idx = pairs.reshape(-1, cfg.top_k)
+    gate = np.random.default_rng(6).uniform(0.1, 1.0, size=idx.shape).astype(np.float32)
+    x = gen.hidden(cfg, 0, 0, idx.shape[0], DEV)
+    y = moeq.moe_layer_forward_routed(layer, x, torch.from_numpy(idx).to(DEV), torch.from_numpy(gate).to(DEV))
+    torch.cuda.synchronize()
+    y_ref = oracle.layer_forward_routed(orc_experts, d, f, 128, int(cfg.swiglu), cfg.top_k, x.float().cpu().numpy(), idx, gate)
+    assert rel_err(y.cpu().numpy(), y_ref).max() < TOL
+
+
+def test_items_of_128_pairs_where_they_are_faster():
+    """64 ReLU experts of 1024 x 2048 with 60 pairs each: us with items of 32 / of 128 pairs 158 / 131; with 5 pairs each 74 / 90.
+    Every call of more than 72 has items of 128, and the forms differ in the order of their sums (W_out is cut for items of 32)."""
+    d, f, E = 1024, 2048, 64
+    cfg = gen.tiny_config("c1", d, f, n_experts=E, n_layers=1, group=128)
+    layer, _, _, _ = build_layer_pair(cfg, 0, DEV, [4] * E, want_oracle=False)
+    n = 74 * E
+    x = gen.hidden(cfg, 0, 0, n, DEV)
+    idx = torch.randint(0, E, (n, 1), generator=torch.Generator().manual_seed(1), dtype=torch.int32).to(DEV)
+    gate = torch.ones((n, 1), device=DEV)
+    most, many, few = (moeq.moe_layer_forward_routed(layer, x[:T], idx[:T], gate[:T]) for T in (n, 60 * E, 5 * E))
+    torch.cuda.synchronize()
+    assert torch.equal(many, most[:60 * E])
+    assert not torch.equal(few, most[:5 * E]) and rel_err(few.cpu().numpy(), most[:5 * E].cpu().numpy()).max() < 1e-5
+
+
 @pytest.mark.parametrize("d,f,E,k,x_dtype,T", [
     (768, 1024, 64, 1, "f32", 300),     # a block of eight experts per wavefront, two tokens a workgroup
     (800, 1024, 9, 3, "bf16", 37),      # two blocks, ranges of columns that do not divide
