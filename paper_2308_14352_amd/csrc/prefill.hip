@@ -1178,7 +1178,9 @@ hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void
   }
   float* Hf = (float*)(ws + w.hf);
   auto stage_lds = [](int cols) { return (size_t)cols * 2 + (size_t)cols / 16 * 4 + 64; };
-  const unsigned h_threads = M <= 1024 ? 1024 : 256;
+  // threads that stage an activation of h: by its width (16 experts of d_model 512, whole call, us with 256 / 512 / 1024: d_ff 512, 2048
+  // pairs 50 / 52 / 58; 2048, 1024 pairs 52 / 53 / 54; 4096, 1024 pairs 68 / 66 / 67.5; 14336, 128 pairs 69 / 67 / 66 and 2048 pairs 331 / 326 / 319)
+  const unsigned h_threads = L.d_ff >= 8192 ? 1024 : L.d_ff >= 4096 ? 512 : 256;
   const unsigned stage_grid = (unsigned)((M + 7) / 8 * 8);
   hipLaunchKernelGGL(k_stage<false>, dim3(stage_grid), dim3(256), stage_lds(L.d_model), st, L, table, x, gpair, gexp,
                      poff, boff, XA, M);

@@ -115,6 +115,21 @@ def test_items_of_128_pairs_where_they_are_faster():
     assert not torch.equal(few, most[:5 * E]) and rel_err(few.cpu().numpy(), most[:5 * E].cpu().numpy()).max() < 1e-5
 
 
+@pytest.mark.parametrize("f", (4096, 8192))
+@pytest.mark.parametrize("T", (40, 230))
+def test_wide_h(f, T):
+    """Activations of h that 512 and 1024 threads stage, for items of 32 and of 128 pairs (230 tokens on three experts)."""
+    cfg = gen.tiny_config("c1", 512, f, n_experts=3, n_layers=1, group=128)
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [2, 4, 8])
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    idx = (np.arange(T, dtype=np.int32) % 3)[:, None]
+    gate = np.linspace(0.3, 1.0, T, dtype=np.float32)[:, None]
+    y = moeq.moe_layer_forward_routed(layer, x, torch.from_numpy(idx.copy()).to(DEV), torch.from_numpy(gate).to(DEV))
+    torch.cuda.synchronize()
+    y_ref = oracle.layer_forward_routed(orc_experts, 512, f, 128, 0, 1, x.float().cpu().numpy(), idx, gate)
+    assert rel_err(y.cpu().numpy(), y_ref).max() < TOL
+
+
 @pytest.mark.parametrize("d,f,E,k,x_dtype,T", [
     (768, 1024, 64, 1, "f32", 300),     # a block of eight experts per wavefront, two tokens a workgroup
     (800, 1024, 9, 3, "bf16", 37),      # two blocks, ranges of columns that do not divide
