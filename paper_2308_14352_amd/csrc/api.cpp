@@ -469,7 +469,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     return MOEQ_EDEVICE;
   if (use_prefill(layer, n_tokens)) {
     // batched path: router kernels, then the pairs grouped by expert through two quantized GEMMs
-    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, st) != hipSuccess) return MOEQ_EDEVICE;
+    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, nullptr, st) != hipSuccess) return MOEQ_EDEVICE;
     const PrefillWs pw = prefill_ws(L, n_tokens);
     return dev(launch_prefill(L, layer->table, x, n_tokens, idx, gate, (char*)ws + w.prefill_off, pw, y,
                               layer->out_layout == MOEQ_OUT_COLUMNS, layer->in_layout == MOEQ_IN_STREAM, layer->mean_bits, st));
@@ -487,7 +487,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     return Prof{here ? layer->prof_which : 0, layer->prof_start, layer->prof_stop};
   };
   if (w.group && per > 0) {
-    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, st) != hipSuccess) return MOEQ_EDEVICE;
+    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, nullptr, st) != hipSuccess) return MOEQ_EDEVICE;
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
     const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
@@ -503,7 +503,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     // the pairs grouped by expert; routed inside for few experts, else by the router kernels
     const bool route_inline = !given && L.n_experts <= (inline_router_max() < batch_inline_router_max() ? inline_router_max()
                                                                                                         : batch_inline_router_max());
-    if (!given && !route_inline && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, st) != hipSuccess)
+    if (!given && !route_inline && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, nullptr, st) != hipSuccess)
       return MOEQ_EDEVICE;
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {

@@ -39,12 +39,13 @@ inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 // logits[t][e] = router_w[e] . x[t] (+ bias[e])
 hipError_t launch_router_logits(const LayerDims& L, const float* router_w, const float* router_bias,
                                 const void* x, int32_t T, float* logits, hipStream_t st);
-// both of the next two in one kernel (logits and probabilities are not kept): calls of many tokens
-hipError_t launch_route(const LayerDims& L, const float* router_w, const float* router_bias, const void* x, int32_t T,
-                        int32_t* idx, float* gate, hipStream_t st);
 // softmax + top-k of every token from its logits
 hipError_t launch_topk(const LayerDims& L, const float* logits, int32_t T, int32_t* idx, float* gate,
                        float* probs, hipStream_t st);
+
+// both in one kernel, with the same bits. probs: null or [T][E].
+hipError_t launch_route(const LayerDims& L, const float* router_w, const float* router_bias, const void* x, int32_t T,
+                        int32_t* idx, float* gate, float* probs, hipStream_t st);
 
 // idx[i], gate[i] = the caller's routing of pair i, or (0, 0.0f) when its expert index is not in [0, E).
 hipError_t launch_take_routing(const int32_t* idx_in, const float* gate_in, int32_t n, int32_t E, int32_t* idx,

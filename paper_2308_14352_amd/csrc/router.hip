@@ -60,101 +60,140 @@ __global__ __launch_bounds__(kThreads) void k_router_logits(LayerDims L, const f
 }
 
 // Router and top-k of TG tokens in one workgroup: the calls of many tokens, where the logits in memory and a second kernel
-// cost as much as the sums. A wavefront's unit is eight experts x a range of the columns: all experts' rows are requested
-// together, four steps of 256 columns at a time, and meet the TG tokens in registers; a transposing fold leaves the sum of
-// expert l % 8 in lane l. With few experts the eight wavefronts split the columns as well. us, with k_router_logits + k_topk
-// before: Mixtral layer (8 experts, d_model 4096) 117 tokens 16.4 + 4.7 -> 6.3, 2048 tokens 22.7 + 4.8 -> 15.0; 64 experts,
-// d_model 768, 500 tokens 12.8 + 4.7 -> 6. A workgroup reads every expert's row, so it takes two tokens from 256 on and four
-// from 1024 on, where all compute units have several workgroups all the same.
-constexpr int kRouteWaves = 8, kRouteSteps = 4;
-template <bool BF16, int TG>
+// cost as much as the sums. The logits are those of k_router_logits, bit for bit, so that a token's routing does not depend on
+// which of the two serves its call: the columns are four classes (256 columns in every 1024), a class is one chain of sums per
+// lane, and lanes, quads, rows and classes are added in the same order. A wavefront's unit is EB experts x a class, or with many
+// experts (WHOLE) EB experts x all four: the rows of all its experts are requested together, four steps of 256 columns at a time
+// (WHOLE on four tokens: two, or the sums spill), and meet the TG tokens in registers. The folds of a class are as many
+// instructions as its products at d_model 768, so they take all tokens' sums at once and leave out the classes without columns.
+// us, with k_router_logits + k_topk before: 8 experts of 4096 columns 117 tokens 8.7 -> 4.3, 2048 tokens 48 -> 12.5; 64 of 768, 500
+// tokens 11 -> 6; 128 of 768, 2100 tokens 66 -> 29.4.
+constexpr int kRouteWaves = 8, kRouteClasses = 4;
+
+// The sums over the lanes of N values, lane l < N that of value l: every step that adds two lanes leaves half of the values to
+// either, in the order of wave_sum (lanes by 1 and 2, quads 0 + 3 and 1 + 2, their sums, rows 0 + 1 and 2 + 3, their sums).
+template <int N>
+__device__ __forceinline__ float route_fold(const float (&a)[N], int lane) {
+  constexpr int kDppMirror = 0x140, kDppXor3 = 0x1B;       // row_mirror, quad_perm [3,2,1,0]: together lane ^ 12
+  static_assert(N >= 4 && N <= 32, "values of a fold");
+  float v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = a[i];
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) v[i] = ((lane & 1) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor1>((lane & 1) ? v[2 * i] : v[2 * i + 1]);
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) v[i] = ((lane & 2) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor2>((lane & 2) ? v[2 * i] : v[2 * i + 1]);
+  if constexpr (N >= 8) {
+#pragma unroll
+    for (int i = 0; i < N / 8; ++i)
+      v[i] = ((lane & 4) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor3>(dpp<kDppMirror>((lane & 4) ? v[2 * i] : v[2 * i + 1]));
+  } else {
+    v[0] += dpp<kDppRor4>(v[0]);
+  }
+  if constexpr (N >= 16) {
+#pragma unroll
+    for (int i = 0; i < N / 16; ++i) v[i] = ((lane & 8) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppRor8>((lane & 8) ? v[2 * i] : v[2 * i + 1]);
+  } else {
+    v[0] += dpp<kDppRor8>(v[0]);
+  }
+  uint32_t x = __float_as_uint(v[0]), y = N == 32 ? __float_as_uint(v[1]) : x;
+  swap16(x, y);
+  x = y = __float_as_uint(__uint_as_float(x) + __uint_as_float(y));
+  swap32(x, y);
+  return __uint_as_float(x) + __uint_as_float(y);
+}
+
+template <bool BF16, int TG, int EB, bool WHOLE>
 __global__ __launch_bounds__(kRouteWaves * 64) void k_route(LayerDims L, const float* __restrict__ Wr, const float* __restrict__ bias,
                                                             const void* __restrict__ x, int32_t T, int32_t* __restrict__ idx,
-                                                            float* __restrict__ gate) {
-  extern __shared__ float rsm[];                 // [column ranges][TG][experts, whole blocks of eight]
+                                                            float* __restrict__ gate, float* __restrict__ probs) {
+  extern __shared__ float rsm[];                 // [class][TG][experts, whole blocks of EB]
+  constexpr int STEPS = WHOLE && TG == 4 ? 2 : 4, SETS = WHOLE ? kRouteClasses : 1;
   const int d = L.d_model, E = L.n_experts, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nb = (E + 7) / 8, t0 = blockIdx.x * TG;
-  const int cs = nb == 1 ? 8 : nb == 2 ? 4 : nb <= 4 ? 2 : 1;              // column ranges
-  const int seg = (d / cs + 255) / 256 * 256;
-  for (int u = wave; u < nb * cs; u += kRouteWaves) {
-    const int eb = u / cs, c_begin = (u - eb * cs) * seg, c_end = min(d, c_begin + seg);
-    float acc[TG][8];
+  const int nb = (E + EB - 1) / EB, t0 = blockIdx.x * TG, stride = nb * EB;
+  for (int u = wave; u < (WHOLE ? nb : nb * kRouteClasses); u += kRouteWaves) {
+    const int eb = WHOLE ? u : u / kRouteClasses, cls = WHOLE ? 0 : u % kRouteClasses;
+    float acc[SETS][TG * EB];
 #pragma unroll
-    for (int t = 0; t < TG; ++t)
+    for (int s = 0; s < SETS; ++s)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[t][i] = 0.f;
-    for (int c0 = c_begin + lane * 4; c0 < c_end; c0 += 256 * kRouteSteps) {
-      float4 w[kRouteSteps][8], v[kRouteSteps][TG];
+      for (int i = 0; i < TG * EB; ++i) acc[s][i] = 0.f;
+    // steps of 256 columns: of all classes one after the other (step j of four is class j), of one class 1024 apart
+    constexpr int STEP = WHOLE ? 256 : 1024;
+    for (int c0 = 256 * cls; c0 < d; c0 += WHOLE ? 1024 : STEP * STEPS) {
 #pragma unroll
-      for (int j = 0; j < kRouteSteps; ++j) {
-        const int c = c0 + 256 * j;
+      for (int j0 = 0; j0 < (WHOLE ? kRouteClasses : STEPS); j0 += STEPS) {
+        float4 w[STEPS][EB], v[STEPS][TG];
+        if (j0) __builtin_amdgcn_sched_barrier(0);           // (their registers are those of the steps before)
 #pragma unroll
-        for (int t = 0; t < TG; ++t) v[j][t] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c < c_end) {
-#pragma unroll
-          for (int t = 0; t < TG; ++t) {
-            const size_t at = (size_t)min(t0 + t, T - 1) * d + c;
-            if (BF16) {
-              const uint2 b = *(const uint2*)((const uint16_t*)x + at);
-              v[j][t] = make_float4(bf16_bits_to_f32(b.x & 0xffffu), bf16_bits_to_f32(b.x >> 16), bf16_bits_to_f32(b.y & 0xffffu), bf16_bits_to_f32(b.y >> 16));
-            } else {
-              v[j][t] = *(const float4*)((const float*)x + at);
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < 8; ++i) w[j][i] = *(const float4*)(Wr + (size_t)min(eb * 8 + i, E - 1) * d + c);     // rows past E repeat the last one
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < kRouteSteps; ++j)
-        if (c0 + 256 * j < c_end)
-#pragma unroll
-          for (int i = 0; i < 8; ++i)
+        for (int j = 0; j < STEPS; ++j)
+          if (c0 + STEP * (j0 + j) < d) {
+            const int c = min(c0 + STEP * (j0 + j) + lane * 4, d - 4);
 #pragma unroll
             for (int t = 0; t < TG; ++t) {
-              acc[t][i] = fmaf(w[j][i].x, v[j][t].x, acc[t][i]); acc[t][i] = fmaf(w[j][i].y, v[j][t].y, acc[t][i]);
-              acc[t][i] = fmaf(w[j][i].z, v[j][t].z, acc[t][i]); acc[t][i] = fmaf(w[j][i].w, v[j][t].w, acc[t][i]);
+              const size_t at = (size_t)min(t0 + t, T - 1) * d + c;
+              if (BF16) {
+                const uint2 b = *(const uint2*)((const uint16_t*)x + at);
+                v[j][t] = make_float4(bf16_bits_to_f32(b.x & 0xffffu), bf16_bits_to_f32(b.x >> 16), bf16_bits_to_f32(b.y & 0xffffu), bf16_bits_to_f32(b.y >> 16));
+              } else {
+                v[j][t] = *(const float4*)((const float*)x + at);
+              }
             }
+#pragma unroll
+            for (int i = 0; i < EB; ++i) w[j][i] = *(const float4*)(Wr + (size_t)min(eb * EB + i, E - 1) * d + c);     // rows past E repeat the last one
+          }
+#pragma unroll
+        for (int j = 0; j < STEPS; ++j)
+          if (c0 + STEP * (j0 + j) + lane * 4 < d) {
+            const int s = WHOLE ? j0 + j : 0;
+#pragma unroll
+            for (int i = 0; i < EB; ++i)
+#pragma unroll
+              for (int t = 0; t < TG; ++t) {
+                float& a = acc[s][t * EB + i];
+                a = fmaf(w[j][i].x, v[j][t].x, a); a = fmaf(w[j][i].y, v[j][t].y, a);
+                a = fmaf(w[j][i].z, v[j][t].z, a); a = fmaf(w[j][i].w, v[j][t].w, a);
+              }
+          }
+      }
     }
 #pragma unroll
-    for (int t = 0; t < TG; ++t) {
-      float a[4], b[2];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float lo = acc[t][2 * i], hi = acc[t][2 * i + 1];
-        a[i] = ((lane & 1) ? hi : lo) + dpp<kDppXor1>((lane & 1) ? lo : hi);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) b[i] = ((lane & 2) ? a[2 * i + 1] : a[2 * i]) + dpp<kDppXor2>((lane & 2) ? a[2 * i] : a[2 * i + 1]);
-      float s = ((lane & 4) ? b[1] : b[0]) + __shfl_xor((lane & 4) ? b[0] : b[1], 4);
-      s += dpp<kDppRor8>(s);
-      s += __shfl_xor(s, 16);
-      s += __shfl_xor(s, 32);
-      if (lane < 8) rsm[((u - eb * cs) * TG + t) * (nb * 8) + eb * 8 + lane] = s;
+    for (int s = 0; s < SETS; ++s) {
+      const float sum = 256 * (cls + s) < d ? route_fold(acc[s], lane) : 0.f;
+      if (lane < TG * EB) rsm[((cls + s) * TG + lane / EB) * stride + eb * EB + lane % EB] = sum;
     }
   }
   __syncthreads();
   if (wave < TG && t0 + wave < T) {
-    float* lg = rsm + wave * (nb * 8);
+    float* lg = rsm + wave * stride;
     for (int e = lane; e < E; e += 64) {
-      float s = lg[e];
-      for (int r = 1; r < cs; ++r) s += lg[r * TG * (nb * 8) + e];
+      float s = 0.f;
+#pragma unroll
+      for (int r = 0; r < kRouteClasses; ++r) s += lg[r * TG * stride + e];
       lg[e] = s + (bias ? bias[e] : 0.f);
     }
-    topk_from_logits(lg, E, L.top_k, L.renorm, lane, idx + (size_t)(t0 + wave) * L.top_k, gate + (size_t)(t0 + wave) * L.top_k, nullptr);
+    const size_t t = (size_t)(t0 + wave);
+    topk_from_logits(lg, E, L.top_k, L.renorm, lane, idx + t * L.top_k, gate + t * L.top_k, probs ? probs + t * E : nullptr);
   }
+}
+
+// Experts of a unit, and whether it takes all classes: units for the eight wavefronts.
+template <bool BF16, int TG>
+auto pick_route(const LayerDims& L) {
+  return L.n_experts <= 8 ? k_route<BF16, TG, 4, false> : L.n_experts <= 32 ? k_route<BF16, TG, 8, false> : k_route<BF16, TG, 8, true>;
 }
 
 }  // namespace
 
 hipError_t launch_route(const LayerDims& L, const float* router_w, const float* router_bias, const void* x, int32_t T,
-                        int32_t* idx, float* gate, hipStream_t st) {
-  const int nb = (L.n_experts + 7) / 8, cs = nb == 1 ? 8 : nb == 2 ? 4 : nb <= 4 ? 2 : 1;
-  const int tg = T >= 1024 ? 4 : T >= 256 ? 2 : 1;
-  const size_t lds = (size_t)cs * tg * nb * 8 * sizeof(float);
-  auto k = L.x_bf16 ? (tg == 4 ? k_route<true, 4> : tg == 2 ? k_route<true, 2> : k_route<true, 1>)
-                    : (tg == 4 ? k_route<false, 4> : tg == 2 ? k_route<false, 2> : k_route<false, 1>);
-  hipLaunchKernelGGL(k, dim3((T + tg - 1) / tg), dim3(kRouteWaves * 64), lds, st, L, router_w, router_bias, x, T, idx, gate);
+                        int32_t* idx, float* gate, float* probs, hipStream_t st) {
+  // tokens of a workgroup: one round of workgroups where that does it (600 tokens on 128 experts of 768 columns with two / four
+  // 16.8 / 10.9 us); four take 64 KB of LDS at 1024 experts
+  const int tg = T > 512 && L.n_experts <= 512 ? 4 : T > 256 ? 2 : 1, eb = L.n_experts <= 8 ? 4 : 8;
+  const size_t lds = (size_t)kRouteClasses * tg * ((L.n_experts + eb - 1) / eb * eb) * sizeof(float);
+  auto k = L.x_bf16 ? (tg == 4 ? pick_route<true, 4>(L) : tg == 2 ? pick_route<true, 2>(L) : pick_route<true, 1>(L))
+                    : (tg == 4 ? pick_route<false, 4>(L) : tg == 2 ? pick_route<false, 2>(L) : pick_route<false, 1>(L));
+  hipLaunchKernelGGL(k, dim3((T + tg - 1) / tg), dim3(kRouteWaves * 64), lds, st, L, router_w, router_bias, x, T, idx, gate, probs);
   return hipGetLastError();
 }
 

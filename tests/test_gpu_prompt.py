@@ -153,3 +153,35 @@ def test_routing_of_many_tokens(d, f, E, k, x_dtype, T):
     assert keep.sum() >= T - 3
     assert np.array_equal(idx.cpu().numpy()[keep], idx_ref[keep])
     assert np.allclose(gate.cpu().numpy()[keep], gate_ref[keep], rtol=2e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("d,f,E,k,group,act,x_dtype,T", [
+    (512, 512, 3, 2, 128, "relu", "f32", 1030),        # units of four experts, four tokens a workgroup
+    (4096, 512, 8, 2, 128, "swiglu", "bf16", 33),
+    (1056, 512, 16, 2, 32, "relu", "f32", 300),        # columns that end inside a class
+    (768, 1024, 64, 1, 32, "relu", "f32", 257),        # all classes in a unit, the last one empty
+    (1024, 512, 130, 2, 128, "relu", "bf16", 64),
+    (2048, 512, 600, 8, 128, "swiglu", "f32", 1100),
+    (4096, 256, 66, 2, 128, "swiglu", "bf16", 100),    # a grouped decode call
+])
+def test_layer_calls_route_like_the_router_entry(d, f, E, k, group, act, x_dtype, T):
+    """A caller that asks the router first (to fetch experts) and then runs the layer meets the same experts and gates, bit for
+    bit, whichever kernels route (decode calls of few experts apart, which route inside their own kernels); and a token's do not
+    depend on how many tokens its call has."""
+    g = torch.Generator().manual_seed(11)
+    Wr, bias = torch.randn((E, d), generator=g).mul_(0.02).to(DEV), torch.randn((E,), generator=g).mul_(0.1).to(DEV)
+    x = torch.randn((T, d), generator=g).to(DEV).to(torch.bfloat16 if x_dtype == "bf16" else torch.float32)
+    w = {"w_in": torch.randn((f, d), generator=g).to(DEV) * 0.02, "w_out": torch.randn((d, f), generator=g).to(DEV) * 0.02}
+    if act == "swiglu":
+        w["w_gate"] = w["w_in"].flip(0).contiguous()
+    expert = pack_expert_gpu(w, 4, group)
+    layer = moeq.Layer(d, f, k, group, moeq.MOEQ_ACT_SWIGLU if act == "swiglu" else moeq.MOEQ_ACT_RELU, True,
+                       moeq.MOEQ_BF16 if x_dtype == "bf16" else moeq.MOEQ_F32, Wr, bias, [expert] * E)
+    _, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
+    idx_r, gate_r, probs = moeq.moe_router_topk(layer, x, want_probs=True)
+    few = [moeq.moe_router_topk(layer, x[:n]) for n in (1, 9, 40)]
+    torch.cuda.synchronize()
+    assert torch.equal(idx, idx_r) and torch.equal(gate, gate_r)
+    assert all(torch.equal(i, idx[:i.shape[0]]) and torch.equal(v, gate[:i.shape[0]]) for i, v in few)
+    _, _, probs_ref, _ = oracle.router_topk(x[:20].float().cpu().numpy(), Wr.cpu().numpy(), bias.cpu().numpy(), k, True, want_logits=True)
+    assert np.allclose(probs[:20].cpu().numpy(), probs_ref, rtol=1e-4, atol=1e-7)
