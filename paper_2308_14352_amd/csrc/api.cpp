@@ -389,9 +389,7 @@ moeq_status moe_router_topk(const moeq_layer* layer, const void* x, int32_t n_to
   if ((uintptr_t)ws & 255u) return MOEQ_EINVAL;
   float* logits = (float*)((char*)ws + w.logits_off);
   hipStream_t st = (hipStream_t)stream;
-  if (launch_router_logits(layer->dims, layer->router_w, layer->router_bias, x, n_tokens, logits, st) != hipSuccess)
-    return MOEQ_EDEVICE;
-  return dev(launch_topk(layer->dims, logits, n_tokens, topk_idx, topk_gate, probs_opt, st));
+  return dev(launch_route(layer->dims, layer->router_w, layer->router_bias, x, n_tokens, logits, topk_idx, topk_gate, probs_opt, st));
 }
 
 moeq_status moe_expert_ffn_q(const moeq_layer* layer, int32_t expert, const void* x, int32_t n_tokens,
@@ -469,7 +467,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     return MOEQ_EDEVICE;
   if (use_prefill(layer, n_tokens)) {
     // batched path: router kernels, then the pairs grouped by expert through two quantized GEMMs
-    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, nullptr, st) != hipSuccess) return MOEQ_EDEVICE;
+    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, logits, idx, gate, nullptr, st) != hipSuccess) return MOEQ_EDEVICE;
     const PrefillWs pw = prefill_ws(L, n_tokens);
     return dev(launch_prefill(L, layer->table, x, n_tokens, idx, gate, (char*)ws + w.prefill_off, pw, y,
                               layer->out_layout == MOEQ_OUT_COLUMNS, layer->in_layout == MOEQ_IN_STREAM, layer->mean_bits, st));
@@ -487,7 +485,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     return Prof{here ? layer->prof_which : 0, layer->prof_start, layer->prof_stop};
   };
   if (w.group && per > 0) {
-    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, nullptr, st) != hipSuccess) return MOEQ_EDEVICE;
+    if (!given && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, logits, idx, gate, nullptr, st) != hipSuccess) return MOEQ_EDEVICE;
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
     const bool cols = layer->out_layout == MOEQ_OUT_COLUMNS;
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
@@ -503,7 +501,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     // the pairs grouped by expert; routed inside for few experts, else by the router kernels
     const bool route_inline = !given && L.n_experts <= (inline_router_max() < batch_inline_router_max() ? inline_router_max()
                                                                                                         : batch_inline_router_max());
-    if (!given && !route_inline && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, idx, gate, nullptr, st) != hipSuccess)
+    if (!given && !route_inline && launch_route(L, layer->router_w, layer->router_bias, x, n_tokens, logits, idx, gate, nullptr, st) != hipSuccess)
       return MOEQ_EDEVICE;
     const size_t x_row = (size_t)L.d_model * (L.x_bf16 ? 2 : 4);
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {

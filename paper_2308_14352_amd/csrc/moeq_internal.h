@@ -43,9 +43,9 @@ hipError_t launch_router_logits(const LayerDims& L, const float* router_w, const
 hipError_t launch_topk(const LayerDims& L, const float* logits, int32_t T, int32_t* idx, float* gate,
                        float* probs, hipStream_t st);
 
-// both in one kernel, with the same bits. probs: null or [T][E].
+// both, in one kernel or in two through logits[T][E], whichever is faster; the results have the same bits. probs: null or [T][E].
 hipError_t launch_route(const LayerDims& L, const float* router_w, const float* router_bias, const void* x, int32_t T,
-                        int32_t* idx, float* gate, float* probs, hipStream_t st);
+                        float* logits, int32_t* idx, float* gate, float* probs, hipStream_t st);
 
 // idx[i], gate[i] = the caller's routing of pair i, or (0, 0.0f) when its expert index is not in [0, E).
 hipError_t launch_take_routing(const int32_t* idx_in, const float* gate_in, int32_t n, int32_t E, int32_t* idx,

@@ -185,8 +185,23 @@ auto pick_route(const LayerDims& L) {
 
 }  // namespace
 
+// One kernel or two (logits through memory). A workgroup of k_route reads every expert's row, which in calls of up to a
+// workgroup's tokens per compute unit takes as long as one of them; the two kernels spread the rows over the chip and read them
+// once per eight tokens, but are two launches. us, one / two kernels: 8 experts of 4096 columns 4.2 / 8.7 (117 tokens), 64 of 768
+// 5.0 / 6.5; 128 of 1536 9.8 / 7.0 (8 tokens), 128 of 4096 21.5 / 9.4 (8 tokens), 22 / 15.4 (117) and 26 / 37 (300); 1024 of 4096
+// 176 / 13.5 (8 tokens), 168 / 208 (300). The line is that of the two times as fitted to 700 calls; where it errs they are within
+// 1.5 us.
+static bool route_in_one(const LayerDims& L, int32_t T) {
+  const double rows = (double)L.d_model * L.n_experts, wide = L.d_model / 2048.0;
+  return T > 256 || 3.2 + rows / 27000.0 < 6.3 + 0.5 * wide * wide * (T < 8 ? T / 8.0 : 1.0) + rows * T / 8e6;
+}
+
 hipError_t launch_route(const LayerDims& L, const float* router_w, const float* router_bias, const void* x, int32_t T,
-                        int32_t* idx, float* gate, float* probs, hipStream_t st) {
+                        float* logits, int32_t* idx, float* gate, float* probs, hipStream_t st) {
+  if (!route_in_one(L, T)) {
+    if (hipError_t e = launch_router_logits(L, router_w, router_bias, x, T, logits, st); e != hipSuccess) return e;
+    return launch_topk(L, logits, T, idx, gate, probs, st);
+  }
   // tokens of a workgroup: one round of workgroups where that does it (600 tokens on 128 experts of 768 columns with two / four
   // 16.8 / 10.9 us); four take 64 KB of LDS at 1024 experts
   const int tg = T > 512 && L.n_experts <= 512 ? 4 : T > 256 ? 2 : 1, eb = L.n_experts <= 8 ? 4 : 8;
