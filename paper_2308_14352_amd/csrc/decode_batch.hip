@@ -31,6 +31,8 @@
 // small kernels 6.5 and 5); canonical layout 204 -> 170 and 23 tokens 846 -> 180. Where grouping pays: batch_pays (api.cpp).
 #include <hip/hip_ext.h>
 
+#include <cmath>
+
 #include "decode_core.h"
 
 namespace moeq {
@@ -668,14 +670,13 @@ struct BatchOutLds {
   int32_t SX[kBOutGroups][2][kBRows];
 };
 
-// A workgroup takes `blocks` blocks of 256 rows with the same activations, its requests running on from one to the next. What
-// lies past its end asks for a cached line: the next chunk's words, requested and dropped, were half as many bytes again at 4
-// bits. W_out in columns is read with the non-temporal hint (4 bits, d_ff 14336, 23 tokens: 64 us at first, 56 without it, 54
-// with it, 4.5 TB/s; the loads alone take 51 without it, the arithmetic alone 36; 8 bits 104 -> 96; 2 bits 38 -> 44, bound by
-// its arithmetic, which more workgroups hid better; 2 and 4 bits mixed 50 -> 45-47).
+// A workgroup takes `blocks` blocks of 256 rows (out_blocks) with the same activations, its requests running on from one to the
+// next. What lies past its end asks for a cached line: the next chunk's words, requested and dropped, were half as many bytes
+// again at 4 bits. NT: words in columns are read with the non-temporal hint (stream_out). Three workgroups are resident per
+// compute unit; with two, the rows form lost what the running requests gain (2 bits, d_ff 14336, 23 tokens 145 us, now 138).
 // Canonical rows: the wavefront's 64 rows are four blocks of 16; lane (n, kb) loads 16-byte piece 4 j + kb of row 16 i + n
 // (64 consecutive bytes of 16 rows: one scale group at 4 bits, two at 2, half of one at 8), operand i belongs to block i.
-template <int BITS, bool COLS, bool STREAM>
+template <int BITS, bool COLS, bool STREAM, bool NT>
 __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, const BatchItem& item, int blocks) {
   using Set = BatchOutSet<BITS>;
   constexpr int TOK = batch_tok(STREAM), PARTS = batch_parts(STREAM);
@@ -719,7 +720,10 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
         const int g = min(g0 + is * Set::GS + gi, g0 + ng - 1);
         const uint8_t* qg = q + (size_t)g * (4 * BITS) * col + (size_t)rows * 4u;
 #pragma unroll
-        for (int j = 0; j < Set::LPG; ++j) R.t[gi * Set::LPG + j] = load_stream16(live ? qg + (size_t)(4 * j) * col + lane_off : dead);
+        for (int j = 0; j < Set::LPG; ++j) {
+          const uint8_t* p = live ? qg + (size_t)(4 * j) * col + lane_off : dead;
+          R.t[gi * Set::LPG + j] = NT ? load_stream16(p) : gload_u32x4(p);
+        }
         R.s[gi] = gload_u32x2(live ? sc + (size_t)g * (kBD * 2) + (rows + (uint32_t)r0) * 2u : dead);
       }
     } else {
@@ -857,17 +861,17 @@ __device__ __forceinline__ void batch_out(const BatchArgs& G, BatchOutLds& S, co
 }
 
 // Grid (d_model / (blocks * 256), chunks of d_ff, upper bound of the items).
-template <bool COLS, bool STREAM>
-__global__ __launch_bounds__(256) void k_batch_out(BatchArgs G, int blocks) {
+template <bool COLS, bool STREAM, bool NT>
+__global__ __launch_bounds__(256, 3) void k_batch_out(BatchArgs G, int blocks) {
   __shared__ BatchOutLds S;
   __shared__ BatchItem item;
   if ((int)blockIdx.z >= *G.n_items) return;
   if (threadIdx.x < 2) ((uint4*)&item)[threadIdx.x] = ((const uint4*)(G.items + blockIdx.z))[threadIdx.x];
   __syncthreads();
   const int bits = __builtin_amdgcn_readfirstlane(item.bits);
-  if (bits == 2) batch_out<2, COLS, STREAM>(G, S, item, blocks);
-  else if (bits == 4) batch_out<4, COLS, STREAM>(G, S, item, blocks);
-  else batch_out<8, COLS, STREAM>(G, S, item, blocks);
+  if (bits == 2) batch_out<2, COLS, STREAM, NT>(G, S, item, blocks);
+  else if (bits == 4) batch_out<4, COLS, STREAM, NT>(G, S, item, blocks);
+  else batch_out<8, COLS, STREAM, NT>(G, S, item, blocks);
 }
 
 // y[t][r] (+)= sum_j gate[t][j] * sum_c part[c][t k + j][r], chunks and choices in order. gate null: 1. Wavefront j sums the
@@ -903,11 +907,6 @@ __global__ __launch_bounds__(512) void k_batch_combine(const float* __restrict__
   for (int i = 0; i < 4; ++i) o[i] = v[i];
 }
 
-// Blocks of 256 rows that a k_batch_out workgroup takes one after the other, for so many (chunk, item) pairs of a call: two
-// where that leaves more workgroups than are resident (three per compute unit). Mixtral layer (2 and 4 bits, stream), one / two /
-// four blocks, us: d_ff 14336, 6 tokens 37.0 / 35.6 / 44, 23 tokens 50.2 / 45.4 / 47; d_ff 4096, 23 tokens 17.4 / 17.8 / 26.7.
-int out_blocks(int64_t pairs) { return pairs * (kBD / kBOutRows / 2) > 768 ? 2 : 1; }
-
 int batch_cus() {
   static const int cus = [] {
     int dev = 0, n = 0;
@@ -915,6 +914,27 @@ int batch_cus() {
     return n;
   }();
   return cus;
+}
+
+// Blocks of 256 rows that a k_batch_out workgroup takes one after the other, for so many (chunk, item) pairs of a call: two where
+// that leaves about a workgroup per compute unit and the arithmetic is not what they wait for. One expert of 4 or 8 bits, whose
+// later items find its words in the caches, us one / two blocks: 8 bits in columns, d_ff 14336, 16 tokens 74 / 69, 32 tokens 130 /
+// 111, 256 and more 988 / 877; 4 bits in rows 83 / 86 (24 tokens), 256 / 244 (128); a narrow one (d_ff 4096, 8 items) 45 / 50. Layer
+// calls (8 experts, words in columns): 4 bits, d_ff 4096, 8 tokens 57 / 54, d_ff 8192 91 / 89, 2 and 4 bits, d_ff 14336, 23 tokens
+// 177 / 170, 2, 4 and 8 bits in stream, d_ff 8192 152 / 145. 2 bits (bound by arithmetic: d_ff 14336 in rows 127 / 132), 8 bits alone
+// (d_ff 4096, 23 tokens 133 / 137) and words in rows (4 bits, d_ff 14336, 8 tokens 171 / 176) take one.
+int out_blocks(int pairs, int bits_mask, bool one_expert, bool columns) {
+  const bool pays = one_expert ? bits_mask != 2 : columns && bits_mask != 2 && bits_mask != 8;
+  return pays && pairs * (kBD / kBOutRows / 2) * 8 >= 7 * batch_cus() ? 2 : 1;
+}
+// Whether a layer call's words of W_out in columns are read with the non-temporal hint: where each is asked for once and the
+// call's experts do not fit the 256 MB of the memory-side cache, which their next call would find them in. us, without / with it:
+// 4 bits in stream, d_ff 14336, 8 tokens 163 / 162, d_ff 8192 (400 MB) 103 / 97, 8 bits, d_ff 4096 (400 MB) 106 / 98; 4 bits, d_ff 4096
+// (200 MB) 56 / 57, 2 bits in columns, d_ff 8192 (200 MB) 96.5 / 99.5. One expert, read once per 16 or 8 tokens: 4 bits in columns,
+// d_ff 14336, 300 tokens 518 / 600.
+bool stream_out(const LayerDims& L, int T, int tok, double bits) {
+  const double E = L.n_experts, touched = E * (1.0 - std::pow(1.0 - L.top_k / E, T)), matrices = L.act == MOEQ_ACT_SWIGLU ? 3.0 : 2.0;
+  return T * L.top_k <= tok * L.n_experts && touched * matrices * L.d_model * L.d_ff * bits / 8.0 > 256e6;
 }
 
 }  // namespace
@@ -949,7 +969,7 @@ hipError_t init_attrs_decode_batch() {
 }
 
 hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
-                            bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T, int32_t* idx,
+                            bool route_inline, int32_t fixed_expert, int32_t bits_mask, double mean_bits, const void* x, int32_t T, int32_t* idx,
                             float* gate, const float* gate_out, int32_t accumulate, bool in_stream, bool out_columns, char* ws,
                             float* y, hipStream_t st, const Prof& prof) {
   const int k = fixed_expert >= 0 ? 1 : L.top_k;
@@ -963,7 +983,7 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
               (float*)(ws + w.hs), (int32_t*)(ws + w.hsum), (BatchItem*)(ws + w.items), (int32_t*)(ws + w.n_items),
               (float*)(ws + w.part)};
   const int P = T * k;
-  const int tok = batch_tok(in_stream), max_items = P < L.n_experts + P / tok ? P : L.n_experts + P / tok;
+  const int tok = batch_tok(in_stream), most = L.n_experts + P / tok, max_items = fixed_expert >= 0 ? (P + tok - 1) / tok : P < most ? P : most;
   const int chunks = (L.d_ff / kBGroup + kBOutGroups - 1) / kBOutGroups;
   prof_start(prof, MOEQ_KERNEL_FUSED, st);
   hipLaunchKernelGGL(in_stream ? k_batch_prep<true> : k_batch_prep<false>, dim3(T), dim3(512), 0, st, G);
@@ -973,8 +993,10 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
   hipLaunchKernelGGL(kin, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
   prof_stop(prof, MOEQ_KERNEL_FFN_IN, st);
   prof_start(prof, MOEQ_KERNEL_FFN_OUT, st);
-  auto kout = in_stream ? k_batch_out<true, true> : out_columns ? k_batch_out<true, false> : k_batch_out<false, false>;
-  const int blocks = out_blocks((int64_t)chunks * max_items);
+  const bool nt = fixed_expert < 0 && stream_out(L, T, tok, mean_bits);
+  auto kout = in_stream ? (nt ? k_batch_out<true, true, true> : k_batch_out<true, true, false>)
+                        : out_columns ? (nt ? k_batch_out<true, false, true> : k_batch_out<true, false, false>) : k_batch_out<false, false, false>;
+  const int blocks = out_blocks(chunks * max_items, bits_mask & 14, fixed_expert >= 0, out_columns);
   hipLaunchKernelGGL(kout, dim3(kBD / kBOutRows / blocks, chunks, max_items), dim3(256), 0, st, G, blocks);
   prof_stop(prof, MOEQ_KERNEL_FUSED, st);
   hipLaunchKernelGGL(k_batch_combine, dim3(kBD / 256, T), dim3(64 * k), 0, st, G.part, gate_out, chunks, T, k, accumulate, y);
