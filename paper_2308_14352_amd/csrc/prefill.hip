@@ -1124,29 +1124,27 @@ int small_split(const LayerDims& L) { return std::min(4, std::min((L.d_ff + L.d_
 // of more reads and unpacks its weights again, which does not pay where items of 128 fill the compute units anyway: many experts,
 // narrow ones, 8 bits. us, items of 32 / of 128: Mixtral layer (8 experts, 2 and 4 bits, stream) of 30 / 72 pairs per expert
 // 228 / 364 and 402 / 485; 128 experts of 1024 x 3072 (4 bits, columns) of 30 / 60 pairs 343 / 373 and 531 / 445; 64 ReLU experts of
-// 1024 x 2048 (4 bits, rows) of 30 / 60 pairs 107 / 103 and 158 / 131. Of the calls of up to 72 pairs 1.2 % are more than 5 % slower
-// for the model's choice than with items of 128, at most 33 % (two or three of many experts holding most pairs, which the host
-// cannot see); with the line at 72 pairs alone 5.9 % were, at most 57 %.
-struct ItemModel { double ceil_part, wg, in0, in_bits, out0, out_bits, out_cols, base, pair; };
-constexpr ItemModel kItems128{0.556, 0.0, 0.996, 0.1374, 1.185, 0.0488, 0.65, 24.7, 5.64e-6};
-constexpr ItemModel kItems32{0.982, 6.64, 1.583, 0.5636, 1.501, 0.7761, 0.739, 11.7, 5.13e-6};
-bool small_items(const LayerDims& L, int64_t M, const PrefillWs& w, double bits, bool out_columns) {
+// 1024 x 2048 (4 bits, rows) of 30 / 60 pairs 107 / 103 and 158 / 131. Of the calls of up to 72 pairs the model's form is more than
+// 5 % slower than the other in 2.4 %, at most 33 % (two or three of many experts holding most pairs, which the host cannot see);
+// with the line at 72 pairs alone 5.9 % were slower than with items of 128, at most 57 %.
+struct ItemModel { double per_item, ceil_part, wg, in0, in_bits, in_stream, out0, out_bits, out_cols, base, pair; };
+constexpr ItemModel kItems128{0.6, 0.466, 0.613, 1.021, 0.1166, 1.197, 1.205, 0.047, 0.632, 23.1, 5.61e-6};
+constexpr ItemModel kItems32{0.5, 1.0, 6.175, 1.496, 0.5203, 0.979, 1.563, 0.6949, 0.701, 12.7, 6.05e-6};
+bool small_items(const LayerDims& L, int64_t M, const PrefillWs& w, double bits, bool out_columns, bool in_stream) {
   if (M > 72 * (int64_t)L.n_experts || L.group != 128 || L.group_out != 128 || L.d_model % kSCols || L.d_ff % kSCols ||
       (size_t)(M / kSTok + L.n_experts) * 4 > w.gpair - w.nblk - kSmallList)
     return false;
   const double m = (double)M, E = L.n_experts, distinct = E * (1.0 - std::exp(-m / E)), d = L.d_model, f = L.d_ff;
-  // both GEMMs in rounds of the workgroups that are resident together, each `in` and `out` units of K long
-  auto us = [&](const ItemModel& q, double in_wgs, double out_wgs, double resident, double in, double out) {
+  // both GEMMs in rounds of the workgroups that are resident together; rows of a workgroup, and units of K that one takes
+  auto us = [&](const ItemModel& q, double pairs, double resident, double in_rows, double in, double out_rows, double out) {
+    const double items = std::fmax(distinct, m / pairs + q.per_item * distinct);      // expected, of evenly spread pairs
     auto rounds = [&](double n) { return q.ceil_part * std::ceil(n / resident) + (1.0 - q.ceil_part) * std::fmax(1.0, n / resident); };
-    return q.base + q.pair * m * (d + f) + rounds(in_wgs) * (q.wg + in * (q.in0 + q.in_bits * bits)) +
-           rounds(out_wgs) * (q.wg + out * (q.out0 + q.out_bits * bits) * (out_columns ? q.out_cols : 1.0));
+    return q.base + q.pair * m * (d + f) + rounds(items * f / in_rows) * (q.wg + in * (q.in0 + q.in_bits * bits) * (in_stream ? q.in_stream : 1.0)) +
+           rounds(items * d / out_rows) * (q.wg + out * (q.out0 + q.out_bits * bits) * (out_columns ? q.out_cols : 1.0));
   };
-  auto items = [&](double n) { return std::fmax(distinct, m / n + 0.5 * distinct); };
   const double rows = L.act == MOEQ_ACT_SWIGLU ? 128.0 : 256.0, split = small_split(L);
-  const double by32 = us(kItems32, items(kSTok) * f / rows, items(kSTok) * d / 256.0 * split, 512.0, d / kSCols, f / kSCols / split);
-  const double by128 = us(kItems128, items(kTB * kItemTiles) * f / rows, items(kTB * kItemTiles) * d / (out_columns ? 128.0 : 256.0), 256.0,
-                          d / 128.0, f / 128.0);
-  return by32 < 0.95 * by128;
+  return us(kItems32, kSTok, 512.0, rows, d / kSCols, 256.0 / split, f / kSCols / split) <
+         us(kItems128, kTB * kItemTiles, 256.0, rows, d / 128.0, out_columns ? 128.0 : 256.0, f / 128.0);
 }
 
 // One workgroup's time grows with both, a ballot per expert and 64 pairs. us, whole call of 512 x 512 experts, k_plan_pairs /
@@ -1168,7 +1166,7 @@ hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void
   char* XA = ws + w.xa;
   char* HA = ws + w.ha;
   float* Ypair = (float*)(ws + w.ypair);
-  const bool small = small_items(L, M, w, mean_bits, out_columns);
+  const bool small = small_items(L, M, w, mean_bits, out_columns, in_stream);
   if (small) blocks = (int2*)(ws + w.nblk + kSmallList);
   if (plan_in_one(M, L.n_experts)) {
     hipLaunchKernelGGL(k_plan_pairs, dim3(1), dim3(1024), 0, st, idx, M, L.n_experts, poff, boff, blocks, nblk, gpair, ginv, gexp, table, small ? kSTok : 0);
