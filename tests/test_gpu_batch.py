@@ -85,7 +85,8 @@ def test_grouped_single_expert_call(bits, f, T, layout):
 @pytest.mark.parametrize("bits", (2, 4, 8))
 @pytest.mark.parametrize("layout,f", [("stream", 5504), ("canonical", 2432), ("columns", 2432)])
 def test_output_blocks_taken_in_turn(bits, layout, f):
-    """Enough items and chunks that a workgroup of the output kernel takes two blocks of rows; a last chunk of three groups."""
+    """Enough items and chunks that a workgroup of the output kernel takes two blocks of rows (4 and 8 bits; 2 bits: one); a last
+    chunk of three groups."""
     cfg = replace(gen.tiny_config("c4", 4096, f, n_experts=2, n_layers=1, group=128), x_dtype="f32")
     layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits, bits], columns=layout == "columns", stream=layout == "stream")
     x = gen.hidden(cfg, 0, 0, 256, DEV)
@@ -96,6 +97,25 @@ def test_output_blocks_taken_in_turn(bits, layout, f):
     assert torch.equal(y[:20], few)
     y_ref = oracle.expert_ffn(orc_experts[1], 4096, f, cfg.group, int(cfg.swiglu), x[:20].cpu().numpy())
     assert rel_err(few.cpu().numpy(), gate[:20].cpu().numpy()[:, None] * y_ref).max() < TOL
+
+
+@pytest.mark.parametrize("layout,f", [("stream", 5504), ("columns", 2432)])
+def test_output_blocks_taken_in_turn_by_experts_of_every_bitwidth(layout, f):
+    """A layer call of 2-, 4- and 8-bit experts, whose output kernel's workgroups take two blocks of rows; a last chunk of three
+    groups."""
+    cfg = replace(gen.tiny_config("c4", 4096, f, n_experts=3, n_layers=1, group=128), x_dtype="f32")
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [2, 4, 8], columns=layout == "columns", stream=layout == "stream")
+    T = 31
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    idx = np.stack([np.arange(T) % 3, (np.arange(T) + 1) % 3], 1).astype(np.int32)
+    gate = np.linspace(0.2, 1.1, 2 * T, dtype=np.float32).reshape(T, 2)
+    args = torch.from_numpy(idx).to(DEV), torch.from_numpy(gate).to(DEV)
+    y = moeq.moe_layer_forward_routed(layer, x, *args)
+    one = moeq.moe_layer_forward_routed(layer, x[:1], args[0][:1], args[1][:1])
+    torch.cuda.synchronize()
+    assert not torch.equal(y[:1], one)          # (the call was grouped)
+    y_ref = oracle.layer_forward_routed(orc_experts, 4096, f, cfg.group, int(cfg.swiglu), 2, x.cpu().numpy(), idx, gate)
+    assert rel_err(y.cpu().numpy(), y_ref).max() < TOL
 
 
 def test_grouped_call_with_the_ungrouped_workspace():

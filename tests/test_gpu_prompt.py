@@ -1,5 +1,5 @@
-"""GPU parity of prompts whose experts hold a few dozen pairs each (GEMMs on items of 32 pairs), and of the kernels that route
-and group the tokens of such calls, through the C ABI against the oracle."""
+"""GPU parity of prompts: the GEMMs on items of 32 and of 128 pairs at their edges and where the one takes over from the other, and
+the kernels that route and group the tokens of such calls, through the C ABI against the oracle."""
 import gen
 import numpy as np
 import oracle
@@ -78,6 +78,43 @@ def test_planning_of_many_pairs_and_experts(base, E, T):
     y = y.cpu().numpy()
     assert np.isfinite(y).all()
     live = np.abs(y_ref).max(axis=1) > 0
+    assert rel_err(y[some][live], y_ref[live]).max() < TOL
+    assert not y[some][~live].any()
+
+
+@pytest.mark.parametrize("base,d,f,layout", [
+    ("c5", 512, 1024, "canonical"),
+    ("c5", 1024, 512, "columns"),
+    ("c1", 512, 512, "canonical"),
+    ("c1", 512, 1024, "columns"),
+    ("c5", 4096, 512, "stream"),
+    ("c1", 4096, 512, "stream"),
+])
+@pytest.mark.parametrize("bits", (2, 4, 8))
+def test_items_of_128_pairs_at_their_edges(base, d, f, layout, bits):
+    """0, 1, 63..65, 127..129 and 255..257 pairs per expert, well over 72 on average, so that every shape has items of 128; an
+    index outside [0, E); tokens between 2^-12 and 2^12 times each other."""
+    counts = [0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257]
+    E = len(counts)
+    assert sum(counts) > 100 * E
+    cfg = gen.tiny_config(base, d, f, n_experts=E, n_layers=1, group=128)
+    layer, orc_experts, _, _ = build_layer_pair(cfg, 0, DEV, [bits] * E, columns=layout == "columns", stream=layout == "stream")
+    pairs = np.concatenate([np.full(c, e, dtype=np.int32) for e, c in enumerate(counts)])
+    rng = np.random.default_rng(17 + bits)
+    rng.shuffle(pairs)
+    k = cfg.top_k
+    pairs = np.concatenate([pairs, np.full(k - len(pairs) % k, E, dtype=np.int32)])
+    idx = pairs.reshape(-1, k)
+    T = idx.shape[0]
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    x = x * torch.from_numpy(2.0 ** rng.integers(-12, 13, (T, 1))).to(DEV).to(x.dtype)
+    gate = rng.uniform(0.1, 1.0, size=(T, k)).astype(np.float32)
+    y = moeq.moe_layer_forward_routed(layer, x, torch.from_numpy(idx).to(DEV), torch.from_numpy(gate).to(DEV))
+    torch.cuda.synchronize()
+    some = np.unique(np.concatenate([[T - 1], rng.integers(0, T, size=400)]))
+    y_ref = oracle.layer_forward_routed(orc_experts, d, f, 128, int(cfg.swiglu), k, x[some].float().cpu().numpy(), idx[some], gate[some])
+    live = np.abs(y_ref).max(axis=1) > 0
+    y = y.cpu().numpy()
     assert rel_err(y[some][live], y_ref[live]).max() < TOL
     assert not y[some][~live].any()
 
