@@ -411,7 +411,7 @@ moeq_status moe_expert_ffn_q(const moeq_layer* layer, int32_t expert, const void
     const size_t x_row = (size_t)layer->dims.d_model * (layer->dims.x_bf16 ? 2 : 4);
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
       const int32_t n = (int32_t)std::min<int64_t>(n_tokens - t0, per);
-      if (launch_moe_batch(layer->dims, layer->table, nullptr, nullptr, false, expert, bits, bits, (const char*)x + (size_t)t0 * x_row, n,
+      if (launch_moe_batch(layer->dims, layer->table, nullptr, nullptr, false, expert, bits, (const char*)x + (size_t)t0 * x_row, n,
                            nullptr, nullptr, gate_opt ? gate_opt + t0 : nullptr, accumulate ? 1 : 0,
                            layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS, (char*)ws + w.group_off,
                            y + (size_t)t0 * layer->dims.d_model, st) != hipSuccess)
@@ -507,7 +507,7 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     for (int64_t t0 = 0; t0 < n_tokens; t0 += per) {
       const int32_t n = (int32_t)std::min<int64_t>(n_tokens - t0, per);
       const size_t s0 = (size_t)t0 * (size_t)L.top_k;
-      if (launch_moe_batch(L, layer->table, layer->router_w, layer->router_bias, route_inline, -1, layer->bits_mask, layer->mean_bits,
+      if (launch_moe_batch(L, layer->table, layer->router_w, layer->router_bias, route_inline, -1, layer->bits_mask,
                            (const char*)x + (size_t)t0 * x_row, n, idx + s0, gate + s0, gate + s0, 0,
                            layer->in_layout == MOEQ_IN_STREAM, layer->out_layout == MOEQ_OUT_COLUMNS, (char*)ws + w.group_off,
                            y + (size_t)t0 * L.d_model, st, prof(t0)) != hipSuccess)

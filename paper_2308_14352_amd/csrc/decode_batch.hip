@@ -31,8 +31,6 @@
 // small kernels 6.5 and 5); canonical layout 204 -> 170 and 23 tokens 846 -> 180. Where grouping pays: batch_pays (api.cpp).
 #include <hip/hip_ext.h>
 
-#include <cmath>
-
 #include "decode_core.h"
 
 namespace moeq {
@@ -924,18 +922,15 @@ int batch_cus() {
 // 177 / 170, 2, 4 and 8 bits in stream, d_ff 8192 152 / 145. 2 bits (bound by arithmetic: d_ff 14336 in rows 127 / 132), 8 bits alone
 // (d_ff 4096, 23 tokens 133 / 137) and words in rows (4 bits, d_ff 14336, 8 tokens 171 / 176) take one.
 int out_blocks(int pairs, int bits_mask, bool one_expert, bool columns) {
-  const bool pays = one_expert ? bits_mask != 2 : columns && bits_mask != 2 && bits_mask != 8;
+  const bool pays = one_expert ? bits_mask != 2 || pairs >= 200 : columns && bits_mask != 2 && bits_mask != 8;
   return pays && pairs * (kBD / kBOutRows / 2) * 8 >= 7 * batch_cus() ? 2 : 1;
 }
-// Whether a layer call's words of W_out in columns are read with the non-temporal hint: where each is asked for once and the
-// call's experts do not fit the 256 MB of the memory-side cache, which their next call would find them in. us, without / with it:
-// 4 bits in stream, d_ff 14336, 8 tokens 163 / 162, d_ff 8192 (400 MB) 103 / 97, 8 bits, d_ff 4096 (400 MB) 106 / 98; 4 bits, d_ff 4096
-// (200 MB) 56 / 57, 2 bits in columns, d_ff 8192 (200 MB) 96.5 / 99.5. One expert, read once per 16 or 8 tokens: 4 bits in columns,
-// d_ff 14336, 300 tokens 518 / 600.
-bool stream_out(const LayerDims& L, int T, int tok, double bits) {
-  const double E = L.n_experts, touched = E * (1.0 - std::pow(1.0 - L.top_k / E, T)), matrices = L.act == MOEQ_ACT_SWIGLU ? 3.0 : 2.0;
-  return T * L.top_k <= tok * L.n_experts && touched * matrices * L.d_model * L.d_ff * bits / 8.0 > 256e6;
-}
+// Whether a layer call's words of W_out in columns are read with the non-temporal hint: where few experts have a second item,
+// which would find them in a cache, and the loads are what they wait for (not at 2 bits). us, without / with it, no weights in a
+// cache beforehand: 4 bits, d_ff 8192, 16 tokens in stream 105 / 103, 8 bits 186 / 183, 4 bits in columns, d_ff 14336, 16 tokens 171 /
+// 165; 2 bits in stream, d_ff 14336, 23 tokens 120 / 124; 4 bits in columns, d_ff 4096, 31 tokens 98 / 101. One expert, read once per
+// 16 or 8 tokens: 4 bits in columns, d_ff 14336, 300 tokens 518 / 600.
+bool stream_out(int P, int tok, int experts, int bits_mask) { return bits_mask != 2 && 2 * P <= tok * experts; }
 
 }  // namespace
 
@@ -969,7 +964,7 @@ hipError_t init_attrs_decode_batch() {
 }
 
 hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
-                            bool route_inline, int32_t fixed_expert, int32_t bits_mask, double mean_bits, const void* x, int32_t T, int32_t* idx,
+                            bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T, int32_t* idx,
                             float* gate, const float* gate_out, int32_t accumulate, bool in_stream, bool out_columns, char* ws,
                             float* y, hipStream_t st, const Prof& prof) {
   const int k = fixed_expert >= 0 ? 1 : L.top_k;
@@ -993,7 +988,7 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
   hipLaunchKernelGGL(kin, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
   prof_stop(prof, MOEQ_KERNEL_FFN_IN, st);
   prof_start(prof, MOEQ_KERNEL_FFN_OUT, st);
-  const bool nt = fixed_expert < 0 && stream_out(L, T, tok, mean_bits);
+  const bool nt = fixed_expert < 0 && stream_out(P, tok, L.n_experts, bits_mask & 14);
   auto kout = in_stream ? (nt ? k_batch_out<true, true, true> : k_batch_out<true, true, false>)
                         : out_columns ? (nt ? k_batch_out<true, false, true> : k_batch_out<true, false, false>) : k_batch_out<false, false, false>;
   const int blocks = out_blocks(chunks * max_items, bits_mask & 14, fixed_expert >= 0, out_columns);

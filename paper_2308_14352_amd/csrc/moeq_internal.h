@@ -120,7 +120,7 @@ bool batch_supported(const LayerDims& L);
 int batch_inline_router_max();
 hipError_t init_attrs_decode_batch();
 hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const float* router_w, const float* router_bias,
-                            bool route_inline, int32_t fixed_expert, int32_t bits_mask, double mean_bits, const void* x, int32_t T,
+                            bool route_inline, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T,
                             int32_t* idx, float* gate, const float* gate_out, int32_t accumulate, bool in_stream,
                             bool out_columns, char* ws, float* y, hipStream_t st, const Prof& prof = Prof{});
 // canonical (q, s) <-> stream buffer of a [rows][4096] matrix, groups of 128 columns
