@@ -1147,10 +1147,11 @@ bool small_items(const LayerDims& L, int64_t M, const PrefillWs& w, double bits,
          us(kItems128, kTB * kItemTiles, 256.0, rows, d / 128.0, out_columns ? 128.0 : 256.0, f / 128.0);
 }
 
-// One workgroup's time grows with both, a ballot per expert and 64 pairs. us, whole call of 512 x 512 experts, k_plan_pairs /
-// two kernels: 8 experts 30 / 32 (128 pairs) and 60 / 65 (4096), 32 experts 46 / 46.5 (2048) and 66 / 65 (4096), 48 experts 41 / 41.5
-// (1024) and 48.5 / 47 (2048), 64 experts 33.5 / 33 (128) and 80 / 69 (4096).
-bool plan_in_one(int64_t M, int E) { return M <= kPlanPairs && E <= 48 && M * E <= 96 * 1024; }
+// One workgroup's time grows with both, a ballot per expert and 64 pairs. us, whole call of 512 x 512 experts called again and
+// again, k_plan_pairs / two kernels: 8 experts 30 / 32 (128 pairs) and 60 / 65 (4096), 32 experts 46 / 46.5 (2048) and 66 / 65 (4096),
+// 64 experts 33.5 / 33 (128), 42 / 42 (1024) and 80 / 69 (4096). Between other kernels, with its code cold, the second kernel costs
+// 4 us more (64 ReLU experts of 1024 x 2048, 76 pairs: 68 / 72).
+bool plan_in_one(int64_t M, int E) { return M <= kPlanPairs && E <= kPlanExperts && M * E <= 96 * 1024; }
 
 hipError_t launch_prefill(const LayerDims& L, const DevExpert* table, const void* x, int32_t T, const int32_t* idx,
                           const float* gate, char* ws, const PrefillWs& w, float* y, bool out_columns, bool in_stream,

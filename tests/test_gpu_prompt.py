@@ -54,8 +54,9 @@ def test_items_at_their_edges(base, d, f, layout, bits):
     ("c5", 97, 64),        # two kernels: many experts, 32-pair items
     ("c5", 24, 2048),      # 4096 pairs on 24 experts, the most that one workgroup plans, in items of 128
     ("c5", 24, 2049),      # ... and two pairs more
-    ("c5", 48, 1024),      # its most experts, in items of 32
-    ("c5", 49, 1024),      # ... and one more
+    ("c5", 64, 768),       # its most experts, with as many pairs as it takes for them, in items of 32
+    ("c5", 64, 769),       # ... and two pairs more
+    ("c5", 65, 40),        # ... and one expert more
     ("c5", 3, 2049),       # many pairs on few experts
     ("c1", 70, 5100),      # more experts, one choice a token
 ])
