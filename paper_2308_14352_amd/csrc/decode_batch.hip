@@ -915,7 +915,7 @@ int batch_cus() {
 }
 
 // Blocks of 256 rows that a k_batch_out workgroup takes one after the other, for so many (chunk, item) pairs of a call: two where
-// that leaves about a workgroup per compute unit and the arithmetic is not what they wait for. One expert of 4 or 8 bits, whose
+// that leaves about a workgroup per compute unit (in rows one and a half) and the arithmetic is not what they wait for. One expert of 4 or 8 bits, whose
 // later items find its words in the caches, us one / two blocks: 8 bits in columns, d_ff 14336, 16 tokens 74 / 69, 32 tokens 130 /
 // 111, 256 and more 988 / 877; 4 bits in rows 83 / 86 (24 tokens), 256 / 244 (128); a narrow one (d_ff 4096, 8 items) 45 / 50. Layer
 // calls (8 experts, words in columns): 4 bits, d_ff 4096, 8 tokens 57 / 54, d_ff 8192 91 / 89, 2 and 4 bits, d_ff 14336, 23 tokens
@@ -923,14 +923,16 @@ int batch_cus() {
 // (d_ff 4096, 23 tokens 133 / 137) and words in rows (4 bits, d_ff 14336, 8 tokens 171 / 176) take one.
 int out_blocks(int pairs, int bits_mask, bool one_expert, bool columns) {
   const bool pays = one_expert ? bits_mask != 2 || pairs >= 200 : columns && bits_mask != 2 && bits_mask != 8;
-  return pays && pairs * (kBD / kBOutRows / 2) * 8 >= 7 * batch_cus() ? 2 : 1;
+  return pays && pairs * (kBD / kBOutRows / 2) * 8 >= (columns ? 7 : 12) * batch_cus() ? 2 : 1;
 }
-// Whether a layer call's words of W_out in columns are read with the non-temporal hint: where few experts have a second item,
-// which would find them in a cache, and the loads are what they wait for (not at 2 bits). us, without / with it, no weights in a
-// cache beforehand: 4 bits, d_ff 8192, 16 tokens in stream 105 / 103, 8 bits 186 / 183, 4 bits in columns, d_ff 14336, 16 tokens 171 /
-// 165; 2 bits in stream, d_ff 14336, 23 tokens 120 / 124; 4 bits in columns, d_ff 4096, 31 tokens 98 / 101. One expert, read once per
-// 16 or 8 tokens: 4 bits in columns, d_ff 14336, 300 tokens 518 / 600.
-bool stream_out(int P, int tok, int experts, int bits_mask) { return bits_mask != 2 && 2 * P <= tok * experts; }
+// Whether the words of W_out in columns are read with the non-temporal hint: where they are asked for once, or few experts of a
+// layer call have a second item that would find them in a cache, and the loads are what the kernel waits for (not at 2 bits). us,
+// without / with it, on several layers in turn: 4 bits, d_ff 8192, 16 tokens in stream 105 / 103, 8 bits 186 / 183, 4 bits in columns,
+// d_ff 14336, 16 tokens 171 / 165; 2 bits in stream, d_ff 14336, 23 tokens 120 / 124; 4 bits in columns, d_ff 4096, 31 tokens 98 / 101.
+// One expert in stream, 12 tokens, 4 bits, d_ff 14336 48.6 / 46.0, 8 bits, d_ff 9728 74 / 67; 300 tokens in columns 518 / 600.
+bool stream_out(int P, int tok, int experts, bool one_expert, int bits_mask) {
+  return bits_mask != 2 && (one_expert ? P <= tok : 2 * P <= tok * experts);
+}
 
 }  // namespace
 
@@ -988,7 +990,7 @@ hipError_t launch_moe_batch(const LayerDims& L, const DevExpert* table, const fl
   hipLaunchKernelGGL(kin, dim3(batch_cus()), dim3(512), sizeof(BatchInLds), st, G);
   prof_stop(prof, MOEQ_KERNEL_FFN_IN, st);
   prof_start(prof, MOEQ_KERNEL_FFN_OUT, st);
-  const bool nt = fixed_expert < 0 && stream_out(P, tok, L.n_experts, bits_mask & 14);
+  const bool nt = stream_out(P, tok, L.n_experts, fixed_expert >= 0, bits_mask & 14);
   auto kout = in_stream ? (nt ? k_batch_out<true, true, true> : k_batch_out<true, true, false>)
                         : out_columns ? (nt ? k_batch_out<true, false, true> : k_batch_out<true, false, false>) : k_batch_out<false, false, false>;
   const int blocks = out_blocks(chunks * max_items, bits_mask & 14, fixed_expert >= 0, out_columns);
