@@ -187,7 +187,9 @@ size_t moe_packed_bytes(int64_t rows, int64_t cols, int32_t bits, int32_t group,
  * expert index, results in descending gate order), gates per `renorm` (Section 1; Section 2.1).
  * x: dev [n_tokens][d_model] in the layer's x_dtype. topk_idx: dev [n_tokens][top_k] int32.
  * topk_gate: dev [n_tokens][top_k] fp32. probs_opt: dev [n_tokens][n_experts] fp32 or NULL.
- * ws holds the logits between the two kernels. n_tokens == 0 is a no-op. */
+ * The logits have the same bits as those moe_layer_forward routes with, in calls of any number of tokens; apart from its calls of
+ * few tokens on layers of up to 16 experts, whose kernels route inside and add in another order (near ties may differ there).
+ * ws holds the logits where two kernels route. n_tokens == 0 is a no-op. */
 moeq_status moe_router_topk(const moeq_layer *layer, const void *x, int32_t n_tokens,
                             int32_t *topk_idx, float *topk_gate, float *probs_opt, void *ws,
                             size_t ws_bytes, void *stream);

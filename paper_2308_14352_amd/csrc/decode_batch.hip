@@ -27,8 +27,8 @@
 //
 // What bounds it: the bytes of the distinct experts. With one workgroup per (slice, token), as for a single token, a
 // call of T tokens pays T times the unpack arithmetic. Mixtral layer (8 experts, 2 / 4 bits, d_ff 14336): 8 tokens
-// 230 -> 128-146 us, 23 tokens 640 -> 150 us (550 MB: 3.7 TB/s over the whole call; k_batch_in 96, k_batch_out 45-47, the two
-// small kernels 6.5 and 5); canonical layout 204 -> 170 and 23 tokens 846 -> 180. Where grouping pays: batch_pays (api.cpp).
+// 230 -> 117-144 us (by the experts they touch), 23 tokens 640 -> 148 us (550 MB: 3.7 TB/s over the whole call; k_batch_in 95,
+// k_batch_out 46-48, the two small kernels 6.5 and 5); canonical layout 204 -> 170 and 23 tokens 846 -> 180. Where grouping pays: batch_pays (api.cpp).
 #include <hip/hip_ext.h>
 
 #include "decode_core.h"

@@ -681,10 +681,12 @@ __global__ __launch_bounds__(WV * 64) void k_gemm_q(GemmArgs G, int n_rb) {
 //     output, and all compute units are needed to reach the memory's rate). The cut depends on the layer's sizes alone.
 // Operands, instructions and scaling are those of k_gemm_q; a lane finds its A operand in the line of the staged tile that
 // holds the columns of its codes, so that every layout of the weights reads the same tiles.
-// Mixtral layer (8 experts, 2 and 4 bits, stream layout), us: 117 tokens GEMM 1 205 -> 129-139, GEMM 2 111 -> 59-64; 32 tokens
-// 341 -> 178 for the whole call (with the kernels around it). What is left of GEMM 1: with the multiplications taken out it
-// takes as long at 4 bits (160 us; 700 MB, experts of more than 32 pairs being read twice), so its loads bound it: 64 bytes of
-// 16 rows each, 4.4 TB/s, where 128 bytes of eight rows would reach 5.6 but leave the codes in the wrong lanes.
+// Mixtral layer (8 experts, 2 and 4 bits, stream layout), us: 117 tokens GEMM 1 205 -> 126-139, GEMM 2 111 -> 59-65; 32 tokens
+// 341 -> 178 for the whole call (with the kernels around it). What is left: GEMM 1 fetches 512 MB for 367 MB of weights, GEMM 2
+// 294 for 184 (an expert's second item of pairs finds part of them in the caches), 3.9 and 4.5 TB/s, and a wavefront spends 48 %
+// of its life in waits; with the multiplications taken out GEMM 1 takes as long at 4 bits (160 us), so its loads bound it: 64
+// bytes of 16 rows each, where 128 bytes of eight rows would reach 5.6 TB/s but leave the codes in the wrong lanes. 128 registers
+// for two workgroups per compute unit: 5 spill on SwiGLU in stream, ReLU and W_out in rows (24 bytes a lane), 9 on SwiGLU in rows.
 // Tried: four streams a wavefront and half the wavefronts (137), items of 64 pairs on one workgroup of 8 wavefronts
 // (238: two wavefronts per SIMD do not hide the latencies), persistent workgroups (150: registers spill).
 constexpr int kSTok = 32;                        // pairs of an item, at most

@@ -1,8 +1,9 @@
 // Router GEMV (Section 1; Section 2.1: a small router scores the experts for every token).
-// logits[t][e] = router_w[e] . x[t] (+ bias[e]) in fp32. One workgroup per (expert, group of up to 8
-// tokens): the expert's row is read once with 128-bit loads and dotted with each token of the group;
-// partial sums are folded with DPP inside each wavefront, then across the wavefronts through LDS.
-// The softmax and the top-k selection run where the result is needed (see the FFN kernels).
+// logits[t][e] = router_w[e] . x[t] (+ bias[e]) in fp32.
+// k_router_logits: one workgroup per (expert, group of up to 8 tokens): the expert's row is read once with 128-bit loads and
+// dotted with each token of the group; partial sums are folded with DPP inside each wavefront, then across the wavefronts
+// through LDS. The softmax and the top-k selection run where the result is needed (k_topk, the FFN kernels).
+// k_route: logits and top-k of one to four tokens per workgroup in one kernel, with the same bits (launch_route chooses).
 #include "decode_core.h"
 
 namespace moeq {

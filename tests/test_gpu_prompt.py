@@ -218,6 +218,8 @@ def test_layer_calls_route_like_the_router_entry(d, f, E, k, group, act, x_dtype
     _, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
     idx_r, gate_r, probs = moeq.moe_router_topk(layer, x, want_probs=True)
     few = [moeq.moe_router_topk(layer, x[:n]) for n in (1, 9, 40)]
+    if E > 16:
+        few += [moeq.moe_layer_forward(layer, x[:n], want_routing=True)[1:] for n in (1, 3)]
     torch.cuda.synchronize()
     assert torch.equal(idx, idx_r) and torch.equal(gate, gate_r)
     assert all(torch.equal(i, idx[:i.shape[0]]) and torch.equal(v, gate[:i.shape[0]]) for i, v in few)
