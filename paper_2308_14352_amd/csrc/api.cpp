@@ -248,7 +248,7 @@ hipError_t init_kernel_attrs() {
   const uint64_t bit = devid >= 0 && devid < 64 ? 1ull << devid : 0ull;
   if (__atomic_load_n(&done, __ATOMIC_ACQUIRE) & bit) return hipSuccess;
   for (hipError_t (*init)() : {init_attrs_decode_fused, init_attrs_ffn_decode, init_attrs_prefill, init_attrs_decode_batch,
-                               init_attrs_group_gemm})
+                               init_attrs_group_gemm, init_attrs_decode_small})
     if (hipError_t e = init(); e != hipSuccess) return e;
   __atomic_fetch_or(&done, bit, __ATOMIC_RELEASE);
   return hipSuccess;

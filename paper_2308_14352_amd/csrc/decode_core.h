@@ -736,14 +736,14 @@ __device__ __forceinline__ void topk_impl(const float* __restrict__ lg, int E, i
 // that route inside a streaming workgroup wait for exactly this. The probabilities use the hardware
 // exponential (relative error of a few 1e-7, far inside what the gates are compared with); the order of the
 // experts is decided on the logits, so it is exact.
-__device__ __forceinline__ void topk_small(const float* __restrict__ lg, int E, int k, int renorm, int lane, int* sel_e,
-                                           float* sel_g, float* __restrict__ probs) {
-  float v = lane < E ? lg[lane] : -INFINITY;
+// topk64: lane e holds logit e (lanes from E on: -INFINITY); lane r < k receives the r-th choice and its gate, every lane the
+// softmax's terms (p / z is its expert's probability).
+struct Top64 { int e; float gate, p, z; };
+__device__ __forceinline__ Top64 topk64(float v, int E, int k, int renorm, int lane) {
   const float m = wave_max(v);
   const float p = lane < E ? __expf(v - m) : 0.f;
   const float z = wave_sum(p);
   const bool defined = z >= 1.0f && z < INFINITY;      // false: NaN or +Inf among the logits, or none finite
-  if (probs && lane < E) probs[lane] = p / z;
   float sum = 0.f, my_p = 0.f;
   int my_e = 0;
   unsigned long long avail = E >= 64 ? ~0ull : ((1ull << E) - 1ull);   // experts not yet taken
@@ -760,9 +760,15 @@ __device__ __forceinline__ void topk_small(const float* __restrict__ lg, int E, 
     sum += pe;
   }
   const float inv = 1.0f / (renorm ? sum : z);
+  return {defined ? my_e : lane, defined ? my_p * inv : __builtin_nanf(""), p, z};
+}
+__device__ __forceinline__ void topk_small(const float* __restrict__ lg, int E, int k, int renorm, int lane, int* sel_e,
+                                           float* sel_g, float* __restrict__ probs) {
+  const Top64 t = topk64(lane < E ? lg[lane] : -INFINITY, E, k, renorm, lane);
+  if (probs && lane < E) probs[lane] = t.p / t.z;
   if (lane < k) {
-    sel_e[lane] = defined ? my_e : lane;
-    sel_g[lane] = defined ? my_p * inv : __builtin_nanf("");
+    sel_e[lane] = t.e;
+    sel_g[lane] = t.gate;
   }
 }
 

@@ -1123,7 +1123,8 @@ __global__ __launch_bounds__(1024) void k_moe_decode_wide(FusedParams P) {
   for (int rb = threadIdx.x; rb < d / 4; rb += nthreads) out[rb] = Y[rb];
 }
 
-// The vector variant for the layers that 256 threads cover (d_model up to 1024): its duration is a chain of memory round
+// The vector variant for the layers that 256 threads cover (d_model up to 1024), where k_small_cols (decode_small.hip) does not
+// serve the call (several tokens on slices of more than 32 columns): its duration is a chain of memory round
 // trips, so the chain is kept short: activations, router logits (or rows) and expert records are requested together;
 // every wavefront routes for itself and requests its first weights at once; the activations are normalised and put in
 // pair order (for the chosen experts' bitwidths only) while those are in flight.
@@ -1506,6 +1507,9 @@ hipError_t launch_moe_decode(const LayerDims& L, const FusedPlan& plan, const De
   if (!plan.SW || T < 1 || T > 65535 || !(bits_mask & 14)) return hipErrorInvalidValue;
   if (!logits && !route_idx && fixed_expert < 0 && L.n_experts > kInlineMaxE) return hipErrorInvalidValue;
   if ((route_idx != nullptr) != (route_gate != nullptr)) return hipErrorInvalidValue;
+  if (small_cols_fits(L, plan, bits_mask, T))
+    return launch_small_cols(L, plan, table, router_w, router_bias, logits, fixed_expert, gate_in, route_idx, route_gate, bits_mask, x,
+                             T, part, idx_out, gate_out, st, ev_start, ev_stop);
   const int k = fixed_expert >= 0 ? 1 : L.top_k;
   const int n_layouts = ((bits_mask >> 1) & 1) + ((bits_mask >> 2) & 1) + ((bits_mask >> 3) & 1);
   const size_t lds = fused_lds_bytes(L, k, plan.SW, n_layouts);

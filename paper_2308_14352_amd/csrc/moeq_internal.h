@@ -84,6 +84,13 @@ hipError_t launch_moe_decode(const LayerDims& L, const FusedPlan& plan, const De
                              const float* route_gate, int32_t bits_mask, const void* x, int32_t T, float* part,
                              int32_t* idx_out, float* gate_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr);
+// The same on layers whose slices are a few KB (decode_small.hip); small_cols_fits: whether it serves a launch of T tokens.
+bool small_cols_fits(const LayerDims& L, const FusedPlan& plan, int32_t bits_mask, int32_t T);
+hipError_t launch_small_cols(const LayerDims& L, const FusedPlan& plan, const DevExpert* table, const float* router_w,
+                             const float* router_bias, const float* logits, int32_t fixed_expert, const float* gate_in,
+                             const int32_t* route_idx, const float* route_gate, int32_t bits_mask, const void* x, int32_t T,
+                             float* part, int32_t* idx_out, float* gate_out, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+hipError_t init_attrs_decode_small();
 // y[t] (+)= sum_s part[t][s], fixed order.
 hipError_t launch_reduce_partials(const float* part, int n_slices, int d, int32_t T, int accumulate,
                                   float* y, hipStream_t st);

@@ -1,0 +1,84 @@
+"""GPU parity of the decode kernels for layers whose slices of d_ff are a few KB (decode_small.hip): widths at the edges of a
+workgroup's threads, slices of 16 to 128 columns, every source of the routing, several choices, scales that are aligned to two
+bytes only, both ends of the range of x."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+import gen
+import oracle
+import paper_2308_14352_amd as moeq
+from helpers import near_tie_tokens, pack_expert_gpu, pack_expert_oracle, rel_err
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# fp32 products and sums throughout: an element of h is a sum of d products, of y one of d_ff, each off by at most a few roundings
+# of the largest partial sum and by the square root of their number times 2^-24 in the norm; two such sums in a row, the largest
+# of up to 2048 outputs, softmax by the hardware exponential (a few 1e-7): 4 * 2 * sqrt(4096) * 2^-24 = 3e-5
+TOL = 3e-5
+
+
+def odd(t):
+    """The same values at an address that is a multiple of two bytes, not of four."""
+    b = torch.empty(t.numel() + 3, dtype=t.dtype, device=t.device)
+    v = b[1:1 + t.numel()]
+    assert v.data_ptr() % 4 == 2
+    v.copy_(t.reshape(-1))
+    return v.view(t.shape)
+
+
+@pytest.mark.parametrize("d,f,group,E,k,act,x_dtype,misaligned", [
+    (64, 128, 32, 3, 1, "relu", "f32", False),       # fewer columns than a row of lanes folds
+    (512, 1024, 32, 64, 2, "relu", "bf16", False),   # logits of 64 experts, one record per lane
+    (768, 3072, 32, 65, 1, "relu", "f32", True),     # ... of 65: records from memory
+    (768, 768, 96, 5, 3, "relu", "f32", False),     # a group that is no power of two: 4 and 8 bits
+    (1024, 3072, 64, 8, 2, "swiglu", "f32", True),   # the widest with two output rows a thread
+    (1088, 768, 32, 8, 1, "relu", "f32", True),      # ... and the narrowest with four
+    (2048, 512, 128, 140, 2, "relu", "bf16", False), # the widest
+    (512, 8192, 32, 4, 1, "relu", "f32", False),     # slices of 32 columns
+    (256, 16384, 64, 3, 2, "swiglu", "f32", False),  # of 64: single tokens only
+    (256, 32768, 128, 2, 1, "relu", "f32", False),   # of 128
+])
+def test_small_slices(d, f, group, E, k, act, x_dtype, misaligned):
+    cfg = replace(gen.tiny_config("c1", d, f, n_experts=E, n_layers=1, group=group), top_k=k, x_dtype=x_dtype, act=act)
+    distinct = [gen.expert_weights(cfg, 0, e, DEV) for e in range(min(E, 6))]
+    widths = (4, 8) if group % 64 and group != 32 else (2, 4) if d == 2048 else (2, 4, 8)     # (8 bits: single tokens only)
+    packed = [(pack_expert_gpu(w, widths[i % len(widths)], group).with_out_columns(f, group), pack_expert_oracle(w, widths[i % len(widths)], group))
+              for i, w in enumerate(distinct)]
+    if misaligned:
+        for ex, _ in packed:
+            ex.s_in, ex.s_out, ex.s_gate = odd(ex.s_in), odd(ex.s_out), None if ex.s_gate is None else odd(ex.s_gate)
+    gpu, orc = [[packed[e % len(packed)][i] for e in range(E)] for i in (0, 1)]
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(d, f, k, group, moeq.MOEQ_ACT_SWIGLU if act == "swiglu" else moeq.MOEQ_ACT_RELU, cfg.renorm,
+                       moeq.MOEQ_BF16 if x_dtype == "bf16" else moeq.MOEQ_F32, Wr, bias, gpu, moeq.MOEQ_OUT_COLUMNS)
+    sw, wr, b = int(act == "swiglu"), Wr.cpu().numpy(), None if bias is None else bias.cpu().numpy()
+    wide = group % 64 == 0 and f // 64 >= 192                          # slices of more than 32 columns
+    for T in (1, 3):
+        x = gen.hidden(cfg, 0, T, T, DEV)
+        xh = x.float().cpu().numpy()
+        y, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
+        y_e = moeq.moe_expert_ffn_q(layer, E - 1, x, gate=gate[:, 0].contiguous())
+        torch.cuda.synchronize()
+        y_ref, idx_ref, gate_ref = oracle.layer_forward(orc, d, f, group, sw, k, cfg.renorm, wr, b, xh)
+        keep = [t for t in range(T) if t not in near_tie_tokens(cfg, Wr, bias, x)]
+        tol = 2e-3 if wide and T > 1 else TOL                          # binary16 activations there
+        assert np.array_equal(idx.cpu().numpy()[keep], idx_ref[keep])
+        assert np.allclose(gate.cpu().numpy()[keep], gate_ref[keep], rtol=2e-5, atol=1e-7)
+        assert rel_err(y.cpu().numpy()[keep], y_ref[keep]).max(initial=0) < tol
+        e_ref = oracle.expert_ffn(orc[E - 1], d, f, group, sw, xh) * gate.cpu().numpy()[:, :1]
+        assert rel_err(y_e.cpu().numpy(), e_ref).max() < tol
+        # routing given, on tokens of very different scales
+        scale = (2.0 ** np.array([-96, 100, 0][:T])[:, None]).astype(np.float32)
+        xs = (gen.hidden(replace(cfg, x_dtype="f32"), 0, T + 9, T, DEV) * torch.from_numpy(scale).to(DEV))
+        xs = xs.to(torch.bfloat16) if x_dtype == "bf16" else xs
+        gi = np.stack([(np.arange(T) * 5 + j) % E for j in range(k)], 1).astype(np.int32)
+        gg = np.linspace(0.2, 0.9, T * k, dtype=np.float32).reshape(T, k)
+        y_g = moeq.moe_layer_forward_routed(layer, xs, torch.from_numpy(gi).to(DEV), torch.from_numpy(gg).to(DEV))
+        torch.cuda.synchronize()
+        # (SwiGLU is not homogeneous: the gate's sigmoid is 0 or 1 at these scales, its products leave fp32's range)
+        rows = [t for t in range(T) if act == "relu" or scale[t, 0] == 1.0]
+        g_ref = oracle.layer_forward_routed(orc, d, f, group, sw, k, xs.float().cpu().numpy(), gi, gg)
+        assert rel_err(y_g.cpu().numpy()[rows], g_ref[rows]).max(initial=0) < tol
