@@ -700,11 +700,14 @@ __device__ __forceinline__ void topk_impl(const float* __restrict__ lg, int E, i
   float sum = 0.f;
   uint32_t taken = 0;                                  // bit j: this lane's expert lane + 64*j is chosen
   for (int r = 0; r < k; ++r) {
-    float bv = -INFINITY;
+    float bv = m;
+    if (r > 0) {
+      bv = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < MPL; ++j)
-      if (!((taken >> j) & 1u)) bv = fmaxf(bv, v[j]);
-    bv = wave_max(bv);
+      for (int j = 0; j < MPL; ++j)
+        if (!((taken >> j) & 1u)) bv = fmaxf(bv, v[j]);
+      bv = wave_max(bv);
+    }
     int be = -1;
 #pragma unroll
     for (int j = 0; j < MPL; ++j) {
@@ -748,7 +751,7 @@ __device__ __forceinline__ Top64 topk64(float v, int E, int k, int renorm, int l
   int my_e = 0;
   unsigned long long avail = E >= 64 ? ~0ull : ((1ull << E) - 1ull);   // experts not yet taken
   for (int r = 0; r < k; ++r) {                              // lane r keeps the r-th choice
-    const float bv = wave_max(v);
+    const float bv = r == 0 ? m : wave_max(v);
     unsigned long long mask = __ballot(v == bv) & avail;
     if (mask == 0ull) mask = avail;                          // only with undefined values; k <= E keeps avail non-empty
     const int be = __ffsll((long long)mask) - 1;             // ties: the lowest expert index

@@ -12,47 +12,49 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kTokensPerWg = 8;
 
-template <bool BF16>
+// TG tokens of a workgroup (of a group that has fewer, the last one stands in for the rest): their activations are requested
+// together. With the loads behind a condition on the number of tokens they went one after the other, 4 us of a kernel's 4.7 at
+// 8 tokens (128 experts of 1024 columns; now 1.6).
+template <bool BF16, int TG>
 __global__ __launch_bounds__(kThreads) void k_router_logits(LayerDims L, const float* __restrict__ Wr,
                                                             const float* __restrict__ bias,
                                                             const void* __restrict__ x, int32_t T,
                                                             float* __restrict__ logits) {
-  __shared__ float part[kThreads / 64][kTokensPerWg];
+  __shared__ float part[kThreads / 64][TG];
   const int d = L.d_model, E = L.n_experts;
   const int e = blockIdx.x;
-  const int t0 = blockIdx.y * kTokensPerWg;
-  const int nt = min(kTokensPerWg, T - t0);
+  const int t0 = blockIdx.y * TG;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* wr = Wr + (size_t)e * d;
-  float acc[kTokensPerWg];
+  float acc[TG];
 #pragma unroll
-  for (int tt = 0; tt < kTokensPerWg; ++tt) acc[tt] = 0.f;
+  for (int tt = 0; tt < TG; ++tt) acc[tt] = 0.f;
   for (int i = tid * 4; i < d; i += kThreads * 4) {
     const float4 w = *(const float4*)(wr + i);
+    float4 v[TG];
 #pragma unroll
-    for (int tt = 0; tt < kTokensPerWg; ++tt) {
-      if (tt < nt) {
-        float4 v;
-        if (BF16) {
-          const ushort4 b = *(const ushort4*)((const uint16_t*)x + (size_t)(t0 + tt) * d + i);
-          v = make_float4(bf16_bits_to_f32(b.x), bf16_bits_to_f32(b.y), bf16_bits_to_f32(b.z), bf16_bits_to_f32(b.w));
-        } else {
-          v = *(const float4*)((const float*)x + (size_t)(t0 + tt) * d + i);
-        }
-        acc[tt] = fmaf(w.x, v.x, acc[tt]); acc[tt] = fmaf(w.y, v.y, acc[tt]);
-        acc[tt] = fmaf(w.z, v.z, acc[tt]); acc[tt] = fmaf(w.w, v.w, acc[tt]);
+    for (int tt = 0; tt < TG; ++tt) {
+      const size_t at = (size_t)min(t0 + tt, T - 1) * d + i;
+      if (BF16) {
+        const ushort4 b = *(const ushort4*)((const uint16_t*)x + at);
+        v[tt] = make_float4(bf16_bits_to_f32(b.x), bf16_bits_to_f32(b.y), bf16_bits_to_f32(b.z), bf16_bits_to_f32(b.w));
+      } else {
+        v[tt] = *(const float4*)((const float*)x + at);
       }
     }
-  }
 #pragma unroll
-  for (int tt = 0; tt < kTokensPerWg; ++tt) {
-    if (tt < nt) {   // uniform over the workgroup
-      const float v = wave_sum(acc[tt]);
-      if (lane == 0) part[wave][tt] = v;
+    for (int tt = 0; tt < TG; ++tt) {
+      acc[tt] = fmaf(w.x, v[tt].x, acc[tt]); acc[tt] = fmaf(w.y, v[tt].y, acc[tt]);
+      acc[tt] = fmaf(w.z, v[tt].z, acc[tt]); acc[tt] = fmaf(w.w, v[tt].w, acc[tt]);
     }
   }
+#pragma unroll
+  for (int tt = 0; tt < TG; ++tt) {
+    const float v = wave_sum(acc[tt]);
+    if (lane == 0) part[wave][tt] = v;
+  }
   __syncthreads();
-  if (tid < nt) {
+  if (tid < TG && t0 + tid < T) {
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < kThreads / 64; ++w) v += part[w][tid];
@@ -190,11 +192,11 @@ auto pick_route(const LayerDims& L) {
 // workgroup's tokens per compute unit takes as long as one of them; the two kernels spread the rows over the chip and read them
 // once per eight tokens, but are two launches. us, one / two kernels: 8 experts of 4096 columns 4.2 / 8.7 (117 tokens), 64 of 768
 // 5.0 / 6.5; 128 of 1536 9.8 / 7.0 (8 tokens), 128 of 4096 21.5 / 9.4 (8 tokens), 22 / 15.4 (117) and 26 / 37 (300); 1024 of 4096
-// 176 / 13.5 (8 tokens), 168 / 208 (300). The line is that of the two times as fitted to 700 calls; where it errs they are within
-// 1.5 us.
+// 176 / 13.5 (8 tokens), 168 / 208 (300); 33 of 4096 10.8 / 8.4 (8 tokens), 11.2 / 12.0 (117). The line is that of the two times as
+// fitted to 700 calls; where it errs they are within 1.5 us.
 static bool route_in_one(const LayerDims& L, int32_t T) {
   const double rows = (double)L.d_model * L.n_experts, wide = L.d_model / 2048.0;
-  return T > 256 || 3.2 + rows / 27000.0 < 6.3 + 0.5 * wide * wide * (T < 8 ? T / 8.0 : 1.0) + rows * T / 8e6;
+  return T > 256 || 3.2 + rows / 27000.0 < 6.3 + 0.25 * wide * wide * (T < 8 ? T / 8.0 : 1.0) + rows * T / 8e6;
 }
 
 hipError_t launch_route(const LayerDims& L, const float* router_w, const float* router_bias, const void* x, int32_t T,
@@ -215,12 +217,15 @@ hipError_t launch_route(const LayerDims& L, const float* router_w, const float* 
 
 hipError_t launch_router_logits(const LayerDims& L, const float* router_w, const float* router_bias, const void* x,
                                 int32_t T, float* logits, hipStream_t st) {
-  const dim3 grid(L.n_experts, (T + kTokensPerWg - 1) / kTokensPerWg);
-  if (L.x_bf16)
-    hipLaunchKernelGGL(k_router_logits<true>, grid, dim3(kThreads), 0, st, L, router_w, router_bias, x, T, logits);
-  else
-    hipLaunchKernelGGL(k_router_logits<false>, grid, dim3(kThreads), 0, st, L, router_w, router_bias, x, T, logits);
-  return hipGetLastError();
+  auto launch = [&](auto tg_tag) {
+    constexpr int TG = decltype(tg_tag)::value;
+    hipLaunchKernelGGL((L.x_bf16 ? k_router_logits<true, TG> : k_router_logits<false, TG>), dim3(L.n_experts, (T + TG - 1) / TG),
+                       dim3(kThreads), 0, st, L, router_w, router_bias, x, T, logits);
+    return hipGetLastError();
+  };
+  if (T == 1) return launch(std::integral_constant<int, 1>{});
+  if (T <= 4) return launch(std::integral_constant<int, 4>{});
+  return launch(std::integral_constant<int, kTokensPerWg>{});
 }
 
 }  // namespace moeq
