@@ -439,10 +439,10 @@ moeq_status moe_expert_ffn_q(const moeq_layer* layer, int32_t expert, const void
     return MOEQ_OK;
   }
   float* h = (float*)((char*)ws + w.h_off);
-  hipError_t e = launch_ffn_in(layer->dims, layer->table, nullptr, nullptr, nullptr, nullptr, expert, x, n_tokens, h,
+  hipError_t e = launch_ffn_in(layer->dims, layer->table, nullptr, nullptr, nullptr, nullptr, expert, bits, x, n_tokens, h,
                                st);
   if (e != hipSuccess) return MOEQ_EDEVICE;
-  return dev(launch_ffn_out(layer->dims, layer->table, nullptr, gate_opt, expert, accumulate ? 1 : 0, h, n_tokens, y,
+  return dev(launch_ffn_out(layer->dims, layer->table, nullptr, gate_opt, expert, bits, accumulate ? 1 : 0, h, n_tokens, y,
                             st));
 }
 
@@ -557,12 +557,12 @@ static moeq_status layer_forward_impl(const moeq_layer* layer, const void* x, in
     return MOEQ_EDEVICE;
   {
     ScopedEvents ev(layer, MOEQ_KERNEL_FFN_IN, st);
-    if (launch_ffn_in(L, layer->table, given ? nullptr : logits, idx, gate, sel_tab, -1, x, n_tokens, h, st) !=
+    if (launch_ffn_in(L, layer->table, given ? nullptr : logits, idx, gate, sel_tab, -1, layer->bits_mask, x, n_tokens, h, st) !=
         hipSuccess)
       return MOEQ_EDEVICE;
   }
   ScopedEvents ev(layer, MOEQ_KERNEL_FFN_OUT, st);
-  return dev(launch_ffn_out(L, layer->table, sel_tab, gate, -1, 0, h, n_tokens, y, st));
+  return dev(launch_ffn_out(L, layer->table, sel_tab, gate, -1, layer->bits_mask, 0, h, n_tokens, y, st));
 }
 
 moeq_status moe_layer_forward(const moeq_layer* layer, const void* x, int32_t n_tokens, float* y,

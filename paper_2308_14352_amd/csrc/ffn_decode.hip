@@ -461,8 +461,9 @@ hipError_t launch_take_routing(const int32_t* idx_in, const float* gate_in, int3
 }
 
 hipError_t launch_ffn_in(const LayerDims& L, const DevExpert* table, const float* logits, int32_t* idx_out,
-                         float* gate_out, DevExpert* sel_tab, int32_t fixed_expert, const void* x, int32_t T,
+                         float* gate_out, DevExpert* sel_tab, int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T,
                          float* h, hipStream_t st) {
+  if (small_rows_fits(L, (int64_t)T * (fixed_expert >= 0 ? 1 : L.top_k))) return launch_small_in(L, table, logits, idx_out, gate_out, sel_tab, fixed_expert, bits_mask, x, T, h, st);
   const Split sp = plan_rows(L.d_ff, min_lanes_per_row(L.d_model), wgs_per_token(T),
                              L.act == MOEQ_ACT_SWIGLU ? kBlock / 2 : kBlock);
   const PhaseLds pl = phase1_lds(L, fixed_expert >= 0 ? 1 : L.top_k);
@@ -473,8 +474,9 @@ hipError_t launch_ffn_in(const LayerDims& L, const DevExpert* table, const float
 }
 
 hipError_t launch_ffn_out(const LayerDims& L, const DevExpert* table, const DevExpert* sel_tab, const float* gate,
-                          int32_t fixed_expert, int32_t accumulate, const float* h, int32_t T, float* y,
+                          int32_t fixed_expert, int32_t bits_mask, int32_t accumulate, const float* h, int32_t T, float* y,
                           hipStream_t st) {
+  if (small_rows_fits(L, (int64_t)T * (fixed_expert >= 0 ? 1 : L.top_k))) return launch_small_out(L, table, sel_tab, gate, fixed_expert, bits_mask, accumulate, h, T, y, st);
   Split sp = plan_rows(L.d_model, min_lanes_per_row(L.d_ff), wgs_per_token(T), kBlock);
   sp.threads = phase2_threads(sp.threads);
   const PhaseLds pl = phase2_lds(L, fixed_expert >= 0 ? 1 : L.top_k, sp.rows_per_wg);

@@ -57,13 +57,20 @@ hipError_t launch_take_routing(const int32_t* idx_in, const float* gate_in, int3
 // table records to sel_tab[slot], and slot = token * top_k + j; with logits == nullptr the routing is
 // READ from idx_out/gate_out instead (caller-supplied routing, already validated).
 hipError_t launch_ffn_in(const LayerDims& L, const DevExpert* table, const float* logits,
-                         int32_t* idx_out, float* gate_out, DevExpert* sel_tab, int32_t fixed_expert,
+                         int32_t* idx_out, float* gate_out, DevExpert* sel_tab, int32_t fixed_expert, int32_t bits_mask,
                          const void* x, int32_t T, float* h, hipStream_t st);
 
 // Phase 2 + combine: y[t] (+)= sum_j gate * W_out h[slot].
 hipError_t launch_ffn_out(const LayerDims& L, const DevExpert* table, const DevExpert* sel_tab,
-                          const float* gate, int32_t fixed_expert, int32_t accumulate,
+                          const float* gate, int32_t fixed_expert, int32_t bits_mask, int32_t accumulate,
                           const float* h, int32_t T, float* y, hipStream_t st);
+// The same two on layers whose rows are a few KB (decode_small.hip); small_rows_fits: whether they serve a call of so many
+// (token, choice) pairs.
+bool small_rows_fits(const LayerDims& L, int64_t pairs);
+hipError_t launch_small_in(const LayerDims& L, const DevExpert* table, const float* logits, int32_t* idx, float* gate, DevExpert* sel_tab,
+                           int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T, float* h, hipStream_t st);
+hipError_t launch_small_out(const LayerDims& L, const DevExpert* table, const DevExpert* sel_tab, const float* gate, int32_t fixed_expert,
+                            int32_t bits_mask, int32_t accumulate, const float* h, int32_t T, float* y, hipStream_t st);
 
 // ---- one-kernel decode path (W_out in the dword-column-major layout) -------------------------------
 // Split of a layer for the fused kernel: slices of SW columns of d_ff, one workgroup of `threads` per

@@ -1,6 +1,6 @@
-"""GPU parity of the decode kernels for layers whose slices of d_ff are a few KB (decode_small.hip): widths at the edges of a
-workgroup's threads, slices of 16 to 128 columns, every source of the routing, several choices, scales that are aligned to two
-bytes only, both ends of the range of x."""
+"""GPU parity of the decode kernels for layers whose slices of d_ff, or rows, are a few KB (decode_small.hip), in both layouts of
+W_out: widths at the edges of a workgroup's threads, slices of 16 to 128 columns, rows in one pass and in several, every source of
+the routing, several choices, scales that are aligned to two bytes only, both ends of the range of x."""
 from dataclasses import replace
 
 import numpy as np
@@ -39,23 +39,31 @@ def odd(t):
     (2048, 512, 128, 140, 2, "relu", "bf16", False), # the widest
     (512, 8192, 32, 4, 1, "relu", "f32", False),     # slices of 32 columns
     (256, 16384, 64, 3, 2, "swiglu", "f32", False),  # of 64: single tokens only
-    (256, 32768, 128, 2, 1, "relu", "f32", False),   # of 128
+    (256, 32768, 128, 2, 1, "relu", "f32", False),   # of 128 (rows: more columns than they take)
+    (2048, 8192, 128, 3, 1, "relu", "f32", False),   # the longest rows of W_out: four of 8 bits a pass (single tokens only)
+    (1024, 2048, 32, 130, 5, "relu", "f32", True),   # more experts than two per lane, five choices, workgroups of several passes
 ])
-def test_small_slices(d, f, group, E, k, act, x_dtype, misaligned):
+@pytest.mark.parametrize("columns", (False, True), ids=("canonical", "columns"))
+def test_small_slices(d, f, group, E, k, act, x_dtype, misaligned, columns):
     cfg = replace(gen.tiny_config("c1", d, f, n_experts=E, n_layers=1, group=group), top_k=k, x_dtype=x_dtype, act=act)
     distinct = [gen.expert_weights(cfg, 0, e, DEV) for e in range(min(E, 6))]
-    widths = (4, 8) if group % 64 and group != 32 else (2, 4) if d == 2048 else (2, 4, 8)     # (8 bits: single tokens only)
-    packed = [(pack_expert_gpu(w, widths[i % len(widths)], group).with_out_columns(f, group), pack_expert_oracle(w, widths[i % len(widths)], group))
+    widths = (4, 8) if group % 64 and group != 32 else (2, 4) if d == 2048 and columns else (2, 4, 8)     # (8 bits: single tokens)
+    packed = [(pack_expert_gpu(w, widths[i % len(widths)], group), pack_expert_oracle(w, widths[i % len(widths)], group))
               for i, w in enumerate(distinct)]
+    if columns:
+        packed = [(ex.with_out_columns(f, group), o) for ex, o in packed]
     if misaligned:
         for ex, _ in packed:
             ex.s_in, ex.s_out, ex.s_gate = odd(ex.s_in), odd(ex.s_out), None if ex.s_gate is None else odd(ex.s_gate)
     gpu, orc = [[packed[e % len(packed)][i] for e in range(E)] for i in (0, 1)]
     Wr, bias = gen.router_weights(cfg, 0, DEV)
     layer = moeq.Layer(d, f, k, group, moeq.MOEQ_ACT_SWIGLU if act == "swiglu" else moeq.MOEQ_ACT_RELU, cfg.renorm,
-                       moeq.MOEQ_BF16 if x_dtype == "bf16" else moeq.MOEQ_F32, Wr, bias, gpu, moeq.MOEQ_OUT_COLUMNS)
+                       moeq.MOEQ_BF16 if x_dtype == "bf16" else moeq.MOEQ_F32, Wr, bias, gpu,
+                       moeq.MOEQ_OUT_COLUMNS if columns else moeq.MOEQ_OUT_CANONICAL)
     sw, wr, b = int(act == "swiglu"), Wr.cpu().numpy(), None if bias is None else bias.cpu().numpy()
-    wide = group % 64 == 0 and f // 64 >= 192                          # slices of more than 32 columns
+    few = 0 if f > 8192 else (34e6 if d % 512 == 0 else 18e6) / (d * f * (1.5 if sw else 1.0))     # pairs of a call in rows
+    if columns:
+        few = k if group % 64 == 0 and f // 64 >= 192 or d * f > 1e7 else 1 << 30     # wide slices, or one workgroup a compute unit
     for T in (1, 3):
         x = gen.hidden(cfg, 0, T, T, DEV)
         xh = x.float().cpu().numpy()
@@ -64,12 +72,12 @@ def test_small_slices(d, f, group, E, k, act, x_dtype, misaligned):
         torch.cuda.synchronize()
         y_ref, idx_ref, gate_ref = oracle.layer_forward(orc, d, f, group, sw, k, cfg.renorm, wr, b, xh)
         keep = [t for t in range(T) if t not in near_tie_tokens(cfg, Wr, bias, x)]
-        tol = 2e-3 if wide and T > 1 else TOL                          # binary16 activations there
+        tol, tol_e = (TOL if n <= few else 2e-3 for n in (T * k, T))   # (binary16 activations beyond)
         assert np.array_equal(idx.cpu().numpy()[keep], idx_ref[keep])
         assert np.allclose(gate.cpu().numpy()[keep], gate_ref[keep], rtol=2e-5, atol=1e-7)
         assert rel_err(y.cpu().numpy()[keep], y_ref[keep]).max(initial=0) < tol
         e_ref = oracle.expert_ffn(orc[E - 1], d, f, group, sw, xh) * gate.cpu().numpy()[:, :1]
-        assert rel_err(y_e.cpu().numpy(), e_ref).max() < tol
+        assert rel_err(y_e.cpu().numpy(), e_ref).max() < tol_e
         # routing given, on tokens of very different scales
         scale = (2.0 ** np.array([-96, 100, 0][:T])[:, None]).astype(np.float32)
         xs = (gen.hidden(replace(cfg, x_dtype="f32"), 0, T + 9, T, DEV) * torch.from_numpy(scale).to(DEV))
