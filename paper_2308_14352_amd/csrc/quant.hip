@@ -94,8 +94,10 @@ __global__ __launch_bounds__(256) void k_quantize_pack(const float* __restrict__
 // bytes of consecutive addresses per step, and kQuantUnroll steps are loaded before the first is used.
 // Bound by the fp32 reads and by the divisions: code = rint(w / scale) with the IEEE quotient. w times the
 // approximate reciprocal is within 2.5 ulp (2^-21.5 relative, 4e-5 for magnitudes up to 128) of that quotient, so the
-// two round to different integers only within 4e-5 of a half-integer; only such elements take the real division.
-// 14336 x 4096 weights at 4 bits: 48 us (5.5 TB/s); 83-98 us with two passes and a division per weight.
+// two round to different integers only within 4e-5 of a half-integer; only float4s with such elements take the real division.
+// A scale (division, rounding to binary16, the bump) is 40 instructions: lane j of a quad makes that of step j, not every lane all
+// four. 14336 x 4096 weights at 4 bits: 43 us (6.2 TB/s); 52 with every lane's own scales and a branch per weight, 83-98 with two
+// passes and a division per weight.
 constexpr int kQuantUnroll = 4;
 template <int BITS>
 __global__ __launch_bounds__(256) void k_quantize_pack_once(const float* __restrict__ w, int64_t n_f4, int n4sh,
@@ -112,10 +114,10 @@ __global__ __launch_bounds__(256) void k_quantize_pack_once(const float* __restr
     const int64_t i = base + k * 256 < n_f4 ? base + k * 256 : n_f4 - 1;
     v[k] = __builtin_nontemporal_load((const float4_t*)w + i);
   }
+  // magnitude of every step's group, in all of its n4 lanes
+  float am[kQuantUnroll];
 #pragma unroll
   for (int k = 0; k < kQuantUnroll; ++k) {
-    const int64_t i = base + k * 256;
-    const bool live = i < n_f4;                  // whole groups: n_f4 is a multiple of n4 and n4 divides 64
     float a = fmaxf(fmaxf(fabsf(v[k].x), fabsf(v[k].y)), fmaxf(fabsf(v[k].z), fabsf(v[k].w)));
     a = fmaxf(a, 0.f);                           // four NaNs: the magnitude 0 that the running maximum starts from
     // maximum over the group's n4 lanes: the lane that differs in the lowest, second, ... bit of its number
@@ -125,8 +127,13 @@ __global__ __launch_bounds__(256) void k_quantize_pack_once(const float* __restr
     if (n4 > 8) a = fmaxf(a, dpp_f32<0x140>(a)); // mirror inside 16 lanes
     if (n4 > 16) a = fmaxf(a, __shfl_xor(a, 16, 64));
     if (n4 > 32) a = fmaxf(a, __shfl_xor(a, 32, 64));
-    uint32_t sh = 0;
-    float sf = 0.f;
+    am[k] = a;
+  }
+  uint32_t shs[kQuantUnroll];
+  float sfs[kQuantUnroll], invs[kQuantUnroll];
+  auto scale_of = [&](float a, uint32_t& sh, float& sf, float& inv) __attribute__((always_inline)) {
+    sh = 0;
+    sf = 0.f;
     if (a > 0.f) {
       const float s32 = __fdiv_rn(a, (float)QMAX);
       sh = f32_to_f16_bits_rne(s32);
@@ -135,22 +142,49 @@ __global__ __launch_bounds__(256) void k_quantize_pack_once(const float* __restr
       if (sh >= 0x7c00u) sh = 0x7bffu;
       sf = f16_bits_to_f32(sh);
     }
-    const float inv = __builtin_amdgcn_rcpf(sf);   // (an all-zero group does not use it)
+    inv = __builtin_amdgcn_rcpf(sf);             // (an all-zero group does not use it)
+  };
+  if (n4 >= 4) {                                 // quads lie inside groups: lane j of a quad makes the scale of step j for all four
+    static_assert(kQuantUnroll == 4, "a step per lane of a quad");
+    const int q4 = (int)threadIdx.x & 3;
+    uint32_t sh;
+    float sf, inv;
+    scale_of(q4 == 0 ? am[0] : q4 == 1 ? am[1] : q4 == 2 ? am[2] : am[3], sh, sf, inv);
+    const float shf = __uint_as_float(sh);
+    sfs[0] = dpp_f32<0x00>(sf); sfs[1] = dpp_f32<0x55>(sf); sfs[2] = dpp_f32<0xAA>(sf); sfs[3] = dpp_f32<0xFF>(sf);
+    invs[0] = dpp_f32<0x00>(inv); invs[1] = dpp_f32<0x55>(inv); invs[2] = dpp_f32<0xAA>(inv); invs[3] = dpp_f32<0xFF>(inv);
+    shs[0] = __float_as_uint(dpp_f32<0x00>(shf)); shs[1] = __float_as_uint(dpp_f32<0x55>(shf));
+    shs[2] = __float_as_uint(dpp_f32<0xAA>(shf)); shs[3] = __float_as_uint(dpp_f32<0xFF>(shf));
+  } else {
+#pragma unroll
+    for (int k = 0; k < kQuantUnroll; ++k) scale_of(am[k], shs[k], sfs[k], invs[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < kQuantUnroll; ++k) {
+    const int64_t i = base + k * 256;
+    const bool live = i < n_f4;                  // whole groups: n_f4 is a multiple of n4 and n4 divides 64
+    const float a = am[k], sf = sfs[k], inv = invs[k];
+    float r[4];
+    bool near = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float d = v[k][j] * inv;
+      r[j] = rintf(d);
+      near = near || fabsf(d - r[j]) > 0.49993f;
+    }
+    if (near) {                                  // one of the four: the IEEE quotients
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = rintf(__fdiv_rn(v[k][j], sf));
+    }
     uint32_t packed = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float r = 0.f;
-      if (a > 0.f) {
-        const float d = v[k][j] * inv;
-        r = rintf(d);
-        if (fabsf(d - r) > 0.49993f) r = rintf(__fdiv_rn(v[k][j], sf));
-        r = fminf(fmaxf(r, (float)-QMAX), (float)QMAX);
-      }
-      packed |= (uint32_t)((int)r + OFF) << (j * BITS);
+      const float c = a > 0.f ? fminf(fmaxf(r[j], (float)-QMAX), (float)QMAX) : 0.f;
+      packed |= (uint32_t)((int)c + OFF) << (j * BITS);
     }
     if (live) {
       ((Code*)q)[i] = (Code)packed;
-      if (((int)threadIdx.x & (n4 - 1)) == 0) s[i >> n4sh] = (uint16_t)sh;
+      if (((int)threadIdx.x & (n4 - 1)) == 0) s[i >> n4sh] = (uint16_t)shs[k];
     }
   }
 }
