@@ -475,6 +475,39 @@ __device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {    // odd qua
   a = r.x; b = r.y;
 }
 
+// The sums over the lanes of N values, lane l < N that of value l: every step that adds two lanes leaves half of the values to
+// either, in the order of wave_sum (lanes by 1 and 2, quads 0 + 3 and 1 + 2, their sums, rows 0 + 1 and 2 + 3, their sums).
+template <int N>
+__device__ __forceinline__ float route_fold(const float (&a)[N], int lane) {
+  constexpr int kDppMirror = 0x140, kDppXor3 = 0x1B;       // row_mirror, quad_perm [3,2,1,0]: together lane ^ 12
+  static_assert(N >= 4 && N <= 32, "values of a fold");
+  float v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = a[i];
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) v[i] = ((lane & 1) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor1>((lane & 1) ? v[2 * i] : v[2 * i + 1]);
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) v[i] = ((lane & 2) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor2>((lane & 2) ? v[2 * i] : v[2 * i + 1]);
+  if constexpr (N >= 8) {
+#pragma unroll
+    for (int i = 0; i < N / 8; ++i)
+      v[i] = ((lane & 4) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor3>(dpp<kDppMirror>((lane & 4) ? v[2 * i] : v[2 * i + 1]));
+  } else {
+    v[0] += dpp<kDppRor4>(v[0]);
+  }
+  if constexpr (N >= 16) {
+#pragma unroll
+    for (int i = 0; i < N / 16; ++i) v[i] = ((lane & 8) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppRor8>((lane & 8) ? v[2 * i] : v[2 * i + 1]);
+  } else {
+    v[0] += dpp<kDppRor8>(v[0]);
+  }
+  uint32_t x = __float_as_uint(v[0]), y = N == 32 ? __float_as_uint(v[1]) : x;
+  swap16(x, y);
+  x = y = __float_as_uint(__uint_as_float(x) + __uint_as_float(y));
+  swap32(x, y);
+  return __uint_as_float(x) + __uint_as_float(y);
+}
+
 // A pointer that is the same in every lane, moved to scalar registers so that loads can use the
 // "scalar base + 32-bit lane offset" addressing mode instead of 64-bit per-lane addresses.
 template <typename T>
@@ -779,16 +812,12 @@ __device__ __forceinline__ void topk_small(const float* __restrict__ lg, int E, 
 // logits (broadcast reads) and selects in its own registers, so the chain is a few dozen dependent vector
 // instructions instead of a dozen DPP / readlane round trips. Same rules: order on the logits, ties to the
 // lowest index, an undefined softmax takes the experts 0 .. k-1 with NaN gates.
+struct TopTiny { int i0, i1; float g0, g1; };
 template <int EMAX>
-__device__ __forceinline__ void topk_tiny(const float* __restrict__ lg, int E, int k, int renorm, int lane, int* sel_e,
-                                          float* sel_g) {
-  float v[EMAX];
+__device__ __forceinline__ TopTiny topk_tiny_regs(const float (&v)[EMAX], int E, int k, int renorm) {
   float m = -INFINITY;
 #pragma unroll
-  for (int e = 0; e < EMAX; ++e) {
-    v[e] = e < E ? lg[e] : -INFINITY;
-    m = fmaxf(m, v[e]);
-  }
+  for (int e = 0; e < EMAX; ++e) m = fmaxf(m, v[e]);
   float z = 0.f;
 #pragma unroll
   for (int e = 0; e < EMAX; ++e) z += e < E ? __expf(v[e] - m) : 0.f;
@@ -812,12 +841,21 @@ __device__ __forceinline__ void topk_tiny(const float* __restrict__ lg, int E, i
   }
   const float p0 = __expf(b0 - m), p1 = k > 1 ? __expf(b1 - m) : 0.f;
   const float inv = 1.0f / (renorm ? p0 + p1 : z);
+  return {defined ? i0 : 0, defined ? i1 : 1, defined ? p0 * inv : __builtin_nanf(""), defined ? p1 * inv : __builtin_nanf("")};
+}
+template <int EMAX>
+__device__ __forceinline__ void topk_tiny(const float* __restrict__ lg, int E, int k, int renorm, int lane, int* sel_e,
+                                          float* sel_g) {
+  float v[EMAX];
+#pragma unroll
+  for (int e = 0; e < EMAX; ++e) v[e] = e < E ? lg[e] : -INFINITY;
+  const TopTiny t = topk_tiny_regs<EMAX>(v, E, k, renorm);
   if (lane == 0) {
-    sel_e[0] = defined ? i0 : 0;
-    sel_g[0] = defined ? p0 * inv : __builtin_nanf("");
+    sel_e[0] = t.i0;
+    sel_g[0] = t.g0;
     if (k > 1) {
-      sel_e[1] = defined ? i1 : 1;
-      sel_g[1] = defined ? p1 * inv : __builtin_nanf("");
+      sel_e[1] = t.i1;
+      sel_g[1] = t.g1;
     }
   }
 }

@@ -95,14 +95,12 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
   __shared__ float XS[32];                // 2^e of every scale group of x (NaN: the group holds a non-finite value)
   __shared__ int SXL[64];                 // sum of x_int over a lane's 64 columns
   __shared__ float rpart[kSWaves * kSInlineMaxE];   // router: every wavefront's part of every logit
-  __shared__ float lgw[kSWaves][kSInlineMaxE];
   __shared__ int sel_ew[kSWaves][8];
   __shared__ float sel_gw[kSWaves][8];
   __shared__ float HF[8][kSSlice];        // h of every chosen expert, fp32
   __shared__ uint4 HD[8][8];              // digits of h for phase 2: per expert 8 x (4 words)
   __shared__ float uph[8];                // 2^e of an expert's h slice (NaN: non-finite)
   __shared__ int SH[8];                   // sum of h_int
-  __shared__ DevExpert tab[kSInlineMaxE]; // the expert table, when it fits
   const LayerDims& L = P.L;
   const int E = L.n_experts;
   const int token = blockIdx.y;
@@ -119,9 +117,19 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
 
   // ---- the activations: thread t holds columns 8t .. 8t+7; a scale group is the 16 threads of a DPP row
   XItem xit = load_x_item(xt, bf16 ? X_BF16 : X_F32, tid);
-  const bool tab_in_lds = E <= kSInlineMaxE;
-  if (tab_in_lds && tid < E * 4) ((uint4*)tab)[tid] = ((const uint4*)P.table)[tid];
-  const DevExpert* tabp = tab_in_lds ? tab : P.table;
+  // of up to 64 experts, the records of expert `lane`: what a request needs of them comes from registers
+  struct Rec { uint2 q_in, q_gate; uint4 out; int bits; };
+  auto load_rec = [&](int e) __attribute__((always_inline)) {
+    const uint4* src = (const uint4*)(P.table + e);
+    Rec v;
+    v.q_in = *(const uint2*)src;
+    if constexpr (SWIGLU) v.q_gate = *(const uint2*)(src + 1);
+    v.out = src[2];
+    v.bits = (int)src[3].x;
+    return v;
+  };
+  const bool lane_recs = E <= kSInlineMaxE;
+  Rec rec = load_rec(lane_recs ? min(lane, E - 1) : 0);
   // ---- digits of the activations, for every bitwidth the layer has, straight from the registers
   auto stage_digits = [&]() __attribute__((always_inline)) {
     float m = 0.f;
@@ -208,66 +216,100 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
         w[i][1] = *(const float4*)(wr + 4);
       }
       if (!staged) { stage_digits(); staged = true; }
+      float acc[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        float acc = w[i][0].x * xit.v[0];
-        acc = fmaf(w[i][0].y, xit.v[1], acc); acc = fmaf(w[i][0].z, xit.v[2], acc); acc = fmaf(w[i][0].w, xit.v[3], acc);
-        acc = fmaf(w[i][1].x, xit.v[4], acc); acc = fmaf(w[i][1].y, xit.v[5], acc);
-        acc = fmaf(w[i][1].z, xit.v[6], acc); acc = fmaf(w[i][1].w, xit.v[7], acc);
-        acc = wave_sum(acc);
-        if (lane == 0 && e0 + i < E) rpart[wave * kSInlineMaxE + e0 + i] = acc;
+        acc[i] = w[i][0].x * xit.v[0];
+        acc[i] = fmaf(w[i][0].y, xit.v[1], acc[i]); acc[i] = fmaf(w[i][0].z, xit.v[2], acc[i]); acc[i] = fmaf(w[i][0].w, xit.v[3], acc[i]);
+        acc[i] = fmaf(w[i][1].x, xit.v[4], acc[i]); acc[i] = fmaf(w[i][1].y, xit.v[5], acc[i]);
+        acc[i] = fmaf(w[i][1].z, xit.v[6], acc[i]); acc[i] = fmaf(w[i][1].w, xit.v[7], acc[i]);
       }
+      const float sum = route_fold(acc, lane);               // lane i: the sum of expert e0 + i
+      if (lane < 8 && e0 + lane < E) rpart[wave * kSInlineMaxE + e0 + lane] = sum;
     }
   }
   if (!staged) stage_digits();
-  __syncthreads();   // digits, XS, SXL, rpart, tab are complete
+  __syncthreads();   // digits, XS, SXL, rpart are complete
 
 
-  // ---- routing, by every wavefront for itself (identical arithmetic, identical result): no second barrier
-  int* sel_e = sel_ew[wave];
-  float* sel_g = sel_gw[wave];
+  // ---- routing, by every wavefront for itself (identical arithmetic, identical result): no second barrier. Lane j < k gets
+  // choice j (its expert, gate and record), and everything behind reads it with v_readlane: through LDS the chain of index, record
+  // and pointer was three round trips ahead of the first request (which leaves 5.4 us after the start, not 6.1; the first data
+  // arrive at 6.7, not 8.5), and wave_sum of eight router products ninety instructions more than their common fold. Layer of 2- and
+  // 4-bit experts 39.2 -> 38.1 us, 2 bits 31.4 -> 30.5, 8 bits 65.6 -> 64.1, with the reduction.
+  int my_e = P.fixed_expert;
+  float my_g = 1.0f;
   if (given) {
-    if (lane < k) {
-      sel_e[lane] = P.route_idx[(size_t)token * k + lane];
-      sel_g[lane] = P.route_gate[(size_t)token * k + lane];
+    my_e = P.route_idx[(size_t)token * k + min(lane, k - 1)];
+    my_g = P.route_gate[(size_t)token * k + min(lane, k - 1)];
+  } else if (inline_router || (routed && E <= 64)) {
+    float v = -INFINITY;
+    if (lane < E) {
+      if (inline_router) {
+        v = rpart[lane];
+#pragma unroll
+        for (int wv = 1; wv < kSWaves; ++wv) v += rpart[wv * kSInlineMaxE + lane];
+        v += P.bias ? P.bias[lane] : 0.f;
+      } else {
+        v = P.logits[(size_t)token * E + lane];
+      }
+    }
+    if (inline_router && E <= 8 && k <= 2) {
+      float l8[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) l8[e] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), e));
+      const TopTiny t = topk_tiny_regs<8>(l8, E, k, L.renorm);
+      my_e = lane == 0 ? t.i0 : t.i1;
+      my_g = lane == 0 ? t.g0 : t.g1;
+    } else if (inline_router && E <= 16 && k <= 2) {
+      float l16[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) l16[e] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), e));
+      const TopTiny t = topk_tiny_regs<16>(l16, E, k, L.renorm);
+      my_e = lane == 0 ? t.i0 : t.i1;
+      my_g = lane == 0 ? t.g0 : t.g1;
+    } else {
+      const Top64 t = topk64(v, E, k, L.renorm, lane);
+      my_e = t.e;
+      my_g = t.gate;
     }
   } else if (routed) {
-    if (inline_router) {
-      float* lg = lgw[wave];
-      if (lane < E) {
-        float t = rpart[lane];
-#pragma unroll
-        for (int wv = 1; wv < kSWaves; ++wv) t += rpart[wv * kSInlineMaxE + lane];
-        lg[lane] = t + (P.bias ? P.bias[lane] : 0.f);
-      }
-      if (E <= 8 && k <= 2) topk_tiny<8>(lg, E, k, L.renorm, lane, sel_e, sel_g);
-      else if (E <= 16 && k <= 2) topk_tiny<16>(lg, E, k, L.renorm, lane, sel_e, sel_g);
-      else topk_from_logits(lg, E, k, L.renorm, lane, sel_e, sel_g, nullptr);
-    } else {
-      topk_from_logits(P.logits + (size_t)token * E, E, k, L.renorm, lane, sel_e, sel_g, nullptr);
-    }
-  } else if (lane == 0) {
-    sel_e[0] = P.fixed_expert;
-    sel_g[0] = P.gate_in ? P.gate_in[token] : 1.0f;
+    topk_from_logits(P.logits + (size_t)token * E, E, k, L.renorm, lane, sel_ew[wave], sel_gw[wave], nullptr);
+    my_e = sel_ew[wave][min(lane, k - 1)];
+    my_g = sel_gw[wave][min(lane, k - 1)];
+  } else if (P.gate_in) {
+    my_g = P.gate_in[token];
   }
-  if (lane < k) sel_e[lane] = min(max(sel_e[lane], 0), E - 1);
+  my_e = min(max(my_e, 0), E - 1);          // an address: whatever produced it, it stays inside the table
   if (routed && !given && slice == 0 && wave == 0 && lane < k) {
-    if (P.idx_out) P.idx_out[(size_t)token * k + lane] = sel_e[lane];
-    if (P.gate_out) P.gate_out[(size_t)token * k + lane] = sel_g[lane];
+    if (P.idx_out) P.idx_out[(size_t)token * k + lane] = my_e;
+    if (P.gate_out) P.gate_out[(size_t)token * k + lane] = my_g;
   }
+  if (lane_recs) {
+    auto of = [&](uint32_t& v) __attribute__((always_inline)) { v = (uint32_t)__shfl((int)v, my_e); };
+    of(rec.q_in.x); of(rec.q_in.y);
+    if constexpr (SWIGLU) { of(rec.q_gate.x); of(rec.q_gate.y); }
+    of(rec.out.x); of(rec.out.y); of(rec.out.z); of(rec.out.w);
+    rec.bits = __shfl(rec.bits, my_e);
+  } else {
+    rec = load_rec(my_e);
+  }
+  auto at_choice = [&](uint32_t v, int j) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane((int)v, j); };
+  auto ptr_at = [&](uint32_t lo, uint32_t hi, int j) __attribute__((always_inline)) {
+    return (const uint8_t*)((uint64_t)at_choice(lo, j) | (uint64_t)at_choice(hi, j) << 32);
+  };
 
   // ---- the list of blocks of a wavefront (the same for every wavefront): lane g computes entries g and g + 64
   // and keeps them in two registers, read with v_readlane when a block is requested. Entry: kind | first << 2 |
   // j << 3 | bits << 6 | index << 10, index = rb * NM + mat in phase 1, q in phase 2. Segment j (0 .. k) holds
   // phase 1 of expert j interleaved with phase 2 of expert j - 1, alternating while both have blocks left.
-  const DevExpert* tabq = tabp;
   int n_total = 0, bm = 0;
   int ent_lo = 0, ent_hi = 0;
   {
     int start = 0, b2 = 0;                                      // b2: bits of expert j - 1
     for (int j = 0; j <= k; ++j) {
       {
-        const int b1 = j < k ? __builtin_amdgcn_readfirstlane(tabq[sel_e[j]].bits) : 0;   // bits of expert j
+        const int b1 = j < k ? (int)at_choice((uint32_t)rec.bits, j) : 0;   // bits of expert j
         bm |= b1;
         const int n1 = (b1 >> 1) * NM, n2 = b2 == 0 ? 0 : (b2 == 2 ? 1 : (b2 == 4 ? 2 : 4));
         const int m = min(n1, n2);
@@ -301,14 +343,14 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
     const uint8_t* sbase = idle;
     int qshift = 3;                                  // tiles i >> qshift select the second row quad
     if (tag.kind != B_NONE) {
-      const DevExpert* ex = tabq + sel_e[tag.j];
       if (tag.kind == B_P1) {
         tag.mat = SWIGLU ? (index & 1) : 0;
         tag.rb = SWIGLU ? (index >> 1) : index;
         const int rbsh = tag.bits == 2 ? 3 : (tag.bits == 4 ? 2 : 1);
         const uint32_t RB = 1u << rbsh, BB = 8192u + 64u * RB;
         const uint32_t blk = (((uint32_t)slice * 64u + (uint32_t)wave * 8u) >> rbsh) + (uint32_t)tag.rb;
-        base = uniform_ptr(tag.mat ? ex->q_gate : ex->q_in) + (size_t)blk * BB;
+        base = SWIGLU && tag.mat ? ptr_at(rec.q_gate.x, rec.q_gate.y, tag.j) : ptr_at(rec.q_in.x, rec.q_in.y, tag.j);
+        base += (size_t)blk * BB;
         tstride = 1024u;
         sbase = base + 8192u;
         // the aligned 8 bytes that hold the lane's RB bytes of scales (always inside the block's scale area)
@@ -320,11 +362,11 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
         const uint32_t first = tag.bits == 8 ? (uint32_t)(tag.q & 1) * 8u : 0u; // 8-bit: two blocks per row quad
         const uint32_t q0 = tag.bits == 2 ? 0u : (tag.bits == 4 ? (uint32_t)tag.q : (uint32_t)(tag.q >> 1));
         qshift = tag.bits == 2 ? 2 : 3;
-        base = uniform_ptr(ex->q_out) + ((size_t)slice * DW + first) * ((size_t)kSD * 4);
+        base = ptr_at(rec.out.x, rec.out.y, tag.j) + ((size_t)slice * DW + first) * ((size_t)kSD * 4);
         tstride = (uint32_t)kSD * 4u;
         qstride = 1024u - wpb * tstride;                                       // from the last word of quad 0 to quad 1
         lane_t = (uint32_t)(64 * (2 * wave + (int)q0) + lane) * 16u;
-        sbase = (const uint8_t*)uniform_ptr(ex->s_out) + (size_t)(slice >> 1) * ((size_t)kSD * 2);
+        sbase = ptr_at(rec.out.z, rec.out.w, tag.j) + (size_t)(slice >> 1) * ((size_t)kSD * 2);
         soff0 = (uint32_t)(64 * (2 * wave + (int)q0) + lane) * 8u;
         soff1 = tag.bits == 2 ? soff0 + 512u : soff0;
       }
@@ -466,7 +508,7 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
   float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int acc8[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};   // 8-bit experts: a row quad's sums run over two blocks
   auto consume_p2 = [&](const BlkSet& S, const BlkTag& tag) __attribute__((always_inline)) {
-    const float gu = sel_g[tag.j] * uph[tag.j];
+    const float gu = __builtin_bit_cast(float, at_choice(__builtin_bit_cast(uint32_t, my_g), tag.j)) * uph[tag.j];
     const uint4* hd = HD[tag.j];
     if ((BM & 4) && tag.bits == 4) {
       int a[4][4];
@@ -561,9 +603,8 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
   };
 
   // ---- between the phases of expert j: digits of its h slice (one wavefront)
-  auto stage_h = [&](int j) __attribute__((always_inline)) {
+  auto stage_h = [&](int j, int bits) __attribute__((always_inline)) {
     if (wave == (j & (kSWaves - 1))) {
-      const int bits = __builtin_amdgcn_readfirstlane(tabp[sel_e[j]].bits);
       const float hv = HF[j][lane];
       float m = !(fabsf(hv) < INFINITY) ? INFINITY : fabsf(hv);
       m = wave_max(m);
@@ -621,7 +662,7 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
     } else if (tag.kind == B_P2) {
       if (tag.first) {          // uniform over the workgroup: every wavefront walks the same list
         __syncthreads();        // the h slice of expert tag.j is complete (fp32)
-        stage_h(tag.j);
+        stage_h(tag.j, tag.bits);
         __syncthreads();
       }
       consume_p2(St, tag);

@@ -73,39 +73,6 @@ __global__ __launch_bounds__(kThreads) void k_router_logits(LayerDims L, const f
 // tokens 11 -> 6; 128 of 768, 2100 tokens 66 -> 29.4.
 constexpr int kRouteWaves = 8, kRouteClasses = 4;
 
-// The sums over the lanes of N values, lane l < N that of value l: every step that adds two lanes leaves half of the values to
-// either, in the order of wave_sum (lanes by 1 and 2, quads 0 + 3 and 1 + 2, their sums, rows 0 + 1 and 2 + 3, their sums).
-template <int N>
-__device__ __forceinline__ float route_fold(const float (&a)[N], int lane) {
-  constexpr int kDppMirror = 0x140, kDppXor3 = 0x1B;       // row_mirror, quad_perm [3,2,1,0]: together lane ^ 12
-  static_assert(N >= 4 && N <= 32, "values of a fold");
-  float v[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = a[i];
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) v[i] = ((lane & 1) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor1>((lane & 1) ? v[2 * i] : v[2 * i + 1]);
-#pragma unroll
-  for (int i = 0; i < N / 4; ++i) v[i] = ((lane & 2) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor2>((lane & 2) ? v[2 * i] : v[2 * i + 1]);
-  if constexpr (N >= 8) {
-#pragma unroll
-    for (int i = 0; i < N / 8; ++i)
-      v[i] = ((lane & 4) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppXor3>(dpp<kDppMirror>((lane & 4) ? v[2 * i] : v[2 * i + 1]));
-  } else {
-    v[0] += dpp<kDppRor4>(v[0]);
-  }
-  if constexpr (N >= 16) {
-#pragma unroll
-    for (int i = 0; i < N / 16; ++i) v[i] = ((lane & 8) ? v[2 * i + 1] : v[2 * i]) + dpp<kDppRor8>((lane & 8) ? v[2 * i] : v[2 * i + 1]);
-  } else {
-    v[0] += dpp<kDppRor8>(v[0]);
-  }
-  uint32_t x = __float_as_uint(v[0]), y = N == 32 ? __float_as_uint(v[1]) : x;
-  swap16(x, y);
-  x = y = __float_as_uint(__uint_as_float(x) + __uint_as_float(y));
-  swap32(x, y);
-  return __uint_as_float(x) + __uint_as_float(y);
-}
-
 template <bool BF16, int TG, int EB, bool WHOLE>
 __global__ __launch_bounds__(kRouteWaves * 64) void k_route(LayerDims L, const float* __restrict__ Wr, const float* __restrict__ bias,
                                                             const void* __restrict__ x, int32_t T, int32_t* __restrict__ idx,
