@@ -124,7 +124,7 @@ inline int64_t batch_tokens(int32_t k) { return kBatchMaxPairs / k; }
 
 // Calls of at least this many tokens on a ReLU layer that use_prefill does not take may group their pairs by expert as well
 // (group_gemm.hip); they are taken in launches of at most group_max_pairs() pairs.
-constexpr int64_t kGroupMinTokens = 32;
+constexpr int64_t kGroupMinTokens = 32, kGroupMinColumns = 6;      // on rows, with W_out in columns
 // Whether they do. With W_out in columns always: 32 tokens 128-308 us token by token, 32-79 grouped (2 to 128 experts,
 // Switch-base and -large layers and one of 1536 x 4096; a 512 x 1024 layer 43 / 40). In canonical rows by two models in
 // microseconds as for batch_pays, fitted to 238 pairs of calls of 24 to 128 tokens on these layers: the GEMV kernels grow with
@@ -132,11 +132,20 @@ constexpr int64_t kGroupMinTokens = 32;
 // lines cross between 24 tokens (2 or 8 experts, Switch-large) and more than 128 (a 512 x 1024 layer of 128 experts). us, token
 // by token / grouped, Switch-base layer of 64 experts (2, 4, 8 bits): 32 tokens 34 / 45, 64 tokens 52 / 55, 128 tokens 88 / 61.
 // The form it picks is 0.5 % slower than the faster one on average, at most 22 % (2 experts, 40 tokens: 37 us, 30 alone).
+// Calls of fewer tokens with W_out in columns do where the model of the grouped kernels is below one of k_small_cols (fitted to 670
+// calls of 6 to 31 tokens on layers of 512 x 1024 to 1536 x 4096; a launch has slices x tokens workgroups, the second choice costs
+// 0.4 of the first). us, token by token / grouped, 4 bits: 64 experts of 768 x 3072, 12 / 20 / 31 tokens 36 / 36.5, 52 / 38, 79 / 45;
+// 8 experts of 1024 x 4096 46 / 34, 70 / 35, 104 / 35; of 512 x 1024 14.5 / 30, 20.5 / 30, 29.4 / 31.
 bool group_pays(const moeq_layer* layer, int64_t T) {
-  if (layer->out_layout == MOEQ_OUT_COLUMNS) return true;
+  const bool columns = layer->out_layout == MOEQ_OUT_COLUMNS;
+  if (columns && T >= kGroupMinTokens) return true;
   const LayerDims& L = layer->dims;
   const double pairs = (double)T * L.top_k, matrix = (double)L.d_model * L.d_ff / (768.0 * 3072.0), E = L.n_experts;
   const double touched = E * (1.0 - std::pow(1.0 - std::fmin(1.0, L.top_k / E), (double)T));
+  if (columns) {
+    const double small = 9.0 + (double)T * layer->plan.n_slices * (0.0082 + 0.0000044 * L.d_model) * (0.6 + 0.4 * L.top_k);
+    return 33.0 + touched * (0.12 + 0.135 * matrix * (layer->mean_bits + 0.42)) + 0.168 * pairs / 32.0 * matrix < small;
+  }
   const double one = 9.2 + pairs / 32.0 * (0.79 + 3.79 * matrix * (layer->mean_bits + 1.34)) * ((T & (T - 1)) ? 1.2 : 1.0);
   return 33.0 + touched * (0.12 + 0.135 * matrix * (layer->mean_bits + 0.42)) + 0.168 * pairs / 32.0 * matrix < one;
 }
@@ -171,7 +180,7 @@ WsLayout ws_layout(const moeq_layer* layer, int64_t T) {
   const bool prefill = use_prefill(layer, T);
   w.group_off = tail;
   w.batch = !prefill && batch_pays_layer(layer, T);
-  const bool may_group = !prefill && T >= kGroupMinTokens && layer->in_layout == MOEQ_IN_CANONICAL && !batch_supported(L) && group_supported(L);
+  const bool may_group = !prefill && T >= (layer->out_layout == MOEQ_OUT_COLUMNS ? kGroupMinColumns : kGroupMinTokens) && layer->in_layout == MOEQ_IN_CANONICAL && !batch_supported(L) && group_supported(L);
   w.group = may_group && group_pays(layer, T);
   size_t most = may_group ? group_bytes(layer, std::min(T, group_tokens(L.top_k))) : 0;
   const int64_t Tb = prefill ? kPrefillMinTokens - 1 : T;         // the largest layer call that may run decode_batch.hip
