@@ -27,8 +27,10 @@
  *     powers of two, with the integer codes, accumulate in fp32 and scale back in fp32. Accuracy therefore does not depend
  *     on the scale of a token as long as its largest magnitude lies in [2^-96, 2^124] and the exact results fit fp32. What
  *     an element keeps beside larger ones:
+ *       fp32, whole: calls that run token by token on layers whose work is small beside a launch's latency (W_in in rows,
+ *         d_model up to 2048; the rest by the sizes and the token count)
  *       binary16, one power of two per token and h vector (or slice of it): single tokens and calls that run token by token on
- *         layers with W_in in rows, and all grouped GEMMs (MOEQ_PATH_GROUPED_GEMM, and the grouped calls of narrow ReLU
+ *         other layers with W_in in rows, and all grouped GEMMs (MOEQ_PATH_GROUPED_GEMM, and the grouped calls of narrow ReLU
  *         layers): 11 bits, in the stored value down to 2^-29 of the token's largest element. The multipliers add up what
  *         shares an instruction relative to its largest operands, zero weights included, so that less than 11 bits remain of
  *         a sum beside operands some 2^10 times its own.
@@ -166,7 +168,8 @@ size_t moe_workspace_bytes(const moeq_layer *layer, int32_t max_tokens);
  * The paths 0, 1, 2 and 4 have a second form, which groups the call's (token, choice) pairs by expert and streams every
  * expert once for several of them, like moe_expert_ffn_q on the first kind of layer:
  *   d_model 4096, scale groups of 128: 2 tokens on (rows: 3), up to the 31 of a layer that the grouped GEMMs take beyond;
- *   ReLU layers with W_in in rows that neither these kernels nor the grouped GEMMs take: 32 tokens on.
+ *   ReLU layers with W_in in rows that these kernels do not take, up to the 31 tokens of a layer that the grouped GEMMs take
+ *   beyond: 32 tokens on, with W_out in columns 6 on.
  * It runs where it is faster by a rule on the sizes, the mean bitwidth and the token count; a workspace that holds less than
  * its least launch keeps the first form (moe_workspace_bytes). The forms round differently (see "Range" above). */
 #define MOEQ_PATH_TWO_KERNELS 0    /* W_out in rows: router, phase-1 and phase-2 GEMV kernels             */

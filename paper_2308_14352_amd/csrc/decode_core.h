@@ -64,8 +64,8 @@ __device__ __forceinline__ uint2 gload_u32x2(const uint8_t* ptr) {
 // a / b for 0 <= a < 2^21, b > 0: the quotient of the floats is off by less than 1.5 * 2^-23 of itself (a reciprocal of one
 // unit in the last place and one rounding; a + 1/2 is exact), and the nearest integer lies 1 / (2 a + 1) of (a + 1/2) / b
 // away, more than 2^-22.01. Five instructions. The kernels of the small layers execute almost every
-// instruction once per launch, and a launch finds the instruction caches cold: some 300 cycles per 64 bytes of code, so
-// that each of the compiler's 40-instruction divisions costs as much as a memory round trip.
+// instruction once per launch: the compiler's 40 of a division stand in the chain from the launch to its last store, and where
+// the instruction caches are cold they cost as much as a memory round trip (180-300 cycles per 64 bytes of code).
 __device__ __forceinline__ int small_div(int a, int b) {
   return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
 }

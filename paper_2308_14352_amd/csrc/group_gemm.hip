@@ -1,5 +1,5 @@
 // Calls of many tokens on layers whose scale groups do not fit the tiles of prefill.hip (the Switch-shaped layers: groups
-// of 32 or 64, a few hundred columns): the (token, choice) pairs are grouped by expert, and every expert's packed rows
+// of 32 or 64, a few hundred columns), and of 6 to 31 tokens with W_out in columns where it pays (api.cpp, group_pays): the (token, choice) pairs are grouped by expert, and every expert's packed rows
 // are streamed once for a tile of up to 32 of its pairs, on the matrix cores (Section 2.1: only the chosen experts work
 // on a token; Section 3.2: the codes are decompressed by the mirror of the linear quantization on their way into the
 // instruction). ReLU layers, W_out canonical or in columns.

@@ -1,4 +1,5 @@
-"""GPU parity of calls of 32 tokens and more on ReLU layers whose scale groups the prefill GEMMs do not take: pairs grouped
+"""GPU parity of calls of 32 tokens and more on ReLU layers whose scale groups the prefill GEMMs do not take, and of fewer
+tokens with W_out in columns where it pays: pairs grouped
 by expert, tiles of 16 and 32 pairs, ragged widths, every group size and both W_out layouts, outliers, calls in several
 launches, and which calls are grouped."""
 from dataclasses import replace
