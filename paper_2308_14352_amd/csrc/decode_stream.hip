@@ -285,31 +285,40 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
     if (P.idx_out) P.idx_out[(size_t)token * k + lane] = my_e;
     if (P.gate_out) P.gate_out[(size_t)token * k + lane] = my_g;
   }
+  // The records in one register, read for every request: lane 8 w + j holds word w of choice j's (W_in, W_gate, W_out, scales of
+  // W_out; two words an address). A register per word, held through the loop, spills where the layer has all three bitwidths (us,
+  // layers of eight such experts, two chosen: d_ff 14336 52.7, now 48.3; in LDS 50.6; 2 and 4 bits alone 38.2 either way).
+  const int choice_e = __shfl(my_e, lane & 7), word = lane >> 3;
+  uint32_t recs, bits;
   if (lane_recs) {
-    auto of = [&](uint32_t& v) __attribute__((always_inline)) { v = (uint32_t)__shfl((int)v, my_e); };
-    of(rec.q_in.x); of(rec.q_in.y);
-    if constexpr (SWIGLU) { of(rec.q_gate.x); of(rec.q_gate.y); }
-    of(rec.out.x); of(rec.out.y); of(rec.out.z); of(rec.out.w);
-    rec.bits = __shfl(rec.bits, my_e);
+    auto of = [&](uint32_t v) __attribute__((always_inline)) { return (uint32_t)__shfl((int)v, choice_e); };
+    uint32_t w[8] = {of(rec.q_in.x), of(rec.q_in.y), 0u, 0u, of(rec.out.x), of(rec.out.y), of(rec.out.z), of(rec.out.w)};
+    if constexpr (SWIGLU) { w[2] = of(rec.q_gate.x); w[3] = of(rec.q_gate.y); }
+    bits = of((uint32_t)rec.bits);                   // (every lane takes part in every exchange; each keeps one of the words)
+    recs = w[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) recs = word == i ? w[i] : recs;
   } else {
-    rec = load_rec(my_e);
+    const uint32_t* src = (const uint32_t*)(P.table + choice_e);
+    recs = src[word < 2 ? word : (word < 4 ? word + 2 : word + 4)];
+    bits = src[12];
   }
   auto at_choice = [&](uint32_t v, int j) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane((int)v, j); };
-  auto ptr_at = [&](uint32_t lo, uint32_t hi, int j) __attribute__((always_inline)) {
-    return (const uint8_t*)((uint64_t)at_choice(lo, j) | (uint64_t)at_choice(hi, j) << 32);
+  auto ptr_at = [&](int w, int j) __attribute__((always_inline)) {      // the address in the words w, w + 1 of choice j
+    return (const uint8_t*)((uint64_t)at_choice(recs, 8 * w + j) | (uint64_t)at_choice(recs, 8 * w + 8 + j) << 32);
   };
 
   // ---- the list of blocks of a wavefront (the same for every wavefront): lane g computes entries g and g + 64
-  // and keeps them in two registers, read with v_readlane when a block is requested. Entry: kind | first << 2 |
-  // j << 3 | bits << 6 | index << 10, index = rb * NM + mat in phase 1, q in phase 2. Segment j (0 .. k) holds
+  // and keeps them in the halves of a register, read with v_readlane when a block is requested. Entry: kind | first << 2 |
+  // j << 3 | bits << 6 | index << 10 (13 bits), index = rb * NM + mat in phase 1, q in phase 2. Segment j (0 .. k) holds
   // phase 1 of expert j interleaved with phase 2 of expert j - 1, alternating while both have blocks left.
   int n_total = 0, bm = 0;
-  int ent_lo = 0, ent_hi = 0;
+  uint32_t entries = 0;
   {
     int start = 0, b2 = 0;                                      // b2: bits of expert j - 1
     for (int j = 0; j <= k; ++j) {
       {
-        const int b1 = j < k ? (int)at_choice((uint32_t)rec.bits, j) : 0;   // bits of expert j
+        const int b1 = j < k ? (int)at_choice(bits, j) : 0;   // bits of expert j
         bm |= b1;
         const int n1 = (b1 >> 1) * NM, n2 = b2 == 0 ? 0 : (b2 == 2 ? 1 : (b2 == 4 ? 2 : 4));
         const int m = min(n1, n2);
@@ -322,7 +331,7 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
             else { kind = n1 > n2 ? B_P1 : B_P2; idx = m + (i - 2 * m); }
             const int ent = kind == B_P1 ? (B_P1 | (j << 3) | (b1 << 6) | (idx << 10))
                                          : (B_P2 | ((idx == 0 ? 1 : 0) << 2) | ((j - 1) << 3) | (b2 << 6) | (idx << 10));
-            if (half == 0) ent_lo = ent; else ent_hi = ent;
+            entries |= (uint32_t)ent << (16 * half);
           }
         }
         start += n1 + n2;
@@ -334,7 +343,7 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
   const uint8_t* idle = (const uint8_t*)xt;       // at least 8 KB of readable, cached bytes
   // Requests block g of the list into S and notes in tag what it is.
   auto issue = [&](BlkSet& S, BlkTag& tag, int g) __attribute__((always_inline)) {
-    const int ent = g >= n_total ? 0 : (g < 64 ? __builtin_amdgcn_readlane(ent_lo, g) : __builtin_amdgcn_readlane(ent_hi, g - 64));
+    const int ent = g >= n_total ? 0 : (int)(((uint32_t)__builtin_amdgcn_readlane((int)entries, g & 63) >> (g < 64 ? 0 : 16)) & 0xffffu);
     tag.kind = ent & 3; tag.first = (ent >> 2) & 1; tag.j = (ent >> 3) & 7; tag.bits = (ent >> 6) & 15;
     const int index = ent >> 10;
     tag.mat = 0; tag.rb = 0; tag.q = index;
@@ -349,7 +358,7 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
         const int rbsh = tag.bits == 2 ? 3 : (tag.bits == 4 ? 2 : 1);
         const uint32_t RB = 1u << rbsh, BB = 8192u + 64u * RB;
         const uint32_t blk = (((uint32_t)slice * 64u + (uint32_t)wave * 8u) >> rbsh) + (uint32_t)tag.rb;
-        base = SWIGLU && tag.mat ? ptr_at(rec.q_gate.x, rec.q_gate.y, tag.j) : ptr_at(rec.q_in.x, rec.q_in.y, tag.j);
+        base = SWIGLU && tag.mat ? ptr_at(2, tag.j) : ptr_at(0, tag.j);
         base += (size_t)blk * BB;
         tstride = 1024u;
         sbase = base + 8192u;
@@ -362,11 +371,11 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
         const uint32_t first = tag.bits == 8 ? (uint32_t)(tag.q & 1) * 8u : 0u; // 8-bit: two blocks per row quad
         const uint32_t q0 = tag.bits == 2 ? 0u : (tag.bits == 4 ? (uint32_t)tag.q : (uint32_t)(tag.q >> 1));
         qshift = tag.bits == 2 ? 2 : 3;
-        base = ptr_at(rec.out.x, rec.out.y, tag.j) + ((size_t)slice * DW + first) * ((size_t)kSD * 4);
+        base = ptr_at(4, tag.j) + ((size_t)slice * DW + first) * ((size_t)kSD * 4);
         tstride = (uint32_t)kSD * 4u;
         qstride = 1024u - wpb * tstride;                                       // from the last word of quad 0 to quad 1
         lane_t = (uint32_t)(64 * (2 * wave + (int)q0) + lane) * 16u;
-        sbase = ptr_at(rec.out.z, rec.out.w, tag.j) + (size_t)(slice >> 1) * ((size_t)kSD * 2);
+        sbase = ptr_at(6, tag.j) + (size_t)(slice >> 1) * ((size_t)kSD * 2);
         soff0 = (uint32_t)(64 * (2 * wave + (int)q0) + lane) * 8u;
         soff1 = tag.bits == 2 ? soff0 + 512u : soff0;
       }
@@ -506,7 +515,7 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
 
   // ---- phase 2 state: the lane's 8 output rows
   float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  int acc8[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};   // 8-bit experts: a row quad's sums run over two blocks
+  int sum8[4] = {0, 0, 0, 0};    // 8-bit experts: a row quad's sums run over two blocks
   auto consume_p2 = [&](const BlkSet& S, const BlkTag& tag) __attribute__((always_inline)) {
     const float gu = __builtin_bit_cast(float, at_choice(__builtin_bit_cast(uint32_t, my_g), tag.j)) * uph[tag.j];
     const uint4* hd = HD[tag.j];
@@ -573,10 +582,7 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
     } else if ((BM & 8) && tag.bits == 8) {
       // 8-bit: word columns 8 * (q & 1) .. + 7 of row quad q >> 1; the digits of h: word i -> HD[j][i / 2], (lo, hi) pairs
       const int half = tag.q & 1;
-      if (half == 0) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc8[r][0] = acc8[r][1] = 0;
-      }
+      int acc8[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const uint4 h4 = hd[4 * half + (i >> 1)];
@@ -589,12 +595,14 @@ __global__ __launch_bounds__(kSThreads) void k_moe_stream(StreamParams P) {
           acc8[r][1] = sdot4(c, hi, acc8[r][1]);
         }
       }
+      // (kept as one integer per row: the low and high digits' sums of the first block would hold four registers more in the loop)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum8[r] = (half ? sum8[r] : 0) + acc8[r][0] + (acc8[r][1] << 8);
       if (half == 1) {
         const uint32_t sc[4] = {S.s[0].x & 0xffffu, S.s[0].x >> 16, S.s[0].y & 0xffffu, S.s[0].y >> 16};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int v = acc8[r][0] + (acc8[r][1] << 8);
-          const float c = (float)v * (f16_bits_to_f32(sc[r]) * gu);
+          const float c = (float)sum8[r] * (f16_bits_to_f32(sc[r]) * gu);
           y[r] += (tag.q >> 1) == 0 ? c : 0.f;
           y[4 + r] += (tag.q >> 1) == 0 ? 0.f : c;
         }
