@@ -1124,7 +1124,7 @@ __global__ __launch_bounds__(1024) void k_moe_decode_wide(FusedParams P) {
 }
 
 // The vector variant for the layers that 256 threads cover (d_model up to 1024), where k_small_cols (decode_small.hip) does not
-// serve the call (several tokens on slices of more than 32 columns): its duration is a chain of memory round
+// serve the call (several tokens on slices of more than 32 columns or of more than half a compute unit's LDS): its duration is a chain of memory round
 // trips, so the chain is kept short: activations, router logits (or rows) and expert records are requested together;
 // every wavefront routes for itself and requests its first weights at once; the activations are normalised and put in
 // pair order (for the chosen experts' bitwidths only) while those are in flight.

@@ -25,6 +25,7 @@ namespace moeq {
 namespace {
 
 constexpr int kSmInlineMaxE = 64, kSmMaxSegs = 8;
+constexpr int kSmRouteBytes = kSmInlineMaxE * kSmMaxSegs * 4;    // k_small_cols: of the routing, in the place of the partial sums
 constexpr size_t kSmLds = 150 * 1024, kSmLdsTwo = 80 * 1024;     // of a compute unit's 160 KB: one workgroup, two
 
 __host__ __device__ inline int pad_to(int v, int a) { return (v + a - 1) / a * a; }
@@ -289,8 +290,6 @@ __global__ __launch_bounds__(kSmThreads, 4) void k_small_cols(SmallCols P) {
   extern __shared__ uint4 smem4[];
   __shared__ int sel_ew[kSmThreads / 64][8];
   __shared__ float sel_gw[kSmThreads / 64][8];
-  __shared__ float rpart[MODE == kInline ? kSmInlineMaxE * kSmMaxSegs : 1];
-  __shared__ float red_m[kSmThreads / 64];
   constexpr int NM = SWIGLU ? 2 : 1, NT = kSmThreads;
   const int d = P.d, E = P.E, k = P.k, SW = P.SW, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -302,6 +301,13 @@ __global__ __launch_bounds__(kSmThreads, 4) void k_small_cols(SmallCols P) {
   float* XS = (float*)(smem + P.xs_off);
   float* HF = (float*)(smem + P.h_off);
   float* red = (float*)(smem + P.red_off);
+  // Two workgroups share a compute unit where the launch asks for half of its LDS (small_cols_fits): what the routing needs lies
+  // where the partial sums and h come later, behind the loop's first barrier or its second. (2 KB beside it: 8-bit experts of
+  // 1024 x 8192, 3 tokens 27.0 us, now 21.4, k_moe_decode_vec 23.7.) The choices of more than 64 experts stay apart: in the place
+  // of the partial sums they cost the scalar registers of every call with logits (3 % of one with several choices).
+  float* rpart = red;                                      // kInline: router sums, unit u = e * n_seg + seg
+  float* red_m = HF;                                       // a wavefront's largest activation
+  static_assert(NT / 64 <= 16, "a slice has at least 16 columns of h");
   const uint32_t lds0 = (uint32_t)(uintptr_t)(MOEQ_LDS char*)smem;
   const char* xt = (const char*)P.x + (size_t)token * d * (P.bf16 ? 2 : 4);
 
@@ -730,7 +736,7 @@ SmallCols small_cols_plan(const LayerDims& L, int k, int SW, int bits_mask) {
   P.xs_off = pad_to(d, 64) * 4;
   P.h_off = P.xs_off + pad_to(d / 16, 4) * 4;
   P.red_off = P.h_off + SW * 4;
-  P.si_off = P.red_off + nm * P.red_stride * 4;
+  P.si_off = P.red_off + std::max(nm * P.red_stride * 4, kSmRouteBytes);
   P.wi_off = pad_to(P.si_off + nm * P.si_stride * 2, 16);
   P.lds = P.wi_off + (nm + (k > 1 ? 2 : 1)) * P.w_stride;
   return P;
@@ -765,7 +771,8 @@ SmallRows small_rows_plan(int cols, int rows, int group, int R, int nm, int room
 // one's: d_ff 16384 (slices of 64), d_model 1024, 4 bits, one token 18.1 / 14.3, 3 tokens 24.5 / 30.9, 31 tokens 189 / 261;
 // one workgroup per compute unit (8 bits, d_model 1024, d_ff 8192, two choices) one token 24.3 / 18.4, 3 tokens 33.9 / 42.8; d_model
 // 1536, d_ff 4096, 4 bits, 1 / 8 / 31 tokens 18.1 / 12.1, 83 / 41, 276 / 140. 440 calls within the line: 1.34 times faster on
-// average, none slower by more than 1 %.
+// average, none slower by more than 1 %; 120 within 2 KB of it 2.0 times, the least 1.06 (8 bits, 1024 x 6144, 3 tokens). With logits
+// a workgroup has 512 bytes beside the launch's, so that shapes of the last half KB run one: still 1.5 times faster or more.
 bool small_cols_fits(const LayerDims& L, const FusedPlan& plan, int32_t bits_mask, int32_t T) {
   if (!plan.SW || plan.mx || L.d_model > 4 * kSmThreads || (T > 1 && plan.SW > 32)) return false;
   return (size_t)small_cols_plan(L, L.top_k, plan.SW, bits_mask).lds <= (T > 1 ? kSmLdsTwo : kSmLds);
