@@ -680,10 +680,11 @@ __global__ __launch_bounds__(kSmThreads, 4) void k_small_in(SmallRows P) {
                            if constexpr (SWIGLU) h[r] = silu(a) * (t[1] * up);
                            else h[r] = fmaxf(a, 0.f);
                          });
-  // what phase 2 and the caller want to know, behind the work
+  // what phase 2 and the caller want to know, behind the work (the gates of more than 128 experts are there: selecting again would
+  // hold the kernel's end up by 4 us)
   if (blockIdx.x == 0 && wave == 0) {
     if constexpr (MODE != kGiven) {
-      topk_from_logits(lg, E, k, P.renorm, lane, sel_ew[0], sel_gw[0], nullptr);
+      if (E <= 128) topk_from_logits(lg, E, k, P.renorm, lane, sel_ew[0], sel_gw[0], nullptr);
       if (lane == 0) {
         P.idx[blockIdx.y] = my_e;
         P.gate[blockIdx.y] = sel_gw[0][jc];
