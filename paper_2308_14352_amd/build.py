@@ -26,7 +26,7 @@ def stale():
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + [os.path.join(CSRC, "moeq_internal.h"), os.path.join(CSRC, "decode_core.h"),
-                        os.path.join(ROOT, "include", "moeq.h")]
+                        os.path.join(CSRC, "small_split.h"), os.path.join(ROOT, "include", "moeq.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

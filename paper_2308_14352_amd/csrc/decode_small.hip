@@ -20,6 +20,7 @@
 #include <hip/hip_ext.h>
 
 #include "decode_core.h"
+#include "small_split.h"
 
 namespace moeq {
 namespace {
@@ -248,7 +249,7 @@ struct SmallCols {
   // with several choices)
   int32_t xs_off, h_off, red_off, red_stride, si_off, si_stride, wi_off, w_stride, lds;
 };
-constexpr int kSmThreads = 512;
+constexpr int kSmThreads = 512;          // (small_split.h counts on them)
 
 // Output rows RPT tid .. over the slice: acc = sum of the codes u times h (dn).
 template <int BITS, int RPT>
@@ -823,25 +824,11 @@ bool small_rows_fits(const LayerDims& L, int64_t pairs) {
   return work <= (L.d_model % 512 == 0 ? 34e6 : 18e6);
 }
 
-// Rows of a workgroup (a multiple of four): rounds of two workgroups per compute unit, each as long as six steps of the rows that
-// the threads cover at once and the steps it has.
-static int rows_of_wg(int rows, int cols, int64_t items) {
-  const int at_once = std::max(1, kSmThreads * 32 / cols);
-  int best = 4;
-  double least = 1e30;
-  for (int R = 4; R <= 256; R += 4) {
-    const int64_t wgs = (rows + R - 1) / R * items;
-    const double cost = (double)((wgs + 511) / 512) * (6 + (R + at_once - 1) / at_once) + 1e-4 * (double)wgs;
-    if (cost < least) { least = cost; best = R; }
-  }
-  return best;
-}
-
 hipError_t launch_small_in(const LayerDims& L, const DevExpert* table, const float* logits, int32_t* idx, float* gate, DevExpert* sel_tab,
                            int32_t fixed_expert, int32_t bits_mask, const void* x, int32_t T, float* h, hipStream_t st) {
   const bool fixed = fixed_expert >= 0, sw = L.act == MOEQ_ACT_SWIGLU;
   const int k = fixed ? 1 : L.top_k, nm = sw ? 2 : 1;
-  const int R = rows_of_wg(L.d_ff, L.d_model, (int64_t)T * k);
+  const int R = small_rows_of_wg(L.d_ff, L.d_model, (int64_t)T * k);
   SmallRows P = small_rows_plan(L.d_model, L.d_ff, L.group, R, nm, kRowsRoom / nm, bits_mask);
   P.table = table; P.logits = logits; P.idx = fixed ? nullptr : idx; P.gate = gate; P.sel_tab = fixed ? nullptr : sel_tab; P.act = x; P.out = h;
   P.fixed_expert = fixed_expert; P.E = L.n_experts; P.k = k; P.renorm = L.renorm; P.bf16 = L.x_bf16;
@@ -855,7 +842,7 @@ hipError_t launch_small_out(const LayerDims& L, const DevExpert* table, const De
                             int32_t bits_mask, int32_t accumulate, const float* h, int32_t T, float* y, hipStream_t st) {
   const bool fixed = fixed_expert >= 0;
   const int k = fixed ? 1 : L.top_k;
-  const int R = rows_of_wg(L.d_model, L.d_ff, T);
+  const int R = small_rows_of_wg(L.d_model, L.d_ff, T);
   SmallRows P = small_rows_plan(L.d_ff, L.d_model, L.group_out, R, 1, kRowsRoom, bits_mask);
   P.table = table; P.gate = (float*)gate; P.sel_tab = (DevExpert*)sel_tab; P.act = h; P.out = y;
   P.fixed_expert = fixed_expert; P.E = L.n_experts; P.k = k; P.accumulate = accumulate;
