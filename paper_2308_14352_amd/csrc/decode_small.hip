@@ -505,7 +505,7 @@ __global__ __launch_bounds__(kSmThreads, 4) void k_small_cols(SmallCols P) {
 
 // ---------------------------------------------------------------------------------------------
 // The canonical layout, one phase a kernel: R consecutive rows of W_in (and W_gate) against x, of W_out against the h of every
-// choice. A workgroup's rows are taken in passes that fill `room` bytes of LDS a matrix; the next pass is requested as soon as
+// choice. A workgroup's rows are taken in passes of up to `room` bytes of LDS a matrix; the next pass is requested as soon as
 // the one before has been multiplied. (Passes of 8 KB in a ring of four, with waits that count a wavefront's copies, multiply
 // while they arrive, but their barriers and the loop around them cost more: 8 tokens on the layer below 23.2 -> 30.3 us.)
 // Time stamps of 8 tokens on a 128-expert Switch-large layer (us from the start of a kernel, medians): k_small_in routed 1, blocks
@@ -744,8 +744,8 @@ SmallCols small_cols_plan(const LayerDims& L, int k, int SW, int bits_mask) {
   return P;
 }
 
-// LDS of a kernel over `rows` rows of `cols` columns, R of them a workgroup, nm matrices.
-SmallRows small_rows_plan(int cols, int rows, int group, int R, int nm, int room, int bits_mask) {
+// LDS of a kernel over `rows` rows of `cols` columns, R of them a workgroup, nm matrices, in passes of up to `room` bytes a matrix.
+SmallRows small_rows_plan_at(int cols, int rows, int group, int R, int nm, int room, int bits_mask) {
   SmallRows P{};
   P.cols = cols; P.rows = rows; P.R = R; P.room = room;
   P.group = group; P.gsh = (group & (group - 1)) == 0 ? __builtin_ctz(group) : -1; P.ng = cols / group;
@@ -764,6 +764,18 @@ SmallRows small_rows_plan(int cols, int rows, int group, int R, int nm, int room
   P.w_off = pad_to(P.si_off + nm * P.si_stride * 2, 16);
   P.lds = P.w_off + nm * room;
   return P;
+}
+// ... that hold the workgroup's rows at the widest bitwidth in as few equal passes as leave two workgroups a compute unit, kRowsRoom
+// bytes in all at least. A pass is a round trip: SwiGLU, 1536 x 2048, 4 and 8 bits, 6 tokens in up to four passes of 16 KB a matrix
+// 29.2 us, now 25.0 (28.7 in the kernels of ffn_decode.hip). Passes as large as fit, the last one small, lose 4 to 8 %.
+SmallRows small_rows_plan(int cols, int rows, int group, int R, int nm, int bits_mask) {
+  const int least = kRowsRoom / nm, row_bytes = cols / 8 * (bits_mask & 8 ? 8 : bits_mask & 4 ? 4 : 2);
+  for (int passes = 1;; ++passes) {
+    const int room = pad_to(pad_to((R + passes - 1) / passes, 4) * row_bytes, 1024);
+    if (room <= least) return small_rows_plan_at(cols, rows, group, R, nm, least, bits_mask);
+    const SmallRows P = small_rows_plan_at(cols, rows, group, R, nm, room, bits_mask);
+    if ((size_t)P.lds <= kSmLdsTwo - 1024) return P;                  // (up to 544 bytes are static)
+  }
 }
 
 }  // namespace
@@ -829,7 +841,7 @@ hipError_t launch_small_in(const LayerDims& L, const DevExpert* table, const flo
   const bool fixed = fixed_expert >= 0, sw = L.act == MOEQ_ACT_SWIGLU;
   const int k = fixed ? 1 : L.top_k, nm = sw ? 2 : 1;
   const int R = small_rows_of_wg(L.d_ff, L.d_model, (int64_t)T * k);
-  SmallRows P = small_rows_plan(L.d_model, L.d_ff, L.group, R, nm, kRowsRoom / nm, bits_mask);
+  SmallRows P = small_rows_plan(L.d_model, L.d_ff, L.group, R, nm, bits_mask);
   P.table = table; P.logits = logits; P.idx = fixed ? nullptr : idx; P.gate = gate; P.sel_tab = fixed ? nullptr : sel_tab; P.act = x; P.out = h;
   P.fixed_expert = fixed_expert; P.E = L.n_experts; P.k = k; P.renorm = L.renorm; P.bf16 = L.x_bf16;
   const dim3 grid(pad_to((L.d_ff + R - 1) / R, 8), T * k);
@@ -843,7 +855,7 @@ hipError_t launch_small_out(const LayerDims& L, const DevExpert* table, const De
   const bool fixed = fixed_expert >= 0;
   const int k = fixed ? 1 : L.top_k;
   const int R = small_rows_of_wg(L.d_model, L.d_ff, T);
-  SmallRows P = small_rows_plan(L.d_ff, L.d_model, L.group_out, R, 1, kRowsRoom, bits_mask);
+  SmallRows P = small_rows_plan(L.d_ff, L.d_model, L.group_out, R, 1, bits_mask);
   P.table = table; P.gate = (float*)gate; P.sel_tab = (DevExpert*)sel_tab; P.act = h; P.out = y;
   P.fixed_expert = fixed_expert; P.E = L.n_experts; P.k = k; P.accumulate = accumulate;
   hipLaunchKernelGGL(k_small_out, dim3(pad_to((L.d_model + R - 1) / R, 8), T), dim3(kSmThreads), (size_t)P.lds, st, P);

@@ -90,3 +90,58 @@ def test_small_slices(d, f, group, E, k, act, x_dtype, misaligned, columns):
         rows = [t for t in range(T) if act == "relu" or scale[t, 0] == 1.0]
         g_ref = oracle.layer_forward_routed(orc, d, f, group, sw, k, xs.float().cpu().numpy(), gi, gg)
         assert rel_err(y_g.cpu().numpy()[rows], g_ref[rows]).max(initial=0) < tol
+
+
+@pytest.mark.parametrize("d,f,group,E,k,act,T", [
+    (1536, 2048, 32, 6, 1, "swiglu", 6),     # 8-bit rows of W_in in passes of half a workgroup's, two matrices
+    (1024, 1024, 32, 30, 1, "relu", 23),     # an uneven last block of rows, in both phases
+    (512, 2048, 128, 9, 1, "relu", 22),      # long rows of W_out in fewer passes than 32 KB hold
+    (512, 512, 64, 4, 1, "relu", 84),        # a token's blocks fewer than the XCDs
+    (1024, 4096, 64, 8, 2, "relu", 4),       # the last call under the line (8 pairs) ...
+    (1024, 4096, 64, 8, 1, "relu", 9),       # ... and one beyond it
+    (768, 3072, 32, 8, 1, "relu", 7),        # the same for widths that are no multiple of 512
+    (768, 3072, 32, 8, 1, "relu", 8),
+    (2048, 8192, 128, 3, 1, "relu", 2),      # rows of W_out that leave one workgroup a compute unit
+])
+def test_small_rows_of_several_tokens(d, f, group, E, k, act, T):
+    cfg = replace(gen.tiny_config("c1", d, f, n_experts=E, n_layers=1, group=group), top_k=k, x_dtype="f32", act=act)
+    distinct = [gen.expert_weights(cfg, 0, e, DEV) for e in range(3)]
+    gpu, orc = ([pack(distinct[e % 3], (2, 4, 8)[e % 3], group) for e in range(3)] for pack in (pack_expert_gpu, pack_expert_oracle))
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(d, f, k, group, moeq.MOEQ_ACT_SWIGLU if act == "swiglu" else moeq.MOEQ_ACT_RELU, cfg.renorm, moeq.MOEQ_F32, Wr,
+                       bias, [gpu[e % 3] for e in range(E)])
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    y, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
+    y_e = moeq.moe_expert_ffn_q(layer, 2, x)
+    torch.cuda.synchronize()
+    line = 34e6 if d % 512 == 0 else 18e6
+    tol, tol_e = (TOL if n * d * f * (1.5 if act == "swiglu" else 1.0) <= line else 2e-3 for n in (T * k, T))
+    sw, xh = int(act == "swiglu"), x.cpu().numpy()
+    ref = oracle.layer_forward_routed([orc[e % 3] for e in range(E)], d, f, group, sw, k, xh, idx.cpu().numpy(), gate.cpu().numpy())
+    assert rel_err(y.cpu().numpy(), ref).max() < tol
+    assert rel_err(y_e.cpu().numpy(), oracle.expert_ffn(orc[2], d, f, group, sw, xh)).max() < tol_e
+
+
+@pytest.mark.parametrize("d,f,group,E,k,act,bits", [
+    (1024, 6144, 32, 8, 1, "relu", 8),       # the launch asks for 78.4 KB of LDS, router inside
+    (1024, 6144, 32, 40, 1, "relu", 8),      # ... from the router kernel's logits
+    (1024, 6144, 32, 80, 1, "relu", 8),      # ... of more than 64 experts
+    (1984, 2048, 32, 70, 1, "relu", 8),      # 80.0 KB: the last of the line
+    (1024, 2048, 64, 6, 2, "swiglu", 8),     # two matrices, two choices
+    (1056, 6144, 32, 6, 1, "relu", 8),       # just beyond the line: single tokens only
+])
+def test_small_slices_at_half_a_compute_units_lds(d, f, group, E, k, act, bits):
+    cfg = replace(gen.tiny_config("c1", d, f, n_experts=E, n_layers=1, group=group), top_k=k, x_dtype="f32", act=act)
+    distinct = [gen.expert_weights(cfg, 0, e, DEV) for e in range(2)]
+    gpu = [pack_expert_gpu(w, bits, group).with_out_columns(f, group) for w in distinct]
+    orc = [pack_expert_oracle(w, bits, group) for w in distinct]
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(d, f, k, group, moeq.MOEQ_ACT_SWIGLU if act == "swiglu" else moeq.MOEQ_ACT_RELU, cfg.renorm, moeq.MOEQ_F32, Wr,
+                       bias, [gpu[e % 2] for e in range(E)], moeq.MOEQ_OUT_COLUMNS)
+    for T in (1, 2, 5):
+        x = gen.hidden(cfg, 0, T, T, DEV)
+        y, idx, gate = moeq.moe_layer_forward(layer, x, want_routing=True)
+        torch.cuda.synchronize()
+        ref = oracle.layer_forward_routed([orc[e % 2] for e in range(E)], d, f, group, int(act == "swiglu"), k, x.cpu().numpy(),
+                                          idx.cpu().numpy(), gate.cpu().numpy())
+        assert rel_err(y.cpu().numpy(), ref).max() < (2e-3 if d == 1056 and T > 1 else TOL), T
