@@ -135,18 +135,29 @@ constexpr int64_t kGroupMinTokens = 32, kGroupMinColumns = 6;      // on rows, w
 // Calls of fewer tokens with W_out in columns do where the model of the grouped kernels is below one of k_small_cols (fitted to 670
 // calls of 6 to 31 tokens on layers of 512 x 1024 to 1536 x 4096; a launch has slices x tokens workgroups, the second choice costs
 // 0.4 of the first). us, token by token / grouped, 4 bits: 64 experts of 768 x 3072, 12 / 20 / 31 tokens 36 / 36.5, 52 / 38, 79 / 45;
-// 8 experts of 1024 x 4096 46 / 34, 70 / 35, 104 / 35; of 512 x 1024 14.5 / 30, 20.5 / 30, 29.4 / 31.
+// 8 experts of 1024 x 4096 46 / 34, 70 / 35, 104 / 35; of 512 x 1024 14.5 / 30, 20.5 / 30, 29.4 / 31. Where k_small_cols does not
+// serve the call (small_cols_fits) the other side is k_moe_decode_vec or, beyond 1024 columns, k_moe_decode_wide: rounds of
+// workgroups, a choice's rows and bits (fitted to 684 calls, 7 and 10 % off in the mean square). us, token by token / grouped: 8
+// experts of 1024 x 24576, 8 bits, two choices, 31 tokens 514 / 108; 8 of 1536 x 8192, 4 bits, two choices, 8 tokens 125 / 45; 64 of
+// 1024 x 16384, 8 bits, 8 tokens 69 / 75. The form it picks there is 0.7 % slower than the faster one on average, by the line of
+// k_small_cols it was 25 %; on 500 calls of any widths 4 %, where odd widths stay ungrouped that should not, and never more than 1 %
+// slower than token by token.
 bool group_pays(const moeq_layer* layer, int64_t T) {
   const bool columns = layer->out_layout == MOEQ_OUT_COLUMNS;
   if (columns && T >= kGroupMinTokens) return true;
   const LayerDims& L = layer->dims;
   const double pairs = (double)T * L.top_k, matrix = (double)L.d_model * L.d_ff / (768.0 * 3072.0), E = L.n_experts;
   const double touched = E * (1.0 - std::pow(1.0 - std::fmin(1.0, L.top_k / E), (double)T));
-  if (columns) {
-    const double small = 9.0 + (double)T * layer->plan.n_slices * (0.0082 + 0.0000044 * L.d_model) * (0.6 + 0.4 * L.top_k);
-    return 33.0 + touched * (0.12 + 0.135 * matrix * (layer->mean_bits + 0.42)) + 0.168 * pairs / 32.0 * matrix < small;
+  double one;
+  if (!columns) {
+    one = 9.2 + pairs / 32.0 * (0.79 + 3.79 * matrix * (layer->mean_bits + 1.34)) * ((T & (T - 1)) ? 1.2 : 1.0);
+  } else if (small_cols_fits(L, layer->plan, layer->bits_mask, (int32_t)T)) {
+    one = 9.0 + (double)T * layer->plan.n_slices * (0.0082 + 0.0000044 * L.d_model) * (0.6 + 0.4 * L.top_k);
+  } else {
+    const double rounds = (double)T * layer->plan.n_slices / 256.0, slice = layer->plan.SW * L.d_model / 16384.0, b = layer->mean_bits;
+    one = 12.6 + rounds * (L.d_model <= 1024 ? 2.56 + L.top_k * (0.84 + slice * (0.236 + 0.089 * b))
+                                             : 4.07 + L.top_k * (2.08 + slice * (0.142 + 0.092 * b)));
   }
-  const double one = 9.2 + pairs / 32.0 * (0.79 + 3.79 * matrix * (layer->mean_bits + 1.34)) * ((T & (T - 1)) ? 1.2 : 1.0);
   return 33.0 + touched * (0.12 + 0.135 * matrix * (layer->mean_bits + 0.42)) + 0.168 * pairs / 32.0 * matrix < one;
 }
 inline int64_t group_tokens(int32_t k) { return group_max_pairs() / k; }

@@ -157,3 +157,27 @@ def test_grouped_with_columns_where_it_pays(d, f, group, E, k, T, grouped):
     ref = oracle.layer_forward_routed([orc[e % 3] for e in range(E)], d, f, group, 0, k, x.cpu().numpy(), idx.cpu().numpy(), gate.cpu().numpy())
     err = rel_err(y.cpu().numpy(), ref).max()
     assert err < (TOL if grouped else 3e-5) and (err > 3e-5) == grouped
+
+
+@pytest.mark.parametrize("d,f,group,E,k,bits,T,grouped", [
+    (1536, 4096, 64, 8, 2, 8, 8, True), (1536, 8192, 64, 8, 2, 4, 8, True), (1024, 24576, 128, 8, 2, 8, 20, True), (512, 16384, 64, 8, 1, 4, 20, True),
+    (1024, 16384, 64, 64, 1, 8, 8, False), (1024, 16384, 64, 64, 2, 8, 6, False),
+])
+def test_grouped_with_columns_on_wide_slices(d, f, group, E, k, bits, T, grouped):
+    """The same where the slices are too wide for the kernel of narrow ones. Up to 5 tokens are never grouped, and a token's bits
+    there do not depend on the others of its call: so they are those of calls of 2 to 5 tokens, or they are not."""
+    cfg = replace(gen.tiny_config("c1", d, f, n_experts=E, n_layers=1, group=group), top_k=k)
+    from helpers import pack_expert_gpu, pack_expert_oracle
+    w = gen.expert_weights(cfg, 0, 0, DEV)
+    gpu, orc = pack_expert_gpu(w, bits, group).with_out_columns(f, group), pack_expert_oracle(w, bits, group)
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(d, f, k, group, moeq.MOEQ_ACT_RELU, cfg.renorm, moeq.MOEQ_F32, Wr, bias, [gpu] * E, moeq.MOEQ_OUT_COLUMNS)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    idx = (torch.arange(T * k, device=DEV, dtype=torch.int32) % E).view(T, k)
+    gate = torch.linspace(0.1, 0.9, T * k, device=DEV).view(T, k)
+    y = moeq.moe_layer_forward_routed(layer, x, idx, gate)
+    few = torch.cat([moeq.moe_layer_forward_routed(layer, x[t:t + 4], idx[t:t + 4], gate[t:t + 4]) for t in range(0, T, 4)])
+    torch.cuda.synchronize()
+    assert torch.equal(y, few) != grouped
+    ref = oracle.layer_forward_routed([orc] * E, d, f, group, 0, k, x.cpu().numpy(), idx.cpu().numpy(), gate.cpu().numpy())
+    assert rel_err(y.cpu().numpy(), ref).max() < TOL and rel_err(few.cpu().numpy(), ref).max() < TOL
