@@ -179,7 +179,8 @@ int64_t launch_tokens(int64_t most, size_t room, Bytes bytes) {
   return lo;
 }
 
-// Every piece grows with T, so a workspace for T tokens serves all calls of fewer tokens in the same way.
+// Every piece grows with T, so a workspace for T tokens serves all calls of fewer tokens in the same way. (Over the line to the
+// prefill GEMMs too: their staging, padded per expert, is larger than the grouped pieces of the 31 tokens before it.)
 WsLayout ws_layout(const moeq_layer* layer, int64_t T) {
   const LayerDims& L = layer->dims;
   WsLayout w{};

@@ -8,7 +8,7 @@ import torch
 import gen
 import paper_2308_14352_amd as moeq
 from paper_2308_14352_amd import binding
-from helpers import build_layer_pair
+from helpers import build_layer_pair, pack_expert_gpu
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -57,3 +57,20 @@ def test_an_experts_call_does_not_depend_on_the_other_experts(f, layout):
     for T in list(range(2, 18)) + [24, 31, 32, 40]:
         a, b = moeq.moe_expert_ffn_q(mixed, 0, x[:T]), moeq.moe_expert_ffn_q(alone, 0, x[:T])
         assert torch.equal(a, b), T
+
+
+@pytest.mark.parametrize("act", ("relu", "swiglu"))
+def test_workspace_grows_with_the_tokens_over_the_line_to_the_prefill_gemms(act):
+    """Layers in columns that group the pairs of 6 to 31 tokens and run other kernels from 32 on: a workspace for more serves those
+    calls in as many launches, with the same bits."""
+    d, f, g, k = 1024, 24576, 128, 8
+    cfg = replace(gen.tiny_config("c1", d, f, n_experts=1, n_layers=1, group=g), x_dtype="f32", act=act)
+    ex = pack_expert_gpu(gen.expert_weights(cfg, 0, 0, DEV), 4, g).with_out_columns(f, g)
+    layer = moeq.Layer(d, f, k, g, moeq.MOEQ_ACT_SWIGLU if act == "swiglu" else moeq.MOEQ_ACT_RELU, False, moeq.MOEQ_F32,
+                       torch.randn((16, d), device=DEV), None, [ex] * 16, moeq.MOEQ_OUT_COLUMNS)
+    sizes = [layer.workspace_bytes(T) for T in range(1, 200)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    x = gen.hidden(cfg, 0, 0, 31, DEV)
+    for T in (5, 6, 20, 31):
+        want = moeq.moe_layer_forward(layer, x[:T], ws=torch.empty(sizes[T - 1], dtype=torch.uint8, device=DEV))
+        assert torch.equal(moeq.moe_layer_forward(layer, x[:T], ws=torch.empty(sizes[31], dtype=torch.uint8, device=DEV)), want), T
