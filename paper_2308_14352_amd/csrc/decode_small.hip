@@ -7,7 +7,9 @@
 //     binary16 pair order to bring them into and no pass over LDS per bitwidth;
 //   - a thread keeps one piece (16 or 32 columns) of the rows and walks the rows, that piece's activations in registers; sixteen
 //     lanes fold a row's partial sums.
-// The routing's source is a template parameter: with all of them in one kernel the scalar registers spill.
+// The routing's source is a template parameter: with all of them in one kernel every instance spills scalar registers. Those that
+// select from the router kernel's logits still spill 40 to 67 of them (they hold the selection of up to 64, 128 and 1024 experts),
+// the others 0 to 11.
 // k_small_in, k_small_out: the two phases on the canonical layout, where a workgroup's rows are one block.
 // k_small_cols: the whole layer for one (slice of d_ff, token), W_out in word columns (partial output vectors, summed by
 // k_reduce_partials). Time stamps of a workgroup on a 64-expert Switch-base layer (us from its start): routed 1.0, all requested
@@ -828,8 +830,12 @@ hipError_t launch_small_cols(const LayerDims& L, const FusedPlan& plan, const De
 // By the multiplications of the call (a SwiGLU layer's third matrix counted). Beyond the line a call is a stream, or its
 // instructions bound it, and the kernels of ffn_decode.hip spend half as many. us, theirs / these: 1024 x 4096, 4 bits, 1 / 4 / 8 / 14
 // tokens on 128 experts 18.1 / 12.9, 22.2 / 17.6, 23.6 / 21 and 28.5 / 29.4; 2048 x 8192, 1 / 2 / 3 tokens 22.0 / 17.2, 24.7 /
-// 21.3, 30.2 / 30; widths whose pieces do not divide the threads evenly cross earlier (768 x 3072, 8 bits, 8 / 10 tokens 21.7 /
-// 21.3, 22 / 24.6). 570 calls within the line: 1.28 times faster on average, none slower.
+// 21.3, 30.2 / 30. 662 calls within the line, of 1 to 84 tokens and 1 to 200 experts: 1.34 times faster on average, none slower (least
+// 1.015). Both lines are cautious:
+// of 174 calls of 34 to 60 million on widths that are a multiple of 512 these kernels are 1.12 times faster on average, but 17 are more
+// than 5 % slower (0.82); of 233 calls of 18 to 34 million on other widths none is slower (1.06 to 6.5 times, 1.7 in the middle). 18
+// was drawn on 768 x 3072 with 8 bits before the rows of a workgroup were chosen by the XCD's places (8 tokens 21.7 / 21.3, 10 tokens
+// 22 / 24.6); calls of 8 and of 24 tokens of that layer run the same kernels by it, which test_gpu_group.py compares by their bits.
 bool small_rows_fits(const LayerDims& L, int64_t pairs) {
   if (L.d_model > 2048 || L.d_ff > kRowsMaxCols) return false;
   const double work = (double)pairs * L.d_model * L.d_ff * (L.act == MOEQ_ACT_SWIGLU ? 1.5 : 1.0);
