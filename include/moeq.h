@@ -28,7 +28,8 @@
  *     on the scale of a token as long as its largest magnitude lies in [2^-96, 2^124] and the exact results fit fp32. What
  *     an element keeps beside larger ones:
  *       fp32, whole: calls that run token by token on layers whose work is small beside a launch's latency (W_in in rows,
- *         d_model up to 2048; the rest by the sizes and the token count)
+ *         d_model up to 2048; the rest by the sizes and the token count). The codes carry an offset that is taken out of the
+ *         fp32 sum at the end: beside activations 2^13 times the others that meet zero weights some 12 bits of a sum remain.
  *       binary16, one power of two per token and h vector (or slice of it): single tokens and calls that run token by token on
  *         other layers with W_in in rows, and all grouped GEMMs (MOEQ_PATH_GROUPED_GEMM, and the grouped calls of narrow ReLU
  *         layers): 11 bits, in the stored value down to 2^-29 of the token's largest element. The multipliers add up what

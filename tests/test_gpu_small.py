@@ -145,3 +145,24 @@ def test_small_slices_at_half_a_compute_units_lds(d, f, group, E, k, act, bits):
         ref = oracle.layer_forward_routed([orc[e % 2] for e in range(E)], d, f, group, int(act == "swiglu"), k, x.cpu().numpy(),
                                           idx.cpu().numpy(), gate.cpu().numpy())
         assert rel_err(y.cpu().numpy(), ref).max() < (2e-3 if d == 1056 and T > 1 else TOL), T
+
+
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("columns", (False, True), ids=("canonical", "columns"))
+def test_outlier_columns_that_meet_zero_weights(bits, columns):
+    """Columns of x 2^13 times the others, on weights of zero. A zero weight is the code 2^(bits - 1) and its product leaves the sum
+    with the offset at the end: d / 128 such products, each in up to 16 roundings of 2^-24 of a partial sum of 2^(bits + 12), are an
+    error of 0.3 at 8 bits beside a sum of some 40 sqrt(768) = 1100, 3e-4 of it, less at fewer bits; the largest of 768 outputs."""
+    d, f, g, T = 768, 3072, 32, 3
+    cfg = gen.tiny_config("c1", d, f, n_experts=1, n_layers=1, group=g)
+    w = gen.expert_weights(cfg, 0, 0, DEV)
+    w["w_in"][:, 5::128] = 0.0
+    ex = pack_expert_gpu(w, bits, g)
+    Wr, bias = gen.router_weights(cfg, 0, DEV)
+    layer = moeq.Layer(d, f, 1, g, moeq.MOEQ_ACT_RELU, False, moeq.MOEQ_F32, Wr, bias, [ex.with_out_columns(f, g) if columns else ex],
+                       moeq.MOEQ_OUT_COLUMNS if columns else moeq.MOEQ_OUT_CANONICAL)
+    x = gen.hidden(cfg, 0, 0, T, DEV)
+    x[:, 5::128] *= 8192.0
+    y = moeq.moe_expert_ffn_q(layer, 0, x)
+    torch.cuda.synchronize()
+    assert rel_err(y.cpu().numpy(), oracle.expert_ffn(pack_expert_oracle(w, bits, g), d, f, g, 0, x.cpu().numpy())).max() < 1e-3
